@@ -42,26 +42,6 @@ __device__ __forceinline__ f32x4s mfma16(bf16x8 a, bf16x8 b, f32x4s c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Buffer descriptor as four scalar words (base, size in bytes; raw 32-bit elements, no swizzle).
-__device__ __forceinline__ u32x4 dma_rsrc(const void* base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  u32x4 r;
-  r[0] = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
-  r[1] = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) & 0xffffu;
-  r[2] = (uint32_t)__builtin_amdgcn_readfirstlane(bytes);
-  r[3] = 0x00020000u;
-  return r;
-}
-
-// One 1 KiB copy global -> LDS: lane l moves the 16 bytes at rsrc.base + soff + 16 l to LDS byte lds_off + 16 l.
-// Counts as one vector-memory load of the issuing wave (vmcnt).  A read beyond the descriptor's size fetches nothing.
-__device__ __forceinline__ void dma_1k(u32x4 rsrc, uint32_t lds_off, uint32_t lane16, uint32_t soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds_off), "v"(lane16), "s"(rsrc), "s"(soff)
-               : "memory");
-}
-
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order, every index a compile-time constant.
 template <int... Is, class F>
 __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, Is...>, F&& f) {
@@ -72,15 +52,6 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-// Wait until at most N of this wave's vector-memory loads are outstanding and all of its LDS operations are done,
-// then meet the other waves.  No fence: loads younger than the N-th youngest stay in flight.
-template <int N>
-__device__ __forceinline__ void dma_barrier() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));  // vmcnt(N) lgkmcnt(0)
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 }  // namespace
 
 constexpr int kStatTile = 64;          // positions per tile = one cache page

@@ -99,6 +99,36 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Wait until at most N of this wave's vector-memory loads are outstanding and all of its LDS operations are done,
+// then meet the other waves.  No fence: loads younger than the N-th youngest stay in flight.
+template <int N>
+__device__ __forceinline__ void dma_barrier() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));  // vmcnt(N) lgkmcnt(0)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Buffer descriptor as four scalar words (base, size in bytes; raw 32-bit elements, no swizzle).
+__device__ __forceinline__ u32x4 dma_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  u32x4 r;
+  r[0] = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
+  r[1] = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) & 0xffffu;
+  r[2] = (uint32_t)__builtin_amdgcn_readfirstlane(bytes);
+  r[3] = 0x00020000u;
+  return r;
+}
+
+// One 1 KiB copy global -> LDS: lane l moves the 16 bytes at rsrc.base + soff + 16 l to LDS byte lds_off + 16 l.
+// Counts as one vector-memory load of the issuing wave (vmcnt).  A read beyond the descriptor's size fetches nothing.
+__device__ __forceinline__ void dma_1k(u32x4 rsrc, uint32_t lds_off, uint32_t lane16, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds_off), "v"(lane16), "s"(rsrc), "s"(soff)
+               : "memory");
+}
+
 // Immediate of s_waitcnt that waits until at most n vector-memory operations are outstanding and leaves the other
 // counters alone (6-bit count split over bits 3:0 and 15:14).
 __host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }

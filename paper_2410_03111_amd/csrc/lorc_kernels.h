@@ -92,8 +92,8 @@ struct PrefillParams {
   const int32_t* block_table;
   uint16_t* out;              // [total x h_q x d] bf16
   const double* rope_tab;     // packed: theta_i
-  uint16_t* krot;             // workspace: rotated keys, fp16 [b][lp][n]
-  uint16_t* vt;               // workspace: values transposed, fp16 [b][n][lp], positions permuted in groups of 16
+  uint16_t* krot;             // workspace: rotated keys, fp16, [b][page] operand blocks (layout: lorc_prefill.hip)
+  uint16_t* vt;               // workspace: values transposed, fp16, likewise
   int b, h_q, h_kv, G, head_dim, r_k, r_v, max_pages, n_pages, tiles_per_seq, lp;
   size_t page_elems;
   float rope_base, q_scale;

@@ -2,186 +2,159 @@
 // to rebuilt keys as in the Appendix on the adjusted position embedding).
 //
 // Two launches per call:
-//   rebuild : one workgroup per (sequence, 64-position page).  K^T = B_k^T C_k^T per KV head on the matrix
-//             cores (same pipeline as decode), rotated in registers, written once to scratch as fp16
-//             K_rot[seq][pos][n]; then the page's V latents are re-tiled through LDS (their cache tiling is
-//             made for contraction over positions, the rebuild contracts over the latent index) and
-//             V^T = B_v^T C_v^T is written as fp16 Vt[seq][n][pos'] with positions permuted inside groups of 16
-//             into the order in which the attention kernel's P accumulators serve as operands.
+//   rebuild : a tiled matrix product over (two pages) x (64 NC columns), keys and values alike (lorc_rebuild_tile.h).
+//             Keys are rotated in registers and written once to scratch as fp16; values likewise, transposed.
 //   attend  : flash-style causal attention.  One workgroup per (sequence, 64-query block, KV head); each wave
 //             owns one query head of the group.  S^T = K Q^T so that a lane owns one query column: row maxima
 //             and sums need a single cross-lane exchange, the P^T accumulators are re-used in place as the
 //             B operand of O^T += V^T P^T, and rescaling is a per-lane scalar.
+// The scratch is laid out in the attention kernel's operand order (krot_block, vt_block below), so that both launches
+// move whole KiB blocks: one store instruction of the rebuild = one operand of the attention.
 #include <type_traits>
 
 #include "lorc_device.h"
 #include "lorc_kernels.h"
-#include "lorc_rebuild.h"
+#include "lorc_rebuild_tile.h"
 
 namespace lorc {
 
 constexpr float kNegInfP = -__builtin_huge_valf();
 
 
-// V^T storage order inside a group of 16 positions: slot 8*hf + e holds position 8*(e/4) + 4*hf + e%4 (position q sits
-// in slot 8*((q>>2)&1) + 4*(q>>3) + (q&3)), so that the 8 positions a lane of a value operand needs are 16 bytes.
+// Scratch layout, in 1 KiB operand blocks of 64 lanes x 8 fp16; page = sequence * tiles_per_seq + page of the sequence.
+// Keys: block (page, KV head, pb, u): lane (l32, hf) holds position 32 pb + l32 and, as element e, head-dim coordinate
+// 16 u + 8 (e >> 2) + 4 hf + (e & 3).  Values: block (page, KV head, db, v): lane (l32, hf) holds coordinate 32 db + l32
+// and, as element e, position 16 v + 8 (e >> 2) + 4 hf + (e & 3).  Both orders are those in which a 32x32 accumulator
+// block lies in registers (eight consecutive registers = one lane's 16 bytes), and the V order is also the one in which
+// the attention kernel's P accumulators serve as operands.
+template <int HD>
+__device__ __forceinline__ size_t krot_block(int page, int h_kv, int g, int pb, int u) {
+  return ((((size_t)page * h_kv + g) * 2 + pb) * (HD / 16) + u) * 512;
+}
+template <int HD>
+__device__ __forceinline__ size_t vt_block(int page, int h_kv, int g, int db, int v) {
+  return ((((size_t)page * h_kv + g) * (HD / 32) + db) * 4 + v) * 512;
+}
 
 // ------------------------------------------------------------------------------------------------ rebuild
-// Ranks above kRebuildPartSteps * 16 do not fit LDS at once: the rank is then walked in parts (the accumulators of a
-// pass stay in registers across the parts; every pass copies the parts again).
-constexpr int kRebuildPartSteps = 64;  // k-steps of 16 latents per part: 64 positions x 1024 x 2 B = 128 KiB
+// One workgroup per (two pages of a sequence, 64 NC columns of K or of V).  Bound by the matrix cores at large sizes
+// (2 (r_k + r_v) n flop per position: 820 TFLOP/s at rank 512, 920 at rank 2048) and by the chip's width at small ones, which is why the columns are dealt to
+// workgroups of their own: before, one workgroup per page walked all columns, and the 8B shape's 45-page batch ran on 45
+// of 256 CUs, a rank-2048 layer copied its latents to LDS once for every eight heads.
+//   8B, rank 512, 4 x 8192 positions: 114 -> 81 us.  8B, rank 576, 2600 positions in 6 prompts: 59 -> 18 us.
+//   13B, rank 2048, 2600 positions in 3 prompts (109 GFLOP): 1277 -> 160 us.
+// NC = 4 unless its workgroups do not cover the CUs twice; NC = 2 then doubles their number.
+constexpr int kRebuildColGroups = 8;  // column groups whose workgroups run side by side on an XCD
+constexpr int kRebuildFewTiles = 64;
+__host__ __device__ inline bool rebuild_by_column(int n_pt, int ncg) { return n_pt < kRebuildFewTiles && 2 * ncg >= 8; }
 
-template <int HD>
-__global__ __launch_bounds__(256, 1) void prefill_rebuild_kernel(PrefillParams p) {
-  constexpr int NPB = 2, T = 64, HALF = HD / 2, PF = 4;
+template <int HD, int NC>
+__global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p) {
+  constexpr int HALF = HD / 2;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int seq = blockIdx.x / p.tiles_per_seq, tile = blockIdx.x % p.tiles_per_seq;
+  // Block id -> (position tile, column group of K or V); an XCD takes the block ids of one residue mod 8.
+  //  * many position tiles: an XCD takes every eighth tile; on it, the column groups run kRebuildColGroups at a time over
+  //    all of its tiles, so that the workgroups in flight share a few factor slices and latent tiles in the XCD's L2;
+  //  * fewer than kRebuildFewTiles: an XCD takes every eighth column group and all tiles.  Its share then does not depend
+  //    on which tiles the prompts' lengths leave empty (13B, prompts of 1500, 689 and 1190: 227 -> 160 us).
+  const int ncb = p.h_kv * HD / 32, ncg = (ncb + 2 * NC - 1) / (2 * NC);  // column blocks of 32; groups of K (and of V)
+  const int tps2 = (p.tiles_per_seq + 1) >> 1, n_pt = p.b * tps2;
+  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  int pt, cgi;
+  if (rebuild_by_column(n_pt, ncg)) {
+    pt = idx % n_pt;
+    cgi = idx / n_pt * 8 + xcd;
+    if (cgi >= 2 * ncg) return;
+  } else {
+    const int t8 = (n_pt + 7) >> 3, chunk = idx / (t8 * kRebuildColGroups), rest = idx - chunk * t8 * kRebuildColGroups;
+    const int left = 2 * ncg - chunk * kRebuildColGroups, width = left < kRebuildColGroups ? left : kRebuildColGroups;
+    pt = (rest / width) * 8 + xcd;
+    cgi = chunk * kRebuildColGroups + rest % width;
+  }
+  if (pt >= n_pt) return;
+  const int seq = pt / tps2, page0 = (pt - seq * tps2) * 2;
   const int len = p.cu_seqlens[seq + 1] - p.cu_seqlens[seq];
-  const int pos0 = tile * T;
-  if (pos0 >= len) return;
-  const int r_k = p.r_k, r_v = p.r_v, n = p.h_kv * HD;
-  const int rmax = r_k > r_v ? r_k : r_v;
-  const int part_cap = (rmax >> 4) < kRebuildPartSteps ? (rmax >> 4) : kRebuildPartSteps;  // k-steps the LDS tile holds
-  uint16_t* ck = reinterpret_cast<uint16_t*>(smem);
-  float2* cs_base = reinterpret_cast<float2*>(smem + (size_t)T * part_cap * 16 * 2);
+  if (page0 * kPage >= len) return;
+  const bool values = cgi >= ncg;
+  const int cb0 = (values ? cgi - ncg : cgi) * 2 * NC;
 
-  const int id = p.block_table[(size_t)seq * p.max_pages + tile];
+  const int my_page = page0 + (w >> 1), pos0 = my_page * kPage;  // the wave's page of the sequence
+  const bool live = pos0 < len;
+  const int id = live ? p.block_table[(size_t)seq * p.max_pages + my_page] : -1;
   const bool page_ok = id >= 0 && id < p.n_pages;
   const uint16_t* page = p.cache + (size_t)(page_ok ? id : 0) * p.page_elems;
+  const int n = p.h_kv * HD, spage = seq * p.tiles_per_seq + my_page;
 
-  // k-steps [ks0, ks0 + steps) of the page's K latents -> LDS, tiled [position block][k-step][64 lanes][8] (a linear
-  // copy per position block: the page tiling is the operand tiling)
-  auto copy_k_part = [&](int ks0, int steps) {
-    const int nks = r_k >> 4;
-    const u32x4* src = reinterpret_cast<const u32x4*>(page);
-    u32x4* dst = reinterpret_cast<u32x4*>(ck);
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int pb = 0; pb < NPB; ++pb)
-      for (int c = tid; c < steps * 64; c += 256)
-        dst[(size_t)pb * steps * 64 + c] = page_ok ? src[((size_t)pb * nks + ks0) * 64 + c] : z;
-  };
-  // V latents [16 ks0, 16 (ks0 + steps)): cache tile (lane = latent index, 8 consecutive positions) -> LDS in the
-  // K-style tiling (lane = position, 8 consecutive latent indices); slots past the sequence are zeroed.
-  auto copy_v_part = [&](int ks0, int steps) {
-    const uint16_t* vpart = page + (size_t)kPage * r_k;
-    const int f0 = (ks0 >> 1) * 4, f1 = ((ks0 + steps) >> 1) * 4;  // blocks of 32 latent indices x 16 positions
-    for (int f = f0 + w; f < f1; f += 4) {
-      const int nb = f >> 2, kp = f & 3;
-      const u32x4 raw = page_ok ? *reinterpret_cast<const u32x4*>(vpart + ((size_t)f * 64 + lane) * 8) : u32x4{0u, 0u, 0u, 0u};
-      const int j = nb * 32 + l32 - 16 * ks0;
+  f32x16 acc[NC][2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int slot = kp * 16 + 8 * hf + e;
-        uint16_t v = (uint16_t)(raw[e >> 1] >> (16 * (e & 1)));
-        if (pos0 + slot >= len) v = 0;
-        ck[k_index(16 * steps, slot, j)] = v;
-      }
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[c][pb][j] = 0.f;
+
+  if (!values) {
+    // rotation bases of the four position blocks: frac(base theta / 2 pi), reduced in fp64, and theta / 2 pi
+    float2* cs_base = reinterpret_cast<float2*>(smem + rt_ring_bytes<NC>());
+    if (tid < 4 * HALF) {
+      const double tr = p.rope_tab[tid % HALF] * 0.15915494309189533576888, turns = (double)(page0 * kPage + 32 * (tid / HALF)) * tr;
+      cs_base[tid] = make_float2((float)(turns - rint(turns)), (float)tr);
     }
-  };
-
-  const int fbase = HD == 128 ? 32 * (w & 1) : 0;
-  float cl[16], sl[16];
+    rebuild_tile<HD, NC, false>(acc, smem, dma_rsrc(p.bk, (uint32_t)n * p.r_k * 2u), dma_rsrc(page, page_ok ? (uint32_t)kPage * p.r_k * 2u : 0u),
+                                cb0, ncb, p.r_k >> 4, w, lane);
+    if (!live) return;
+    const float l32f = (float)l32;
 #pragma unroll
-  for (int jj = 0; jj < 16; ++jj) {
-    const float th = (float)rope_theta(fbase + acc_row(jj, hf), HD, p.rope_base);
-    sincosf((float)l32 * th, &sl[jj], &cl[jj]);
-  }
-  if (tid < NPB * HALF) cs_base[tid] = cos_sin_reduced((double)(pos0 + 32 * (tid / HALF)) * rope_theta(tid % HALF, HD, p.rope_base));
-
-  const int n_tasks = n / 64;
-  const int n_pass = (n_tasks + 3) >> 2;
-  // One pass = one task per wave (two column blocks x two position blocks), accumulated over the rank parts.
-  auto rebuild_pass = [&](f32x16 (&acc)[2][NPB], bool active, int cb0, int cb1, const uint16_t* factor, int rank, bool keys,
-                          bool first_pass) {
-    const int nks = rank >> 4;
-    const int n_parts = (nks + part_cap - 1) / part_cap;
+    for (int pr = 0; pr < NC / 2; ++pr) {  // pairs of RoPE partner blocks
+      const int ca = HD == 128 ? pr : 2 * pr, cc = HD == 128 ? pr + NC / 2 : 2 * pr + 1;
+      const int cb = cb0 + rt_col_block<HD, NC>((w & 1) * NC + ca);
+      if (cb >= ncb) continue;
+      const int g = cb / (HD / 32), fbase = 32 * (cb % (HD / 32));
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+      for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
-      for (int pb = 0; pb < NPB; ++pb)
+        for (int u = 0; u < 2; ++u) {
+          f16x8 lo, hi;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc[a][pb][j] = 0.f;
-    for (int part = 0; part < n_parts; ++part) {
-      const int ks0 = part * part_cap, steps = nks - ks0 < part_cap ? nks - ks0 : part_cap;
-      if (n_parts > 1 || first_pass) {  // a rank that fits stays in LDS for all passes
-        __syncthreads();
-        if (keys) copy_k_part(ks0, steps);
-        else copy_v_part(ks0, steps);
-        __syncthreads();
-      }
-      if (active) {  // values with the operands swapped: a lane then owns a column of V^T and 8 consecutive storage slots
-        if (keys)
-          rebuild_pair<NPB, PF, false>(acc, make_rsrc(factor, (uint32_t)n * rank * 2u), (uint32_t)(cb0 * nks + ks0) * 1024u,
-                                       (uint32_t)(cb1 * nks + ks0) * 1024u, (uint32_t)lane * 16u, ck + (size_t)lane * 8, steps);
-        else
-          rebuild_pair<NPB, PF, true>(acc, make_rsrc(factor, (uint32_t)n * rank * 2u), (uint32_t)(cb0 * nks + ks0) * 1024u,
-                                      (uint32_t)(cb1 * nks + ks0) * 1024u, (uint32_t)lane * 16u, ck + (size_t)lane * 8, steps);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  uint16_t* krot = p.krot + ((size_t)seq * p.lp + pos0) * n;
-  for (int ps = 0; ps < n_pass; ++ps) {
-    const int task = ps * 4 + w;
-    const bool active = task < n_tasks;
-    const int g = HD == 128 ? task >> 1 : task, wh = HD == 128 ? task & 1 : 0;
-    const int cb0 = HD == 128 ? g * 4 + wh : g * 2, cb1 = cb0 + (HD == 128 ? 2 : 1);
-    f32x16 acc[2][NPB];
-    rebuild_pass(acc, active, cb0, cb1, p.bk, r_k, true, ps == 0);
-    if (active) {
-#pragma unroll
-      for (int pb = 0; pb < NPB; ++pb) {
-        uint16_t* row = krot + (size_t)(pb * 32 + l32) * n + g * HD + fbase;
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          uint16_t lo[4], hi[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int jj = 4 * q4 + i;
-            const float2 cb = cs_base[pb * HALF + fbase + acc_row(jj, hf)];
-            const float cA = cb.x * cl[jj] - cb.y * sl[jj];
-            const float sA = cb.y * cl[jj] + cb.x * sl[jj];
-            const float x = acc[0][pb][jj], y = acc[1][pb][jj];
-            lo[i] = f16_bits(x * cA - y * sA);
-            hi[i] = f16_bits(y * cA + x * sA);
+          for (int e = 0; e < 8; ++e) {
+            const int j = 8 * u + e;
+            const float2 bt = cs_base[(2 * (w >> 1) + pb) * HALF + fbase + acc_row(j, hf)];
+            const float turns = __builtin_fmaf(l32f, bt.y, bt.x);
+            const float cs = __builtin_amdgcn_cosf(turns), sn = __builtin_amdgcn_sinf(turns);
+            const float x = acc[ca][pb][j], y = acc[cc][pb][j];
+            lo[e] = static_cast<_Float16>(x * cs - y * sn);
+            hi[e] = static_cast<_Float16>(y * cs + x * sn);
           }
-          const int c0 = 8 * q4 + 4 * hf;  // first of 4 consecutive head-dim coordinates
-          const u32x2 plo = {(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
-          const u32x2 phi = {(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
-          *reinterpret_cast<u32x2*>(row + c0) = plo;
-          *reinterpret_cast<u32x2*>(row + c0 + HALF) = phi;
+          *reinterpret_cast<f16x8*>(p.krot + krot_block<HD>(spage, p.h_kv, g, pb, fbase / 16 + u) + lane * 8) = lo;
+          *reinterpret_cast<f16x8*>(p.krot + krot_block<HD>(spage, p.h_kv, g, pb, (fbase + HALF) / 16 + u) + lane * 8) = hi;
         }
-      }
     }
-  }
-
-  uint16_t* vt = p.vt + (size_t)seq * n * p.lp + pos0;
-  for (int ps = 0; ps < n_pass; ++ps) {
-    const int task = ps * 4 + w;
-    const bool active = task < n_tasks;
-    const int g = HD == 128 ? task >> 1 : task, wh = HD == 128 ? task & 1 : 0;
-    const int cb0 = HD == 128 ? g * 4 + wh : g * 2, cb1 = cb0 + (HD == 128 ? 2 : 1);
-    f32x16 acc[2][NPB];
-    rebuild_pass(acc, active, cb0, cb1, p.bv, r_v, false, ps == 0);
-    if (active) {
+  } else {
+    const unsigned char* vpart = reinterpret_cast<const unsigned char*>(page) + (page_ok ? (size_t)kPage * p.r_k * 2 : 0);
+    rebuild_tile<HD, NC, true>(acc, smem, dma_rsrc(p.bv, (uint32_t)n * p.r_v * 2u), dma_rsrc(vpart, page_ok ? (uint32_t)kPage * p.r_v * 2u : 0u),
+                               cb0, ncb, p.r_v >> 4, w, lane);
+    if (!live) return;
+    const bool ragged = !page_ok || pos0 + kPage > len;  // slots past the sequence hold anything: written as zeros
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+    for (int c = 0; c < NC; ++c) {
+      const int cb = cb0 + rt_col_block<HD, NC>((w & 1) * NC + c);
+      if (cb >= ncb) continue;
+      const int g = cb / (HD / 32), db = cb % (HD / 32);
 #pragma unroll
-        for (int pb = 0; pb < NPB; ++pb) {
-          // accumulator rows = positions acc_row(jj, hf) of the block, lane = column: registers 8 u .. 8 u + 7 are the
-          // positions that the storage order keeps in slots 8 hf .. 8 hf + 7 of the block's u-th group of 16
-          uint16_t* dst = vt + (size_t)(g * HD + fbase + a * HALF + l32) * p.lp + pb * 32 + 8 * hf;
+      for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            uint32_t w4[4];
+        for (int u = 0; u < 2; ++u) {
+          f16x8 v;
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-              w4[c] = (uint32_t)f16_bits(acc[a][pb][8 * u + 2 * c]) | ((uint32_t)f16_bits(acc[a][pb][8 * u + 2 * c + 1]) << 16);
-            *reinterpret_cast<u32x4*>(dst + 16 * u) = u32x4{w4[0], w4[1], w4[2], w4[3]};
+          for (int e = 0; e < 8; ++e) {
+            const int j = 8 * u + e;
+            float x = acc[c][pb][j];
+            if (ragged && (!page_ok || pos0 + 32 * pb + acc_row(j, hf) >= len)) x = 0.f;
+            v[e] = static_cast<_Float16>(x);
           }
+          *reinterpret_cast<f16x8*>(p.vt + vt_block<HD>(spage, p.h_kv, g, db, 2 * pb + u) + lane * 8) = v;
         }
     }
   }
@@ -192,9 +165,19 @@ __global__ __launch_bounds__(256, 1) void prefill_rebuild_kernel(PrefillParams p
 // nothing to multiply.  One workgroup per (sequence, page); wave w takes position block w % 2 and the KV heads of
 // parity w / 2.  Keys: a lane of a K operand block holds one position and 8 consecutive head-dim coordinates, its
 // rotation partner the same lane and element four blocks further; rotated (angles reduced in fp64, hardware sine /
-// cosine in turns), rounded to fp16 and written as 16-byte pieces of K_rot rows.  Values: a lane of a V operand
-// block holds one column and 8 consecutive positions, which go to V^T in the permuted order the attention kernel
-// reads (two 8-byte pieces).  Slots past the sequence and pages that are not cached are written as zeros.
+// cosine in turns) and rounded to fp16.  Values: a lane of a V operand block holds one column and 8 consecutive
+// positions.  Both blocks differ from the scratch's only in which half of the wave holds which four of sixteen
+// elements (permute_halves).  Slots past the sequence and pages that are not cached are written as zeros.
+
+// Lane half hf of an operand block holds elements 8 hf .. 8 hf + 7 of sixteen; afterwards it holds 4 hf .. 4 hf + 3 and
+// 8 + 4 hf .. 8 + 4 hf + 3.
+__device__ __forceinline__ u32x4 permute_halves(u32x4 v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+  const uint32_t a0 = a[0], a1 = a[1], b0 = b[0], b1 = b[1];
+  return u32x4{a0, b0, a1, b1};
+}
+
 __global__ __launch_bounds__(256, 2) void prefill_plain_gather_kernel(PrefillParams p) {
   constexpr int HD = 128, T = 64;
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
@@ -224,7 +207,7 @@ __global__ __launch_bounds__(256, 2) void prefill_plain_gather_kernel(PrefillPar
   }
   const int blocks_per_row = n >> 4;
   const bool k_live = pos0 + 32 * pb + l32 < len;
-  uint16_t* krow = p.krot + ((size_t)seq * p.lp + pos0 + 32 * pb + l32) * n + 8 * hf;
+  const int spage = seq * p.tiles_per_seq + tile;
   for (int g = w >> 1; g < p.h_kv; g += 2) {
     u32x4 raw[8];
 #pragma unroll
@@ -246,19 +229,17 @@ __global__ __launch_bounds__(256, 2) void prefill_plain_gather_kernel(PrefillPar
         plo[c] = (uint32_t)lo[2 * c] | ((uint32_t)lo[2 * c + 1] << 16);
         phi[c] = (uint32_t)hi[2 * c] | ((uint32_t)hi[2 * c + 1] << 16);
       }
-      *reinterpret_cast<u32x4*>(krow + g * HD + 16 * kb) = plo;
-      *reinterpret_cast<u32x4*>(krow + g * HD + 16 * kb + 64) = phi;
+      *reinterpret_cast<u32x4*>(p.krot + krot_block<HD>(spage, p.h_kv, g, pb, kb) + lane * 8) = permute_halves(plo);
+      *reinterpret_cast<u32x4*>(p.krot + krot_block<HD>(spage, p.h_kv, g, pb, kb + 4) + lane * 8) = permute_halves(phi);
     }
   }
   // values: operand block (jb, kp) = columns 32 jb .. +31, positions 16 kp .. +15; wave w takes the blocks jb = w mod 4
   const uint32_t v_base = (uint32_t)kPage * n * 2u;
-  uint16_t* vt = p.vt + (size_t)seq * n * p.lp + pos0;
   for (int jb = w; jb < (n >> 5); jb += 4) {
     u32x4 raw[4];
 #pragma unroll
     for (int kp = 0; kp < 4; ++kp)
       raw[kp] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(pr, lane * 16, v_base + (jb * 4 + kp) * 1024, 0));
-    const int col = jb * 32 + l32;
 #pragma unroll
     for (int kp = 0; kp < 4; ++kp) {
       uint16_t h[8];
@@ -267,12 +248,9 @@ __global__ __launch_bounds__(256, 2) void prefill_plain_gather_kernel(PrefillPar
         const bool live = pos0 + kp * 16 + 8 * hf + e < len;
         h[e] = live ? f16_bits(bf16_to_float((uint16_t)(raw[kp][e >> 1] >> (16 * (e & 1))))) : (uint16_t)0;
       }
-      // positions 8 hf + e of the group go to storage slots 4 hf + e (e < 4) and 8 + 4 hf + e - 4 (e >= 4)
-      uint16_t* dst = vt + (size_t)col * p.lp + kp * 16;
-      const u32x2 a = {(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-      const u32x2 b = {(uint32_t)h[4] | ((uint32_t)h[5] << 16), (uint32_t)h[6] | ((uint32_t)h[7] << 16)};
-      *reinterpret_cast<u32x2*>(dst + 4 * hf) = a;
-      *reinterpret_cast<u32x2*>(dst + 8 + 4 * hf) = b;
+      const u32x4 v = {(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16),
+                       (uint32_t)h[4] | ((uint32_t)h[5] << 16), (uint32_t)h[6] | ((uint32_t)h[7] << 16)};
+      *reinterpret_cast<u32x4*>(p.vt + vt_block<HD>(spage, p.h_kv, jb >> 2, jb & 3, kp) + lane * 8) = permute_halves(v);
     }
   }
 }
@@ -292,13 +270,8 @@ __global__ __launch_bounds__(64 * kAttnWaves, kAttnWaves == 4 ? 2 : 1) void pref
   constexpr int NKF = 2 * KS, NVF = 4 * ND;  // K and V operand fragments per tile
   constexpr int RING = 8;                    // fragments in flight from LDS
   static_assert(NKF % RING == 0 && NVF % RING == 0, "fragment ring");
-  // LDS tiles with one 16-byte pad chunk per row: K tile [kpos][d] rows of HD/8 + 1 chunks, V tile [d][kpos'] rows
-  // of 9 chunks.  Padding (not XOR swizzling) keeps every operand address = one per-lane base + a compile-time
-  // offset, and the 16 rows a quarter-wave reads start in 16 different bank groups.
-  constexpr int KROW = HD / 8 + 1, VROW = BK / 8 + 1;          // chunks per padded row
-  constexpr int KTILE = BK * KROW, VTILE = HD * VROW;           // chunks per tile
-  constexpr int KINS = (KTILE + 63) / 64, VINS = (VTILE + 63) / 64;  // wave-wide 1 KiB copies per tile
-  constexpr int KELE = KINS * 64 * 8, VELE = VINS * 64 * 8;     // elements reserved per stage
+  constexpr int KINS = 4 * KS / 2, VINS = 4 * ND;               // 1 KiB operand blocks per K and V tile
+  constexpr int KELE = KINS * 512, VELE = VINS * 512;           // elements per stage
   extern __shared__ __align__(16) unsigned char smem_attn[];
   uint16_t* const sK = reinterpret_cast<uint16_t*>(smem_attn);          // [2][KELE]
   uint16_t* const sV = sK + 2 * KELE;                                   // [2][VELE]
@@ -320,45 +293,22 @@ __global__ __launch_bounds__(64 * kAttnWaves, kAttnWaves == 4 ? 2 : 1) void pref
   const int qw0 = qb * BQW + wq * 32;           // this wave's first query
   const int t_w = qw0 / BK;                     // the tile that holds this wave's diagonal
   const int dq = qw0 - t_w * BK;                // offset of the wave's first query inside that tile
-  const uint16_t* krot = p.krot + (size_t)seq * p.lp * n + g * HD;
-  const uint16_t* vt = p.vt + ((size_t)seq * n + g * HD) * p.lp;
-  const uint16_t* const kfrag = sK + (l32 * KROW + hf) * 8;  // + (mb*32*KROW + 2*ks)*8 : operand (mb, ks)
-  const uint16_t* const vfrag = sV + (l32 * VROW + hf) * 8;  // + (db*32*VROW + 2*k4)*8 : operand (db, k4)
-
-  // One K/V tile, global -> LDS directly (no staging registers).  A wave's 64 lanes fill 64 consecutive 16-byte
-  // LDS chunks; each lane fetches the global chunk that belongs there (pad chunks re-fetch the row's first).
-  constexpr int KI = (KINS + NW - 1) / NW, VI = (VINS + NW - 1) / NW;
-  uint32_t koff[KI], voff[VI];  // this lane's source offsets (elements) inside a tile, fixed for the kernel
-  static_assert(KI + VI <= NKF, "one copy per score MFMA");
-#pragma unroll
-  for (int i = 0; i < KI; ++i) {
-    int L = (i * NW + w < KINS ? i * NW + w : KINS - 1) * 64 + lane;
-    L = L < KTILE ? L : KTILE - 1;
-    const int row = L / KROW, c = L % KROW;
-    koff[i] = (uint32_t)row * n + (c < HD / 8 ? c : 0) * 8;
-  }
-#pragma unroll
-  for (int i = 0; i < VI; ++i) {
-    int L = (i * NW + w < VINS ? i * NW + w : VINS - 1) * 64 + lane;
-    L = L < VTILE ? L : VTILE - 1;
-    const int row = L / VROW, c = L % VROW;
-    voff[i] = (uint32_t)row * p.lp + (c < BK / 8 ? c : 0) * 8;
-  }
-  // (buffer loads: descriptors of this sequence's rotated keys and of this head's value rows)
-  const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(krot, (uint32_t)(((size_t)p.lp * n - g * HD) * 2));
-  const __amdgpu_buffer_rsrc_t v_rsrc = make_rsrc(vt, (uint32_t)((size_t)HD * p.lp * 2));
-  auto tile_dma_one = [&](int t, int buf, int i) {  // copy i < KI + VI of this wave's share (branch-free: a copy past
-                                                    // the tile's last one repeats the last one)
-    const uint32_t ks_off = (uint32_t)t * BK * n * 2u, vs_off = (uint32_t)t * BK * 2u;
+  // One K/V tile = one page's blocks of this KV head, global -> LDS as they lie (an operand read is 1 KiB of consecutive
+  // LDS: no conflicts).  Wave w copies the blocks w, w + 4, ...
+  constexpr int KI = KINS / NW, VI = VINS / NW;
+  static_assert(KINS % NW == 0 && VINS % NW == 0 && KI + VI <= NKF, "one copy per score MFMA");
+  const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(p.krot + (size_t)seq * p.lp * n, (uint32_t)((size_t)p.lp * n * 2));
+  const __amdgpu_buffer_rsrc_t v_rsrc = make_rsrc(p.vt + (size_t)seq * p.lp * n, (uint32_t)((size_t)p.lp * n * 2));
+  auto tile_dma_one = [&](int t, int buf, int i) {  // copy i < KI + VI of this wave's share
+    const uint32_t src = ((uint32_t)t * p.h_kv + g) * (BK * HD * 2u);
     if (i < KI) {
-      const int ins = i * NW + w < KINS ? i * NW + w : KINS - 1;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (__attribute__((address_space(3))) void*)(sK + (size_t)buf * KELE + (size_t)ins * 512), 16,
-                                               (int)(koff[i] * 2), (int)ks_off, 0, 0);
+      const int blk = i * NW + w;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (__attribute__((address_space(3))) void*)(sK + (size_t)buf * KELE + (size_t)blk * 512), 16,
+                                               lane * 16, (int)(src + blk * 1024u), 0, 0);
     } else {
-      const int j = i - KI;
-      const int ins = j * NW + w < VINS ? j * NW + w : VINS - 1;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (__attribute__((address_space(3))) void*)(sV + (size_t)buf * VELE + (size_t)ins * 512), 16,
-                                               (int)(voff[j] * 2), (int)vs_off, 0, 0);
+      const int blk = (i - KI) * NW + w;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (__attribute__((address_space(3))) void*)(sV + (size_t)buf * VELE + (size_t)blk * 512), 16,
+                                               lane * 16, (int)(src + blk * 1024u), 0, 0);
     }
   };
   auto tile_dma = [&](int t, int buf) {
@@ -378,14 +328,17 @@ __global__ __launch_bounds__(64 * kAttnWaves, kAttnWaves == 4 ? 2 : 1) void pref
       const int qpos = qw0 + l32;
       const bool ok = active && qpos < len;
       const uint16_t* qrow = p.q + ((size_t)(tok0 + (ok ? qpos : 0)) * p.h_q + (active ? h : 0)) * HD;
-      bf16x8 raw[KS];
+      bf16x8 raw[KS];  // coordinates in the order of the key blocks
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) raw[ks] = load_frag(qrow + ks * 16 + 8 * hf);
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x4 a = *reinterpret_cast<const bf16x4*>(qrow + ks * 16 + 4 * hf), b = *reinterpret_cast<const bf16x4*>(qrow + ks * 16 + 8 + 4 * hf);
+        raw[ks] = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
 #pragma unroll
       for (int ks = 0; ks < KS / 2; ++ks)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const double turns = (double)qpos * p.rope_tab[ks * 16 + 8 * hf + e] * 0.15915494309189533576888;
+          const double turns = (double)qpos * p.rope_tab[ks * 16 + acc_row(e, hf)] * 0.15915494309189533576888;
           const float fr = (float)(turns - rint(turns));
           const float c = __builtin_amdgcn_cosf(fr), sn = __builtin_amdgcn_sinf(fr);
           const float lo = (float)raw[ks][e], hi = (float)raw[ks + KS / 2][e];
@@ -412,10 +365,10 @@ __global__ __launch_bounds__(64 * kAttnWaves, kAttnWaves == 4 ? 2 : 1) void pref
     // in the issue of the loads); past the workgroup's last tile the copies repeat that tile into the idle stage.
     auto tile_step = [&](int t, auto diag_c) {  // the wave's diagonal tile is the only one that needs the mask
       const int buf = t & 1;
-      const uint16_t* const kt = kfrag + buf * KELE;
-      const uint16_t* const vtile = vfrag + buf * VELE;
-      auto k_at = [&](int i) { return load_frag_f16(kt + ((i & 1) * 32 * KROW + 2 * (i >> 1)) * 8); };    // i = 2 ks + mb
-      auto v_at = [&](int j) { return load_frag_f16(vtile + ((j % ND) * 32 * VROW + 2 * (j / ND)) * 8); };  // j = ND k4 + db
+      const uint16_t* const kt = sK + buf * KELE + lane * 8;
+      const uint16_t* const vtile = sV + buf * VELE + lane * 8;
+      auto k_at = [&](int i) { return load_frag_f16(kt + ((i & 1) * KS + (i >> 1)) * 512); };         // i = 2 ks + mb
+      auto v_at = [&](int j) { return load_frag_f16(vtile + ((j % ND) * 4 + j / ND) * 512); };      // j = ND k4 + db
       f16x8 fr[RING];
 #pragma unroll
       for (int i = 0; i < RING; ++i) fr[i] = k_at(i);
@@ -547,45 +500,48 @@ PrefillPlan make_prefill_plan(const lorc_layer_desc& d, int b, int max_seqlen) {
   return pl;
 }
 
-static size_t attn_lds_bytes(int hd) {  // two stages of padded K and V tiles, whole 1 KiB copies
-  const int ktile = 64 * (hd / 8 + 1), vtile = hd * 9;
-  return (size_t)2 * (((ktile + 63) / 64) + ((vtile + 63) / 64)) * 1024;
-}
+static size_t attn_lds_bytes(int hd) { return (size_t)2 * 2 * 64 * hd * 2; }  // two stages of a K and a V tile
 
 static int attn_grid(const PrefillParams& p) {  // one workgroup per (sequence, block of queries, KV head)
   const int bqw = 32 * (kAttnWaves / attn_heads_per_pass(p.G));
   return p.b * ((p.lp + bqw - 1) / bqw) * p.h_kv;
 }
 
+template <int HD, int NC>
+static int launch_rebuild(const PrefillParams& p, hipStream_t s) {
+  const int ncg = (p.h_kv * HD / 32 + 2 * NC - 1) / (2 * NC), n_pt = p.b * ((p.tiles_per_seq + 1) / 2);
+  const size_t lds = (size_t)rt_ring_bytes<NC>() + (size_t)4 * (HD / 2) * 8;
+  const int grid = rebuild_by_column(n_pt, ncg) ? (2 * ncg + 7) / 8 * 8 * n_pt : (n_pt + 7) / 8 * 8 * 2 * ncg;
+  return launch_kernel(prefill_rebuild_kernel<HD, NC>, dim3(grid), dim3(256), lds, s, p);
+}
+
 int set_kernel_attributes_prefill() {
   const void* kernels[] = {reinterpret_cast<const void*>(prefill_attn_kernel<128>),
                            reinterpret_cast<const void*>(prefill_attn_kernel<64>),
-                           reinterpret_cast<const void*>(prefill_rebuild_kernel<128>),
-                           reinterpret_cast<const void*>(prefill_rebuild_kernel<64>)};
+                           reinterpret_cast<const void*>(prefill_rebuild_kernel<128, 4>),
+                           reinterpret_cast<const void*>(prefill_rebuild_kernel<128, 2>),
+                           reinterpret_cast<const void*>(prefill_rebuild_kernel<64, 4>),
+                           reinterpret_cast<const void*>(prefill_rebuild_kernel<64, 2>)};
   for (const void* k : kernels)
     if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return LORC_EHIP;
   return LORC_OK;
 }
 
 int launch_prefill(const PrefillParams& p, hipStream_t s, bool plain) {
+  const bool d128 = p.head_dim == 128;
+  int rc;
   if (plain) {  // uncompressed layer: keys and values are gathered from the pages, then the same attention kernel
-    if (p.head_dim != 128) return LORC_EUNSUPPORTED;
-    const dim3 grid_g(p.b * p.tiles_per_seq), grid_att(attn_grid(p));
-    if (int rc = launch_kernel(prefill_plain_gather_kernel, grid_g, dim3(256), 0, s, p)) return rc;
-    return launch_kernel(prefill_attn_kernel<128>, grid_att, dim3(64 * kAttnWaves), attn_lds_bytes(128), s, p);
+    if (!d128) return LORC_EUNSUPPORTED;
+    rc = launch_kernel(prefill_plain_gather_kernel, dim3(p.b * p.tiles_per_seq), dim3(256), 0, s, p);
+  } else {
+    const long wgs4 = (long)p.b * ((p.tiles_per_seq + 1) / 2) * 2 * ((p.h_kv * p.head_dim + 255) / 256);
+    if (wgs4 >= 2 * 256) rc = d128 ? launch_rebuild<128, 4>(p, s) : launch_rebuild<64, 4>(p, s);
+    else rc = d128 ? launch_rebuild<128, 2>(p, s) : launch_rebuild<64, 2>(p, s);
   }
-  const int rmax = p.r_k > p.r_v ? p.r_k : p.r_v;
-  const int part = rmax < kRebuildPartSteps * 16 ? rmax : kRebuildPartSteps * 16;  // ranks beyond that are walked in parts
-  const size_t lds = (size_t)64 * part * 2 + (size_t)2 * (p.head_dim / 2) * 8;
-  if (lds > 160 * 1024) return LORC_EUNSUPPORTED;
-  const dim3 grid_r(p.b * p.tiles_per_seq), grid_a(attn_grid(p));
-  if (p.head_dim == 128) {
-    if (int rc = launch_kernel(prefill_rebuild_kernel<128>, grid_r, dim3(256), lds, s, p)) return rc;
-    return launch_kernel(prefill_attn_kernel<128>, grid_a, dim3(64 * kAttnWaves), attn_lds_bytes(128), s, p);
-  }
-  if (int rc = launch_kernel(prefill_rebuild_kernel<64>, grid_r, dim3(256), lds, s, p)) return rc;
+  if (rc != LORC_OK) return rc;
+  const dim3 grid_a(attn_grid(p));
+  if (d128) return launch_kernel(prefill_attn_kernel<128>, grid_a, dim3(64 * kAttnWaves), attn_lds_bytes(128), s, p);
   return launch_kernel(prefill_attn_kernel<64>, grid_a, dim3(64 * kAttnWaves), attn_lds_bytes(64), s, p);
 }
 
 }  // namespace lorc
-

@@ -57,3 +57,29 @@ def test_last_prefill_row_equals_decode():
     dec = layer.decode()
     last = np.stack([o[-1] for o in pre])
     assert rel_err(last, dec) <= 1e-2
+
+
+# The rebuild launch picks its columns per workgroup (256 or 128) and its block order from the number of workgroups and of
+# position tiles: each combination, with prompts that leave half of a two-page tile empty and column groups past the last
+# head.
+REBUILD = {
+    "cols256_by_tile": dict(n_q_heads=8, n_kv_heads=8, head_dim=128, rank_k=64, rank_v=96, ctx=[1 + 7 * i % 70 for i in range(70)]),
+    "cols256_by_column": dict(n_q_heads=10, n_kv_heads=10, head_dim=128, rank_k=96, rank_v=32, ctx=[1 + 11 * i % 67 for i in range(52)]),
+    "cols128_by_column_d64": dict(n_q_heads=17, n_kv_heads=17, head_dim=64, rank_k=32, rank_v=64, ctx=[190, 64, 65, 129]),
+    "cols128_by_tile_d64": dict(n_q_heads=5, n_kv_heads=5, head_dim=64, rank_k=64, rank_v=32, ctx=[63, 257]),
+}
+
+
+@pytest.mark.parametrize("name", list(REBUILD))
+def test_rebuild_dispatch(name):
+    shape = REBUILD[name]
+    n = shape["n_kv_heads"] * shape["head_dim"]
+    pb = Problem(d_model=(n + 63) // 64 * 64, rope_base=10000.0, seed=19, **shape).build()
+    layer = GpuLayer(pb)
+    layer.append_all()
+    Q = make_queries(pb, 7200)
+    ref = oracle_prefill(pb, Q)
+    scale = max(np.max(np.abs(r)) for r in ref)
+    worst = max(float(np.max(np.abs(g - r))) / scale for g, r in zip(layer.prefill(Q), ref))
+    print(f"{name}: rel err {worst:.3e}")
+    assert worst <= TOL
