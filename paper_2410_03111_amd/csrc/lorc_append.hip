@@ -5,6 +5,7 @@
 #include "lorc_device.h"
 #include "lorc_kernels.h"
 #include "lorc_rebuild.h"
+#include "lorc_tile_product.h"
 
 namespace lorc {
 
@@ -49,7 +50,7 @@ __global__ void pack_factors_kernel(const uint16_t* __restrict__ A_k, const uint
 }
 
 // ------------------------------------------------------------------------------------------------ append
-// Mid-size batches.  Block tile: BM latent rows x BN tokens (128 x 128 or 64 x 64), k-tile 64; 4 waves as 2x2.
+// Short prompts.  Block tile: 64 latent rows x 64 tokens, k-tile 64; 4 waves as 2x2.
 // LDS rows are 64 bf16 = 8 chunks of 16 B; chunk c of row r is stored at c ^ (r & 7) so that the 32 rows a
 // fragment load touches spread over all banks.  With so few workgroups the walk over the model dimension is a
 // chain of memory latencies, so every thread keeps PF k-tiles of both operands in flight in registers (buffer
@@ -58,9 +59,8 @@ constexpr int kApBK = 64;
 
 __device__ __forceinline__ int swz(int row, int chunk) { return (row * 8 + (chunk ^ (row & 7))) * 8; }
 
-template <int BM, int PF>
 __global__ __launch_bounds__(256) void append_kernel(AppendParams p) {
-  constexpr int BN = BM, NB = BM / 64, LD = BM / 32;  // accumulator blocks per wave and side; 16-byte loads per thread, operand and k-tile
+  constexpr int BM = 64, PF = 8, BN = BM, NB = BM / 64, LD = BM / 32;  // accumulator blocks per wave and side; 16-byte loads per thread, operand and k-tile
   static_assert(PF % 2 == 0, "the LDS buffer of a k-tile is chosen by its stage's parity");
   __shared__ __align__(16) uint16_t sA[2][BM * kApBK];
   __shared__ __align__(16) uint16_t sB[2][BN * kApBK];
@@ -174,6 +174,116 @@ __global__ __launch_bounds__(256) void append_kernel(AppendParams p) {
         } else {
 #pragma unroll
           for (int i = 0; i < 4; ++i) base[v_index(p.r_k, slot, j - p.r_k + i)] = v[i];
+        }
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------ append, tiled
+// 64 NC latent rows (of K or of V) x 128 tokens per workgroup (lorc_tile_product.h).  A CU takes 64 bytes per clock through
+// its vector memory path, so 32 of the model dimension cannot be faster than 256 cycles at NC = 2 (16 KiB for 256
+// matrix-core cycles) or 384 at NC = 4 (24 KiB for 512); with barrier and operand reads one workgroup alone needs about
+// 500 and 850, two on a CU overlap.  Forms (NC, NS, KT): (2, 5, 4) all of LDS, for at most one workgroup per CU;
+// (2, 2, 4) and (4, 3, 2) leave room for two.
+// Epilogue: lanes own tokens in K row blocks and latent indices in V row blocks (operands swapped), so that after
+// permute_halves a lane holds one 16-byte piece of a page's tiling: eight latent indices of a token, or eight
+// consecutive slots of a latent index.
+template <int NC, int NS, int KT>
+__global__ __launch_bounds__(256, 2) void append_tile_kernel(AppendParams p) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Block id -> tile.  An XCD (block id mod 8) takes a contiguous eighth of the tiles in an order whose inner index runs
+  // over the operand with fewer bytes, so that its L2 holds a slice of the larger operand and streams the smaller.
+  const int ncg_k = (p.r_k + 64 * NC - 1) / (64 * NC), ncg_v = (p.r_v + 64 * NC - 1) / (64 * NC), ncg = ncg_k + ncg_v;
+  const int n_t = (p.T + 127) >> 7, total = ncg * n_t, per_xcd = (total + 7) >> 3;
+  const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || lin >= total) return;
+  const bool rows_inner = p.T > p.r_k + p.r_v;
+  const int cg = rows_inner ? lin % ncg : lin / n_t, t0 = (rows_inner ? lin / ncg : lin % n_t) * 128;
+  const bool v_rows = cg >= ncg_k;
+  const int rank = v_rows ? p.r_v : p.r_k, cb0 = (v_rows ? cg - ncg_k : cg) * 2 * NC, ncb = rank >> 5, nks = p.D >> 4;
+
+  // where the tile's tokens go (looked up now: the latency hides behind the product)
+  long long my_page = -1;
+  int my_slot = 0;
+  if (tid < 128 && t0 + tid < p.T) {
+    const int seq = p.slot_seq[t0 + tid], pos = p.slot_pos[t0 + tid];
+    if (seq >= 0 && seq < p.n_seqs && pos >= 0 && pos < p.max_pages * kPage) {
+      const int page = p.block_table[(size_t)seq * p.max_pages + pos / kPage];
+      if (page >= 0 && page < p.n_pages) {
+        my_page = (long long)page * (long long)p.page_elems;
+        my_slot = pos % kPage;
+      }
+    }
+  }
+  f32x16 acc[NC][2];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[c][pb][j] = 0.f;
+  const u32x4 at = dma_rsrc(p.at_tiled + (v_rows ? (size_t)p.r_k * p.D : 0), (uint32_t)rank * (uint32_t)p.D * 2u);
+  const int left = p.T - t0 < 128 ? p.T - t0 : 128;
+  const u32x4 x = dma_rsrc(p.x + (size_t)t0 * p.D, (uint32_t)left * (uint32_t)p.D * 2u);
+  const int n_kt = p.D / (16 * KT);
+  if (v_rows) tile_product<64, NC, NS, kRows, true, KT>(acc, smem, at, x, cb0, ncb, nks, w, lane, n_kt, (uint32_t)p.D * 2u);
+  else tile_product<64, NC, NS, kRows, false, KT>(acc, smem, at, x, cb0, ncb, nks, w, lane, n_kt, (uint32_t)p.D * 2u);
+  __syncthreads();
+  long long* tok_page = reinterpret_cast<long long*>(smem);
+  int* tok_slot = reinterpret_cast<int*>(tok_page + 128);
+  if (tid < 128) {
+    tok_page[tid] = my_page;
+    tok_slot[tid] = my_slot;
+  }
+  __syncthreads();
+  auto pack8 = [&](const f32x16& a, int u) {
+    u32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (uint32_t)bf16_bits(a[8 * u + 2 * i]) | ((uint32_t)bf16_bits(a[8 * u + 2 * i + 1]) << 16);
+    return permute_halves(v);
+  };
+#pragma unroll
+  for (int pb = 0; pb < 2; ++pb) {
+    const int tl = 64 * (w >> 1) + 32 * pb;  // first token (of the tile) of the position block
+    if (!v_rows) {
+      const long long page = tok_page[tl + l32];
+      const int slot = tok_slot[tl + l32];
+      uint16_t* dst = p.cache + (page < 0 ? 0 : page) + ((size_t)(slot >> 5) * (p.r_k >> 4) * 64 + (slot & 31) + 32 * hf) * 8;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int cb = cb0 + (w & 1) * NC + c;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const u32x4 v = pack8(acc[c][pb], u);
+          if (cb < ncb && page >= 0) *reinterpret_cast<u32x4*>(dst + (size_t)(2 * cb + u) * 512) = v;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int t8 = tl + 16 * u + 8 * hf;  // this lane's eight tokens
+        const long long page0 = tok_page[t8];
+        const int s0 = tok_slot[t8];
+        bool run = page0 >= 0 && (s0 & 7) == 0;  // eight consecutive slots of one page: one piece of the V tiling
+#pragma unroll
+        for (int i = 1; i < 8; ++i) run = run && tok_page[t8 + i] == page0 && tok_slot[t8 + i] == s0 + i;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const int cb = cb0 + (w & 1) * NC + c;
+          const u32x4 v = pack8(acc[c][pb], u);
+          if (cb >= ncb) continue;
+          if (run) {
+            *reinterpret_cast<u32x4*>(p.cache + page0 + v_index(p.r_k, s0, 32 * cb + l32)) = v;
+          } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              const long long page = tok_page[t8 + i];
+              if (page >= 0) p.cache[page + v_index(p.r_k, tok_slot[t8 + i], 32 * cb + l32)] = (uint16_t)(v[i >> 1] >> (16 * (i & 1)));
+            }
+          }
         }
       }
     }
@@ -620,35 +730,53 @@ int launch_pack(const lorc_layer_desc& d, const void* A_k, const void* A_v, cons
 }
 
 int set_kernel_attributes_append() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(append_gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             160 * 1024) == hipSuccess ? LORC_OK : LORC_EHIP;
+  const void* kernels[] = {reinterpret_cast<const void*>(append_gemm_kernel), reinterpret_cast<const void*>(append_tile_kernel<4, 3, 2>),
+                           reinterpret_cast<const void*>(append_tile_kernel<2, 5, 4>), reinterpret_cast<const void*>(append_tile_kernel<2, 2, 4>)};
+  for (const void* k : kernels)
+    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return LORC_EHIP;
+  return LORC_OK;
 }
 
-// Which kernel takes which batch (measured, 8B shape, us per call):  T = 64: dot-product kernel 21, 64-tile GEMM 23;
-// T = 128: 38 / 23;  T = 256 .. 1024: 64-tile GEMM 21 .. 27;  T = 2048: 64-tile 39 .. 45, 128-tile 45 .. 55;
-// T = 4096: 64-tile 73 .. 81, 128-tile 49, 256-tile 75;  T = 8192: 128-tile 97, 256-tile 86;  T = 16384: 185 / 114.
-// Below a few thousand tokens every GEMM is bound by its serial walk over the model dimension with few workgroups
-// (splitting it would need scratch memory, which this entry point does not take).
-constexpr int kSkinnyMaxT = 64, kGemmMinT = 8192, kSmallTileMaxWgs = 512;
+// Which kernel takes which batch.  Up to 64 tokens: dot products (8B shape: 21 us at T = 64, 34 at T = 100; the 64-tile
+// GEMM takes 20 from T = 65 on).  Then the 64-tile GEMM while it has about one workgroup per CU: 8B rank 576, 24 us at
+// T = 777 (234 workgroups) against 35 for 128 x 128 tiles; 13B rank 2048, 52 against 41 at T = 300 (320 workgroups).
+// Beyond, the cheapest of three tile sizes by the estimates below: microseconds per 32 of the model dimension, fitted to
+// D 4096 .. 8192, ranks 512 .. 2048, T 300 .. 32768 (measured us, 128 x 128 / 256 x 128 / 256 x 256 tiles):
+//   8B rank 576: T = 3116: 40 / 58 / 98,  6002: 67 / 101 / 105,  12288: - / 158 / 110,  16384: - / 185 / 199;
+//   13B rank 2048: T = 777: 43 / 64 / -,  3116: 144 / 139 / 136,  6002: 274 / 246 / 273,  8192: - / 325 / 278.
+constexpr int kSkinnyMaxT = 64, kSmallTileMaxWgs = 288;
+
+static double append_tile_cost(int tile, int rows_k, int rows_v, int T, int n_cus) {  // tile 0: 128 x 128, 1: 256 x 128, 2: 256 x 256
+  const int rows = tile == 0 ? 128 : 256, cols = tile == 2 ? 256 : 128;
+  auto up = [](int x, int y) { return (x + y - 1) / y; };
+  const int groups = tile == 2 ? up(rows_k + rows_v, rows) : up(rows_k, rows) + up(rows_v, rows);
+  const double load = (double)groups * up(T, cols) / n_cus;  // tiles per CU
+  if (tile == 0) return load <= 1 ? 0.31 : (load <= 2 ? 0.24 + 0.155 * load : (load <= 3.14 ? 0.88 : 0.28 * load));
+  if (tile == 1) return load <= 1 ? 0.36 + 0.18 * load : (load <= 1.64 ? 0.82 : 0.50 * load);
+  const double rest = load - (int)load;  // one workgroup per CU: whole rounds, the last one shorter when it is not full
+  return 0.9 * (int)load + (rest > 0 ? 0.55 + 0.35 * rest : 0);
+}
 
 int launch_append(const AppendParams& p, int n_cus, hipStream_t s) {
-  if (p.T <= kSkinnyMaxT) return launch_kernel(append_skinny_kernel, dim3((p.r_k + p.r_v) / kSkRows), dim3(256), 0, s, p);
-  if (p.T >= kGemmMinT && p.D % kGmBK == 0 && p.D / kGmBK >= 2) {
-    const size_t lds = kGmLdsBytes;
-    const int nx = (p.T + kGmBN - 1) / kGmBN, ny = (p.r_k + p.r_v + kGmBM - 1) / kGmBM;
-    const int n_virtual = ((nx + 7) / 8) * 8 * ny, slots = (n_cus / 8) * 8;
-    dim3 grid(n_virtual < slots ? n_virtual : slots);
-    return launch_kernel(append_gemm_kernel, grid, dim3(256), lds, s, p);
-  }
-  // the small tile while all its workgroups are resident at once (two per CU)
   const int rt = p.r_k + p.r_v;
-  const long wg64 = (long)((p.T + 63) / 64) * ((rt + 63) / 64);
-  if (wg64 <= kSmallTileMaxWgs) {
-    dim3 grid((p.T + 63) / 64, (rt + 63) / 64);
-    return launch_kernel(append_kernel<64, 8>, grid, dim3(256), 0, s, p);
+  if (p.T <= kSkinnyMaxT) return launch_kernel(append_skinny_kernel, dim3(rt / kSkRows), dim3(256), 0, s, p);
+  const dim3 grid64((p.T + 63) / 64, (rt + 63) / 64);
+  if ((long)grid64.x * grid64.y <= (long)kSmallTileMaxWgs * n_cus / 256) return launch_kernel(append_kernel, grid64, dim3(256), 0, s, p);
+  double cost[3];
+  for (int i = 0; i < 3; ++i) cost[i] = append_tile_cost(i, p.r_k, p.r_v, p.T, n_cus);
+  if (cost[2] < cost[0] && cost[2] < cost[1] && p.D / kGmBK >= 2) {
+    const int nx = (p.T + kGmBN - 1) / kGmBN, ny = (rt + kGmBM - 1) / kGmBM;
+    const int n_virtual = ((nx + 7) / 8) * 8 * ny, slots = (n_cus / 8) * 8;
+    return launch_kernel(append_gemm_kernel, dim3(n_virtual < slots ? n_virtual : slots), dim3(256), kGmLdsBytes, s, p);
   }
-  dim3 grid((p.T + 127) / 128, (rt + 127) / 128);
-  return launch_kernel(append_kernel<128, 4>, grid, dim3(256), 0, s, p);
+  auto grid = [&](int rows) {
+    const int tiles = ((p.r_k + rows - 1) / rows + (p.r_v + rows - 1) / rows) * ((p.T + 127) / 128);
+    return dim3((tiles + 7) / 8 * 8);
+  };
+  if (cost[1] < cost[0]) return launch_kernel(append_tile_kernel<4, 3, 2>, grid(256), dim3(256), rt_ring_bytes<4, 3, 2>(), s, p);
+  const dim3 g = grid(128);
+  if ((int)g.x <= n_cus) return launch_kernel(append_tile_kernel<2, 5, 4>, g, dim3(256), rt_ring_bytes<2, 5, 4>(), s, p);
+  return launch_kernel(append_tile_kernel<2, 2, 4>, g, dim3(256), rt_ring_bytes<2, 2, 4>(), s, p);
 }
 
 int launch_stream_probe(const void* src, size_t bytes, void* sink, hipStream_t s) {

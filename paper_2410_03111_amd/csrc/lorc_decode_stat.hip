@@ -21,9 +21,6 @@
 // tile while another is being read.  Their completion is tracked by hand (fixed number of loads per wave between
 // any two waits, s_waitcnt vmcnt(N) immediates).  The K tile is a ring of four chunks, each refilled for the next
 // tile as soon as all waves have consumed it, so every chunk has a whole tile time to arrive.
-#include <type_traits>
-#include <utility>
-
 #include "lorc_device.h"
 #include "lorc_kernels.h"
 #include "lorc_rebuild.h"
@@ -40,16 +37,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4s;
 // it receives D[m = 4*(l/16) + j][n = l%16] in register j.
 __device__ __forceinline__ f32x4s mfma16(bf16x8 a, bf16x8 b, f32x4s c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order, every index a compile-time constant.
-template <int... Is, class F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, Is...>, F&& f) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
 }  // namespace

@@ -5,6 +5,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "lorc_layout.h"
 
 namespace lorc {
@@ -84,6 +87,27 @@ __device__ __forceinline__ float2 half_pair(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
   const uint32_t r0 = r[0], r1 = r[1];
   return make_float2(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1));
+}
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order, every index a compile-time constant.
+template <int... Is, class F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, Is...>, F&& f) {
+  (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
+
+// Sixteen 16-bit elements over the two halves of a wave: lane half hf holds elements 8 hf .. 8 hf + 7 before, and
+// 4 hf .. 4 hf + 3, 8 + 4 hf .. 8 + 4 hf + 3 afterwards (the order of eight consecutive accumulator registers).  Its own
+// inverse.
+__device__ __forceinline__ u32x4 permute_halves(u32x4 v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+  const uint32_t a0 = a[0], a1 = a[1], b0 = b[0], b1 = b[1];
+  return u32x4{a0, b0, a1, b1};
 }
 
 // Index of the lane in its wavefront, from the hardware mask counters: two VALU ops, no register kept alive.

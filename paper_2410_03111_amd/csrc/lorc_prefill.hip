@@ -2,7 +2,7 @@
 // to rebuilt keys as in the Appendix on the adjusted position embedding).
 //
 // Two launches per call:
-//   rebuild : a tiled matrix product over (two pages) x (64 NC columns), keys and values alike (lorc_rebuild_tile.h).
+//   rebuild : a tiled matrix product over (two pages) x (64 NC columns), keys and values alike (lorc_tile_product.h).
 //             Keys are rotated in registers and written once to scratch as fp16; values likewise, transposed.
 //   attend  : flash-style causal attention.  One workgroup per (sequence, 64-query block, KV head); each wave
 //             owns one query head of the group.  S^T = K Q^T so that a lane owns one query column: row maxima
@@ -14,7 +14,7 @@
 
 #include "lorc_device.h"
 #include "lorc_kernels.h"
-#include "lorc_rebuild_tile.h"
+#include "lorc_tile_product.h"
 
 namespace lorc {
 
@@ -97,13 +97,13 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
 
   if (!values) {
     // rotation bases of the four position blocks: frac(base theta / 2 pi), reduced in fp64, and theta / 2 pi
-    float2* cs_base = reinterpret_cast<float2*>(smem + rt_ring_bytes<NC>());
+    float2* cs_base = reinterpret_cast<float2*>(smem + rt_ring_bytes<NC, 3>());
     if (tid < 4 * HALF) {
       const double tr = p.rope_tab[tid % HALF] * 0.15915494309189533576888, turns = (double)(page0 * kPage + 32 * (tid / HALF)) * tr;
       cs_base[tid] = make_float2((float)(turns - rint(turns)), (float)tr);
     }
-    rebuild_tile<HD, NC, false>(acc, smem, dma_rsrc(p.bk, (uint32_t)n * p.r_k * 2u), dma_rsrc(page, page_ok ? (uint32_t)kPage * p.r_k * 2u : 0u),
-                                cb0, ncb, p.r_k >> 4, w, lane);
+    tile_product<HD, NC, 3, kPageKeys, false>(acc, smem, dma_rsrc(p.bk, (uint32_t)n * p.r_k * 2u), dma_rsrc(page, page_ok ? (uint32_t)kPage * p.r_k * 2u : 0u),
+                                cb0, ncb, p.r_k >> 4, w, lane, p.r_k >> 5);
     if (!live) return;
     const float l32f = (float)l32;
 #pragma unroll
@@ -133,8 +133,8 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
     }
   } else {
     const unsigned char* vpart = reinterpret_cast<const unsigned char*>(page) + (page_ok ? (size_t)kPage * p.r_k * 2 : 0);
-    rebuild_tile<HD, NC, true>(acc, smem, dma_rsrc(p.bv, (uint32_t)n * p.r_v * 2u), dma_rsrc(vpart, page_ok ? (uint32_t)kPage * p.r_v * 2u : 0u),
-                               cb0, ncb, p.r_v >> 4, w, lane);
+    tile_product<HD, NC, 3, kPageValues, true>(acc, smem, dma_rsrc(p.bv, (uint32_t)n * p.r_v * 2u), dma_rsrc(vpart, page_ok ? (uint32_t)kPage * p.r_v * 2u : 0u),
+                               cb0, ncb, p.r_v >> 4, w, lane, p.r_v >> 5);
     if (!live) return;
     const bool ragged = !page_ok || pos0 + kPage > len;  // slots past the sequence hold anything: written as zeros
 #pragma unroll
@@ -168,15 +168,6 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
 // cosine in turns) and rounded to fp16.  Values: a lane of a V operand block holds one column and 8 consecutive
 // positions.  Both blocks differ from the scratch's only in which half of the wave holds which four of sixteen
 // elements (permute_halves).  Slots past the sequence and pages that are not cached are written as zeros.
-
-// Lane half hf of an operand block holds elements 8 hf .. 8 hf + 7 of sixteen; afterwards it holds 4 hf .. 4 hf + 3 and
-// 8 + 4 hf .. 8 + 4 hf + 3.
-__device__ __forceinline__ u32x4 permute_halves(u32x4 v) {
-  const auto a = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
-  const auto b = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
-  const uint32_t a0 = a[0], a1 = a[1], b0 = b[0], b1 = b[1];
-  return u32x4{a0, b0, a1, b1};
-}
 
 __global__ __launch_bounds__(256, 2) void prefill_plain_gather_kernel(PrefillParams p) {
   constexpr int HD = 128, T = 64;
@@ -510,7 +501,7 @@ static int attn_grid(const PrefillParams& p) {  // one workgroup per (sequence, 
 template <int HD, int NC>
 static int launch_rebuild(const PrefillParams& p, hipStream_t s) {
   const int ncg = (p.h_kv * HD / 32 + 2 * NC - 1) / (2 * NC), n_pt = p.b * ((p.tiles_per_seq + 1) / 2);
-  const size_t lds = (size_t)rt_ring_bytes<NC>() + (size_t)4 * (HD / 2) * 8;
+  const size_t lds = (size_t)rt_ring_bytes<NC, 3>() + (size_t)4 * (HD / 2) * 8;
   const int grid = rebuild_by_column(n_pt, ncg) ? (2 * ncg + 7) / 8 * 8 * n_pt : (n_pt + 7) / 8 * 8 * 2 * ncg;
   return launch_kernel(prefill_rebuild_kernel<HD, NC>, dim3(grid), dim3(256), lds, s, p);
 }

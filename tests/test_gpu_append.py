@@ -9,7 +9,7 @@ from lorc_testlib import GpuLayer, Problem, PAGE, page_gather_indices
 pytestmark = pytest.mark.gpu
 
 
-def _append_and_compare_pool(geom, ctx, density=1.0, seed=5):
+def _append_and_compare_pool(geom, ctx, density=1.0, seed=5, shuffle=True):
     """Appends integer-valued tokens (a fraction `density` of them non-zero) and compares the whole pool, byte for
     byte, with the latents placed by the documented index formulas.  Returns (L, desc, idx) for further checks."""
     import torch
@@ -35,7 +35,7 @@ def _append_and_compare_pool(geom, ctx, density=1.0, seed=5):
     # tokens in shuffled order: the slot arrays, not the order in x, decide where a latent goes
     seq = np.concatenate([np.full(N, s, np.int32) for s, N in enumerate(ctx)])
     pos = np.concatenate([np.arange(N, dtype=np.int32) for N in ctx])
-    perm = rng.permutation(T)
+    perm = rng.permutation(T) if shuffle else np.arange(T)
     L.append_latent(desc, bf(X[perm]), packed, torch.from_numpy(seq[perm]).to(dev), torch.from_numpy(pos[perm]).to(dev),
                     torch.from_numpy(bt).to(dev), cache)
     torch.cuda.synchronize()
@@ -78,6 +78,19 @@ def test_model_dimension_tails_are_bit_exact(D, case):
                  "128_row_tile": ((D, 4, 64, 256, 224), [4100, 1, 90]),
                  "256_row_tile": ((D, 2, 64, 64, 32), [8100, 1, 90])}[case]
     _append_and_compare_pool(geom, ctx, density=0.2, seed=D)
+
+
+# Sizes on either side of the rules that pick the tile of a prompt's down-projection (256 CUs): workgroup counts that make
+# 128 x 128, 256 x 128 and 256 x 256 tiles the cheapest; row groups that end inside a tile, ragged token tiles.
+TILES = {"128x128": ((512, 544), [1107, 1, 64, 78]), "256x128": ((480, 512), [77, 4058, 1, 64]), "256x256": ((512, 512), [64, 15759, 77])}
+
+
+@pytest.mark.parametrize("shuffle", [False, True], ids=["prompt_order", "shuffled"])
+@pytest.mark.parametrize("D", [64, 192, 640])
+@pytest.mark.parametrize("case", list(TILES))
+def test_prompt_tiles_are_bit_exact(case, D, shuffle):
+    (r_k, r_v), ctx = TILES[case]
+    _append_and_compare_pool((D, 8, 128, r_k, r_v), ctx, density=0.2, seed=D, shuffle=shuffle)
 
 
 def test_out_of_range_slots_are_skipped():
