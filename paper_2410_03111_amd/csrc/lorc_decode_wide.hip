@@ -1,13 +1,13 @@
 // Decode attention in three launches, for the shapes the single-pass split kernels do not take:
 //   * wide layers: ranks above 1024 (Table 2's LLaMA-2-13B row: MHA, 40 heads, n = 5120 compressed to 2048).  A tile's
 //     K latents no longer fit LDS and the latent-space output of all heads no longer fits one workgroup's registers,
-//     so the rank is walked in parts and o_lat in column chunks;
+//     so the rank is walked through a ring and o_lat in column chunks;
 //   * layers that Algorithm 1's threshold leaves uncompressed (Section 6.2): the cache pages hold the un-rotated
 //     keys and the values themselves (rank = n, identity read-side factors that are never stored or multiplied).
 //
 //   scores : S[seq][h][t] = softmax_scale * log2(e) * <R(q_pos) q_h, R(t) k_t>   (Eq. 1; the Appendix on the adjusted
-//            position embedding: keys are rotated when they are read).  Wide layers rebuild k_t = c_t B_k per KV head
-//            on the matrix cores, the rank in parts of up to 512 that pass through LDS; uncompressed layers read k_t.
+//            position embedding: keys are rotated when they are read).  Wide layers rebuild k_t = c_t B_k on the matrix
+//            cores, the rank walked through an LDS ring; uncompressed layers read k_t.
 //   values : per (sequence, context split, column chunk): row maxima of the split's scores, P = exp2(S - m), row
 //            sums, o = P C_v for the chunk's columns on the matrix cores; written as split partials (m, l, o / l) in
 //            the format of the single-pass kernels.  Wide layers: all heads x 512 latent columns per workgroup (the
@@ -16,161 +16,151 @@
 #include "lorc_device.h"
 #include "lorc_kernels.h"
 #include "lorc_rebuild.h"
+#include "lorc_tile_product.h"
 
 namespace lorc {
 
 namespace {
 constexpr float kNegInfW = -__builtin_huge_valf();
-constexpr int kWideT = 64;           // positions per tile = one page
-constexpr int kWidePartSteps = 32;   // k-steps (of 16 latents) of one rank part in LDS: 64 x 512 x 2 B = 64 KiB, two workgroups per CU
-constexpr int kWideHeadsPerWg = 4;   // KV heads per workgroup of the wide scores kernel (one per wave)
+constexpr int kWideT = 64;           // positions per tile of the value kernel = one page
 constexpr int kWideMaxG = 8;
+constexpr int kScoreNC = 4;          // column blocks per wave of the scores kernel: the 128 columns of one KV head
+constexpr int kScorePairs = 8;       // head pairs whose workgroups run side by side on an XCD
+constexpr int kScoreFewTiles = 64;
 
-__host__ __device__ inline size_t wide_scores_lds_bytes(int r_k, int G) {
-  const int part = r_k < kWidePartSteps * 16 ? r_k : kWidePartSteps * 16;
-  size_t b = (size_t)kWideT * part * 2;              // one rank part of the tile's K latents
-  b += (size_t)2 * 64 * 8;                           // rotation bases of the two position blocks
-  b += (size_t)kWideHeadsPerWg * G * 128 * 2;        // rotated, scaled queries of the workgroup's heads (fp16)
-  return b;
+constexpr int kScoreSlots = 3;       // ring of 3 x 24 KiB: two workgroups share a CU
+constexpr int kScorePages = 2;       // pages per workgroup
+// ring, rotation bases of the four position blocks, rotated and scaled queries of two KV heads (fp16)
+constexpr int kScoreLdsBytes = rt_ring_bytes<kScoreNC, kScoreSlots>() + 4 * 64 * 8 + 2 * kWideMaxG * 128 * 2;
+__host__ __device__ inline bool scores_by_pair(int n_pt, int n_pairs) { return n_pt < kScoreFewTiles && n_pairs >= 8; }
+// Block ids of the scores launch (the kernel's mapping, below): eight XCDs' shares of equal length.
+inline unsigned scores_grid(int n_pt, int n_pairs) {
+  if (scores_by_pair(n_pt, n_pairs)) return 8u * n_pt * ((n_pairs + 7) / 8);
+  return 8u * ((n_pt + 7) / 8) * n_pairs;
 }
 }  // namespace
 
-// ------------------------------------------------------------------------------------------------ scores, wide
-// One workgroup per (group of four KV heads, sequence, 64-position tile), the head group outermost in the block
-// index: the workgroups in flight at one time work on the same four heads, whose B_k slice (4 x 128 columns x r_k)
-// stays in the L2 caches while the latents stream past.  Wave w owns KV head 4 * group + w.  Two passes (the two
-// halves of the head's rotation pairs: columns [32 wh, 32 wh + 32) and their partners 64 further), each walking the
-// rank in parts: a part of the tile's K latents is copied to LDS, every wave accumulates its 2 x 2 blocks of K^T
-// over the part's k-steps with B_k operands streamed from L2, and after the last part rotates the blocks and
-// multiplies them with its head group's query rows (fp16 matrix-core op, accumulated over the two passes).
-// Two workgroups share a CU: while one copies a part (direct global -> LDS loads) the other multiplies.
+// ------------------------------------------------------------------------------------------------ scores, compressed
+// One workgroup per (pair of KV heads, two cached pages of a sequence): the rebuild K^T = B_k^T C_k^T of 256 columns x 128
+// positions as a tiled matrix product (lorc_tile_product.h).  A wave's accumulators hold whole keys (one KV head, one page):
+// they are rotated in registers and multiplied with the group's query rows (fp16 matrix-core op), and the scores are
+// complete without an exchange between waves.  Bound by the matrix cores: 2 r_k n flop per position.
+//   13B layer, rank 2048, 16 x 4096 positions, whole call with append: 1684 -> 1270 us (1.1 PFLOP/s).  Before, a wave
+//   streamed its factor operands from L2, two products per operand, and copied a page's latents twice.
+//   Tried: 256 positions per workgroup (256 accumulators per lane, one workgroup per CU, two products per operand read):
+//   no faster there (1238 against 1247 us), 592 against 539 at rank 768 (8B layer, 32 x 8192) and 62 against 55 at one short sequence: with one
+//   workgroup per CU nothing runs under another's prologue and rotation.
 __global__ __launch_bounds__(256, 2) void wide_scores_kernel(DecodeParams p) {
-  constexpr int HD = 128, HALF = 64, T = kWideT, NPB = 2, PF = 4;
+  constexpr int HD = 128, HALF = 64, NC = kScoreNC, NS = kScoreSlots, PB = 2;
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tiles = p.score_stride / T;
-  const int per_group = p.b * tiles;
-  const int hg = blockIdx.x / per_group, rem = blockIdx.x % per_group;
-  const int seq = rem / tiles, tile = rem % tiles;
+  // Block id -> (position tile, head pair); an XCD takes the block ids of one residue mod 8: every eighth position tile,
+  // kScorePairs head pairs at a time over all of them, so that the workgroups in flight share factor slices and latents in
+  // the XCD's L2; with few position tiles every eighth head pair and all tiles.
+  const int pages = p.score_stride / kPage, tps = (pages + kScorePages - 1) / kScorePages, n_pt = p.b * tps, n_pairs = (p.h_kv + 1) >> 1;
+  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  int pt, pair;
+  if (scores_by_pair(n_pt, n_pairs)) {
+    pt = idx % n_pt;
+    pair = idx / n_pt * 8 + xcd;
+    if (pair >= n_pairs) return;
+  } else {
+    const int t8 = (n_pt + 7) >> 3, chunk = idx / (t8 * kScorePairs), rest = idx - chunk * t8 * kScorePairs;
+    const int left = n_pairs - chunk * kScorePairs, width = left < kScorePairs ? left : kScorePairs;
+    pt = (rest / width) * 8 + xcd;
+    pair = chunk * kScorePairs + rest % width;
+  }
+  if (pt >= n_pt) return;
+  const int seq = pt / tps, page0 = (pt - seq * tps) * kScorePages, pos0 = page0 * kPage;
   int ctx = p.ctx_len[seq];
   ctx = ctx < 0 ? 0 : (ctx > p.max_ctx ? p.max_ctx : ctx);
-  const int pos0 = tile * T;
   if (pos0 >= ctx) return;  // whole workgroup: nothing of this tile is attended to
-  const int r_k = p.r_k, G = p.G, nks = r_k >> 4;
-  const int part_steps = nks < kWidePartSteps ? nks : kWidePartSteps;
-  const int n_parts = (nks + part_steps - 1) / part_steps;
+  const int G = p.G, r_k = p.r_k, ncb = p.h_kv * (HD / 32);
 
-  uint16_t* ck = reinterpret_cast<uint16_t*>(smem);
-  float2* cs_base = reinterpret_cast<float2*>(smem + (size_t)T * part_steps * 16 * 2);
-  _Float16* qrot = reinterpret_cast<_Float16*>(cs_base + NPB * HALF);  // [4 heads x G][HD]
-
-  const int id = p.block_table[(size_t)seq * p.max_pages + tile];
+  // the wave's page; one that is not cached, or past the context, reads as zeros (nothing is fetched)
+  const int cpage = page0 + (w >> 1);
+  const int id = cpage * kPage < ctx ? p.block_table[(size_t)seq * p.max_pages + cpage] : -1;
   const bool page_ok = id >= 0 && id < p.n_pages;
-  const uint16_t* page = uniform_ptr(p.cache + (size_t)(page_ok ? id : 0) * p.page_elems);
-  const __amdgpu_buffer_rsrc_t page_rsrc = make_rsrc(page, (uint32_t)kPage * r_k * 2u);
-  const int q_pos = p.q_pos[seq];
+  const u32x4 page = dma_rsrc(p.cache + (size_t)(page_ok ? id : 0) * p.page_elems, page_ok ? (uint32_t)kPage * r_k * 2u : 0u);
 
-  // rotation bases of the tile's two position blocks, and the workgroup's query rows rotated at q_pos
-  if (tid < NPB * HALF) cs_base[tid] = cos_sin_reduced((double)(pos0 + 32 * (tid / HALF)) * p.rope_tab[tid % HALF]);
-  const int g0 = hg * kWideHeadsPerWg;
-  for (int idx = tid; idx < kWideHeadsPerWg * G * HALF; idx += 256) {
-    const int hl = idx / HALF, i = idx % HALF;
-    const int h = g0 * G + hl;
-    if (h < p.h_q) {
-      const float2 cs = cos_sin_reduced((double)q_pos * p.rope_tab[i]);
-      const uint16_t* qs = p.q + ((size_t)seq * p.h_q + h) * HD;
-      const float lo = bf16_to_float(qs[i]) * p.q_scale, hi = bf16_to_float(qs[i + HALF]) * p.q_scale;
-      qrot[hl * HD + i] = static_cast<_Float16>(lo * cs.x - hi * cs.y);
-      qrot[hl * HD + i + HALF] = static_cast<_Float16>(hi * cs.x + lo * cs.y);
+  float2* const cs_base = reinterpret_cast<float2*>(smem + rt_ring_bytes<NC, NS>());  // [4 position blocks][HALF]
+  _Float16* const qrot = reinterpret_cast<_Float16*>(cs_base + 4 * HALF);               // [2 heads x G][HD]
+  // rotation bases of the position blocks, and the two groups' query rows rotated at q_pos and scaled
+  auto setup = [&]() {
+    cs_base[tid] = cos_sin_reduced((double)(pos0 + 32 * (tid / HALF)) * p.rope_tab[tid % HALF]);  // 4 x HALF = 256
+    const int q_pos = p.q_pos[seq];
+    for (int i = tid; i < 2 * G * HALF; i += 256) {
+      const int hl = i / HALF, f = i % HALF, h = pair * 2 * G + hl;
+      if (h < p.h_q) {
+        const float2 cs = cos_sin_reduced((double)q_pos * p.rope_tab[f]);
+        const uint16_t* qs = p.q + ((size_t)seq * p.h_q + h) * HD;
+        const float lo = bf16_to_float(qs[f]) * p.q_scale, hi = bf16_to_float(qs[f + HALF]) * p.q_scale;
+        qrot[hl * HD + f] = static_cast<_Float16>(lo * cs.x - hi * cs.y);
+        qrot[hl * HD + f + HALF] = static_cast<_Float16>(hi * cs.x + lo * cs.y);
+      }
     }
-  }
-
-  const int g = g0 + w;
-  const bool active = g < p.h_kv;
-  const __amdgpu_buffer_rsrc_t bk_rsrc = make_rsrc(p.bk, (uint32_t)p.h_kv * HD * r_k * 2u);
-  f32x16 S[NPB];
+  };
+  f32x16 acc[NC][PB];
 #pragma unroll
-  for (int pb = 0; pb < NPB; ++pb)
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[c][pb][j] = 0.f;
+  tile_product<HD, NC, NS, kPageKeys, false>(acc, smem, dma_rsrc(p.bk, (uint32_t)p.h_kv * HD * r_k * 2u), page, pair * 2 * NC, ncb,
+                                                    r_k >> 4, w, lane, r_k >> 5, 0, setup);
+  const int gl = w & 1, g = pair * 2 + gl;
+  if (g >= p.h_kv) return;
+  const bool qreal = l32 < G;
+  const _Float16* qh = qrot + (size_t)(gl * G + (qreal ? l32 : 0)) * HD + 4 * hf;
+  f32x16 S[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
     for (int j = 0; j < 16; ++j) S[pb][j] = 0.f;
-
-  for (int wh = 0; wh < 2; ++wh) {
-    const int fbase = 32 * wh;
-    const int cb0 = g * 4 + wh, cb1 = cb0 + 2;
-    f32x16 acc[2][NPB];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+  for (int wh = 0; wh < 2; ++wh) {  // halves of the head's rotation pairs: columns [32 wh, 32 wh + 32) and their partners
+    // Query operands (m = query head of the group, k = 16 head-dim coordinates) in the order in which the rotated K^T
+    // accumulators serve as B operands: element e of operand s4 is coordinate 16 (s4 & 1) + 8 (e >> 2) + 4 hf + (e & 3) of
+    // half s4 >> 1 of the head, + 32 wh.
+    f16x8 qf[4];
 #pragma unroll
-      for (int pb = 0; pb < NPB; ++pb)
+    for (int s4 = 0; s4 < 4; ++s4) {
+      const _Float16* src = qh + 32 * wh + HALF * (s4 >> 1) + 16 * (s4 & 1);
+      const u32x2 lo = *reinterpret_cast<const u32x2*>(src), hi = *reinterpret_cast<const u32x2*>(src + 8);
+      const u32x4 v = {qreal ? lo[0] : 0u, qreal ? lo[1] : 0u, qreal ? hi[0] : 0u, qreal ? hi[1] : 0u};
+      qf[s4] = __builtin_bit_cast(f16x8, v);
+    }
+    float2 cl[16];  // rotation by the lane's offset inside a position block, the same for all blocks (at most 5 turns)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc[a][pb][j] = 0.f;
-    for (int part = 0; part < n_parts; ++part) {
-      const int ks0 = part * part_steps;
-      const int steps = nks - ks0 < part_steps ? nks - ks0 : part_steps;
-      if (!(n_parts == 1 && wh == 1)) {  // a single part stays in LDS for the second pass
-        __syncthreads();                 // the previous part's operand reads are over
-        if (page_ok) {                   // 1 KiB per instruction, the LDS image being the page's own tiling
-          for (int pb = 0; pb < NPB; ++pb)
-            for (int blk = w; blk < steps; blk += 4)
-              __builtin_amdgcn_raw_ptr_buffer_load_lds(page_rsrc, (__attribute__((address_space(3))) void*)(ck + (size_t)(pb * steps + blk) * 512),
-                                                       16, lane * 16, (pb * nks + ks0 + blk) * 1024, 0, 0);
-        } else {
-          const u32x4 z = {0u, 0u, 0u, 0u};
-          u32x4* dst = reinterpret_cast<u32x4*>(ck);
-          for (int c = tid; c < NPB * steps * 64; c += 256) dst[c] = z;
-        }
+    for (int jj = 0; jj < 16; ++jj) cl[jj] = p.lane_cs[l32 * HALF + 32 * wh + acc_row(jj, hf)];
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      f16x8 kf[4];
+#pragma unroll
+      for (int jj = 0; jj < 16; ++jj) {
+        const float2 cb = cs_base[((w >> 1) * PB + pb) * HALF + 32 * wh + acc_row(jj, hf)];
+        const float cA = cb.x * cl[jj].x - cb.y * cl[jj].y;
+        const float sA = cb.y * cl[jj].x + cb.x * cl[jj].y;
+        const float x = acc[wh][pb][jj], y = acc[wh + 2][pb][jj];
+        kf[jj >> 3][jj & 7] = static_cast<_Float16>(x * cA - y * sA);
+        kf[2 + (jj >> 3)][jj & 7] = static_cast<_Float16>(y * cA + x * sA);
       }
-      __syncthreads();                   // (its fence also waits for the copies)
-      if (active)
-        rebuild_pair<NPB, PF>(acc, bk_rsrc, (uint32_t)(cb0 * nks + ks0) * 1024u, (uint32_t)(cb1 * nks + ks0) * 1024u,
-                              (uint32_t)lane * 16u, ck + (size_t)lane * 8, steps);
+#pragma unroll
+      for (int s4 = 0; s4 < 4; ++s4) S[pb] = mfma32_f16(qf[s4], kf[s4], S[pb]);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (active) {
-      // Query operands (m = query head of the group, k = 16 head-dim coordinates) in the order in which the rotated
-      // K^T accumulators serve as B operands: element e of operand s4 is coordinate 16 (s4 & 1) + 8 (e >> 2) + 4 hf
-      // + (e & 3) of half s4 >> 1 of the head, + 32 wh.
-      f16x8 qf[4];
-      {
-        const bool qreal = l32 < G && g * G + l32 < p.h_q;
-        const _Float16* qh = qrot + (size_t)(w * G + (qreal ? l32 : 0)) * HD + fbase + 4 * hf;
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) {
-          const _Float16* src = qh + HALF * (s4 >> 1) + 16 * (s4 & 1);
-          const u32x2 lo = *reinterpret_cast<const u32x2*>(src), hi = *reinterpret_cast<const u32x2*>(src + 8);
-          const u32x4 v = {qreal ? lo[0] : 0u, qreal ? lo[1] : 0u, qreal ? hi[0] : 0u, qreal ? hi[1] : 0u};
-          qf[s4] = __builtin_bit_cast(f16x8, v);
-        }
-      }
-#pragma unroll
-      for (int pb = 0; pb < NPB; ++pb) {
-        f16x8 kf[4];
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-          const int fi = fbase + acc_row(jj, hf);
-          const float2 cb = cs_base[pb * HALF + fi];
-          const float2 cl = p.lane_cs[l32 * HALF + fi];
-          const float cA = cb.x * cl.x - cb.y * cl.y;
-          const float sA = cb.y * cl.x + cb.x * cl.y;
-          const float x = acc[0][pb][jj], y = acc[1][pb][jj];
-          kf[jj >> 3][jj & 7] = static_cast<_Float16>(x * cA - y * sA);
-          kf[2 + (jj >> 3)][jj & 7] = static_cast<_Float16>(y * cA + x * sA);
-        }
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) S[pb] = mfma32_f16(qf[s4], kf[s4], S[pb]);
-      }
-    }
   }
-  if (active) {
 #pragma unroll
-    for (int jr = 0; jr < 4; ++jr) {  // rows 0 .. 7 of the score block hold the group's (at most eight) heads
-      const int m = acc_row(jr, hf);
-      const int h = g * G + m;
-      if (m < G && h < p.h_q) {
-        float* row = p.scores + ((size_t)seq * p.h_q + h) * p.score_stride + pos0;
+  for (int jr = 0; jr < 4; ++jr) {  // rows 0 .. 7 of the score block hold the group's (at most eight) heads
+    const int m = acc_row(jr, hf);
+    if (m < G) {
+      float* row = p.scores + ((size_t)seq * p.h_q + g * G + m) * p.score_stride;
 #pragma unroll
-        for (int pb = 0; pb < NPB; ++pb) row[pb * 32 + l32] = S[pb][jr];
+      for (int pb = 0; pb < PB; ++pb) {
+        const int pos = pos0 + kPage * (w >> 1) + 32 * pb;
+        if (pos < p.score_stride) row[pos + l32] = S[pb][jr];
       }
     }
   }
@@ -537,8 +527,7 @@ static size_t align256w(size_t x) { return (x + 255) & ~(size_t)255; }
 
 bool wide_shape_ok(const lorc_layer_desc& d) {
   const int G = d.n_q_heads / d.n_kv_heads;
-  return d.head_dim == 128 && G <= kWideMaxG && d.n_q_heads <= 64 && d.rank_k <= kWideMaxRank && d.rank_v <= kWideMaxRank &&
-         wide_scores_lds_bytes(d.rank_k, G) <= 160 * 1024;
+  return d.head_dim == 128 && G <= kWideMaxG && d.n_q_heads <= 64 && d.rank_k <= kWideMaxRank && d.rank_v <= kWideMaxRank;
 }
 
 bool plain_shape_ok(const lorc_layer_desc& d) {
@@ -578,7 +567,7 @@ DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cu
 }
 
 int set_kernel_attributes_decode_wide() {
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(wide_scores_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(wide_scores_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kScoreLdsBytes) != hipSuccess)
     return LORC_EHIP;
   return LORC_OK;
 }
@@ -605,10 +594,10 @@ int launch_decode_wide(const DecodeParams& p, const DecodePlan& plan, hipStream_
     if (int rc = launch_kernel(plain_scores_kernel, dim3(p.b * tiles), dim3(256), lds, s, p)) return rc;
     return launch_kernel(latent_pv_kernel<1, 1, true>, dim3(p.b * p.n_splits * p.h_kv), dim3(256), 0, s, p);
   }
-  const size_t lds = wide_scores_lds_bytes(p.r_k, p.G);
-  if (lds > 160 * 1024 || p.G > kWideMaxG) return LORC_EUNSUPPORTED;
-  const int groups = (p.h_kv + kWideHeadsPerWg - 1) / kWideHeadsPerWg;
-  if (int rc = launch_kernel(wide_scores_kernel, dim3(groups * p.b * tiles), dim3(256), lds, s, p)) return rc;
+  if (p.G > kWideMaxG) return LORC_EUNSUPPORTED;
+  const int n_pairs = (p.h_kv + 1) / 2;
+  const int n_pt = p.b * ((tiles + kScorePages - 1) / kScorePages);
+  if (int rc = launch_kernel(wide_scores_kernel, dim3(scores_grid(n_pt, n_pairs)), dim3(256), kScoreLdsBytes, s, p)) return rc;
   const dim3 grid(p.b * p.n_splits * p.v_chunks);
   if (qb == 1) return launch_kernel(latent_pv_kernel<1, 4, false>, grid, dim3(256), 0, s, p);
   return launch_kernel(latent_pv_kernel<2, 4, false>, grid, dim3(256), 0, s, p);

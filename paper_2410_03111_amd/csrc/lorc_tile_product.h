@@ -34,10 +34,12 @@ enum TileSource {
 //              ncb: blocks in all (a block past the last repeats it; its results are not to be used)
 //   source   : descriptor of the K (or V) part of page w >> 1 (size zero: a page that is not cached reads as zeros), or of
 //              the tile's token rows (rows past its size read as zeros)
+//   setup    : called once the first copies are on their way; its LDS writes outside the ring are visible afterwards
 // SWAP: the operands change places, so that a lane owns a factor column and its registers walk the positions.
-template <int HD, int NC, int NS, TileSource SRC, bool SWAP, int KT = 2>
+struct NoSetup { __device__ __forceinline__ void operator()() const {} };
+template <int HD, int NC, int NS, TileSource SRC, bool SWAP, int KT = 2, class Setup = NoSetup>
 __device__ __forceinline__ void tile_product(f32x16 (&acc)[NC][2], unsigned char* ring, u32x4 factor, u32x4 source, int cb0, int ncb,
-                                             int nks, int w, int lane, int n_kt, uint32_t row_bytes = 0) {
+                                             int nks, int w, int lane, int n_kt, uint32_t row_bytes = 0, Setup setup = Setup{}) {
   static_assert(KT == 2 || (KT == 4 && SRC == kRows), "k-steps per slot");
   constexpr int FC = NC * KT / 2, COPIES = FC + KT;  // copies per wave and slot
   const int hf = lane >> 5;
@@ -95,21 +97,26 @@ __device__ __forceinline__ void tile_product(f32x16 (&acc)[NC][2], unsigned char
       return load_frag(reinterpret_cast<const uint16_t*>(ls + (pb * 2 + ks) * 1024));
     }
   };
+  // k-tiles past the last one are asked for with descriptors of size zero: the number of copies in flight stays fixed and
+  // nothing is fetched
+  u32x4 factor_kt = factor, source_kt = source;
+  auto select_tile = [&](int kt) {
+    factor_kt[2] = kt < n_kt ? factor[2] : 0u;
+    source_kt[2] = kt < n_kt ? source[2] : 0u;
+  };
   auto copy_one = [&](int kt, uint32_t slot, int i) {
     if (i < FC) {
       const int j = i / KT, ks = i % KT;
-      dma_1k(factor, ring_off + slot + (uint32_t)((w * (NC / 2) + j) * KT + ks) * 1024u, lane16, fsrc[j] + (uint32_t)(KT * kt + ks) * 1024u);
+      dma_1k(factor_kt, ring_off + slot + (uint32_t)((w * (NC / 2) + j) * KT + ks) * 1024u, lane16, fsrc[j] + (uint32_t)(KT * kt + ks) * 1024u);
     } else {
       const int u = i - FC;
       const uint32_t dst = ring_off + slot + (uint32_t)(2 * NC * KT + KT * w + u) * 1024u;
-      if constexpr (SRC == kPageValues) dma_1k(source, dst, vlane[u], (uint32_t)(4 * kt + 2 * (w & 1) + u) * 1024u);
-      else if constexpr (SRC == kRows) dma_1k(source, dst, vlane[u], (uint32_t)kt * (KT * 32u));
-      else dma_1k(source, dst, lane16, (uint32_t)((w & 1) * nks + 2 * kt + u) * 1024u);
+      if constexpr (SRC == kPageValues) dma_1k(source_kt, dst, vlane[u], (uint32_t)(4 * kt + 2 * (w & 1) + u) * 1024u);
+      else if constexpr (SRC == kRows) dma_1k(source_kt, dst, vlane[u], (uint32_t)kt * (KT * 32u));
+      else dma_1k(source_kt, dst, lane16, (uint32_t)((w & 1) * nks + 2 * kt + u) * 1024u);
     }
   };
   constexpr int SLOT = rt_ring_bytes<NC, 1, KT>();
-  // k-tiles past the last one repeat it (their copies are never used): the number of copies in flight stays fixed
-  auto clamped = [&](int kt) { return kt < n_kt ? kt : n_kt - 1; };
   bf16x8 a[2][KT][NC], b[2][KT][2];  // operands of the k-tile that is multiplied and of the next one: [set][k-step]
   constexpr int READS = KT * (NC + 2), PRODUCTS = 2 * KT * NC;
   auto read_one = [&](auto set_c, const unsigned char* fs, const unsigned char* ls, auto i_c) {  // in the order of use
@@ -124,7 +131,8 @@ __device__ __forceinline__ void tile_product(f32x16 (&acc)[NC][2], unsigned char
   auto k_tile = [&](auto set_c, int kt) {
     constexpr int SET = decltype(set_c)::value;
     dma_barrier<(NS - 2) * COPIES>();  // k-tile kt + 1 has landed, younger ones may be in flight
-    const int k_new = clamped(kt + NS);
+    const int k_new = kt + NS;
+    select_tile(k_new);
     const unsigned char *fs = fbase + s_next, *ls = lbase + s_next;
     static_for<PRODUCTS>([&](auto i_c) {
       constexpr int i = decltype(i_c)::value, ks = i / (2 * NC), c = (i % (2 * NC)) >> 1, pb = i & 1;
@@ -138,16 +146,19 @@ __device__ __forceinline__ void tile_product(f32x16 (&acc)[NC][2], unsigned char
   };
   static_assert(READS <= PRODUCTS && 2 * COPIES <= PRODUCTS, "one read per product, one copy per two");
 #pragma unroll
-  for (int t = 0; t < NS; ++t)
+  for (int t = 0; t < NS; ++t) {
+    select_tile(t);
 #pragma unroll
-    for (int i = 0; i < COPIES; ++i) copy_one(clamped(t), t * SLOT, i);
+    for (int i = 0; i < COPIES; ++i) copy_one(t, t * SLOT, i);
+  }
+  setup();
   dma_barrier<(NS - 1) * COPIES>();
   static_for<READS>([&](auto i_c) { read_one(std::integral_constant<int, 0>{}, fbase, lbase, i_c); });
   for (int kt = 0; kt < n_kt; kt += 2) {
     k_tile(std::integral_constant<int, 0>{}, kt);
     if (kt + 1 < n_kt) k_tile(std::integral_constant<int, 1>{}, kt + 1);
   }
-  __builtin_amdgcn_s_waitcnt(0);  // the repeated copies have landed before the ring is reused
+  __builtin_amdgcn_s_waitcnt(0);  // the copies past the end have written their zeros before the ring is reused
 }
 
 }  // namespace lorc
