@@ -568,39 +568,56 @@ __global__ __launch_bounds__(256, 1) void append_gemm_kernel(AppendParams p) {
 }
 
 // ------------------------------------------------------------------------------------------- append, small T
-// Decode-time append: a handful of tokens against the whole down-projection.  The work is one pass over the
-// weights (8 MiB for the 8B shape); a CU pulls a few tens of GB/s at best, so the pass must be spread over all of
-// them: one workgroup per FOUR latent rows (256 workgroups for 1024 rows), no matrix cores.  Each thread owns an
-// 8-wide slice of the model dimension per trip, multiplies it against up to 16 tokens with packed bf16 dot
-// products (fp32 accumulation), and the 4 x 16 partial sums of the 256 threads meet in LDS.
-constexpr int kSkRows = 4, kSkTok = 16;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-// Pair c of an 8-element operand.  Taken with a vector shuffle: re-interpreting one 32-bit element of an integer
-// vector as a bf16 pair was observed to be mis-compiled (every pair read element 0) by this toolchain.
-__device__ __forceinline__ bf16x2 bf16_pair(bf16x8 v, int c) {
-  switch (c) {
-    case 0: return __builtin_shufflevector(v, v, 0, 1);
-    case 1: return __builtin_shufflevector(v, v, 2, 3);
-    case 2: return __builtin_shufflevector(v, v, 4, 5);
-    default: return __builtin_shufflevector(v, v, 6, 7);
-  }
-}
+// Decode-time append: a handful of tokens against the whole down-projection.  The work is one pass over the weights (8 MiB
+// for the 8B shape) and a CU pulls a few tens of GB/s at best, so the rows are dealt evenly to all CUs: `rows` of them
+// (at most 16) per workgroup of sixteen waves.  A wave owns a sixteenth of the model dimension: 16x16x32 products, A = the
+// workgroup's rows (rows past them read as zeros through the descriptor and fetch nothing), B = 16 tokens, every operand
+// of a trip requested before the first product; the waves' partial sums meet in LDS.  The work is a chain of one load
+// latency, the reduction and a store, so a mostly empty row operand costs nothing.
+//   Kernel, us (dot products over 4 rows per workgroup before): 8B rank 512, T = 16: 6.2 -> 4.5; T = 32: 16 -> 13;
+//   8B uncompressed, T = 16: 11.4 -> 9.5; 13B rank 2048, T = 16: 31 -> 18.
 
-__global__ __launch_bounds__(256) void append_skinny_kernel(AppendParams p) {
-  constexpr int NO = kSkRows * kSkTok, RS = NO + 1;  // outputs per workgroup; padded row stride (bank-conflict free)
-  __shared__ float red[128 * RS];                    // [thread pair][output]
-  const int tid = threadIdx.x;
-  const int j0 = blockIdx.x * kSkRows;
-  const int D = p.D;
-  for (int t0 = 0; t0 < p.T; t0 += kSkTok) {
-    const int nt = p.T - t0 < kSkTok ? p.T - t0 : kSkTok;
-    // Where output (row o / 16, token t0 + o % 16) goes: looked up by thread o now, so that the chain of
-    // dependent loads overlaps the pass over the weights.
+constexpr int kSkWaves = 16, kSkSteps = 8, kSkMaxRows = 16;
+template <int TG>  // groups of 16 tokens
+__global__ __launch_bounds__(64 * kSkWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void append_skinny_kernel(AppendParams p, int rows) {
+  __shared__ float red[kSkWaves][TG][16][16];  // [wave][token group][row][token]
+  const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, q = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int D = p.D, rt = p.r_k + p.r_v, j0 = blockIdx.x * rows;
+  const int n_rows = rt - j0 < rows ? rt - j0 : rows;
+  const int n_steps = D >> 5, per_wave = (n_steps + kSkWaves - 1) / kSkWaves, s_begin = w * per_wave;
+  const int s_end = s_begin + per_wave < n_steps ? s_begin + per_wave : n_steps;
+  const __amdgpu_buffer_rsrc_t ar = make_rsrc(uniform_ptr(p.at + (size_t)j0 * D), (uint32_t)n_rows * (uint32_t)D * 2u);
+  constexpr uint32_t kPast = 0x80000000u;  // past every descriptor: reads as zero
+  for (int t0 = 0; t0 < p.T; t0 += 16 * TG) {
+    const int nt = p.T - t0 < 16 * TG ? p.T - t0 : 16 * TG;
+    const __amdgpu_buffer_rsrc_t xr = make_rsrc(uniform_ptr(p.x + (size_t)t0 * D), (uint32_t)nt * (uint32_t)D * 2u);
+    f32x4 acc[TG];
+#pragma unroll
+    for (int g = 0; g < TG; ++g)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[g][j] = 0.f;
+    for (int s0 = s_begin; s0 < s_end; s0 += kSkSteps) {
+      bf16x8 a[kSkSteps], b[kSkSteps][TG];
+#pragma unroll
+      for (int u = 0; u < kSkSteps; ++u) {
+        const uint32_t at_k = s0 + u < s_end ? (uint32_t)(s0 + u) * 64u + (uint32_t)q * 16u : kPast;
+        a[u] = buf_frag(ar, m < n_rows ? (uint32_t)(m * D) * 2u + at_k : kPast, 0);
+#pragma unroll
+        for (int g = 0; g < TG; ++g) b[u][g] = buf_frag(xr, (uint32_t)((16 * g + m) * D) * 2u + at_k, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // every request before the first product
+#pragma unroll
+      for (int u = 0; u < kSkSteps; ++u)
+#pragma unroll
+        for (int g = 0; g < TG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], b[u][g], acc[g], 0, 0, 0);
+    }
+    // Where output (row o / 16 TG, token t0 + o % 16 TG) goes: looked up by thread o.
+    const int o = tid, orow = o / (16 * TG), ot = o % (16 * TG);
     long long dst_page = -1;
     int dst_slot = 0;
-    if (tid < kSkRows * kSkTok && (tid % kSkTok) < nt) {
-      const int t = t0 + tid % kSkTok;
-      const int seq = p.slot_seq[t], pos = p.slot_pos[t];
+    if (orow < n_rows && ot < nt) {
+      const int seq = p.slot_seq[t0 + ot], pos = p.slot_pos[t0 + ot];
       if (seq >= 0 && seq < p.n_seqs && pos >= 0 && pos < p.max_pages * kPage) {
         const int page = p.block_table[(size_t)seq * p.max_pages + pos / kPage];
         if (page >= 0 && page < p.n_pages) {
@@ -609,65 +626,18 @@ __global__ __launch_bounds__(256) void append_skinny_kernel(AppendParams p) {
         }
       }
     }
-    float acc[kSkRows][kSkTok];
-#pragma unroll
-    for (int r = 0; r < kSkRows; ++r)
-#pragma unroll
-      for (int t = 0; t < kSkTok; ++t) acc[r][t] = 0.f;
-    // two 8-wide slices per trip: 40 independent 16-byte loads in flight per thread
-    for (int k0 = tid * 8; k0 < D; k0 += 2 * 256 * 8) {
-      const int k1 = k0 + 256 * 8 < D ? k0 + 256 * 8 : k0;  // second slice (repeated and weighted zero past the end)
-      const bool two = k0 + 256 * 8 < D;
-      bf16x8 wv[2][kSkRows], xv[2][kSkTok];
-#pragma unroll
-      for (int r = 0; r < kSkRows; ++r) {
-        wv[0][r] = load_frag(p.at + (size_t)(j0 + r) * D + k0);
-        wv[1][r] = load_frag(p.at + (size_t)(j0 + r) * D + k1);
-      }
-#pragma unroll
-      for (int t = 0; t < kSkTok; ++t) {  // tokens past the batch re-read the last one; their sums are never stored
-        const uint16_t* xr = p.x + (size_t)(t0 + (t < nt ? t : nt - 1)) * D;
-        xv[0][t] = load_frag(xr + k0);
-        xv[1][t] = load_frag(xr + k1);
-      }
-      if (!two) {
-#pragma unroll
-        for (int r = 0; r < kSkRows; ++r) wv[1][r] = zero_frag();
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int r = 0; r < kSkRows; ++r)
-#pragma unroll
-          for (int t = 0; t < kSkTok; ++t)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-              acc[r][t] = __builtin_amdgcn_fdot2_f32_bf16(bf16_pair(wv[h][r], c), bf16_pair(xv[h][t], c), acc[r][t], false);
-    }
     __syncthreads();  // the previous token pass is done with red
-    // neighbouring threads are added in registers (one DPP step), the even one files the pair's sums
 #pragma unroll
-    for (int r = 0; r < kSkRows; ++r)
+    for (int g = 0; g < TG; ++g)
 #pragma unroll
-      for (int t = 0; t < kSkTok; ++t) {
-        const float v = acc[r][t] + half_wave_peer<0>(acc[r][t]);
-        if ((tid & 1) == 0) red[(tid >> 1) * RS + r * kSkTok + t] = v;
-      }
+      for (int j = 0; j < 4; ++j) red[w][g][4 * q + j][m] = acc[g][j];  // accumulator: row 4 q + j, token m
     __syncthreads();
-    float part = 0.f;
-    {
-      const int o = tid & 63, q = tid >> 6;  // output o, quarter q of the pairs
-#pragma unroll 16
-      for (int i = 0; i < 32; ++i) part += red[(q * 32 + i) * RS + o];
-    }
-    __syncthreads();  // everyone has read its partial sums: the front of red is reused for the four quarters
-    red[tid] = part;
-    __syncthreads();
-    if (tid < kSkRows * kSkTok && dst_page >= 0) {
-      const float v = red[tid] + red[64 + tid] + red[128 + tid] + red[192 + tid];  // kSkRows * kSkTok == 64 outputs
-      const int j = j0 + tid / kSkTok;
-      uint16_t* base = p.cache + dst_page;
-      base[j < p.r_k ? k_index(p.r_k, dst_slot, j) : v_index(p.r_k, dst_slot, j - p.r_k)] = bf16_bits(v);
+    if (dst_page >= 0) {
+      float v = 0.f;
+#pragma unroll
+      for (int i = 0; i < kSkWaves; ++i) v += red[i][ot >> 4][orow][ot & 15];
+      const int j = j0 + orow;
+      p.cache[dst_page + (j < p.r_k ? k_index(p.r_k, dst_slot, j) : v_index(p.r_k, dst_slot, j - p.r_k))] = bf16_bits(v);
     }
   }
 }
@@ -759,7 +729,13 @@ static double append_tile_cost(int tile, int rows_k, int rows_v, int T, int n_cu
 
 int launch_append(const AppendParams& p, int n_cus, hipStream_t s) {
   const int rt = p.r_k + p.r_v;
-  if (p.T <= kSkinnyMaxT) return launch_kernel(append_skinny_kernel, dim3(rt / kSkRows), dim3(256), 0, s, p);
+  if (p.T <= kSkinnyMaxT) {
+    int rows = (rt + n_cus - 1) / n_cus;  // one workgroup per CU while 16 rows each suffice
+    if (rows > kSkMaxRows) rows = kSkMaxRows;
+    const dim3 grid((rt + rows - 1) / rows), block(64 * kSkWaves);
+    if (p.T <= 16) return launch_kernel(append_skinny_kernel<1>, grid, block, 0, s, p, rows);
+    return launch_kernel(append_skinny_kernel<2>, grid, block, 0, s, p, rows);
+  }
   const dim3 grid64((p.T + 63) / 64, (rt + 63) / 64);
   if ((long)grid64.x * grid64.y <= (long)kSmallTileMaxWgs * n_cus / 256) return launch_kernel(append_kernel, grid64, dim3(256), 0, s, p);
   double cost[3];

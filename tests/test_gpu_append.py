@@ -93,6 +93,14 @@ def test_prompt_tiles_are_bit_exact(case, D, shuffle):
     _append_and_compare_pool((D, 8, 128, r_k, r_v), ctx, density=0.2, seed=D, shuffle=shuffle)
 
 
+# Rows per workgroup of the small-batch kernel (256 CUs): 1, 5 with a single row left over, and 16; model dimensions of fewer
+# k-steps than it has waves, of one trip and of a second, mostly empty one; both token-group counts and a second pass.
+@pytest.mark.parametrize("D", [64, 192, 4096, 4160])
+@pytest.mark.parametrize("r_k,r_v,ctx", [(32, 32, [1]), (544, 512, [9, 7]), (544, 512, [17]), (2048, 2016, [1, 2]), (2048, 2016, [30, 3, 1])])
+def test_small_batch_row_groups_are_bit_exact(D, r_k, r_v, ctx):
+    _append_and_compare_pool((D, (max(r_k, r_v) + 127) // 128, 128, r_k, r_v), ctx, density=0.2 if D < 4096 else 0.02, seed=D + r_k)
+
+
 def test_out_of_range_slots_are_skipped():
     import torch
     import paper_2410_03111_amd as L
