@@ -10,6 +10,13 @@ import ctypes
 import os
 from dataclasses import dataclass
 
+try:
+    # torch bundles its own HIP runtime under the same soname as the system's; loading torch before the library makes the
+    # library bind to that copy, so that stream handles and device pointers belong to one runtime
+    import torch
+except ImportError:  # the host functions need numpy alone
+    torch = None
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "liblorc.so")
 
@@ -44,12 +51,6 @@ def layer_desc(d_model, n_q_heads, n_kv_heads, head_dim, rank_k, rank_v, rope_ba
 def _load():
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: build it with `python paper_2410_03111_amd/build.py`")
-    try:
-        # torch bundles its own HIP runtime under the same soname; loading torch first makes this library
-        # bind to that copy, so that stream handles and device pointers belong to one runtime
-        import torch  # noqa: F401
-    except ImportError:
-        pass
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
     dp = ctypes.POINTER(ctypes.c_double)
@@ -107,17 +108,18 @@ def _check(code: int, where: str):
         raise LorcError(code, where)
 
 
+# A decode call launches 15 to 30 us of GPU work at small sizes, so the marshalling is kept below that: plain integers for
+# pointers, the current stream's handle without a Stream object, sizes asked of the library only where they are used
+# (append + decode of one 8B sequence: 24 -> 16 us of host time).
 def _ptr(t):
-    return ctypes.c_void_p(None if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev(t, dtype, name):
-    import torch
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype):
         raise TypeError(f"{name}: expected a contiguous CUDA tensor of dtype {dtype}")
     return t
@@ -209,7 +211,6 @@ def pack_factors(desc: LayerDesc, A_k, A_v, B_k, B_v, packed=None):
     """A_k [D, r_k], A_v [D, r_v], B_k [r_k, n], B_v [r_v, n] bf16 CUDA tensors -> packed uint8 buffer.
 
     B_k = B_v = None packs an uncompressed layer (rank_k = rank_v = n, A = W)."""
-    import torch
     for t, nm in ((A_k, "A_k"), (A_v, "A_v")) + (() if B_k is None and B_v is None else ((B_k, "B_k"), (B_v, "B_v"))):
         _dev(t, torch.bfloat16, nm)
     assert tuple(A_k.shape) == (desc.d_model, desc.rank_k) and tuple(A_v.shape) == (desc.d_model, desc.rank_v)
@@ -227,7 +228,6 @@ def pack_factors(desc: LayerDesc, A_k, A_v, B_k, B_v, packed=None):
 
 def append_latent(desc: LayerDesc, x, packed, slot_seq, slot_pos, block_table, cache):
     """x [T, D] bf16; slot_seq/slot_pos [T] int32; block_table [n_seqs, max_pages] int32; cache uint8 pool."""
-    import torch
     _dev(x, torch.bfloat16, "x")
     _dev(slot_seq, torch.int32, "slot_seq")
     _dev(slot_pos, torch.int32, "slot_pos")
@@ -245,7 +245,6 @@ def append_latent(desc: LayerDesc, x, packed, slot_seq, slot_pos, block_table, c
 def decode_attention_latent(desc: LayerDesc, q, q_pos, ctx_len, max_ctx, packed, cache, block_table, out=None,
                             workspace=None):
     """Decode attention that stops in latent space: out [b, h_q, r_v] bf16 (see lorc_decode_attention_latent)."""
-    import torch
     _dev(q, torch.bfloat16, "q")
     _dev(q_pos, torch.int32, "q_pos")
     _dev(ctx_len, torch.int32, "ctx_len")
@@ -256,9 +255,8 @@ def decode_attention_latent(desc: LayerDesc, q, q_pos, ctx_len, max_ctx, packed,
     n_seqs, max_pages = block_table.shape
     assert n_seqs >= b
     n_pages = cache.numel() // page_bytes(desc)
-    need = decode_workspace_bytes(desc, b, max_ctx)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(decode_workspace_bytes(desc, b, max_ctx), 256), dtype=torch.uint8, device=q.device)
     if out is None:
         out = torch.empty(b, desc.n_q_heads, desc.rank_v, dtype=torch.bfloat16, device=q.device)
     _check(_lib.lorc_decode_attention_latent(ctypes.byref(desc), _ptr(q), _ptr(q_pos), _ptr(ctx_len), b, max_ctx,
@@ -273,7 +271,6 @@ def decode_attention(desc: LayerDesc, q, q_pos, ctx_len, max_ctx, packed, cache,
     """q [b, h_q, d] bf16 (un-rotated); q_pos, ctx_len [b] int32 -> out [b, h_q, d] bf16.
 
     events: optional (begin, end) raw hipEvent_t handles recorded around the split kernel."""
-    import torch
     _dev(q, torch.bfloat16, "q")
     _dev(q_pos, torch.int32, "q_pos")
     _dev(ctx_len, torch.int32, "ctx_len")
@@ -284,9 +281,8 @@ def decode_attention(desc: LayerDesc, q, q_pos, ctx_len, max_ctx, packed, cache,
     n_seqs, max_pages = block_table.shape
     assert n_seqs >= b
     n_pages = cache.numel() // page_bytes(desc)
-    need = decode_workspace_bytes(desc, b, max_ctx)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(decode_workspace_bytes(desc, b, max_ctx), 256), dtype=torch.uint8, device=q.device)
     if out is None:
         out = torch.empty_like(q)
     args = (ctypes.byref(desc), _ptr(q), _ptr(q_pos), _ptr(ctx_len), b, max_ctx, _ptr(packed), _ptr(cache),
@@ -306,7 +302,6 @@ def decode_plain_workspace_bytes(desc: LayerDesc, b: int, max_ctx: int) -> int:
 def decode_attention_plain(desc: LayerDesc, q, q_pos, ctx_len, max_ctx, packed, cache, block_table, out=None,
                            workspace=None):
     """Decode attention over an uncompressed layer (see lorc_decode_attention_plain): out [b, h_q, d] bf16."""
-    import torch
     _dev(q, torch.bfloat16, "q")
     _dev(q_pos, torch.int32, "q_pos")
     _dev(ctx_len, torch.int32, "ctx_len")
@@ -336,7 +331,6 @@ STATIC_WORKSPACE_BYTES = 32 << 20
 
 def decode_attention_static(desc: LayerDesc, q, q_pos, ctx_len, max_ctx, packed, cache, block_table, out):
     """lorc_decode_attention_static: no workspace argument, nothing allocated (the caller passes `out`)."""
-    import torch
     _dev(q, torch.bfloat16, "q")
     _dev(q_pos, torch.int32, "q_pos")
     _dev(ctx_len, torch.int32, "ctx_len")
@@ -359,7 +353,6 @@ def decode_attention_absorbed(desc: LayerDesc, q_lat, ctx_len, max_ctx, packed, 
     """No positional rotation, key factor folded into the query: q_lat [b, h_q, r_k] bf16 -> out [b, h_q, d] bf16.
 
     events: optional (begin, end) raw hipEvent_t handles recorded around the streaming kernel."""
-    import torch
     _dev(q_lat, torch.bfloat16, "q_lat")
     _dev(ctx_len, torch.int32, "ctx_len")
     _dev(block_table, torch.int32, "block_table")
@@ -369,9 +362,8 @@ def decode_attention_absorbed(desc: LayerDesc, q_lat, ctx_len, max_ctx, packed, 
     n_seqs, max_pages = block_table.shape
     assert n_seqs >= b
     n_pages = cache.numel() // page_bytes(desc)
-    need = decode_absorbed_workspace_bytes(desc, b, max_ctx)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q_lat.device)
+        workspace = torch.empty(max(decode_absorbed_workspace_bytes(desc, b, max_ctx), 256), dtype=torch.uint8, device=q_lat.device)
     if out is None:
         out = torch.empty(b, desc.n_q_heads, desc.head_dim, dtype=torch.bfloat16, device=q_lat.device)
     args = (ctypes.byref(desc), _ptr(q_lat), _ptr(ctx_len), b, max_ctx, _ptr(packed), _ptr(cache), _ptr(block_table),
@@ -389,7 +381,6 @@ def prefill_attention(desc: LayerDesc, q, cu_seqlens, max_seqlen, packed, cache,
     """q [total, h_q, d] bf16 packed over sequences; cu_seqlens [b+1] int32 -> out [total, h_q, d] bf16.
 
     plain: the layer is uncompressed (lorc_prefill_attention_plain)."""
-    import torch
     _dev(q, torch.bfloat16, "q")
     _dev(cu_seqlens, torch.int32, "cu_seqlens")
     _dev(block_table, torch.int32, "block_table")
@@ -398,9 +389,8 @@ def prefill_attention(desc: LayerDesc, q, cu_seqlens, max_seqlen, packed, cache,
     b = cu_seqlens.numel() - 1
     n_seqs, max_pages = block_table.shape
     n_pages = cache.numel() // page_bytes(desc)
-    need = prefill_workspace_bytes(desc, b, max_seqlen)
     if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(prefill_workspace_bytes(desc, b, max_seqlen), 256), dtype=torch.uint8, device=q.device)
     if out is None:
         out = torch.empty_like(q)
     fn, name = ((_lib.lorc_prefill_attention_plain, "lorc_prefill_attention_plain") if plain else
