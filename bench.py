@@ -426,7 +426,7 @@ def main():
         lat_bytes = sum(pos2 * 4 * r2 for r2 in ranks)
         fl = sum(pos2 * ((0 if plain else 2 * r2 * n2) + 2 * hq2 * d + 2 * hq2 * (d if plain else r2)) for r2 in ranks)
         t_split = sum(per_layer_ms) * 1e-3
-        kname = "plain_scores_kernel + latent_pv_kernel + decode_merge_kernel" if plain else sorted({L.decode_plan_info(ds, b2, N2)[0] for ds, _, _ in layers})
+        kname = "decode_plain_kernel + decode_merge_kernel" if plain else sorted({L.decode_plan_info(ds, b2, N2)[0] for ds, _, _ in layers})
         rec2 = {"workload": tag, "layers": len(ranks), "batch": b2, "context": N2, "ranks": sorted(set(ranks), reverse=True), "kernels": kname,
                 "cache_fill": "latents sampled directly, N(0, sigma_j^2); factors sampled (orthonormal B)",
                 "ms_per_step": round(ms_step, 4), "tok_per_s": round(b2 / (ms_step * 1e-3), 1),

@@ -1,4 +1,4 @@
-// Decode attention in three launches, for the shapes the single-pass split kernels do not take:
+// Decode attention in two or three launches, for the shapes the single-pass split kernels do not take:
 //   * wide layers: ranks above 1024 (Table 2's LLaMA-2-13B row: MHA, 40 heads, n = 5120 compressed to 2048).  A tile's
 //     K latents no longer fit LDS and the latent-space output of all heads no longer fits one workgroup's registers,
 //     so the rank is walked through a ring and o_lat in column chunks;
@@ -13,6 +13,7 @@
 //            the format of the single-pass kernels.  Wide layers: all heads x 512 latent columns per workgroup (the
 //            latent is joint across heads, Section 4.1).  Uncompressed layers: one KV head's group x its 128 columns.
 //   merge  : the common merge kernel (wide: softmax-merge of the splits, then B_v; uncompressed: the merge alone).
+// Uncompressed layers of eight KV heads (or a multiple) take scores and values in one launch (decode_plain_kernel).
 #include "lorc_device.h"
 #include "lorc_kernels.h"
 #include "lorc_rebuild.h"
@@ -248,6 +249,242 @@ __global__ __launch_bounds__(256, 2) void plain_scores_kernel(DecodeParams p) {
     for (int j = 0; j < 16; ++j) {
       const int m = acc_row(j, hf);
       if (m < G) p.scores[((size_t)seq * p.h_q + g * G + m) * p.score_stride + pos0 + 32 * pb + l32] = S[j];
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------ uncompressed, one pass
+// Decode of an uncompressed layer with eight KV heads (or a multiple) and groups of up to sixteen query heads in one pass over
+// the pages: one workgroup per (eight KV heads, split, sequence), wave w owns the KV heads w and w + 4 of the eight and walks
+// the split's positions 32 at a time with online softmax; the waves exchange nothing.  Bound by the page stream.  A wave keeps
+// one step of keys and one of values (16 KiB each) in flight: the next keys are requested when the scores have used the
+// current ones, the next values when the weighted sum has.  16x16x32 products throughout:
+//   S^T = K Q^T: row r = 4 q + j of block b (lane group q = lane / 16) is position 8 q + 4 b + j of the step, so that a lane's
+//   eight weights are those of eight consecutive positions, which is what it holds of V^T as an operand of O^T = V^T P^T.
+// Keys are rotated in registers: the lane's offset inside a step (constant) times the step's base angle (64 frequencies, one
+// per lane, handed round through LDS).
+//   8B layer (n = 1024), 16 x 4096 positions, call with append: 82 us as scores, values and merge -> 68 (268 MB of pages);
+//   64 x 8192, ragged: 344 -> 278; 1 x 2000: 31 -> 24; 4 x 1000: 32 -> 25.
+constexpr int kPlainHeads = 8, kPlainStep = 32;
+__global__ __launch_bounds__(256, 1) void decode_plain_kernel(DecodeParams p) {
+  constexpr int HD = 128, HALF = 64;
+  __shared__ __align__(16) float2 base_cs[4][HALF];  // per wave: rotation of the step's first position
+  const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, q = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_hg = p.h_kv / kPlainHeads, hg = blockIdx.x % n_hg, ss = blockIdx.x / n_hg;
+  const int split = ss % p.n_splits, seq = ss / p.n_splits;
+  int ctx = p.ctx_len[seq];
+  ctx = ctx < 0 ? 0 : (ctx > p.max_ctx ? p.max_ctx : ctx);
+  const int G = p.G, n = p.h_kv * HD, blocks_per_row = n >> 4;
+  const int t_begin = split * p.tiles_per_split * kPage;
+  int t_end = t_begin + p.tiles_per_split * kPage;
+  if (t_end > ctx) t_end = ctx;
+  const int n_steps = t_end > t_begin ? (t_end - t_begin + kPlainStep - 1) / kPlainStep : 0;
+  const int g0 = hg * kPlainHeads + w;  // the wave's KV heads: g0, g0 + 4
+
+  // lane offsets of the operands inside a page (bytes)
+  const int po[2] = {8 * (m >> 2) + (m & 3), 8 * (m >> 2) + 4 + (m & 3)};  // position of key row m, block b
+  uint32_t koff[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) koff[b] = (uint32_t)(q >> 1) * 1024u + (uint32_t)(po[b] + 32 * (q & 1)) * 16u;
+  const uint32_t voff = (uint32_t)(q >> 1) * 1024u + (uint32_t)(m + 32 * (q & 1)) * 16u;
+  const uint32_t part_bytes = (uint32_t)kPage * n * 2u;
+  u32x4 kraw[2][2][4], vraw[2][8];
+  // Requests of step i; past the last one nothing is fetched (descriptor of size zero, as for a page that is not cached).
+  auto page_of = [&](int i, bool& ok) {
+    const int tile = i < n_steps ? (t_begin + i * kPlainStep) / kPage : 0;
+    const int id = __builtin_amdgcn_readfirstlane(i < n_steps ? p.block_table[(size_t)seq * p.max_pages + tile] : -1);
+    ok = id >= 0 && id < p.n_pages;
+    return uniform_ptr(p.cache + (size_t)(ok ? id : 0) * p.page_elems);
+  };
+  auto k_request = [&](int i) {
+    bool ok;
+    const uint16_t* page = page_of(i, ok);
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(page, ok ? part_bytes : 0u);
+    const int row = (i & 1) * blocks_per_row;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          kraw[h][b][kk] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, koff[b], (row + (g0 + 4 * h) * 8 + 2 * kk) * 1024, 0));
+  };
+  auto v_request = [&](int i) {
+    bool ok;
+    const uint16_t* page = page_of(i, ok);
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(page + (size_t)kPage * n, ok ? part_bytes : 0u);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb)
+        vraw[h][mb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                    r, voff, (((g0 + 4 * h) * 4 + (mb >> 1)) * 4 + 2 * (i & 1)) * 1024 + (mb & 1) * 256, 0));
+  };
+  k_request(0);
+  v_request(0);
+
+  // query operands (n = query head of the group, k = 32 coordinates), rotated at q_pos and scaled; rows past the group: zeros
+  f16x8 qf[2][4];
+  {
+    const double q_pos = (double)p.q_pos[seq];
+    float qc[2][8], qs[2][8];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double turns = q_pos * p.rope_tab[32 * kk + 8 * q + e] * 0.15915494309189533576888;
+        const float fr = (float)(turns - rint(turns));
+        qc[kk][e] = __builtin_amdgcn_cosf(fr);
+        qs[kk][e] = __builtin_amdgcn_sinf(fr);
+      }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float scale = m < G ? p.q_scale : 0.f;
+      const uint16_t* row = p.q + ((size_t)seq * p.h_q + (size_t)(g0 + 4 * h) * G + (m < G ? m : 0)) * HD + 8 * q;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf16x8 lo = load_frag(row + 32 * kk), hi = load_frag(row + 32 * kk + HALF);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = m < G ? (float)lo[e] * scale : 0.f, y = m < G ? (float)hi[e] * scale : 0.f;
+          qf[h][kk][e] = static_cast<_Float16>(x * qc[kk][e] - y * qs[kk][e]);
+          qf[h][kk + 2][e] = static_cast<_Float16>(y * qc[kk][e] + x * qs[kk][e]);
+        }
+      }
+    }
+  }
+  float2 cl[2][2][8];  // rotation of the lane's offset inside a step
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) cl[b][kk][e] = p.lane_cs[po[b] * HALF + 32 * kk + 8 * q + e];
+  const double theta = p.rope_tab[lane] * 0.15915494309189533576888;  // turns per position
+
+  float m_run[2] = {kNegInfW, kNegInfW}, l_run[2] = {0.f, 0.f};
+  f32x4 o[2][8];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[h][mb][j] = 0.f;
+
+  for (int i = 0; i < n_steps; ++i) {
+    const int pos0 = t_begin + i * kPlainStep;
+    {
+      const double turns = (double)pos0 * theta;
+      const float fr = (float)(turns - rint(turns));
+      base_cs[w][lane] = make_float2(__builtin_amdgcn_cosf(fr), __builtin_amdgcn_sinf(fr));
+      __builtin_amdgcn_wave_barrier();  // a wave's LDS operations run in order
+    }
+    // ---- scores
+    f32x4 S[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) S[h][b][j] = 0.f;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        float c[8], s[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float2 bs = base_cs[w][32 * kk + 8 * q + e], l = cl[b][kk][e];
+          c[e] = bs.x * l.x - bs.y * l.y;
+          s[e] = bs.y * l.x + bs.x * l.y;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          f16x8 lo, hi;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float x = bf16_to_float((uint16_t)(kraw[h][b][kk][e >> 1] >> (16 * (e & 1))));
+            const float y = bf16_to_float((uint16_t)(kraw[h][b][kk + 2][e >> 1] >> (16 * (e & 1))));
+            lo[e] = static_cast<_Float16>(x * c[e] - y * s[e]);
+            hi[e] = static_cast<_Float16>(y * c[e] + x * s[e]);
+          }
+          S[h][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, qf[h][kk], S[h][b], 0, 0, 0);
+          S[h][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, qf[h][kk + 2], S[h][b], 0, 0, 0);
+        }
+      }
+    __builtin_amdgcn_wave_barrier();
+    k_request(i + 1);
+    // ---- online softmax: a lane holds eight positions of query head m; the four lane groups meet in the maximum
+    bf16x8 pf[2];
+    float alpha[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float sv[8], mx = kNegInfW;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        sv[e] = pos0 + 8 * q + e < t_end ? S[h][e >> 2][e & 3] : kNegInfW;
+        mx = fmaxf(mx, sv[e]);
+      }
+      const float2 a = row_pair(mx);
+      mx = fmaxf(a.x, a.y);
+      const float2 c = half_pair(mx);
+      mx = fmaxf(c.x, c.y);
+      const float m_new = fmaxf(m_run[h], mx);
+      alpha[h] = exp2f(m_run[h] - m_new);
+      m_run[h] = m_new;
+      float sum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float pe = pos0 + 8 * q + e < t_end ? exp2f(sv[e] - m_new) : 0.f;
+        pf[h][e] = static_cast<__bf16>(pe);
+        sum += (float)pf[h][e];  // the weights as they are multiplied: they add up to one whatever their rounding
+      }
+      l_run[h] = l_run[h] * alpha[h] + sum;
+    }
+    // ---- o += V^T P^T
+    if (pos0 + kPlainStep > t_end) {
+      // slots past the context hold whatever the pool held before (possibly NaN patterns) and 0 * NaN is not zero
+      int nv = t_end - pos0 - 8 * q;
+      nv = nv < 0 ? 0 : (nv > 8 ? 8 : nv);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            vraw[h][mb][c] &= (2 * c < nv ? 0x0000ffffu : 0u) | (2 * c + 1 < nv ? 0xffff0000u : 0u);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[h][mb][j] *= alpha[h];
+        o[h][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vraw[h][mb]), pf[h], o[h][mb], 0, 0, 0);
+      }
+    v_request(i + 1);
+  }
+
+  // ---- partials: O^T has columns along the accumulator rows (16 mb + 4 q + j) and query head m
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float2 a = row_pair(l_run[h]);
+    const float2 c = half_pair(a.x + a.y);
+    const float l = c.x + c.y, inv = l > 0.f ? 1.f / l : 0.f;
+    if (m < G) {
+      const size_t row = ((size_t)seq * p.n_splits + split) * p.h_q + (size_t)(g0 + 4 * h) * G + m;
+      if (q == 0) {
+        p.part_ml[row * 2] = m_run[h];
+        p.part_ml[row * 2 + 1] = l;
+      }
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) {
+        const f32x4 v = o[h][mb];
+        const u32x2 pk = {(uint32_t)f16_bits(v[0] * inv) | ((uint32_t)f16_bits(v[1] * inv) << 16),
+                          (uint32_t)f16_bits(v[2] * inv) | ((uint32_t)f16_bits(v[3] * inv) << 16)};
+        *reinterpret_cast<u32x2*>(p.part_o + row * HD + 16 * mb + 4 * q) = pk;
+      }
     }
   }
 }
@@ -535,24 +772,47 @@ bool plain_shape_ok(const lorc_layer_desc& d) {
   return d.head_dim == 128 && d.rank_k == n && d.rank_v == n && G <= 32 && d.n_q_heads <= 64;
 }
 
-// Splits for the value kernel: enough workgroups for about two per CU, each walking at least four tiles.
+// Uncompressed layers in one pass: all eight KV heads of a workgroup are real, and a group's rows fit one 16-wide operand.
+static bool plain_one_pass(int G, int h_kv) { return G <= 16 && h_kv % kPlainHeads == 0; }
+
+// Splits for the value kernel: enough workgroups for about two per CU, each walking at least four tiles; for the one-pass
+// kernel of uncompressed layers see below.
 DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain) {
   DecodePlan pl{};
   pl.tile = kWideT;
   pl.occupancy = 1;
   pl.stationary = 0;
   pl.wide = plain ? 2 : 1;
+  const bool one_pass = plain && plain_one_pass(d.n_q_heads / d.n_kv_heads, d.n_kv_heads);
   int n_tiles = (max_ctx + kWideT - 1) / kWideT;
   if (n_tiles < 1) n_tiles = 1;
   pl.score_stride = n_tiles * kWideT;
   pl.v_chunks = plain ? d.n_kv_heads : (d.rank_v + 511) / 512;
-  // uncompressed layers: a workgroup streams only one head's 16 KiB per tile, so many more of them are kept in flight
-  const long want = (plain ? 8L : 2L) * (n_cus > 0 ? n_cus : 256);
-  long ns = (want + (long)b * pl.v_chunks - 1) / ((long)b * pl.v_chunks);
-  if (ns > (n_tiles + 3) / 4) ns = (n_tiles + 3) / 4;
-  if (ns < 1) ns = 1;
-  if (ns > 512) ns = 512;
-  pl.tiles_per_split = (int)((n_tiles + ns - 1) / ns);
+  const int cus = n_cus > 0 ? n_cus : 256;
+  if (one_pass) {
+    // The cheapest of one to eight tiles per split (more would let sequences of different lengths leave CUs idle) by an
+    // estimate in microseconds: rounds of one workgroup per CU, 5 per tile and 5 to start and end, and the merge's walk over
+    // the splits.  With four tiles at least 1 x 2000 positions take 38 us instead of 24, 4 x 1000 39 instead of 25.
+    pl.v_chunks = d.n_kv_heads / kPlainHeads;
+    const int first = (n_tiles + 511) / 512;  // at most 512 splits
+    double best = 0;
+    for (int tps = first; tps <= 8 || tps == first; ++tps) {
+      const long ns = (n_tiles + tps - 1) / tps, rounds = ((long)b * pl.v_chunks * ns + cus - 1) / cus;
+      const double cost = 5.0 * rounds * (tps + 1) + 0.09 * ns;
+      if (tps == first || cost < best) {
+        best = cost;
+        pl.tiles_per_split = tps;
+      }
+    }
+  } else {
+    // uncompressed layers: a workgroup streams only one head's 16 KiB per tile, so many more of them are kept in flight
+    const long want = (plain ? 8L : 2L) * cus;
+    long ns = (want + (long)b * pl.v_chunks - 1) / ((long)b * pl.v_chunks);
+    if (ns > (n_tiles + 3) / 4) ns = (n_tiles + 3) / 4;
+    if (ns < 1) ns = 1;
+    if (ns > 512) ns = 512;
+    pl.tiles_per_split = (int)((n_tiles + ns - 1) / ns);
+  }
   pl.n_splits = (n_tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;
   const int out_w = plain ? d.head_dim : d.rank_v;
   size_t off = 0;
@@ -561,7 +821,7 @@ DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cu
   pl.off_o = off;
   off = align256w(off + (size_t)b * pl.n_splits * d.n_q_heads * out_w * 2);
   pl.off_scores = off;
-  off = align256w(off + (size_t)b * d.n_q_heads * pl.score_stride * 4);
+  if (!one_pass) off = align256w(off + (size_t)b * d.n_q_heads * pl.score_stride * 4);
   pl.total_bytes = off;
   return pl;
 }
@@ -589,6 +849,8 @@ int launch_decode_wide(const DecodeParams& p, const DecodePlan& plan, hipStream_
     if (int rc = launch_kernel(absorbed_scores_kernel<2>, dim3(p.b * tiles), dim3(256), 0, s, p)) return rc;
     return launch_kernel(latent_pv_kernel<2, 4, false>, grid, dim3(256), 0, s, p);
   }
+  if (plan.wide == 2 && plain_one_pass(p.G, p.h_kv))
+    return launch_kernel(decode_plain_kernel, dim3(p.b * p.n_splits * (p.h_kv / kPlainHeads)), dim3(256), 0, s, p);
   if (plan.wide == 2) {
     const size_t lds = (size_t)p.h_q * 128 * 2;
     if (int rc = launch_kernel(plain_scores_kernel, dim3(p.b * tiles), dim3(256), lds, s, p)) return rc;

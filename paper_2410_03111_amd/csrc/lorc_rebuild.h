@@ -1,5 +1,5 @@
 // Internal: the rank-r rebuild K^T = B^T C^T of one wave -- two 32-column blocks of the output (RoPE partners) times NPB
-// blocks of 32 cached positions -- shared by the decode kernels that stream the factor from L2.
+// blocks of 32 cached positions -- for the decode kernel that streams the factor from L2; and the decode kernels' angle helpers.
 #ifndef LORC_REBUILD_H_
 #define LORC_REBUILD_H_
 

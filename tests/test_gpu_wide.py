@@ -105,6 +105,37 @@ def test_uncompressed_unmapped_page_shifted_and_long_positions():
     _check(pb, layer, q_pos=q_pos, ref=ref, tag="uncompressed, unmapped pages, positions to 20 k")
 
 
+# The one-pass kernel (KV heads a multiple of eight): group sizes 1 to 8, one and two workgroups per split, contexts on either
+# side of its 32-position steps and of a page, empty splits and sequences; slots past a context hold NaN patterns.
+ONE_PASS = {
+    "g1": dict(n_q_heads=8, n_kv_heads=8, ctx=[1, 31, 32, 33, 64, 65, 0]),
+    "g3_one_unmapped": dict(n_q_heads=24, n_kv_heads=8, ctx=[200, 97], unmapped=(0, 1)),
+    "g8_many_splits": dict(n_q_heads=64, n_kv_heads=8, ctx=[5000, 40]),
+    "16_kv_heads": dict(n_q_heads=32, n_kv_heads=16, ctx=[330, 63]),
+}
+
+
+@pytest.mark.parametrize("name", list(ONE_PASS))
+def test_uncompressed_layer_in_one_pass_matches_oracle(name):
+    import torch
+    shape = dict(ONE_PASS[name])
+    unmapped = shape.pop("unmapped", None)
+    n = shape["n_kv_heads"] * 128
+    pb = Problem(d_model=512, head_dim=128, rank_k=n, rank_v=n, rope_base=500000.0, seed=211 + len(name), **shape).build()
+    layer = GpuLayer(pb, plain=True)
+    ref = None
+    if unmapped is not None:  # a page that is not mapped counts as zero keys and values
+        s, page = unmapped
+        bt = layer.block_table_np.copy()
+        bt[s, page] = -1
+        layer.block_table_np, layer.block_table = bt, torch.from_numpy(bt).to(layer.dev)
+        X = [x.copy() for x in pb.X]
+        X[s][64 * page:64 * page + 64] = 0.0
+        ref = oracle_decode(Problem(**{**pb.__dict__, "X": X}))
+    layer.append_all()
+    _check(pb, layer, ref=ref, tag=f"one pass {name}")
+
+
 def test_plain_entry_point_refuses_a_compressed_desc():
     import paper_2410_03111_amd as L
     assert L.decode_plain_workspace_bytes(L.layer_desc(512, 8, 2, 128, 128, 256, 1e4), 1, 64) == 0
