@@ -574,9 +574,9 @@ __global__ __launch_bounds__(256, 1) void append_gemm_kernel(AppendParams p) {
 // workgroup's rows (rows past them read as zeros through the descriptor and fetch nothing), B = 16 tokens, every operand
 // of a trip requested before the first product; the waves' partial sums meet in LDS.  The work is a chain of one load
 // latency, the reduction and a store, so a mostly empty row operand costs nothing.
-//   Kernel, us (dot products over 4 rows per workgroup before): 8B rank 512, T = 16: 6.2 -> 4.5; T = 32: 16 -> 13;
-//   8B uncompressed, T = 16: 11.4 -> 9.5; 13B rank 2048, T = 16: 31 -> 18.
-
+//   Kernel, us, weights cold (dot products over 4 rows per workgroup before): 8B rank 512, T = 1: 7.1 -> 5.4; T = 16: 7.1 -> 7.7
+//   (no difference in a decode call: 101.1 and 101.4 us at 16 x 4096); T = 32: 17 -> 13; 8B uncompressed, T = 16: 11.4 -> 8.5;
+//   13B rank 2048, T = 16: 30 -> 18; tiny layer, T = 1: 6.6 -> 3.7.
 constexpr int kSkWaves = 16, kSkSteps = 8, kSkMaxRows = 16;
 template <int TG>  // groups of 16 tokens
 __global__ __launch_bounds__(64 * kSkWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void append_skinny_kernel(AppendParams p, int rows) {
