@@ -327,6 +327,7 @@ int prefill_common(const lorc_layer_desc* desc, const void* q, const int32_t* cu
   p.block_table = block_table;
   p.out = static_cast<uint16_t*>(out);
   p.rope_tab = reinterpret_cast<const double*>(pk + packed_off_rope(desc->d_model, desc->rank_k, desc->rank_v, n));
+  p.lane_cs = reinterpret_cast<const float2*>(p.rope_tab + 64);
   p.krot = reinterpret_cast<uint16_t*>(ws + plan.off_krot);
   p.vt = reinterpret_cast<uint16_t*>(ws + plan.off_vt);
   p.b = b;

@@ -92,6 +92,7 @@ struct PrefillParams {
   const int32_t* block_table;
   uint16_t* out;              // [total x h_q x d] bf16
   const double* rope_tab;     // packed: theta_i
+  const float2* lane_cs;      // packed: (cos, sin)(l * theta_i), l < 32, [l][head_dim / 2]
   uint16_t* krot;             // workspace: rotated keys, fp16, [b][page] operand blocks (layout: lorc_prefill.hip)
   uint16_t* vt;               // workspace: values transposed, fp16, likewise
   int b, h_q, h_kv, G, head_dim, r_k, r_v, max_pages, n_pages, tiles_per_seq, lp;

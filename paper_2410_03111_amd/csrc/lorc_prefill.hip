@@ -14,6 +14,7 @@
 
 #include "lorc_device.h"
 #include "lorc_kernels.h"
+#include "lorc_rebuild.h"
 #include "lorc_tile_product.h"
 
 namespace lorc {
@@ -96,22 +97,26 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
       for (int j = 0; j < 16; ++j) acc[c][pb][j] = 0.f;
 
   if (!values) {
-    // rotation bases of the four position blocks: frac(base theta / 2 pi), reduced in fp64, and theta / 2 pi
+    // Rotations of the four position blocks' first positions (angles reduced in fp64).  A key's rotation is its block's times
+    // that of its offset inside the block, from the packed table.  (One fp32 angle per key in the hardware sine and cosine takes
+    // 0.5 to 1 us less per call -- 8B rank 576, six prompts: 102 against 103 -- but rounds a fifth to a third more keys to the
+    // wrong fp16 value.)
     float2* cs_base = reinterpret_cast<float2*>(smem + rt_ring_bytes<NC, 3>());
-    if (tid < 4 * HALF) {
-      const double tr = p.rope_tab[tid % HALF] * 0.15915494309189533576888, turns = (double)(page0 * kPage + 32 * (tid / HALF)) * tr;
-      cs_base[tid] = make_float2((float)(turns - rint(turns)), (float)tr);
-    }
+    auto setup = [&]() {  // behind the product's first copies
+      if (tid < 4 * HALF) cs_base[tid] = cos_sin_reduced((double)(page0 * kPage + 32 * (tid / HALF)) * p.rope_tab[tid % HALF]);
+    };
     tile_product<HD, NC, 3, kPageKeys, false>(acc, smem, dma_rsrc(p.bk, (uint32_t)n * p.r_k * 2u), dma_rsrc(page, page_ok ? (uint32_t)kPage * p.r_k * 2u : 0u),
-                                cb0, ncb, p.r_k >> 4, w, lane, p.r_k >> 5);
+                                cb0, ncb, p.r_k >> 4, w, lane, p.r_k >> 5, 0, setup);
     if (!live) return;
-    const float l32f = (float)l32;
 #pragma unroll
     for (int pr = 0; pr < NC / 2; ++pr) {  // pairs of RoPE partner blocks
       const int ca = HD == 128 ? pr : 2 * pr, cc = HD == 128 ? pr + NC / 2 : 2 * pr + 1;
       const int cb = cb0 + rt_col_block<HD, NC>((w & 1) * NC + ca);
       if (cb >= ncb) continue;
       const int g = cb / (HD / 32), fbase = 32 * (cb % (HD / 32));
+      float2 cl[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) cl[j] = p.lane_cs[l32 * HALF + fbase + acc_row(j, hf)];
 #pragma unroll
       for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
@@ -121,8 +126,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
           for (int e = 0; e < 8; ++e) {
             const int j = 8 * u + e;
             const float2 bt = cs_base[(2 * (w >> 1) + pb) * HALF + fbase + acc_row(j, hf)];
-            const float turns = __builtin_fmaf(l32f, bt.y, bt.x);
-            const float cs = __builtin_amdgcn_cosf(turns), sn = __builtin_amdgcn_sinf(turns);
+            const float cs = bt.x * cl[j].x - bt.y * cl[j].y, sn = bt.y * cl[j].x + bt.x * cl[j].y;
             const float x = acc[ca][pb][j], y = acc[cc][pb][j];
             lo[e] = static_cast<_Float16>(x * cs - y * sn);
             hi[e] = static_cast<_Float16>(y * cs + x * sn);

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import lorc_inputs as gen
-from lorc_testlib import GpuLayer, Problem, TOL, oracle_prefill, rel_err
+from lorc_testlib import GpuLayer, Problem, TOL, oracle_prefill, page_gather_indices, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -83,3 +83,55 @@ def test_rebuild_dispatch(name):
     worst = max(float(np.max(np.abs(g - r))) / scale for g, r in zip(layer.prefill(Q), ref))
     print(f"{name}: rel err {worst:.3e}")
     assert worst <= TOL
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_rotated_keys_are_rounded_once(head_dim):
+    """With an identity as key factor the rebuilt keys are the latents themselves, and the scratch (1 KiB operand blocks of
+    64 lanes x 8 fp16, see lorc_prefill.hip) holds them rotated and rounded to fp16.  An error e of the rotated key moves it to
+    a neighbouring fp16 value with probability e / ulp, so the share of keys that are not the nearest fp16 value measures the
+    rotation's error below the rounding: composed in fp32 from a base and an offset rotation, each within an ulp or two,
+    6.4e-4 (errors of about 1e-6 of the larger coordinate, ulp 2^-11 to 2^-10); with one fp32 angle of up to 31 radians past
+    the base in the hardware sine and cosine, 8.5e-4 (head_dim 64) and 7.9e-4 (128)."""
+    import torch
+    import paper_2410_03111_amd as L
+    n, N, h_kv = 2 * head_dim, 8192, 2
+    dev = torch.device("cuda:0")
+    desc = L.layer_desc(256, 2, h_kv, head_dim, n, n, 10000.0)
+    g = torch.Generator().manual_seed(5)
+    eye = torch.eye(n, dtype=torch.bfloat16, device=dev)
+    A = torch.randn(256, n, generator=g).mul_(0.1).to(dev, torch.bfloat16)
+    x = torch.randn(N, 256, generator=g).to(dev, torch.bfloat16)
+    i32 = lambda a: torch.as_tensor(a, dtype=torch.int32, device=dev)
+    pages = (N + 63) // 64
+    table = i32(np.random.default_rng(3).permutation(pages)).view(1, pages)
+    cache = torch.zeros(pages * L.page_bytes(desc), dtype=torch.uint8, device=dev)
+    packed = L.pack_factors(desc, A, A, eye, eye)
+    L.append_latent(desc, x, packed, i32(np.zeros(N)), i32(np.arange(N)), table, cache)
+    workspace = torch.zeros(L.prefill_workspace_bytes(desc, 1, N), dtype=torch.uint8, device=dev)
+    q = torch.zeros(N, 2, head_dim, dtype=torch.bfloat16, device=dev)
+    L.prefill_attention(desc, q, i32([0, N]), N, packed, cache, table, workspace=workspace)
+    torch.cuda.synchronize()
+    # latents as stored, then the keys in fp64
+    idx = page_gather_indices(n, n)
+    pool = cache.cpu().numpy().view(np.uint16).reshape(pages, -1)
+    lat = np.concatenate([pool[p][idx] for p in table.cpu().numpy()[0]])[:N, :n]
+    key = gen.bf16_to_f32(lat).astype(np.float64).reshape(N, h_kv, head_dim)
+    half = head_dim // 2
+    angle = np.arange(N)[:, None] * 10000.0 ** (-2.0 * np.arange(half) / head_dim)
+    c, s = np.cos(angle)[:, None], np.sin(angle)[:, None]
+    lo, hi = key[..., :half], key[..., half:]
+    exact = np.concatenate([lo * c - hi * s, hi * c + lo * s], axis=-1).astype(np.float16)
+    # scratch: [page][KV head][position block][16 coordinates][lane][element], behind a table of 64 doubles (512 bytes)
+    raw = workspace.cpu().numpy()[512:512 + pages * 64 * n * 2].view(np.float16).reshape(pages, h_kv, 2, head_dim // 16, 2, 32, 8)
+    e = np.arange(8)
+    got = np.empty((pages * 64, h_kv, head_dim), np.float16)
+    for u in range(head_dim // 16):
+        for hf in range(2):
+            coord = 16 * u + 8 * (e >> 2) + 4 * hf + (e & 3)
+            got[:, :, coord] = raw[:, :, :, u, hf].transpose(0, 2, 3, 1, 4).reshape(pages * 64, h_kv, 8)
+    got = got[:N]
+    assert np.max(np.abs(got.astype(np.float64) - exact.astype(np.float64))) <= 2.0 ** -9 * np.max(np.abs(key))
+    differ = float(np.mean(got != exact))
+    print(f"head_dim {head_dim}: {differ:.2e} of the keys are not the nearest fp16 value")
+    assert differ <= 7.1e-4
