@@ -37,6 +37,13 @@ __device__ __forceinline__ size_t vt_block(int page, int h_kv, int g, int db, in
   return ((((size_t)page * h_kv + g) * (HD / 32) + db) * 4 + v) * 512;
 }
 
+// Positions of a sequence, as far as its scratch reaches: the launch is sized by the host's max_seqlen, and a longer entry of
+// cu_seqlens, which only the device sees, must not lead past the sequence's pages (rows beyond them are left as they are).
+__device__ __forceinline__ int prompt_len(const PrefillParams& p, int seq) {
+  const int len = p.cu_seqlens[seq + 1] - p.cu_seqlens[seq];
+  return len < p.lp ? len : p.lp;
+}
+
 // ------------------------------------------------------------------------------------------------ rebuild
 // One workgroup per (two pages of a sequence, 64 NC columns of K or of V).  Bound by the matrix cores at large sizes
 // (2 (r_k + r_v) n flop per position: 820 TFLOP/s at rank 512, 920 at rank 2048) and by the chip's width at small ones, which is why the columns are dealt to
@@ -76,7 +83,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
   }
   if (pt >= n_pt) return;
   const int seq = pt / tps2, page0 = (pt - seq * tps2) * 2;
-  const int len = p.cu_seqlens[seq + 1] - p.cu_seqlens[seq];
+  const int len = prompt_len(p, seq);
   if (page0 * kPage >= len) return;
   const bool values = cgi >= ncg;
   const int cb0 = (values ? cgi - ncg : cgi) * 2 * NC;
@@ -178,7 +185,7 @@ __global__ __launch_bounds__(256, 2) void prefill_plain_gather_kernel(PrefillPar
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int seq = blockIdx.x / p.tiles_per_seq, tile = blockIdx.x % p.tiles_per_seq;
-  const int len = p.cu_seqlens[seq + 1] - p.cu_seqlens[seq];
+  const int len = prompt_len(p, seq);
   const int pos0 = tile * T;
   if (pos0 >= len) return;
   const int n = p.h_kv * HD, pb = w & 1;
@@ -281,7 +288,7 @@ __global__ __launch_bounds__(64 * kAttnWaves, kAttnWaves == 4 ? 2 : 1) void pref
   const int qb = nqb - 1 - rest % nqb;          // longest blocks first
   const int seq = rest / nqb;
   const int tok0 = p.cu_seqlens[seq];
-  const int len = p.cu_seqlens[seq + 1] - tok0;
+  const int len = prompt_len(p, seq);
   if (qb * BQW >= len) return;
   const int q_last = qb * BQW + BQW - 1 < p.lp - 1 ? qb * BQW + BQW - 1 : p.lp - 1;
   const int t_wg = q_last / BK;                 // the last tile any wave of the workgroup needs

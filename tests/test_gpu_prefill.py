@@ -135,3 +135,36 @@ def test_rotated_keys_are_rounded_once(head_dim):
     differ = float(np.mean(got != exact))
     print(f"head_dim {head_dim}: {differ:.2e} of the keys are not the nearest fp16 value")
     assert differ <= 7.1e-4
+
+
+@pytest.mark.parametrize("n_q_heads,head_dim,plain", [(2, 64, False), (2, 128, False), (8, 128, False), (2, 128, True)])
+@pytest.mark.parametrize("max_seqlen", [64, 150])
+def test_sequences_longer_than_max_seqlen_stay_inside_their_scratch(n_q_heads, head_dim, plain, max_seqlen):
+    """cu_seqlens lives on the device, max_seqlen on the host; where the first says more than the second (one and three pages:
+    odd, so that half of the last two-page tile is no page of the sequence), the rows inside the pages of max_seqlen are right,
+    the others untouched, and so is what follows the workspace."""
+    import torch
+    n = 2 * head_dim
+    pb = Problem(d_model=256, n_q_heads=n_q_heads, n_kv_heads=2, head_dim=head_dim, rank_k=n if plain else 64,
+                 rank_v=n if plain else 32, rope_base=10000.0, ctx=[330, 290], seed=31).build()
+    layer = GpuLayer(pb, plain=plain)
+    layer.append_all()
+    L, dev = layer.L, layer.dev
+    Q = make_queries(pb, 7300)
+    full = layer.prefill(Q)
+    pages = (max_seqlen + 63) // 64
+    need = L.prefill_workspace_bytes(layer.desc, 2, max_seqlen)
+    canary = 4 * 64 * n * 2 + 256
+    buf = torch.full((need + canary,), 0x5A, dtype=torch.uint8, device=dev)
+    q = torch.from_numpy(np.concatenate(Q, axis=0)).to(dev).to(torch.bfloat16).contiguous()
+    out = torch.full_like(q, 77.0)
+    cu = torch.tensor([0, 330, 620], dtype=torch.int32, device=dev)
+    table = layer.block_table[:, :pages].contiguous()
+    L.prefill_attention(layer.desc, q, cu, max_seqlen, layer.packed, layer.cache, table, out=out, workspace=buf[:need], plain=plain)
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == 0x5A).all())
+    o = out.float().cpu().numpy()
+    for s, ref in enumerate(full):
+        rows = o[330 * s:330 * s + pb.ctx[s]]
+        assert rel_err(rows[:64 * pages], ref[:64 * pages]) <= 1e-2
+        assert np.all(rows[64 * pages:] == 77.0)
