@@ -568,77 +568,119 @@ __global__ __launch_bounds__(256, 1) void append_gemm_kernel(AppendParams p) {
 }
 
 // ------------------------------------------------------------------------------------------- append, small T
-// Decode-time append: a handful of tokens against the whole down-projection.  The work is one pass over the weights (8 MiB
-// for the 8B shape) and a CU pulls a few tens of GB/s at best, so the rows are dealt evenly to all CUs: `rows` of them
-// (at most 16) per workgroup of sixteen waves.  A wave owns a sixteenth of the model dimension: 16x16x32 products, A = the
-// workgroup's rows (rows past them read as zeros through the descriptor and fetch nothing), B = 16 tokens, every operand
-// of a trip requested before the first product; the waves' partial sums meet in LDS.  The work is a chain of one load
-// latency, the reduction and a store, so a mostly empty row operand costs nothing.
-//   Kernel, us, weights cold (dot products over 4 rows per workgroup before): 8B rank 512, T = 1: 7.1 -> 5.4; T = 16: 7.1 -> 7.7
-//   (no difference in a decode call: 101.1 and 101.4 us at 16 x 4096); T = 32: 17 -> 13; 8B uncompressed, T = 16: 11.4 -> 8.5;
-//   13B rank 2048, T = 16: 30 -> 18; tiny layer, T = 1: 6.6 -> 3.7.
-constexpr int kSkWaves = 16, kSkSteps = 8, kSkMaxRows = 16;
-template <int TG>  // groups of 16 tokens
+// Decode-time append: up to 64 tokens against the whole down-projection in one pass over the weights (8 MiB for the 8B shape).
+// The rows are dealt evenly to all CUs: `rows` of them (at most 16) per workgroup of sixteen waves; wave w owns the lines (64 of
+// the model dimension) w, w + 16, ... of all of them: 16x16x32 products, A = the workgroup's rows, B = 16 tokens; the waves'
+// partial sums meet in LDS.  Bound by one load latency and the reduction for a few tokens (about 4 us), and then by the tokens,
+// which every CU reads whole: 48 bytes per ns and CU past the L1 whatever the order of the lines, the rows per workgroup or the
+// number of requests in flight (0.17 us per token at D = 4096, 0.34 at 8192).  A request costs its 16 cycles of address work
+// even where it fetches nothing, hence a form per number of tokens, and rows past eight only where there are any.
+//   us, weights cold (dot products over 4 rows, 16 tokens a pass / this kernel with 32 tokens a pass, a wave on consecutive
+//   lines, slots looked up behind the products / now):
+//   8B rank 512, T = 1: 7.4 / 5.6 / 4.1;  16: 7.9 / 7.7 / 7.0;  48: 17.0 / 18.9 / 14.2;  64: 21.6 / 21.3 / 17.7
+//   70B rank 512, T = 1: 10.3 / 8.6 / 5.7;  16: 11.2 / 13.0 / 11.6;  48: 25.2 / 33.6 / 25.6;  64: 32.0 / 38.7 / 32.7
+//   13B rank 2048, T = 16: 24.2 / 15.1 / 14.9;  64: 75.6 / 39.4 / 29.1;  tiny layer, T = 1: 5.5 / 3.0 / 2.4
+constexpr int kSkWaves = 16, kSkMaxRows = 16;
+
+// Rows x 64 of the contraction (a 128-byte line of each row) as the operands of two k-steps: lane m + 16 q holds the pieces q
+// and 4 + q (of eight, 16 bytes each) of row m.  Sixteen rows take two requests of 64 bytes per row; eight rows take one request
+// of whole lines -- lane m + 16 q fetches piece q + 4 (m / 8) of row m % 8 -- and the second k-step has the halves of each row of
+// lanes changed round (rows 8 .. 15 of the operands then repeat and are not to be used).
+template <bool SIXTEEN>
+struct RowLines {
+  u32x4 v[SIXTEEN ? 2 : 1];
+  static __device__ __forceinline__ uint32_t lane_offset(int lane, uint32_t row_bytes) {
+    const int m = lane & 15, q = lane >> 4;
+    return SIXTEEN ? (uint32_t)m * row_bytes + (uint32_t)q * 16u : (uint32_t)(m & 7) * row_bytes + (uint32_t)(q + 4 * (m >> 3)) * 16u;
+  }
+  template <int AUX>  // cache policy bits of the load
+  __device__ __forceinline__ void request(__amdgpu_buffer_rsrc_t r, uint32_t at) {
+    v[0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, AUX));
+    if constexpr (SIXTEEN) v[1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at + 64u, 0, AUX));
+  }
+  __device__ __forceinline__ bf16x8 step(int s) const {
+    if constexpr (SIXTEEN) return __builtin_bit_cast(bf16x8, v[s]);
+    if (s == 0) return __builtin_bit_cast(bf16x8, v[0]);
+    u32x4 r;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t x = v[0][c];
+      r[c] = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xF, 0xF, false);  // row_ror:8
+    }
+    return __builtin_bit_cast(bf16x8, r);
+  }
+};
+
+// TG: groups of 16 tokens, all of the call's (0: at most eight tokens);  R16: more than eight rows
+template <int TG, bool R16>
 __global__ __launch_bounds__(64 * kSkWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void append_skinny_kernel(AppendParams p, int rows) {
-  __shared__ float red[kSkWaves][TG][16][16];  // [wave][token group][row][token]
+  constexpr int NG = TG > 0 ? TG : 1, PF = 2;  // lines in flight (four: no faster, and more requests past a wave's share)
+  __shared__ float red[kSkWaves][NG][16][16];  // [wave][token group][row][token]
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, q = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int D = p.D, rt = p.r_k + p.r_v, j0 = blockIdx.x * rows;
-  const int n_rows = rt - j0 < rows ? rt - j0 : rows;
-  const int n_steps = D >> 5, per_wave = (n_steps + kSkWaves - 1) / kSkWaves, s_begin = w * per_wave;
-  const int s_end = s_begin + per_wave < n_steps ? s_begin + per_wave : n_steps;
-  const __amdgpu_buffer_rsrc_t ar = make_rsrc(uniform_ptr(p.at + (size_t)j0 * D), (uint32_t)n_rows * (uint32_t)D * 2u);
-  constexpr uint32_t kPast = 0x80000000u;  // past every descriptor: reads as zero
-  for (int t0 = 0; t0 < p.T; t0 += 16 * TG) {
-    const int nt = p.T - t0 < 16 * TG ? p.T - t0 : 16 * TG;
-    const __amdgpu_buffer_rsrc_t xr = make_rsrc(uniform_ptr(p.x + (size_t)t0 * D), (uint32_t)nt * (uint32_t)D * 2u);
-    f32x4 acc[TG];
+  const int rt = p.r_k + p.r_v, j0 = blockIdx.x * rows, n_rows = rt - j0 < rows ? rt - j0 : rows;
+  // Output (row o / 16 NG, token o % 16 NG) is thread o's: its token's slot is asked for before the operands, and its page
+  // behind them, so that neither look-up is waited for.
+  const int orow = tid / (16 * NG), ot = tid % (16 * NG);
+  const bool out = orow < n_rows && ot < p.T;
+  const int seq = out ? p.slot_seq[ot] : -1, pos = out ? p.slot_pos[ot] : -1;
+  __builtin_amdgcn_sched_barrier(0);
+
+  const int n_mine = ((p.D >> 6) - w + kSkWaves - 1) / kSkWaves;  // this wave's lines: w, w + 16, ...
+  const uint32_t row_bytes = (uint32_t)p.D * 2u;
+  const __amdgpu_buffer_rsrc_t ar = make_rsrc(uniform_ptr(p.at + (size_t)j0 * p.D), (uint32_t)n_rows * row_bytes);
+  const __amdgpu_buffer_rsrc_t xr = make_rsrc(p.x, (uint32_t)p.T * row_bytes);
+  using Rows = RowLines<R16>;
+  using Tokens = RowLines<(TG > 0)>;
+  const uint32_t a_off = Rows::lane_offset(lane, row_bytes), b_off = Tokens::lane_offset(lane, row_bytes);
+  f32x4 acc[NG];
 #pragma unroll
-    for (int g = 0; g < TG; ++g)
+  for (int g = 0; g < NG; ++g)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[g][j] = 0.f;
-    for (int s0 = s_begin; s0 < s_end; s0 += kSkSteps) {
-      bf16x8 a[kSkSteps], b[kSkSteps][TG];
+    for (int j = 0; j < 4; ++j) acc[g][j] = 0.f;
+  Rows a[PF];
+  Tokens b[PF][NG];
+  // rows past the descriptors read as zeros and fetch nothing; so do lines past the wave's share (offset past 2 GiB)
+  auto request = [&](int u, int i) {
+    const uint32_t at = i < n_mine ? (uint32_t)(w + kSkWaves * i) * 128u : 0x80000000u;
+    a[u].template request<2>(ar, a_off + at);  // (non-temporal: a row is one workgroup's alone)
 #pragma unroll
-      for (int u = 0; u < kSkSteps; ++u) {
-        const uint32_t at_k = s0 + u < s_end ? (uint32_t)(s0 + u) * 64u + (uint32_t)q * 16u : kPast;
-        a[u] = buf_frag(ar, m < n_rows ? (uint32_t)(m * D) * 2u + at_k : kPast, 0);
+    for (int g = 0; g < NG; ++g) b[u][g].template request<0>(xr, b_off + (uint32_t)(16 * g) * row_bytes + at);
+  };
+  auto multiply = [&](int u) {
 #pragma unroll
-        for (int g = 0; g < TG; ++g) b[u][g] = buf_frag(xr, (uint32_t)((16 * g + m) * D) * 2u + at_k, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);  // every request before the first product
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int u = 0; u < kSkSteps; ++u)
+      for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u].step(s), b[u][g].step(s), acc[g], 0, 0, 0);
+  };
 #pragma unroll
-        for (int g = 0; g < TG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], b[u][g], acc[g], 0, 0, 0);
+  for (int u = 0; u < PF; ++u) request(u, u);
+  __builtin_amdgcn_sched_barrier(0);  // every request before the first product
+  const bool in_table = seq >= 0 && seq < p.n_seqs && pos >= 0 && pos < p.max_pages * kPage;
+  const int page = in_table ? p.block_table[(size_t)seq * p.max_pages + pos / kPage] : -1;
+  __builtin_amdgcn_sched_barrier(0);
+  for (int i0 = 0; i0 + PF < n_mine; i0 += PF) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      multiply(u);
+      request(u, i0 + PF + u);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // Where output (row o / 16 TG, token t0 + o % 16 TG) goes: looked up by thread o.
-    const int o = tid, orow = o / (16 * TG), ot = o % (16 * TG);
-    long long dst_page = -1;
-    int dst_slot = 0;
-    if (orow < n_rows && ot < nt) {
-      const int seq = p.slot_seq[t0 + ot], pos = p.slot_pos[t0 + ot];
-      if (seq >= 0 && seq < p.n_seqs && pos >= 0 && pos < p.max_pages * kPage) {
-        const int page = p.block_table[(size_t)seq * p.max_pages + pos / kPage];
-        if (page >= 0 && page < p.n_pages) {
-          dst_page = (long long)page * (long long)p.page_elems;
-          dst_slot = pos % kPage;
-        }
-      }
-    }
-    __syncthreads();  // the previous token pass is done with red
+  }
 #pragma unroll
-    for (int g = 0; g < TG; ++g)
+  for (int u = 0; u < PF; ++u) multiply(u);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) red[w][g][4 * q + j][m] = acc[g][j];  // accumulator: row 4 q + j, token m
-    __syncthreads();
-    if (dst_page >= 0) {
-      float v = 0.f;
+  for (int g = 0; g < NG; ++g)
 #pragma unroll
-      for (int i = 0; i < kSkWaves; ++i) v += red[i][ot >> 4][orow][ot & 15];
-      const int j = j0 + orow;
-      p.cache[dst_page + (j < p.r_k ? k_index(p.r_k, dst_slot, j) : v_index(p.r_k, dst_slot, j - p.r_k))] = bf16_bits(v);
-    }
+    for (int j = 0; j < 4; ++j) red[w][g][4 * q + j][m] = acc[g][j];  // accumulator: row 4 q + j, token m
+  __syncthreads();
+  if (page >= 0 && page < p.n_pages) {
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < kSkWaves; ++i) v += red[i][ot >> 4][orow][ot & 15];
+    const int j = j0 + orow, slot = pos % kPage;
+    uint16_t* dst = p.cache + (size_t)page * p.page_elems;
+    dst[j < p.r_k ? k_index(p.r_k, slot, j) : v_index(p.r_k, slot, j - p.r_k)] = bf16_bits(v);
   }
 }
 
@@ -707,8 +749,8 @@ int set_kernel_attributes_append() {
   return LORC_OK;
 }
 
-// Which kernel takes which batch.  Up to 64 tokens: dot products (8B shape: 21 us at T = 64, 34 at T = 100; the 64-tile
-// GEMM takes 20 from T = 65 on).  Then the 64-tile GEMM while it has about one workgroup per CU: 8B rank 576, 24 us at
+// Which kernel takes which batch.  Up to 64 tokens the one-pass kernel (at T = 64, against the 64-tile GEMM: 8B rank 512 17.7
+// and 23.7 us, 13B rank 2048 29.1 and 32.5, 70B rank 512 32.7 and 40.3).  Then the 64-tile GEMM while it has about one workgroup per CU: 8B rank 576, 24 us at
 // T = 777 (234 workgroups) against 35 for 128 x 128 tiles; 13B rank 2048, 52 against 41 at T = 300 (320 workgroups).
 // Beyond, the cheapest of three tile sizes by the estimates below: microseconds per 32 of the model dimension, fitted to
 // D 4096 .. 8192, ranks 512 .. 2048, T 300 .. 32768 (measured us, 128 x 128 / 256 x 128 / 256 x 256 tiles):
@@ -727,14 +769,22 @@ static double append_tile_cost(int tile, int rows_k, int rows_v, int T, int n_cu
   return 0.9 * (int)load + (rest > 0 ? 0.55 + 0.35 * rest : 0);
 }
 
+template <bool R16>
+static int launch_skinny(const AppendParams& p, int rows, hipStream_t s) {
+  const dim3 grid((p.r_k + p.r_v + rows - 1) / rows), block(64 * kSkWaves);
+  if (p.T <= 8) return launch_kernel(append_skinny_kernel<0, R16>, grid, block, 0, s, p, rows);
+  if (p.T <= 16) return launch_kernel(append_skinny_kernel<1, R16>, grid, block, 0, s, p, rows);
+  if (p.T <= 32) return launch_kernel(append_skinny_kernel<2, R16>, grid, block, 0, s, p, rows);
+  if (p.T <= 48) return launch_kernel(append_skinny_kernel<3, R16>, grid, block, 0, s, p, rows);
+  return launch_kernel(append_skinny_kernel<4, R16>, grid, block, 0, s, p, rows);
+}
+
 int launch_append(const AppendParams& p, int n_cus, hipStream_t s) {
   const int rt = p.r_k + p.r_v;
   if (p.T <= kSkinnyMaxT) {
     int rows = (rt + n_cus - 1) / n_cus;  // one workgroup per CU while 16 rows each suffice
     if (rows > kSkMaxRows) rows = kSkMaxRows;
-    const dim3 grid((rt + rows - 1) / rows), block(64 * kSkWaves);
-    if (p.T <= 16) return launch_kernel(append_skinny_kernel<1>, grid, block, 0, s, p, rows);
-    return launch_kernel(append_skinny_kernel<2>, grid, block, 0, s, p, rows);
+    return rows > 8 ? launch_skinny<true>(p, rows, s) : launch_skinny<false>(p, rows, s);
   }
   const dim3 grid64((p.T + 63) / 64, (rt + 63) / 64);
   if ((long)grid64.x * grid64.y <= (long)kSmallTileMaxWgs * n_cus / 256) return launch_kernel(append_kernel, grid64, dim3(256), 0, s, p);

@@ -94,11 +94,19 @@ def test_prompt_tiles_are_bit_exact(case, D, shuffle):
 
 
 # Rows per workgroup of the small-batch kernel (256 CUs): 1, 5 with a single row left over, and 16; model dimensions of fewer
-# k-steps than it has waves, of one trip and of a second, mostly empty one; both token-group counts and a second pass.
+# lines than it has waves, of a whole number of trips and of one more line.
 @pytest.mark.parametrize("D", [64, 192, 4096, 4160])
 @pytest.mark.parametrize("r_k,r_v,ctx", [(32, 32, [1]), (544, 512, [9, 7]), (544, 512, [17]), (2048, 2016, [1, 2]), (2048, 2016, [30, 3, 1])])
 def test_small_batch_row_groups_are_bit_exact(D, r_k, r_v, ctx):
     _append_and_compare_pool((D, (max(r_k, r_v) + 127) // 128, 128, r_k, r_v), ctx, density=0.2 if D < 4096 else 0.02, seed=D + r_k)
+
+
+# The same kernel's forms per number of tokens (8, 16, 32, 48, 64), at their edges, with up to eight and with more rows per
+# workgroup; model dimensions of one line, of one line more than it has waves, and of several lines each.
+@pytest.mark.parametrize("T", [8, 9, 16, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("D,r_k,r_v", [(64, 96, 32), (1088, 992, 1056), (3136, 1184, 1152)])
+def test_small_batch_token_groups_are_bit_exact(D, r_k, r_v, T):
+    _append_and_compare_pool((D, (max(r_k, r_v) + 127) // 128, 128, r_k, r_v), [T - T // 3 - 1, T // 3, 1], density=64 / D if D > 64 else 1.0, seed=D + T)
 
 
 def test_out_of_range_slots_are_skipped():
@@ -162,8 +170,8 @@ def test_latents_match_oracle(shape):
 
 @pytest.mark.parametrize("T", [1, 5, 16, 17, 32, 33, 64, 65, 100, 129, 200])
 def test_small_batches_are_bit_exact(T):
-    """The dot-product kernel of small batches (T <= 64, one pass per 16 tokens) and the 64-row-tile kernel just
-    above it, with integer data: every latent must land bit-exact at its documented place, one call per batch size."""
+    """The kernel of small batches (T <= 64) and the 64-row-tile kernel just above it, with integer data: every latent
+    must land bit-exact at its documented place, one call per batch size."""
     import torch
     import paper_2410_03111_amd as L
     D, h_kv, d, r_k, r_v = 256, 2, 64, 96, 32
