@@ -145,6 +145,9 @@ int64_t lorc_cache_index_v(const lorc_layer_desc* desc, int32_t slot, int32_t j)
 int lorc_append_latent(const lorc_layer_desc* desc, const void* x, int32_t T, const void* packed,
                        const int32_t* slot_seq, const int32_t* slot_pos, const int32_t* block_table,
                        int32_t n_seqs, int32_t max_pages, int32_t n_pages, void* cache, void* stream);
+/* The name of the kernel that lorc_append_latent would launch for T tokens on the current device (a static string, the symbol
+ * a profiler shows; NULL for an invalid desc or T <= 0).  HOST call; for benchmarks, profiles and tests that must name it. */
+const char* lorc_append_plan_info(const lorc_layer_desc* desc, int32_t T);
 
 /* Decode attention (Eq. 1 over the cached latents; Section 4.3; Appendix on RoPE).  DEVICE pointers.
  *   q        [b x h_q x d] bf16, un-rotated;  q_pos [b] int32 position of the query token

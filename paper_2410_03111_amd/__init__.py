@@ -66,6 +66,7 @@ def _load():
         "lorc_cache_index_k": (ctypes.c_int64, [dsc, i32, i32]),
         "lorc_cache_index_v": (ctypes.c_int64, [dsc, i32, i32]),
         "lorc_append_latent": (ctypes.c_int, [dsc, vp, i32, vp, vp, vp, vp, i32, i32, i32, vp, vp]),
+        "lorc_append_plan_info": (ctypes.c_char_p, [dsc, i32]),
         "lorc_decode_workspace_bytes": (sz, [dsc, i32, i32]),
         "lorc_decode_plan_info": (ctypes.c_char_p, [dsc, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]),
         "lorc_decode_attention": (ctypes.c_int, [dsc, vp, vp, vp, i32, i32, vp, vp, vp, i32, i32, vp, vp, sz, vp]),
@@ -92,6 +93,7 @@ def _load():
 _lib = _load()
 EXPORTS = ("lorc_strerror", "lorc_factorize", "lorc_rank_schedule", "lorc_error_bound", "lorc_packed_bytes", "lorc_pack_factors",
            "lorc_page_bytes", "lorc_cache_index_k", "lorc_cache_index_v", "lorc_append_latent",
+           "lorc_append_plan_info",
            "lorc_decode_workspace_bytes", "lorc_decode_plan_info", "lorc_decode_attention", "lorc_decode_attention_timed",
            "lorc_decode_attention_latent", "lorc_decode_plain_workspace_bytes", "lorc_decode_attention_plain", "lorc_decode_attention_static", "lorc_decode_absorbed_workspace_bytes", "lorc_decode_attention_absorbed",
            "lorc_decode_attention_absorbed_timed",
@@ -187,6 +189,14 @@ def cache_index_v(desc: LayerDesc, slot: int, j: int) -> int:
 
 def decode_workspace_bytes(desc: LayerDesc, b: int, max_ctx: int) -> int:
     return _lib.lorc_decode_workspace_bytes(ctypes.byref(desc), b, max_ctx)
+
+
+def append_plan_info(desc: LayerDesc, T: int) -> str:
+    """The kernel that append_latent launches for T tokens (see lorc_append_plan_info)."""
+    name = _lib.lorc_append_plan_info(ctypes.byref(desc), T)
+    if name is None:
+        raise LorcError(EUNSUPPORTED, "lorc_append_plan_info")
+    return name.decode()
 
 
 def decode_plan_info(desc: LayerDesc, b: int, max_ctx: int):

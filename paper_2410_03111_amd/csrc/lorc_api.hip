@@ -190,6 +190,11 @@ int lorc_append_latent(const lorc_layer_desc* desc, const void* x, int32_t T, co
   return launch_append(p, n_cus, static_cast<hipStream_t>(stream));
 }
 
+const char* lorc_append_plan_info(const lorc_layer_desc* desc, int32_t T) {
+  if (!desc || check_desc(*desc) != LORC_OK || T <= 0) return nullptr;
+  return append_kernel_name(desc->d_model, desc->rank_k, desc->rank_v, T, cu_count_or_default());
+}
+
 size_t lorc_decode_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx) {
   if (!desc || check_desc(*desc) != LORC_OK || b <= 0 || max_ctx < 0) return 0;
   return make_decode_plan(*desc, b, max_ctx, cu_count_or_default()).total_bytes;

@@ -750,23 +750,76 @@ int set_kernel_attributes_append() {
 }
 
 // Which kernel takes which batch.  Up to 64 tokens the one-pass kernel (at T = 64, against the 64-tile GEMM: 8B rank 512 17.7
-// and 23.7 us, 13B rank 2048 29.1 and 32.5, 70B rank 512 32.7 and 40.3).  Then the 64-tile GEMM while it has about one workgroup per CU: 8B rank 576, 24 us at
-// T = 777 (234 workgroups) against 35 for 128 x 128 tiles; 13B rank 2048, 52 against 41 at T = 300 (320 workgroups).
-// Beyond, the cheapest of three tile sizes by the estimates below: microseconds per 32 of the model dimension, fitted to
-// D 4096 .. 8192, ranks 512 .. 2048, T 300 .. 32768 (measured us, 128 x 128 / 256 x 128 / 256 x 256 tiles):
-//   8B rank 576: T = 3116: 40 / 58 / 98,  6002: 67 / 101 / 105,  12288: - / 158 / 110,  16384: - / 185 / 199;
-//   13B rank 2048: T = 777: 43 / 64 / -,  3116: 144 / 139 / 136,  6002: 274 / 246 / 273,  8192: - / 325 / 278.
-constexpr int kSkinnyMaxT = 64, kSmallTileMaxWgs = 288;
+// and 23.7 us, 13B rank 2048 29.1 and 32.5, 70B rank 512 32.7 and 40.3).  Beyond, the cheapest of four tile sizes by the
+// estimates below: microseconds per 32 of the model dimension, fitted to D 4096 .. 8192, ranks 256 .. 5120, T 65 .. 32768
+// (460 sizes measured with every tile: the choice is 0.4 % behind the best on average and 8 % at most; sequences whose tokens
+// do not start at a multiple of eight slots store V latents one by one, which costs the 256 x 256 tiles up to 15 %).  The 64-tile GEMM needs 0.16 to 0.19 while
+// every CU has at most one workgroup.  With two it depends on the number of token tiles: block ids go to the XCDs in turn, so
+// a multiple of eight gives an XCD the same tokens for every row tile (0.25 to 0.29), another number spreads them over all
+// XCDs (0.31 to 0.35).  From 2049 tokens on the 128 x 128 tiles are faster in either case.  Measured, us, 64 x 64 / 128 x 128 /
+// 256 x 128 / 256 x 256 tiles:
+//   8B rank 576: T = 777: 24.5 / 33 / 66 / 102,  900: 37 / 33 / 65 / 102,  1500: 36 / 41 / 77 / 103,  1700: 48 / 36 / 69 / 102,
+//     3116: - / 40 / 58 / 98,  6002: - / 67 / 101 / 105,  12288: - / - / 158 / 110,  16384: - / - / 185 / 199;
+//   13B rank 2048: T = 300: 56 / 44 / 84 / 130,  777: 64 / 43 / 80 / 128,  3000: - / 144 / 133 / 155,  6002: - / 274 / 246 / 273,
+//     8192: - / - / 325 / 278;   13B uncompressed: T = 777: 233 / 136 / 112 / 240,  1500: 327 / 171 / 166 / 241.
+constexpr int kSkinnyMaxT = 64;
 
-static double append_tile_cost(int tile, int rows_k, int rows_v, int T, int n_cus) {  // tile 0: 128 x 128, 1: 256 x 128, 2: 256 x 256
-  const int rows = tile == 0 ? 128 : 256, cols = tile == 2 ? 256 : 128;
+static double append_tile_cost(AppendForm form, int rows_k, int rows_v, int T, int n_cus) {
   auto up = [](int x, int y) { return (x + y - 1) / y; };
-  const int groups = tile == 2 ? up(rows_k + rows_v, rows) : up(rows_k, rows) + up(rows_v, rows);
-  const double load = (double)groups * up(T, cols) / n_cus;  // tiles per CU
-  if (tile == 0) return load <= 1 ? 0.31 : (load <= 2 ? 0.24 + 0.155 * load : (load <= 3.14 ? 0.88 : 0.28 * load));
-  if (tile == 1) return load <= 1 ? 0.36 + 0.18 * load : (load <= 1.64 ? 0.82 : 0.50 * load);
-  const double rest = load - (int)load;  // one workgroup per CU: whole rounds, the last one shorter when it is not full
-  return 0.9 * (int)load + (rest > 0 ? 0.55 + 0.35 * rest : 0);
+  if (form == AppendForm::kTile64) {
+    const int token_tiles = up(T, 64);
+    const double load = (double)token_tiles * up(rows_k + rows_v, 64) / n_cus;  // tiles per CU, here and below
+    if (load <= 1) return 0.18;
+    if (load > 2) return 1e9;
+    return token_tiles % 8 == 0 && token_tiles <= 32 ? 0.285 : 0.34;
+  }
+  if (form == AppendForm::kTile256) {
+    // One workgroup per CU walks rounds of block ids, 0.55 and up to 0.35 more each, by how full it is.  Token tiles come in
+    // eights (one per XCD): whole eights first, then ny turns of the `odd` ones.
+    const int slots = n_cus / 8 * 8, ny = up(rows_k + rows_v, 256), nx = up(T, 256), odd = nx % 8;
+    const long whole = (long)(nx - odd) * ny;
+    double cost = 0.9 * (whole / slots);
+    long here = whole % slots, left = (long)odd * ny;
+    do {
+      const long room = (slots - here) / 8 * odd, n = here + (left < room ? left : room);
+      if (n > 0) cost += 0.55 + 0.35 * n / slots;
+      left -= n - here;
+      here = 0;
+    } while (left > 0);
+    return cost;
+  }
+  const int rows = form == AppendForm::kTile128 ? 128 : 256;
+  const double load = (double)(up(rows_k, rows) + up(rows_v, rows)) * up(T, 128) / n_cus;
+  if (form == AppendForm::kTile128) return load <= 1 ? 0.31 : (load <= 2 ? 0.24 + 0.155 * load : (load <= 3.14 ? 0.88 : 0.28 * load));
+  return load <= 1 ? 0.36 + 0.18 * load : (load <= 1.52 ? 0.82 : 0.54 * load);
+}
+
+AppendForm append_form(int D, int rows_k, int rows_v, int T, int n_cus) {
+  if (T <= kSkinnyMaxT) return AppendForm::kSkinny;
+  AppendForm best = AppendForm::kTile64;
+  double best_cost = append_tile_cost(best, rows_k, rows_v, T, n_cus);
+  for (AppendForm f : {AppendForm::kTile128, AppendForm::kTile256x128, AppendForm::kTile256}) {
+    if (f == AppendForm::kTile256 && D / kGmBK < 2) continue;  // its ring wants two k-tiles
+    const double cost = append_tile_cost(f, rows_k, rows_v, T, n_cus);
+    if (cost < best_cost) best = f, best_cost = cost;
+  }
+  return best;
+}
+
+static unsigned tile_grid(int rows_k, int rows_v, int T, int rows) {  // of append_tile_kernel: eight XCDs' equal shares
+  const int tiles = ((rows_k + rows - 1) / rows + (rows_v + rows - 1) / rows) * ((T + 127) / 128);
+  return (tiles + 7) / 8 * 8;
+}
+
+const char* append_kernel_name(int D, int rows_k, int rows_v, int T, int n_cus) {
+  switch (append_form(D, rows_k, rows_v, T, n_cus)) {
+    case AppendForm::kSkinny: return "append_skinny_kernel";
+    case AppendForm::kTile64: return "append_kernel";
+    case AppendForm::kTile128:
+      return (int)tile_grid(rows_k, rows_v, T, 128) <= n_cus ? "append_tile_kernel<2, 5, 4>" : "append_tile_kernel<2, 2, 4>";
+    case AppendForm::kTile256x128: return "append_tile_kernel<4, 3, 2>";
+    default: return "append_gemm_kernel";
+  }
 }
 
 template <bool R16>
@@ -781,28 +834,27 @@ static int launch_skinny(const AppendParams& p, int rows, hipStream_t s) {
 
 int launch_append(const AppendParams& p, int n_cus, hipStream_t s) {
   const int rt = p.r_k + p.r_v;
-  if (p.T <= kSkinnyMaxT) {
-    int rows = (rt + n_cus - 1) / n_cus;  // one workgroup per CU while 16 rows each suffice
-    if (rows > kSkMaxRows) rows = kSkMaxRows;
-    return rows > 8 ? launch_skinny<true>(p, rows, s) : launch_skinny<false>(p, rows, s);
+  switch (append_form(p.D, p.r_k, p.r_v, p.T, n_cus)) {
+    case AppendForm::kSkinny: {
+      int rows = (rt + n_cus - 1) / n_cus;  // one workgroup per CU while 16 rows each suffice
+      if (rows > kSkMaxRows) rows = kSkMaxRows;
+      return rows > 8 ? launch_skinny<true>(p, rows, s) : launch_skinny<false>(p, rows, s);
+    }
+    case AppendForm::kTile64:
+      return launch_kernel(append_kernel, dim3((p.T + 63) / 64, (rt + 63) / 64), dim3(256), 0, s, p);
+    case AppendForm::kTile128: {
+      const dim3 grid(tile_grid(p.r_k, p.r_v, p.T, 128));
+      if ((int)grid.x <= n_cus) return launch_kernel(append_tile_kernel<2, 5, 4>, grid, dim3(256), rt_ring_bytes<2, 5, 4>(), s, p);
+      return launch_kernel(append_tile_kernel<2, 2, 4>, grid, dim3(256), rt_ring_bytes<2, 2, 4>(), s, p);
+    }
+    case AppendForm::kTile256x128:
+      return launch_kernel(append_tile_kernel<4, 3, 2>, dim3(tile_grid(p.r_k, p.r_v, p.T, 256)), dim3(256), rt_ring_bytes<4, 3, 2>(), s, p);
+    default: {
+      const int nx = (p.T + kGmBN - 1) / kGmBN, ny = (rt + kGmBM - 1) / kGmBM;
+      const int n_virtual = ((nx + 7) / 8) * 8 * ny, slots = (n_cus / 8) * 8;
+      return launch_kernel(append_gemm_kernel, dim3(n_virtual < slots ? n_virtual : slots), dim3(256), kGmLdsBytes, s, p);
+    }
   }
-  const dim3 grid64((p.T + 63) / 64, (rt + 63) / 64);
-  if ((long)grid64.x * grid64.y <= (long)kSmallTileMaxWgs * n_cus / 256) return launch_kernel(append_kernel, grid64, dim3(256), 0, s, p);
-  double cost[3];
-  for (int i = 0; i < 3; ++i) cost[i] = append_tile_cost(i, p.r_k, p.r_v, p.T, n_cus);
-  if (cost[2] < cost[0] && cost[2] < cost[1] && p.D / kGmBK >= 2) {
-    const int nx = (p.T + kGmBN - 1) / kGmBN, ny = (rt + kGmBM - 1) / kGmBM;
-    const int n_virtual = ((nx + 7) / 8) * 8 * ny, slots = (n_cus / 8) * 8;
-    return launch_kernel(append_gemm_kernel, dim3(n_virtual < slots ? n_virtual : slots), dim3(256), kGmLdsBytes, s, p);
-  }
-  auto grid = [&](int rows) {
-    const int tiles = ((p.r_k + rows - 1) / rows + (p.r_v + rows - 1) / rows) * ((p.T + 127) / 128);
-    return dim3((tiles + 7) / 8 * 8);
-  };
-  if (cost[1] < cost[0]) return launch_kernel(append_tile_kernel<4, 3, 2>, grid(256), dim3(256), rt_ring_bytes<4, 3, 2>(), s, p);
-  const dim3 g = grid(128);
-  if ((int)g.x <= n_cus) return launch_kernel(append_tile_kernel<2, 5, 4>, g, dim3(256), rt_ring_bytes<2, 5, 4>(), s, p);
-  return launch_kernel(append_tile_kernel<2, 2, 4>, g, dim3(256), rt_ring_bytes<2, 2, 4>(), s, p);
 }
 
 int launch_stream_probe(const void* src, size_t bytes, void* sink, hipStream_t s) {

@@ -169,6 +169,32 @@ def test_decode_plan_info_names_the_kernel_and_covers_the_context():
         L.decode_plan_info(L.layer_desc(4096, 32, 8, 96, 512, 512, 1e4), 1, 64)
 
 
+@pytest.mark.parametrize("D,r_k,r_v,T,kernel", [
+    (256, 32, 32, 64, "append_skinny_kernel"), (4096, 512, 512, 65, "append_kernel"),
+    (4096, 512, 512, 1024, "append_kernel"),                # one 64 x 64 tile per CU
+    (4096, 576, 576, 1500, "append_kernel"), (4096, 768, 768, 1000, "append_kernel"), (8192, 512, 512, 1500, "append_kernel"),
+    (4096, 1024, 1024, 1000, "append_kernel"),              # up to two, token tiles a multiple of eight
+    (4096, 576, 576, 900, "append_tile_kernel<2, 5, 4>"), (5120, 2048, 2048, 300, "append_tile_kernel<2, 5, 4>"),
+    (4096, 384, 384, 2500, "append_tile_kernel<2, 5, 4>"),  # ... of which there are more than 32
+    (4096, 576, 576, 6002, "append_tile_kernel<2, 2, 4>"), (4096, 512, 512, 12000, "append_gemm_kernel"),
+    (5120, 5120, 5120, 777, "append_tile_kernel<4, 3, 2>"), (5120, 5120, 5120, 1500, "append_tile_kernel<4, 3, 2>"),
+    (4096, 576, 576, 12288, "append_gemm_kernel"), (4096, 512, 512, 32768, "append_gemm_kernel"),
+    (5120, 2048, 2048, 10000, "append_gemm_kernel"), (8192, 512, 512, 25000, "append_gemm_kernel"),
+    (4096, 768, 768, 18000, "append_gemm_kernel"), (4096, 576, 576, 12320, "append_tile_kernel<2, 2, 4>"),
+    (64, 512, 512, 32768, "append_tile_kernel<4, 3, 2>")])  # (the 256 x 256 tiles' ring wants two k-tiles)
+def test_append_takes_the_kernel_measured_fastest(D, r_k, r_v, T, kernel):
+    """The kernel that measurement found fastest at sizes on either side of the rule's lines (256 CUs)."""
+    n = (max(r_k, r_v) + 127) // 128 * 128
+    assert L.append_plan_info(L.layer_desc(D, n // 128, n // 128, 128, r_k, r_v, 1e4), T) == kernel
+
+
+def test_append_plan_info_refuses_what_append_refuses():
+    with pytest.raises(L.LorcError):
+        L.append_plan_info(L.layer_desc(4096, 32, 8, 96, 512, 512, 1e4), 1)
+    with pytest.raises(L.LorcError):
+        L.append_plan_info(L.layer_desc(4096, 32, 8, 128, 512, 512, 1e4), 0)
+
+
 def test_bench_refuses_more_than_one_gpu():
     """The build is single-GPU: asking bench.py for more exits with a message before anything touches a device."""
     import subprocess
