@@ -9,13 +9,15 @@ from lorc_testlib import GpuLayer, Problem, PAGE, page_gather_indices
 pytestmark = pytest.mark.gpu
 
 
-def _append_and_compare_pool(geom, ctx, density=1.0, seed=5, shuffle=True):
+def _append_and_compare_pool(geom, ctx, density=1.0, seed=5, shuffle=True, kernel=None):
     """Appends integer-valued tokens (a fraction `density` of them non-zero) and compares the whole pool, byte for
-    byte, with the latents placed by the documented index formulas.  Returns (L, desc, idx) for further checks."""
+    byte, with the latents placed by the documented index formulas.  kernel: the one that the dispatch must take for
+    this size.  Returns (L, desc, idx) for further checks."""
     import torch
     import paper_2410_03111_amd as L
     D, h_kv, d, r_k, r_v = geom
     desc = L.layer_desc(D, 2 * h_kv, h_kv, d, r_k, r_v, 10000.0)
+    assert kernel is None or L.append_plan_info(desc, sum(ctx)) == kernel
     rng = np.random.default_rng(seed)
     A_k = rng.integers(-1, 2, (D, r_k)).astype(np.float32)
     A_v = rng.integers(-1, 2, (D, r_v)).astype(np.float32)
@@ -52,15 +54,16 @@ def _append_and_compare_pool(geom, ctx, density=1.0, seed=5, shuffle=True):
     return L, desc, idx
 
 
-@pytest.mark.parametrize("geom,ctx", [((128, 2, 64, 64, 32), [130, 1, 64, 77]),
-                                      ((256, 4, 64, 256, 224), [4100, 1, 64, 77]),
-                                      ((128, 2, 64, 64, 32), [8100, 1, 64, 77])],
-                         ids=["272_tokens", "4242_tokens_wide", "8242_tokens"])
-def test_indexing_is_bit_exact_with_integer_data(geom, ctx):
+@pytest.mark.parametrize("geom,ctx,kernel", [((128, 2, 64, 64, 32), [130, 1, 64, 77], "append_kernel"),
+                                             ((256, 4, 64, 256, 224), [4100, 1, 64, 77], "append_tile_kernel<2, 5, 4>"),
+                                             ((128, 2, 64, 64, 32), [8100, 1, 64, 77], "append_tile_kernel<2, 5, 4>"),
+                                             ((128, 2, 64, 64, 32), [32900, 1, 64, 77], "append_gemm_kernel")],
+                         ids=["272_tokens", "4242_tokens_wide", "8242_tokens", "33042_tokens"])
+def test_indexing_is_bit_exact_with_integer_data(geom, ctx, kernel):
     """Integer-valued inputs make every latent exactly representable, so the pool can be compared byte for
     byte: each (sequence, position) must sit at its documented place and nothing else may change.  The
-    cases go through the 64-row-tile, the 128-row-tile and the 256-row-tile kernel."""
-    L, desc, idx = _append_and_compare_pool(geom, ctx)
+    cases go through the 64 x 64, the 128 x 128 and the 256 x 256 tile kernel."""
+    L, desc, idx = _append_and_compare_pool(geom, ctx, kernel=kernel)
     r_k, r_v = geom[3], geom[4]
     # the library's own index helpers agree with the documented formulas
     for slot, j in [(0, 0), (33, 17), (63, r_k - 1), (17, 40)]:
@@ -70,27 +73,39 @@ def test_indexing_is_bit_exact_with_integer_data(geom, ctx):
 
 
 @pytest.mark.parametrize("D", [64, 192, 640, 832])
-@pytest.mark.parametrize("case", ["64_row_tile", "128_row_tile", "256_row_tile"])
+@pytest.mark.parametrize("case", ["64_row_tile", "128_row_tile", "64_row_tile_8191_tokens", "256_row_tile_few_rows"])
 def test_model_dimension_tails_are_bit_exact(D, case):
     """Model dimensions of 1, 3, 10 and 13 k-tiles: fewer k-tiles than a kernel keeps in flight, and counts that
-    leave a remainder after its unrolled groups, for each of the three tiled kernels."""
-    geom, ctx = {"64_row_tile": ((D, 2, 64, 64, 32), [100, 37]),
-                 "128_row_tile": ((D, 4, 64, 256, 224), [4100, 1, 90]),
-                 "256_row_tile": ((D, 2, 64, 64, 32), [8100, 1, 90])}[case]
-    _append_and_compare_pool(geom, ctx, density=0.2, seed=D)
+    leave a remainder after its unrolled groups, for each of the tiled kernels (256 x 128: below).  "few_rows": fewer
+    latent rows than one tile of the 256 x 256 kernel, which does not take a single k-tile."""
+    geom, ctx, kernel = {"64_row_tile": ((D, 2, 64, 64, 32), [100, 37], "append_kernel"),
+                         "128_row_tile": ((D, 4, 64, 256, 224), [4100, 1, 90], "append_tile_kernel<2, 5, 4>"),
+                         "64_row_tile_8191_tokens": ((D, 2, 64, 64, 32), [8100, 1, 90], "append_kernel"),
+                         "256_row_tile_few_rows": ((D, 2, 64, 64, 64), [32800, 1, 90],
+                                                   "append_gemm_kernel" if D > 64 else "append_tile_kernel<2, 2, 4>")}[case]
+    _append_and_compare_pool(geom, ctx, density=0.2, seed=D, kernel=kernel)
 
 
-# Sizes on either side of the rules that pick the tile of a prompt's down-projection (256 CUs): workgroup counts that make
-# 128 x 128, 256 x 128 and 256 x 256 tiles the cheapest; row groups that end inside a tile, ragged token tiles.
-TILES = {"128x128": ((512, 544), [1107, 1, 64, 78]), "256x128": ((480, 512), [77, 4058, 1, 64]), "256x256": ((512, 512), [64, 15759, 77])}
+# Sizes on either side of the rules that pick the tile of a prompt's down-projection (256 CUs): 128 x 128 with all of LDS and
+# with half of it, 256 x 128 (from D = 192 on its three-slot ring wraps), 256 x 256; row groups that end inside a tile, ragged
+# token tiles.  "rows_slid": 256 x 256 with the boundary of K and V inside a wave's rows and a last row tile that is slid back.
+TILES = {
+    "128x128_one_per_cu": ((512, 544), [1107, 1, 64, 78], "append_tile_kernel<2, 5, 4>"),
+    "128x128": ((480, 512), [77, 4058, 1, 64], "append_tile_kernel<2, 2, 4>"),
+    "256x128": ((480, 512), [77, 7650, 1, 64], "append_tile_kernel<4, 3, 2>"),
+    "256x256": ((512, 512), [64, 15759, 77], "append_gemm_kernel"),
+    "256x256_rows_slid": ((576, 576), [64, 9003, 77], "append_gemm_kernel"),
+}
 
 
 @pytest.mark.parametrize("shuffle", [False, True], ids=["prompt_order", "shuffled"])
 @pytest.mark.parametrize("D", [64, 192, 640])
 @pytest.mark.parametrize("case", list(TILES))
 def test_prompt_tiles_are_bit_exact(case, D, shuffle):
-    (r_k, r_v), ctx = TILES[case]
-    _append_and_compare_pool((D, 8, 128, r_k, r_v), ctx, density=0.2, seed=D, shuffle=shuffle)
+    (r_k, r_v), ctx, kernel = TILES[case]
+    if D == 64 and kernel == "append_gemm_kernel":
+        kernel = None  # its ring wants two k-tiles: another tile takes it
+    _append_and_compare_pool((D, 9, 128, r_k, r_v), ctx, density=0.2, seed=D, shuffle=shuffle, kernel=kernel)
 
 
 # Rows per workgroup of the small-batch kernel (256 CUs): 1, 5 with a single row left over, and 16; model dimensions of fewer
@@ -135,11 +150,12 @@ def test_out_of_range_slots_are_skipped():
     dict(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=64, rank_k=32, rank_v=32, rope_base=10000.0, ctx=[128]),
     dict(d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=128, rank_k=64, rank_v=96, rope_base=10000.0, ctx=[1, 77, 300]),
     dict(d_model=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, rank_k=512, rank_v=512, rope_base=500000.0, ctx=[200, 513]),
-    # above a thousand tokens in one call, with ragged token and latent-row tails (64- and 128-row-tile GEMM)
+    # above a thousand tokens in one call, with ragged token and latent-row tails (64 x 64 and 128 x 128 tiles)
     dict(d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=128, rank_k=96, rank_v=64, rope_base=10000.0, ctx=[700, 1, 530]),
     dict(d_model=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, rank_k=768, rank_v=384, rope_base=500000.0, ctx=[1700, 333]),
-    # 8192 tokens and more in one call: the 256-row-tile GEMM of long prompts, same ragged tails
+    # more than 8192 tokens in one call, same ragged tails: 128 x 128 tiles, and at more rows the 256 x 256 ones
     dict(d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=128, rank_k=96, rank_v=64, rope_base=10000.0, ctx=[7900, 1, 530]),
+    dict(d_model=512, n_q_heads=8, n_kv_heads=4, head_dim=128, rank_k=352, rank_v=224, rope_base=10000.0, ctx=[15500, 1, 530]),
 ])
 def test_latents_match_oracle(shape):
     pb = Problem(seed=3, **shape).build()
