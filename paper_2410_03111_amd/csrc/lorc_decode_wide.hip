@@ -815,11 +815,24 @@ DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cu
   }
   pl.n_splits = (n_tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;
   const int out_w = plain ? d.head_dim : d.rank_v;
+  // A loop that sizes its workspace once, for its longest context and largest batch, calls with less of either, and the cheapest
+  // split often takes more splits for fewer tiles (16 x 1024 positions: 16 splits, 16 x 1088: 9).  So the one-pass kernel's
+  // partials are given room for a number that no call with fewer tiles or sequences exceeds: with P = b x head groups, a choice
+  // of t tiles costs at least 5 P (n_tiles + splits) / cus + 0.09 splits, and no more than eight tiles per split, which cost at
+  // most 45 (P (n_tiles / 8 + 1) / cus + 1) + 0.09 (n_tiles / 8 + 1).
+  size_t room = pl.n_splits;
+  if (one_pass) {
+    const double P = (double)b * pl.v_chunks;
+    room = (size_t)(n_tiles / 8.0 + (45.0 * (P + cus) + 0.09 * cus) / (5.0 * P + 0.09 * cus)) + 1;
+    if (room > (size_t)n_tiles) room = n_tiles;
+    if (room > 512) room = 512;
+    if (room < (size_t)pl.n_splits) room = pl.n_splits;  // (rounding in the estimates)
+  }
   size_t off = 0;
   pl.off_ml = off;
-  off = align256w(off + (size_t)b * pl.n_splits * d.n_q_heads * 2 * 4);
+  off = align256w(off + (size_t)b * room * d.n_q_heads * 2 * 4);
   pl.off_o = off;
-  off = align256w(off + (size_t)b * pl.n_splits * d.n_q_heads * out_w * 2);
+  off = align256w(off + (size_t)b * room * d.n_q_heads * out_w * 2);
   pl.off_scores = off;
   if (!one_pass) off = align256w(off + (size_t)b * d.n_q_heads * pl.score_stride * 4);
   pl.total_bytes = off;

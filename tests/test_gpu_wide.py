@@ -136,6 +136,29 @@ def test_uncompressed_layer_in_one_pass_matches_oracle(name):
     _check(pb, layer, ref=ref, tag=f"one pass {name}")
 
 
+def test_uncompressed_decode_with_a_workspace_sized_for_longer_contexts_and_more_sequences():
+    """One workspace for the longest context (17 pages, batch 16) serves shorter calls, whose split plans take more splits,
+    and nothing behind it is written."""
+    import torch
+    pb = Problem(d_model=256, n_q_heads=8, n_kv_heads=8, head_dim=128, rank_k=1024, rank_v=1024, rope_base=10000.0,
+                 ctx=[1088] + [300, 64, 1] * 5, seed=37).build()
+    layer = GpuLayer(pb, plain=True)
+    layer.append_all()
+    L, dev = layer.L, layer.dev
+    need = L.decode_plain_workspace_bytes(layer.desc, 16, 1088)
+    buf = torch.full((need + 65536,), 0x5A, dtype=torch.uint8, device=dev)
+    q = torch.from_numpy(pb.q).to(dev).to(torch.bfloat16)
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device=dev)
+    for b, longest in ((16, 1088), (16, 1024), (16, 960), (16, 130), (9, 1024), (1, 1088), (1, 64)):
+        ctx = [min(N, longest) for N in pb.ctx[:b]]
+        args = (layer.desc, q[:b].contiguous(), i32([N - 1 for N in ctx]), i32(ctx), longest, layer.packed, layer.cache, layer.block_table)
+        want = L.decode_attention_plain(*args)
+        got = L.decode_attention_plain(*args, workspace=buf[:need])
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), (b, longest)
+    assert bool((buf[need:] == 0x5A).all())
+
+
 def test_plain_entry_point_refuses_a_compressed_desc():
     import paper_2410_03111_amd as L
     assert L.decode_plain_workspace_bytes(L.layer_desc(512, 8, 2, 128, 128, 256, 1e4), 1, 64) == 0

@@ -150,6 +150,25 @@ def test_workspace_helpers_accept_an_empty_context():
     assert L.decode_workspace_bytes(L.layer_desc(4096, 32, 8, 128, 512, 512, 5e5), 16, -1) == 0
 
 
+@pytest.mark.parametrize("n_q_heads,n_kv_heads", [(32, 8), (8, 8), (64, 16), (40, 40), (64, 64)])
+def test_uncompressed_workspace_grows_with_context_and_batch(n_q_heads, n_kv_heads):
+    """KV heads a multiple of eight (the one-pass kernel): a workspace sized for the longest context and the largest batch
+    serves every smaller call, and it never exceeds scores and partials of the three-launch path (256 bytes per head and
+    position tile, 264 per head and split)."""
+    n = 128 * n_kv_heads
+    desc = L.layer_desc(1024, n_q_heads, n_kv_heads, 128, n, n, 1e4)
+    previous = None
+    for b in (1, 2, 3, 5, 8, 16, 33, 64, 100, 256, 1000):
+        sizes = [L.decode_plain_workspace_bytes(desc, b, 64 * t) for t in list(range(0, 700)) + list(range(700, 9000, 37))]
+        assert all(x <= y for x, y in zip(sizes, sizes[1:]))
+        assert previous is None or all(x <= y for x, y in zip(previous, sizes))
+        for t in (1, 2, 7, 64, 300, 699):
+            splits = max(1, min((t + 3) // 4, 512, -(-2048 // (b * n_kv_heads))))
+            splits = -(-t // -(-t // splits))
+            assert sizes[t] <= b * n_q_heads * (256 * t + 264 * splits) + 768
+        previous = sizes
+
+
 def test_decode_plan_info_names_the_kernel_and_covers_the_context():
     """Host-only: the reported plan names the kernel the launch will use and its splits cover every tile."""
     for desc, b, ctx in ((L.layer_desc(4096, 32, 8, 128, 512, 512, 5e5), 16, 4096),
