@@ -622,7 +622,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
     }
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) L += __shfl_xor(L, off);
-    const float invL = L > 0.f ? 1.f / L : 0.f;
+    const float invL = L > 0.f ? 1.f / L : (M == kNoWeight ? __builtin_nanf("") : 0.f);
     for (int s = lane; s < ns; s += 64) wgt[s] *= invL;
   }
   __syncthreads();

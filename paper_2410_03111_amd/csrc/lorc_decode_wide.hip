@@ -363,7 +363,8 @@ __global__ __launch_bounds__(256, 1) void decode_plain_kernel(DecodeParams p) {
       for (int e = 0; e < 8; ++e) cl[b][kk][e] = p.lane_cs[po[b] * HALF + 32 * kk + 8 * q + e];
   const double theta = p.rope_tab[lane] * 0.15915494309189533576888;  // turns per position
 
-  float m_run[2] = {kNegInfW, kNegInfW}, l_run[2] = {0.f, 0.f};
+  // finite from the start: while every score so far is -inf, the weights and the rescaling are exp2(-inf) and exp2(0)
+  float m_run[2] = {kNoWeight, kNoWeight}, l_run[2] = {0.f, 0.f};
   f32x4 o[2][8];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -475,7 +476,7 @@ __global__ __launch_bounds__(256, 1) void decode_plain_kernel(DecodeParams p) {
     if (m < G) {
       const size_t row = ((size_t)seq * p.n_splits + split) * p.h_q + (size_t)(g0 + 4 * h) * G + m;
       if (q == 0) {
-        p.part_ml[row * 2] = m_run[h];
+        p.part_ml[row * 2] = n_steps > 0 ? m_run[h] : kNegInfW;
         p.part_ml[row * 2 + 1] = l;
       }
 #pragma unroll

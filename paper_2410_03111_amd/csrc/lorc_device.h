@@ -20,6 +20,10 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
+// Maximum of a split that has positions, but only ones whose score is -inf: it weighs nothing next to any other split, and
+// differs from the -inf of a split without positions (the output of a row that has nothing else is NaN, not zero).
+constexpr float kNoWeight = -3.4028234663852886e38f;
+
 // D[32x32] += A[32x16] B[16x32].  Lane l supplies A[m = l%32][k = 8*(l/32) .. +7] and
 // B[k = 8*(l/32) .. +7][n = l%32]; it receives D[m = 8*(j/4) + 4*(l/32) + j%4][n = l%32] in register j.
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {

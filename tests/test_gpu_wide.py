@@ -5,7 +5,8 @@ oracle cheap; one case runs the 13B layer shape itself with LAPACK factors."""
 import numpy as np
 import pytest
 
-from lorc_testlib import GpuLayer, Problem, TOL, numpy_factors, oracle_decode, rel_err
+from oracle import lorc_oracle as orc
+from lorc_testlib import GpuLayer, Problem, TOL, numpy_factors, oracle_decode, page_gather_indices, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -157,6 +158,48 @@ def test_uncompressed_decode_with_a_workspace_sized_for_longer_contexts_and_more
         torch.cuda.synchronize()
         assert torch.equal(got, want), (b, longest)
     assert bool((buf[need:] == 0x5A).all())
+
+
+@pytest.mark.parametrize("n_kv_heads", [2, 8])
+def test_uncompressed_scores_of_minus_infinity_weigh_nothing(n_kv_heads):
+    """Keys beyond fp16 give scores of -inf.  Such positions drop out of the softmax wherever they lie -- at the start of a
+    context for longer than a step of the one-pass kernel, or in its middle -- and only a row that has nothing else is NaN."""
+    import lorc_inputs as gen
+    import torch
+    import paper_2410_03111_amd as L
+    n, base, ctx = 128 * n_kv_heads, 500000.0, [100, 150, 70]
+    dropped = [slice(0, 40), slice(64, 97), slice(0, 70)]
+    dev = torch.device("cuda:0")
+    desc = L.layer_desc(256, n_kv_heads, n_kv_heads, 128, n, n, base)
+    rng = np.random.default_rng(8)
+    K, V = (gen.bf16_round(rng.standard_normal((3, 192, n_kv_heads, 128)).astype(np.float32)) for _ in range(2))
+    q = gen.bf16_round(rng.standard_normal((3, n_kv_heads, 128)).astype(np.float32))
+    # the slowest rotation pair (63, 127): 2e-6 radians per position, so that it stays with coordinate 63
+    K[..., 63] = K[..., 127] = q[..., 127] = 0.0
+    q[..., 63] = 1.0
+    for s, d in enumerate(dropped):
+        K[s, d, :, 63] = gen.bf16_round(np.float32(-1e5))
+    idx = page_gather_indices(n, n)
+    pool = np.empty((9, 64 * 2 * n), np.uint16)
+    for s in range(3):
+        for p in range(3):
+            rows = slice(64 * p, 64 * p + 64)
+            pool[3 * s + p][idx] = gen.bf16_bits(np.concatenate([K[s, rows].reshape(64, n), V[s, rows].reshape(64, n)], axis=1))
+    cache = torch.from_numpy(pool.view(np.uint8).reshape(-1).copy()).to(dev)
+    z = torch.zeros(256, n, dtype=torch.bfloat16, device=dev)
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device=dev)
+    out = L.decode_attention_plain(desc, torch.from_numpy(q).to(dev, torch.bfloat16), i32([N - 1 for N in ctx]), i32(ctx), max(ctx),
+                                   L.pack_factors(desc, z, z, None, None), cache, i32([[0, 1, 2], [3, 4, 5], [6, 7, 8]]))
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy().astype(np.float64)
+    for s, N in enumerate(ctx):
+        keep = np.setdiff1d(np.arange(N), np.arange(192)[dropped[s]])
+        if len(keep) == 0:
+            assert np.all(np.isnan(got[s]))
+            continue
+        ref = orc.attention_decode(q[s].astype(np.float64), N - 1, K[s, keep].astype(np.float64),
+                                   V[s, keep].astype(np.float64), keep, base)
+        assert np.all(np.isfinite(got[s])) and rel_err(got[s], ref) <= TOL
 
 
 def test_plain_entry_point_refuses_a_compressed_desc():
