@@ -320,7 +320,8 @@ int prefill_common(const lorc_layer_desc* desc, const void* q, const int32_t* cu
   // the attention kernel addresses one sequence's rebuilt keys with 32-bit byte offsets
   if ((size_t)plan.lp * n * 2 > 0x7fffffffu) return LORC_EUNSUPPORTED;
   if (workspace_bytes < plan.total_bytes) return LORC_EWORKSPACE;
-  if (int rc = device_ready(nullptr)) return rc;
+  int n_cus = 0;
+  if (int rc = device_ready(&n_cus)) return rc;
   const uint16_t* pk = static_cast<const uint16_t*>(packed);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   PrefillParams p;
@@ -349,7 +350,7 @@ int prefill_common(const lorc_layer_desc* desc, const void* q, const int32_t* cu
   p.page_elems = page_elems(desc->rank_k, desc->rank_v);
   p.rope_base = desc->rope_base;
   p.q_scale = softmax_scale_log2(*desc);
-  return launch_prefill(p, static_cast<hipStream_t>(stream), plain);
+  return launch_prefill(p, n_cus, static_cast<hipStream_t>(stream), plain);
 }
 }  // namespace
 

@@ -254,9 +254,9 @@ __global__ __launch_bounds__(256, 2) void plain_scores_kernel(DecodeParams p) {
 }
 
 // ------------------------------------------------------------------------------------------------ uncompressed, one pass
-// Decode of an uncompressed layer with eight KV heads (or a multiple) and groups of up to sixteen query heads in one pass over
-// the pages: one workgroup per (eight KV heads, split, sequence), wave w owns the KV heads w and w + 4 of the eight and walks
-// the split's positions 32 at a time with online softmax; the waves exchange nothing.  Bound by the page stream.  A wave keeps
+// Decode of an uncompressed layer with eight KV heads (or a multiple; the groups then have at most eight query heads, which fill
+// half of a 16-wide operand) in one pass over the pages: one workgroup per (eight KV heads, split, sequence), wave w owns the KV
+// heads w and w + 4 of the eight and walks the split's positions 32 at a time with online softmax; the waves exchange nothing.  Bound by the page stream.  A wave keeps
 // one step of keys and one of values (16 KiB each) in flight: the next keys are requested when the scores have used the
 // current ones, the next values when the weighted sum has.  16x16x32 products throughout:
 //   S^T = K Q^T: row r = 4 q + j of block b (lane group q = lane / 16) is position 8 q + 4 b + j of the step, so that a lane's
@@ -773,8 +773,9 @@ bool plain_shape_ok(const lorc_layer_desc& d) {
   return d.head_dim == 128 && d.rank_k == n && d.rank_v == n && G <= 32 && d.n_q_heads <= 64;
 }
 
-// Uncompressed layers in one pass: all eight KV heads of a workgroup are real, and a group's rows fit one 16-wide operand.
-static bool plain_one_pass(int G, int h_kv) { return G <= 16 && h_kv % kPlainHeads == 0; }
+// Uncompressed layers in one pass: all eight KV heads of a workgroup are real.  (Its sixteen operand columns hold any group
+// then: 64 query heads at most.)
+static bool plain_one_pass(int h_kv) { return h_kv % kPlainHeads == 0; }
 
 // Splits for the value kernel: enough workgroups for about two per CU, each walking at least four tiles; for the one-pass
 // kernel of uncompressed layers see below.
@@ -784,7 +785,7 @@ DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cu
   pl.occupancy = 1;
   pl.stationary = 0;
   pl.wide = plain ? 2 : 1;
-  const bool one_pass = plain && plain_one_pass(d.n_q_heads / d.n_kv_heads, d.n_kv_heads);
+  const bool one_pass = plain && plain_one_pass(d.n_kv_heads);
   int n_tiles = (max_ctx + kWideT - 1) / kWideT;
   if (n_tiles < 1) n_tiles = 1;
   pl.score_stride = n_tiles * kWideT;
@@ -863,7 +864,7 @@ int launch_decode_wide(const DecodeParams& p, const DecodePlan& plan, hipStream_
     if (int rc = launch_kernel(absorbed_scores_kernel<2>, dim3(p.b * tiles), dim3(256), 0, s, p)) return rc;
     return launch_kernel(latent_pv_kernel<2, 4, false>, grid, dim3(256), 0, s, p);
   }
-  if (plan.wide == 2 && plain_one_pass(p.G, p.h_kv))
+  if (plan.wide == 2 && plain_one_pass(p.h_kv))
     return launch_kernel(decode_plain_kernel, dim3(p.b * p.n_splits * (p.h_kv / kPlainHeads)), dim3(256), 0, s, p);
   if (plan.wide == 2) {
     const size_t lds = (size_t)p.h_q * 128 * 2;

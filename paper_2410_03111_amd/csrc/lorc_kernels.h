@@ -47,10 +47,12 @@ struct DecodePlan {
   int tile;             // positions per tile (64 or 128)
   int occupancy;        // workgroups meant to share a CU (1 or 2)
   int stationary;       // 1: the split kernel with the key factor held in registers (lorc_decode_stat.hip)
-  int wide;             // three-launch path (lorc_decode_wide.hip): 1 ranks above 1024, 2 uncompressed layer, 3 absorbed query
+  int wide;             // lorc_decode_wide.hip: 1 ranks above 1024, 2 uncompressed layer, 3 absorbed query (scores, values, merge;
+                        // uncompressed layers of eight KV heads or a multiple: one pass, merge)
   int score_stride;     // wide: positions per score row (max_ctx rounded up to whole tiles)
-  int v_chunks;         // wide: column chunks of the value kernel (512 latent columns each; uncompressed: KV heads)
-  size_t off_scores;    // wide: fp32 scores [b][h_q][score_stride]
+  int v_chunks;         // wide: column chunks of the value kernel (512 latent columns each; uncompressed: KV heads, in one pass
+                        // groups of eight)
+  size_t off_scores;    // wide: fp32 scores [b][h_q][score_stride] (none in one pass)
   int n_splits;         // context splits per sequence
   int tiles_per_split;  // tiles each split walks
   size_t off_ml, off_o, total_bytes;  // workspace carve-up (bytes)
@@ -102,7 +104,7 @@ struct PrefillParams {
 
 // Every launcher returns LORC_OK or the lorc_status of the first launch (or event record) that failed.
 PrefillPlan make_prefill_plan(const lorc_layer_desc& d, int b, int max_seqlen);
-int launch_prefill(const PrefillParams& p, hipStream_t s, bool plain = false);
+int launch_prefill(const PrefillParams& p, int n_cus, hipStream_t s, bool plain = false);
 
 DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus);
 

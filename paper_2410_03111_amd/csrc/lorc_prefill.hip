@@ -529,7 +529,7 @@ int set_kernel_attributes_prefill() {
   return LORC_OK;
 }
 
-int launch_prefill(const PrefillParams& p, hipStream_t s, bool plain) {
+int launch_prefill(const PrefillParams& p, int n_cus, hipStream_t s, bool plain) {
   const bool d128 = p.head_dim == 128;
   int rc;
   if (plain) {  // uncompressed layer: keys and values are gathered from the pages, then the same attention kernel
@@ -537,7 +537,7 @@ int launch_prefill(const PrefillParams& p, hipStream_t s, bool plain) {
     rc = launch_kernel(prefill_plain_gather_kernel, dim3(p.b * p.tiles_per_seq), dim3(256), 0, s, p);
   } else {
     const long wgs4 = (long)p.b * ((p.tiles_per_seq + 1) / 2) * 2 * ((p.h_kv * p.head_dim + 255) / 256);
-    if (wgs4 >= 2 * 256) rc = d128 ? launch_rebuild<128, 4>(p, s) : launch_rebuild<64, 4>(p, s);
+    if (wgs4 >= 2L * n_cus) rc = d128 ? launch_rebuild<128, 4>(p, s) : launch_rebuild<64, 4>(p, s);
     else rc = d128 ? launch_rebuild<128, 2>(p, s) : launch_rebuild<64, 2>(p, s);
   }
   if (rc != LORC_OK) return rc;
