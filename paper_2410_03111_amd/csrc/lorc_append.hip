@@ -752,16 +752,19 @@ int set_kernel_attributes_append() {
 // Which kernel takes which batch.  Up to 64 tokens the one-pass kernel (at T = 64, against the 64-tile GEMM: 8B rank 512 17.7
 // and 23.7 us, 13B rank 2048 29.1 and 32.5, 70B rank 512 32.7 and 40.3).  Beyond, the cheapest of four tile sizes by the
 // estimates below: microseconds per 32 of the model dimension, fitted to D 4096 .. 8192, ranks 256 .. 5120, T 65 .. 32768
-// (460 sizes measured with every tile: the choice is 0.4 % behind the best on average and 8 % at most; sequences whose tokens
-// do not start at a multiple of eight slots store V latents one by one, which costs the 256 x 256 tiles up to 15 %).  The 64-tile GEMM needs 0.16 to 0.19 while
-// every CU has at most one workgroup.  With two it depends on the number of token tiles: block ids go to the XCDs in turn, so
-// a multiple of eight gives an XCD the same tokens for every row tile (0.25 to 0.29), another number spreads them over all
-// XCDs (0.31 to 0.35).  From 2049 tokens on the 128 x 128 tiles are faster in either case.  Measured, us, 64 x 64 / 128 x 128 /
-// 256 x 128 / 256 x 256 tiles:
+// (460 sizes measured with every tile, weights in HBM, 130 of them also with weights the caches still hold: the choice is 0.5 %
+// behind the best on average).  The 64-tile GEMM needs 0.16 to 0.19 while every CU has at most one workgroup.  Just beyond, it
+// depends on the number of token tiles: block ids go to the XCDs in turn, so a multiple of eight gives an XCD the same tokens
+// for every row tile (0.28), another number spreads them over all XCDs (0.29 to 0.33).  With up to two per CU, a multiple of
+// eight is 10 % faster than 128 x 128 tiles on weights from HBM and 10 % slower on cached ones (8B rank 768, 1000 tokens: 37
+// and 41 us, 36 and 34), and another number slower on both, so that the line is drawn at 1.125.  Measured, us, 64 x 64 /
+// 128 x 128 / 256 x 128 / 256 x 256 tiles, weights in HBM:
 //   8B rank 576: T = 777: 24.5 / 33 / 66 / 102,  900: 37 / 33 / 65 / 102,  1500: 36 / 41 / 77 / 103,  1700: 48 / 36 / 69 / 102,
 //     3116: - / 40 / 58 / 98,  6002: - / 67 / 101 / 105,  12288: - / - / 158 / 110,  16384: - / - / 185 / 199;
 //   13B rank 2048: T = 300: 56 / 44 / 84 / 130,  777: 64 / 43 / 80 / 128,  3000: - / 144 / 133 / 155,  6002: - / 274 / 246 / 273,
 //     8192: - / - / 325 / 278;   13B uncompressed: T = 777: 233 / 136 / 112 / 240,  1500: 327 / 171 / 166 / 241.
+// (Sequences whose tokens do not start at a multiple of eight slots store V latents one by one, which costs the 256 x 256 tiles
+// up to 15 %; where tokens go is not known here.)
 constexpr int kSkinnyMaxT = 64;
 
 static double append_tile_cost(AppendForm form, int rows_k, int rows_v, int T, int n_cus) {
@@ -770,8 +773,8 @@ static double append_tile_cost(AppendForm form, int rows_k, int rows_v, int T, i
     const int token_tiles = up(T, 64);
     const double load = (double)token_tiles * up(rows_k + rows_v, 64) / n_cus;  // tiles per CU, here and below
     if (load <= 1) return 0.18;
-    if (load > 2) return 1e9;
-    return token_tiles % 8 == 0 && token_tiles <= 32 ? 0.285 : 0.34;
+    if (load > 1.125) return 1e9;
+    return token_tiles % 8 == 0 ? 0.285 : 0.34;
   }
   if (form == AppendForm::kTile256) {
     // One workgroup per CU walks rounds of block ids, 0.55 and up to 0.35 more each, by how full it is.  Token tiles come in
@@ -791,7 +794,7 @@ static double append_tile_cost(AppendForm form, int rows_k, int rows_v, int T, i
   const int rows = form == AppendForm::kTile128 ? 128 : 256;
   const double load = (double)(up(rows_k, rows) + up(rows_v, rows)) * up(T, 128) / n_cus;
   if (form == AppendForm::kTile128) return load <= 1 ? 0.31 : (load <= 2 ? 0.24 + 0.155 * load : (load <= 3.14 ? 0.88 : 0.28 * load));
-  return load <= 1 ? 0.36 + 0.18 * load : (load <= 1.52 ? 0.82 : 0.54 * load);
+  return load <= 1 ? 0.36 + 0.18 * load : (load <= 1.58 ? 0.82 : 0.52 * load);
 }
 
 AppendForm append_form(int D, int rows_k, int rows_v, int T, int n_cus) {
