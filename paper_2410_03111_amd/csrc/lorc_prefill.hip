@@ -106,11 +106,20 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
   if (!values) {
     // Rotations of the four position blocks' first positions (angles reduced in fp64).  A key's rotation is its block's times
     // that of its offset inside the block, from the packed table.  (One fp32 angle per key in the hardware sine and cosine takes
-    // 0.5 to 1 us less per call -- 8B rank 576, six prompts: 102 against 103 -- but rounds a fifth to a third more keys to the
+    // 0.1 to 0.5 us less per call -- 8B rank 576, six prompts: 106.4 against 107.0 -- but rounds a fifth to a third more keys to the
     // wrong fp16 value.)
     float2* cs_base = reinterpret_cast<float2*>(smem + rt_ring_bytes<NC, 3>());
+    const double theta = p.rope_tab[tid % HALF];
+    float2 cl[16];  // offsets of pair pr; NC = 2 has the registers to ask for them ahead of the product
+    auto offsets = [&](int pr) {
+      const int fbase = 32 * ((cb0 + rt_col_block<HD, NC>((w & 1) * NC + (HD == 128 ? pr : 2 * pr))) % (HD / 32));
+#pragma unroll
+      for (int j = 0; j < 16; ++j) cl[j] = p.lane_cs[l32 * HALF + fbase + acc_row(j, hf)];
+    };
+    if constexpr (NC == 2) offsets(0);
+    __builtin_amdgcn_sched_barrier(0);  // (asked for behind the copies, either would wait for them)
     auto setup = [&]() {  // behind the product's first copies
-      if (tid < 4 * HALF) cs_base[tid] = cos_sin_reduced((double)(page0 * kPage + 32 * (tid / HALF)) * p.rope_tab[tid % HALF]);
+      if (tid < 4 * HALF) cs_base[tid] = cos_sin_reduced((double)(page0 * kPage + 32 * (tid / HALF)) * theta);
     };
     tile_product<HD, NC, 3, kPageKeys, false>(acc, smem, dma_rsrc(p.bk, (uint32_t)n * p.r_k * 2u), dma_rsrc(page, page_ok ? (uint32_t)kPage * p.r_k * 2u : 0u),
                                 cb0, ncb, p.r_k >> 4, w, lane, p.r_k >> 5, 0, setup);
@@ -121,9 +130,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
       const int cb = cb0 + rt_col_block<HD, NC>((w & 1) * NC + ca);
       if (cb >= ncb) continue;
       const int g = cb / (HD / 32), fbase = 32 * (cb % (HD / 32));
-      float2 cl[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) cl[j] = p.lane_cs[l32 * HALF + fbase + acc_row(j, hf)];
+      if constexpr (NC != 2) offsets(pr);
 #pragma unroll
       for (int pb = 0; pb < 2; ++pb)
 #pragma unroll
