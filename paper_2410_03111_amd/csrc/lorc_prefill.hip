@@ -45,12 +45,14 @@ __device__ __forceinline__ int prompt_len(const PrefillParams& p, int seq) {
 }
 
 // ------------------------------------------------------------------------------------------------ rebuild
-// One workgroup per (two pages of a sequence, 64 NC columns of K or of V).  Bound by the matrix cores at large sizes
-// (2 (r_k + r_v) n flop per position: 820 TFLOP/s at rank 512, 920 at rank 2048) and by the chip's width at small ones, which is why the columns are dealt to
-// workgroups of their own: before, one workgroup per page walked all columns, and the 8B shape's 45-page batch ran on 45
-// of 256 CUs, a rank-2048 layer copied its latents to LDS once for every eight heads.
-//   8B, rank 512, 4 x 8192 positions: 114 -> 81 us.  8B, rank 576, 2600 positions in 6 prompts: 59 -> 18 us.
-//   13B, rank 2048, 2600 positions in 3 prompts (109 GFLOP): 1277 -> 160 us.
+// One workgroup per (two pages of a sequence, 64 NC columns of K or of V).  At large sizes two workgroups per CU keep the matrix
+// cores busy 42 % (rank 512) to 54 % (rank 2048) of the time at the 1.75 and 1.93 GHz that the power limit leaves (counters;
+// 2 (r_k + r_v) n flop per position: 800 and 1030 TFLOP/s), the rest is prologue, rotation and stores; at small ones the chip's
+// width decides, which is why the columns are dealt to workgroups of their own: before, one workgroup per page walked all
+// columns, and the 8B shape's 53-page batch ran on 53 of 256 CUs, a rank-2048 layer copied its latents to LDS once for every
+// eight heads.
+//   8B, rank 512, 4 x 8192 positions: 114 -> 82 us.  8B, rank 576, 3116 positions in 6 prompts: 59 -> 18 us.
+//   13B, rank 2048, 3378 positions in 3 prompts (142 GFLOP): 1277 -> 137 us.
 // NC = 4 unless its workgroups do not cover the CUs twice; NC = 2 then doubles their number.
 constexpr int kRebuildColGroups = 8;  // column groups whose workgroups run side by side on an XCD
 constexpr int kRebuildFewTiles = 64;
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rebuild_kernel(PrefillParams p
   //  * many position tiles: an XCD takes every eighth tile; on it, the column groups run kRebuildColGroups at a time over
   //    all of its tiles, so that the workgroups in flight share a few factor slices and latent tiles in the XCD's L2;
   //  * fewer than kRebuildFewTiles: an XCD takes every eighth column group and all tiles.  Its share then does not depend
-  //    on which tiles the prompts' lengths leave empty (13B, prompts of 1500, 689 and 1190: 227 -> 160 us).
+  //    on which tiles the prompts' lengths leave empty (13B, prompts of 1500, 688 and 1190: 227 -> 160 us).
   const int ncb = p.h_kv * HD / 32, ncg = (ncb + 2 * NC - 1) / (2 * NC);  // column blocks of 32; groups of K (and of V)
   const int tps2 = (p.tiles_per_seq + 1) >> 1, n_pt = p.b * tps2;
   const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
