@@ -122,6 +122,8 @@ def _stream():
 
 
 def _dev(t, dtype, name):
+    if torch is None:
+        raise ImportError("the device functions need torch")
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype):
         raise TypeError(f"{name}: expected a contiguous CUDA tensor of dtype {dtype}")
     return t

@@ -206,6 +206,15 @@ def test_append_takes_the_kernel_measured_fastest(D, r_k, r_v, T, kernel):
     assert L.append_plan_info(L.layer_desc(D, n // 128, n // 128, 128, r_k, r_v, 1e4), T) == kernel
 
 
+def test_device_functions_without_torch_raise_import_error(monkeypatch):
+    monkeypatch.setattr(L, "torch", None)
+    desc = L.layer_desc(4096, 32, 8, 128, 512, 512, 1e4)
+    with pytest.raises(ImportError):
+        L.append_latent(desc, None, None, None, None, None, None)
+    with pytest.raises(ImportError):
+        L.pack_factors(desc, None, None, None, None)
+
+
 def test_append_plan_info_refuses_what_append_refuses():
     with pytest.raises(L.LorcError):
         L.append_plan_info(L.layer_desc(4096, 32, 8, 96, 512, 512, 1e4), 1)
