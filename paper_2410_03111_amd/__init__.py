@@ -10,12 +10,17 @@ import ctypes
 import os
 from dataclasses import dataclass
 
+class _NoTorch:
+    def __getattr__(self, name):
+        raise ImportError("the device functions need torch")
+
+
 try:
     # torch bundles its own HIP runtime under the same soname as the system's; loading torch before the library makes the
     # library bind to that copy, so that stream handles and device pointers belong to one runtime
     import torch
 except ImportError:  # the host functions need numpy alone
-    torch = None
+    torch = _NoTorch()
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "liblorc.so")
@@ -122,8 +127,6 @@ def _stream():
 
 
 def _dev(t, dtype, name):
-    if torch is None:
-        raise ImportError("the device functions need torch")
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype):
         raise TypeError(f"{name}: expected a contiguous CUDA tensor of dtype {dtype}")
     return t

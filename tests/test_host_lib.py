@@ -207,7 +207,7 @@ def test_append_takes_the_kernel_measured_fastest(D, r_k, r_v, T, kernel):
 
 
 def test_device_functions_without_torch_raise_import_error(monkeypatch):
-    monkeypatch.setattr(L, "torch", None)
+    monkeypatch.setattr(L, "torch", L._NoTorch())
     desc = L.layer_desc(4096, 32, 8, 128, 512, 512, 1e4)
     with pytest.raises(ImportError):
         L.append_latent(desc, None, None, None, None, None, None)
