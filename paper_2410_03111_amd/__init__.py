@@ -10,6 +10,7 @@ import ctypes
 import os
 from dataclasses import dataclass
 
+
 class _NoTorch:
     def __getattr__(self, name):
         raise ImportError("the device functions need torch")
