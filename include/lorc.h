@@ -180,7 +180,9 @@ int lorc_decode_attention(const lorc_layer_desc* desc, const void* q, const int3
  *
  * Decode attention over an uncompressed layer (packed with B_k = B_v = NULL; rank_k = rank_v = n; head_dim 128,
  * h_q <= 64): same arguments, conventions and result as lorc_decode_attention, without the rebuild and without the
- * value up-projection -- the pages hold keys (rotated as they are read) and values. */
+ * value up-projection -- the pages hold keys (rotated as they are read) and values.  A score of -inf (a key beyond
+ * fp16) weighs nothing; a row of nothing else is NaN.  Where h_kv is a multiple of eight the workspace size never
+ * decreases with b or max_ctx: one sized for the largest call serves them all. */
 size_t lorc_decode_plain_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx);
 int lorc_decode_attention_plain(const lorc_layer_desc* desc, const void* q, const int32_t* q_pos,
                                 const int32_t* ctx_len, int32_t b, int32_t max_ctx, const void* packed,
@@ -250,7 +252,8 @@ int lorc_decode_attention_absorbed_timed(const lorc_layer_desc* desc, const void
  *   q           [total_tokens x h_q x d] bf16, sequences packed back to back, un-rotated
  *   cu_seqlens  [b+1] int32 prefix sums of the sequence lengths (token i of sequence s is at position i;
  *               lorc_append_latent must have cached the whole prompt first)
- *   total_tokens, max_seqlen  host copies of cu_seqlens[b] and of the longest sequence
+ *   total_tokens, max_seqlen  host copies of cu_seqlens[b] and of the longest sequence (a longer entry of
+ *               cu_seqlens is clamped to max_seqlen rounded up to pages: the rows beyond are not written)
  *   out         [total_tokens x h_q x d] bf16
  *   workspace   lorc_prefill_workspace_bytes(desc, b, max_seqlen) bytes, 256-byte aligned (rebuilt K/V, fp16)
  * One sequence's rebuilt keys (max_seqlen rounded up to pages x h_kv x d x 2 bytes) must stay below 2 GiB:
