@@ -125,13 +125,15 @@ int decode_params(DecodeParams& p, const lorc_layer_desc* desc, const void* q, c
 int decode_rotary(const lorc_layer_desc* desc, const void* q, const int32_t* q_pos, const int32_t* ctx_len, int32_t b,
                   int32_t max_ctx, const void* packed, const void* cache, const int32_t* block_table, int32_t max_pages,
                   int32_t n_pages, void* out, void* workspace, size_t workspace_bytes, void* stream, void* ev_begin,
-                  void* ev_end, int latent_out, bool plain = false) {
+                  void* ev_end, int latent_out, bool plain = false, bool fit = false) {
   if (int rc = decode_args(desc, q, q_pos, true, ctx_len, b, max_ctx, packed, cache, block_table, max_pages, n_pages, out, workspace))
     return rc;
   if (plain && !plain_shape_ok(*desc)) return LORC_EUNSUPPORTED;
   int n_cus = 0;
   if (int rc = device_ready(&n_cus)) return rc;
-  const DecodePlan plan = plain ? make_wide_plan(*desc, b, max_ctx, n_cus, true) : make_decode_plan(*desc, b, max_ctx, n_cus);
+  const DecodePlan plan = plain ? make_wide_plan(*desc, b, max_ctx, n_cus, true)
+                          : fit ? make_decode_plan_within(*desc, b, max_ctx, n_cus, workspace_bytes)
+                                : make_decode_plan(*desc, b, max_ctx, n_cus);
   DecodeParams p;
   if (int rc = decode_params(p, desc, q, q_pos, true, ctx_len, b, max_ctx, packed, cache, block_table, max_pages, n_pages,
                              out, workspace, workspace_bytes, plan, latent_out))
@@ -207,7 +209,7 @@ const char* lorc_decode_plan_info(const lorc_layer_desc* desc, int32_t b, int32_
   if (plan.total_bytes == 0) return nullptr;
   if (n_splits) *n_splits = plan.n_splits;
   if (tiles_per_split) *tiles_per_split = plan.tiles_per_split;
-  return plan.wide ? "wide_scores_kernel" : (plan.stationary ? "decode_stationary_kernel" : "decode_split_kernel");
+  return plan.wide ? "wide_scores_kernel" : (plan.stationary && desc->rank_k > kStatSmallRank ? "decode_stationary_kernel" : "decode_split_kernel");
 }
 
 size_t lorc_decode_plain_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx) {
@@ -258,9 +260,9 @@ int lorc_decode_attention_static(const lorc_layer_desc* desc, const void* q, con
   if (int rc = device_ready(nullptr)) return rc;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return LORC_EHIP;
-  // a problem whose partials do not fit the array is refused by the workspace check (LORC_EWORKSPACE)
+  // a problem whose partials do not fit the array in any plan is refused by the workspace check (LORC_EWORKSPACE)
   return decode_rotary(desc, q, q_pos, ctx_len, b, max_ctx, packed, cache, block_table, max_pages, n_pages, out,
-                       g_scratch_ptr[dev], kStaticScratchBytes, stream, nullptr, nullptr, 0);
+                       g_scratch_ptr[dev], kStaticScratchBytes, stream, nullptr, nullptr, 0, false, true);
 }
 
 // ---- decode without positional rotation, absorbed query (Section 4.1, Eq. 7)

@@ -1115,8 +1115,8 @@ static void plan_workspace(DecodePlan& pl, const lorc_layer_desc& d, int b) {
   pl.total_bytes = off;
 }
 
-DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
-  if (stationary_shape_ok(d)) return make_stationary_plan(d, b, max_ctx, n_cus);
+// The plan of every shape that the stationary kernel does not take (and of those that it does, had it not been there).
+static DecodePlan make_streaming_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
   const int qb_ = (d.n_q_heads + 31) / 32;
   // More than 32 query heads: the streaming kernel needs two score blocks per wave and spills; scores + values + merge
   // as three launches is 1.1x (rank 256) to 1.6x (rank 1024) faster at 64 heads, b 32, context 8192.
@@ -1144,6 +1144,19 @@ DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_
   plan_splits(pl, b, max_ctx, (n_cus > 0 ? n_cus : 256) * pl.occupancy);
   plan_workspace(pl, d, b);
   return pl;
+}
+
+DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
+  return stationary_shape_ok(d) ? make_stationary_plan(d, b, max_ctx, n_cus) : make_streaming_plan(d, b, max_ctx, n_cus);
+}
+
+DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes) {
+  const DecodePlan pl = make_decode_plan(d, b, max_ctx, n_cus);
+  if (pl.total_bytes <= bytes || !pl.stationary) return pl;
+  const DecodePlan few = make_stationary_plan(d, b, max_ctx, n_cus, true);  // (its splits walk at most 512 pages)
+  if (few.total_bytes <= bytes) return few;
+  const DecodePlan streaming = make_streaming_plan(d, b, max_ctx, n_cus);
+  return streaming.total_bytes != 0 && streaming.total_bytes <= bytes ? streaming : pl;
 }
 
 template <int HD, int NPB, int QB, int NBW, int JR, int OCC>

@@ -72,7 +72,7 @@ constexpr int kStatThreads = 64 * kStatWaves;
 constexpr int kStatMaxHeads = 16;      // query heads per workgroup: 2 KV heads x G <= 8
 constexpr int kStatMaxTiles = 512;     // tiles one workgroup walks at most (page ids of the split live in LDS)
 constexpr int kStatVLoads = 64 / kStatWaves;  // 1 KiB V copies per wave and tile (r_v <= 512)
-constexpr int kStatNks = 32;           // k-steps the K tile is padded to in the one instantiation that is launched (ranks 400 .. 512)
+constexpr int kStatMaxNks = 32;        // k-steps (of 16 latent indices) whose factor operands a wave holds at most
 constexpr int kStatQPitch = 68;        // (x, y) query pairs of 4 bytes per head row in LDS: 64, and 4 that shift the next row's banks
 
 __host__ __device__ inline size_t stat_lds_bytes(int nks_pad, int tiles_per_split) {
@@ -95,7 +95,7 @@ __host__ __device__ inline size_t stat_lds_bytes(int nks_pad, int tiles_per_spli
 // each costs issue time next to the matrix-core stream, and a burst fills the memory pipeline's queue.
 template <int NKS>
 struct CopySched {
-  static constexpr int H = NKS / 2, NG = 4 * H, D = 3, KI = H / kStatWaves, NV = kStatVLoads, MAXI = 4;
+  static constexpr int H = NKS / 2, NG = 4 * H, D = 3, KI = (H + kStatWaves - 1) / kStatWaves, NV = kStatVLoads, MAXI = 4;
   static constexpr int kB0 = NG - D, kB1 = H - D, kB2 = 2 * H - D, kB3 = 3 * H - D, kB4 = 3 * H + H / 2;
   int n[NG];            // copies issued in k-step gi (after the step's barrier, if it has one)
   int kind[NG][MAXI];   // 0 .. 3: chunk of the K tile, 4: V tile
@@ -134,9 +134,9 @@ struct CopySched {
 // factor operands with a zeroed part of the tile.  PPL: positions of a tile that one lane takes through the softmax: a
 // wave for each of up to eight query heads (1), or half a wave for each of up to sixteen (2).
 template <int NKS, int PPL>
-__global__ __launch_bounds__(kStatThreads, 2) void decode_stationary_kernel(DecodeParams p) {
+__device__ __forceinline__ void stationary_split(const DecodeParams& p) {
   constexpr int HD = 128, HALF = 64, T = kStatTile, NW = kStatWaves, NT = kStatThreads;
-  static_assert(NKS % (2 * NW) == 0 && NKS <= 32, "chunks of the K ring");
+  static_assert(NKS % 4 == 0 && NKS <= 32, "chunks of the K ring");
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kStatThreads, 2) void decode_stationary_kernel(Deco
   const uint32_t lane16 = (uint32_t)lane * 16u;
   auto issue_k_copy = [&](const u32x4& kr, int c, int j) {
     const int pb = c >> 1, ks = (c & 1) * H + w + NW * j;
-    const bool real = ks < nks;
+    const bool real = ks < nks && w + NW * j < H;
     dma_1k(kr, real ? kbuf_off + (uint32_t)(pb * NKS + ks) * 1024u : sink_off, lane16, real ? (uint32_t)(pb * nks + ks) * 1024u : 0u);
   };
   // copy j of a V tile: block w + 8 j (1 KiB: 16 positions x 32 latent indices)
@@ -469,11 +469,11 @@ __global__ __launch_bounds__(kStatThreads, 2) void decode_stationary_kernel(Deco
   // results filed.  This tile's first block waits with its scores until the previous tile's P C_v is through (registers; and
   // the softmax of the previous tile has read its scores then).
   constexpr int kRot1 = 2, kSc1 = kRot1 + kRotSteps, kRot0 = 2 * H + 2, kSc0 = kB0 - 2;
-  constexpr int kQuery = kRot1 + kRotSteps + (H > 8 ? 5 : 0);  // this tile's queries: nine stages
+  constexpr int kQuery = kB1 - 2;                          // this tile's queries: nine stages, the fifth and the last file them
   auto sm_at = [](int stage) constexpr { return kB2 + (stage * (H - 1)) / 6; };  // the seven softmax stages, between kB2 and kB3
   constexpr int kPvPrep = kB3, kPvFirst = kB3 + 1, kPvSpan = kB0 - 2 - kPvFirst;  // block I: operands at kPvFirst + I kPvSpan / NB, product two steps later
   static_assert(kSc1 + 4 < kB2 && kRot0 + kRotSteps <= kSc0 && kSc0 + 4 < NG && kSc1 - 2 < kB1, "stream schedule: scores");
-  static_assert(kQuery > kB1 && kQuery + 8 < kB2 && kPvSpan >= NB && NG % (D + 1) == 0 && kIdUse < NG && sm_at(6) < kB3, "stream schedule");
+  static_assert(kQuery + 4 > kB1 && kQuery + 8 < kB2 && kPvSpan >= NB && NG % (D + 1) == 0 && kIdUse < NG && sm_at(6) < kB3, "stream schedule");
 
   f32x16 acc[2];
 #pragma unroll
@@ -710,17 +710,29 @@ __global__ __launch_bounds__(kStatThreads, 2) void decode_stationary_kernel(Deco
   }
 }
 
-// ------------------------------------------------------------------------------------------------ host
-// Shapes the kernel is built for, and (last condition) those where it measures faster than the streaming kernel of
-// lorc_decode.hip: its per-tile cost outside the matrix cores does not shrink with the rank, so below rank 384 the
-// streaming kernel with two workgroups per CU wins (8B shape, batch 32, context 8192: rank 256: 229 against 256 us,
-// rank 384: 313 against 334, rank 512: 355 against 355; 70B shape, batch 64, context 32768: 3.35 against 2.68 ms).
-bool stationary_shape_ok(const lorc_layer_desc& d) {
-  const int G = d.n_q_heads / d.n_kv_heads;
-  return d.head_dim == 128 && d.n_kv_heads % 2 == 0 && G <= 8 && d.rank_k <= 512 && d.rank_v <= 512 && d.rank_k > 384;
+// The two names under which the kernel runs: ranks above 384, and the smaller ranks of what decode_split_kernel serves.
+template <int NKS, int PPL>
+__global__ __launch_bounds__(kStatThreads, 2) void decode_stationary_kernel(DecodeParams p) {
+  stationary_split<NKS, PPL>(p);
+}
+template <int NKS, int PPL>
+__global__ __launch_bounds__(kStatThreads, 2) void decode_split_kernel(DecodeParams p) {
+  stationary_split<NKS, PPL>(p);
 }
 
-DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
+// ------------------------------------------------------------------------------------------------ host
+// Shapes the kernel is built for.  Up to rank 128 the streaming kernel of lorc_decode.hip, which does not pad the rank to 256, is
+// faster on large problems (8B shape, 32 x 8192 positions, us per layer-step, streaming / this: rank 64 160 / 182, 128 173 / 174,
+// 192 201 / 190, 256 243 / 223, 320 273 / 243, 384 294 / 259; one sequence of 700 positions at rank 256 31.3 / 18.6, of 12000 at rank 384 58 / 29) and
+// keeps those of up to 32 query heads; beyond 32 it would need two score blocks, and the other way is three launches (64 heads, 32 x 8192: rank
+// 64 246 / 184, rank 384 405 / 277).
+bool stationary_shape_ok(const lorc_layer_desc& d) {
+  const int G = d.n_q_heads / d.n_kv_heads;
+  return d.head_dim == 128 && d.n_kv_heads % 2 == 0 && G <= 8 && d.rank_k <= 16 * kStatMaxNks && d.rank_v <= 512 &&
+         (d.rank_k > 128 || d.n_q_heads > 32);
+}
+
+DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool fewest_splits) {
   DecodePlan pl{};
   pl.tile = kStatTile;
   pl.occupancy = 1;
@@ -734,7 +746,7 @@ DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, in
   int min_splits = (n_tiles + kStatMaxTiles - 1) / kStatMaxTiles;
   int best = min_splits;
   double best_cost = 0;
-  for (int ns = min_splits; ns <= n_tiles && ns <= 64; ++ns) {
+  for (int ns = min_splits; ns <= n_tiles && ns <= (fewest_splits ? min_splits : 64); ++ns) {
     const int tps = (n_tiles + ns - 1) / ns;
     const int ns_eff = (n_tiles + tps - 1) / tps;
     const long rounds = (wgs_per_split * ns_eff + cus - 1) / cus;
@@ -755,19 +767,37 @@ DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, in
   return pl;
 }
 
+namespace {
+using StatKernel = void (*)(DecodeParams);
+// k-steps the rank is padded to: 16 to 32 in steps of 4 (64 latent indices)
+int stat_nks(int r_k) { return r_k <= 256 ? 16 : (r_k + 63) / 64 * 4; }
+template <int PPL>
+StatKernel stat_kernel(int nks_pad) {
+  switch (nks_pad) {
+    case 16: return decode_split_kernel<16, PPL>;
+    case 20: return decode_split_kernel<20, PPL>;
+    case 24: return decode_split_kernel<24, PPL>;
+    case 28: return decode_stationary_kernel<28, PPL>;
+    default: return decode_stationary_kernel<32, PPL>;
+  }
+}
+}  // namespace
+
 int set_kernel_attributes_decode_stationary() {
-  for (const void* f : {reinterpret_cast<const void*>(decode_stationary_kernel<kStatNks, 1>),
-                        reinterpret_cast<const void*>(decode_stationary_kernel<kStatNks, 2>)})
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return LORC_EHIP;
+  for (int nks_pad = 16; nks_pad <= kStatMaxNks; nks_pad += 4)
+    for (StatKernel k : {stat_kernel<1>(nks_pad), stat_kernel<2>(nks_pad)})
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+        return LORC_EHIP;
   return LORC_OK;
 }
 
 int launch_decode_stationary_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s) {
-  const size_t lds = stat_lds_bytes(kStatNks, plan.tiles_per_split);
-  if (lds > 160 * 1024 || plan.tiles_per_split > kStatMaxTiles || 2 * p.G > kStatMaxHeads || p.r_k > 16 * kStatNks) return LORC_EUNSUPPORTED;
+  const int nks_pad = stat_nks(p.r_k);
+  const size_t lds = stat_lds_bytes(nks_pad, plan.tiles_per_split);
+  if (lds > 160 * 1024 || plan.tiles_per_split > kStatMaxTiles || 2 * p.G > kStatMaxHeads || p.r_k > 16 * kStatMaxNks) return LORC_EUNSUPPORTED;
   const int units = p.b * p.n_splits, nq = p.h_kv / 2;
   const dim3 grid(((units + 7) / 8) * 8 * nq), block(kStatThreads);
-  return launch_kernel(2 * p.G <= 8 ? decode_stationary_kernel<kStatNks, 1> : decode_stationary_kernel<kStatNks, 2>, grid, block, lds, s, p);
+  return launch_kernel(2 * p.G <= 8 ? stat_kernel<1>(nks_pad) : stat_kernel<2>(nks_pad), grid, block, lds, s, p);
 }
 
 }  // namespace lorc

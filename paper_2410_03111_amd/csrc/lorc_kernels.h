@@ -107,6 +107,8 @@ PrefillPlan make_prefill_plan(const lorc_layer_desc& d, int b, int max_seqlen);
 int launch_prefill(const PrefillParams& p, int n_cus, hipStream_t s, bool plain = false);
 
 DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus);
+// The same for a workspace of a given size: where the plan above does not fit, the one that needs least (which may not fit either).
+DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes);
 
 int launch_pack(const lorc_layer_desc& d, const void* A_k, const void* A_v, const void* B_k, const void* B_v,
                 void* packed, hipStream_t s);
@@ -130,9 +132,10 @@ int set_kernel_attributes_prefill();
 int set_kernel_attributes_decode_stationary();
 
 // Split kernel that keeps the key factor in registers (head_dim 128, an even number of KV heads, G <= 8, ranks
-// <= 512); its plan and launch.  The merge launch that follows is the common one.
+// 160 to 512); its plan and launch.  The merge launch that follows is the common one.
+constexpr int kStatSmallRank = 384;  // up to here it runs as decode_split_kernel, above as decode_stationary_kernel
 bool stationary_shape_ok(const lorc_layer_desc& d);
-DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus);
+DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool fewest_splits = false);
 int launch_decode_stationary_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
 
 // Three-launch decode (scores, values in column chunks, merge) for ranks above 1024 and for uncompressed layers.

@@ -1,0 +1,64 @@
+"""The split kernel with the key factor in registers at the ranks its k-step paddings serve (16, 20, 24, 28 steps of 16), both
+head counts per workgroup (up to eight: one position per lane in the softmax, up to sixteen: two), value ranks that leave
+latent blocks empty, contexts around tile edges; and the fixed-array entry point where only a plan of fewer splits fits."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from lorc_testlib import GpuLayer, Problem, TOL, oracle_decode, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("r_k,r_v,h_q,h_kv,ctx", [
+    (160, 160, 8, 2, [1, 63, 64, 65, 200]),      # rank below the smallest padding
+    (256, 32, 16, 2, [700, 129]),                # rank equal to it; sixteen heads per workgroup, one block of values
+    (288, 512, 16, 4, [31, 32, 33, 640]),        # 20 k-steps, two of them empty
+    (320, 96, 4, 4, [2000, 0]),                  # groups of one head, an empty context
+    (352, 352, 12, 4, [333, 1]),                 # 24 k-steps, three heads per group, odd number of value blocks per wave
+    (384, 384, 32, 4, [127, 128, 1000]),
+    (448, 480, 20, 4, [65, 500]),                # 28 k-steps, ten heads per workgroup
+    (64, 64, 64, 8, [300, 70]),                  # small rank, more than 32 query heads
+])
+def test_ranks_match_oracle(r_k, r_v, h_q, h_kv, ctx):
+    pb = Problem(d_model=max(512, h_kv * 128), n_q_heads=h_q, n_kv_heads=h_kv, head_dim=128, rank_k=r_k, rank_v=r_v,
+                 rope_base=10000.0, ctx=ctx, seed=r_k + h_q).build()
+    layer = GpuLayer(pb)
+    name = layer.L.decode_plan_info(layer.desc, len(ctx), max(ctx))[0]
+    assert name == ("decode_stationary_kernel" if r_k > 384 else "decode_split_kernel")
+    layer.append_all()
+    got, ref = layer.decode(), oracle_decode(pb)
+    assert np.all(np.isfinite(got))
+    for s, n in enumerate(ctx):
+        if n == 0:
+            assert np.all(got[s] == 0.0)
+    live = [s for s, n in enumerate(ctx) if n > 0]
+    assert rel_err(got[live], ref[live]) <= TOL
+
+
+def test_fixed_array_takes_a_plan_of_fewer_splits_where_the_best_one_does_not_fit():
+    """484 sequences in a launch sized for 25911 positions: the partials of the best plan exceed the array, those of a plan
+    of fewer splits fit.  Same cached latents, so the two differ by the rounding of the partials (fp16) and of the outputs (bf16)."""
+    import torch
+    b, max_ctx = 484, 25911
+    pb = Problem(d_model=1024, n_q_heads=32, n_kv_heads=8, head_dim=128, rank_k=384, rank_v=384, rope_base=10000.0, ctx=[150], seed=5).build()
+    layer = GpuLayer(pb)
+    layer.append_all()
+    L, dev = layer.L, layer.dev
+    assert L.decode_workspace_bytes(layer.desc, b, max_ctx) > L.STATIC_WORKSPACE_BYTES
+    table = torch.full((b, (max_ctx + 63) // 64), -1, dtype=torch.int32, device=dev)
+    table[:, :layer.block_table.shape[1]] = layer.block_table
+    q = torch.from_numpy(pb.q).to(dev).to(torch.bfloat16).expand(b, -1, -1).contiguous()
+    ctx = torch.randint(1, 151, (b,), generator=torch.Generator().manual_seed(3)).to(torch.int32).to(dev)
+    ref = L.decode_attention(layer.desc, q, ctx - 1, ctx, max_ctx, layer.packed, layer.cache, table)
+    out = torch.full_like(q, float("nan"))
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    q_pos = ctx - 1
+    rc = L._lib.lorc_decode_attention_static(ctypes.byref(layer.desc), ptr(q), ptr(q_pos), ptr(ctx), b, max_ctx, ptr(layer.packed),
+                                             ptr(layer.cache), ptr(table), table.shape[1], layer.n_pages, ptr(out), None)
+    assert rc == L.OK, L.strerror(rc)
+    torch.cuda.synchronize()
+    got, ref = out.float(), ref.float()
+    assert bool(torch.isfinite(got).all())
+    assert float((got - ref).norm() / ref.norm()) <= 2 ** -8   # bf16 outputs (2^-9 each) and fp16 partials (2^-11)
