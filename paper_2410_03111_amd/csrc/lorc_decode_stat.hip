@@ -40,7 +40,7 @@ namespace lorc {
 
 namespace {
 constexpr float kNegInfS = -__builtin_huge_valf();
-constexpr float kLazy = 8.0f;  // log2 of the largest exponential a tile may produce before the reference maximum moves
+constexpr float kBelow = 24.0f;  // log2 of the largest weight that an earlier tile may have next to a later one's 1
 
 typedef __attribute__((ext_vector_type(4))) float f32x4s;
 
@@ -333,16 +333,16 @@ __device__ __forceinline__ void stationary_split(const DecodeParams& p) {
 
   // ---- softmax of one tile over the workgroup's heads, in stages that the rebuild stream spreads over consecutive
   // k-steps (each stage only consumes what the one before requested): 64 / PPL lanes per head, PPL positions per lane; waves
-  // past the workgroup's last head repeat it (same values to the same words).  The reference maximum of a head only moves
-  // when a tile's maximum exceeds it by more than kLazy (exponentials then stay below 2^kLazy): most tiles leave o_lat
-  // unscaled, alpha = 1.  The running sum stays per lane until the end.
+  // past the workgroup's last head repeat it (same values to the same words).  The reference is the tile's own maximum (its
+  // largest weight is then 1, which bf16 holds exactly), but at most 2^kBelow below the largest so far.  A reference that only moves
+  // up by large steps leaves the largest weights rounded and costs the outputs 10 to 15 % of error against fp64.  The running sum stays per lane until the end.
   const int sm_h_raw = PPL == 1 ? w : 2 * w + hf;
   const int sm_h = sm_h_raw < n_heads ? sm_h_raw : n_heads - 1;
   const int sm_pos = PPL == 1 ? lane : 2 * l32;
   const float* s_src = sbuf + (size_t)(sm_h < G ? sm_h : 8 + sm_h - G) * T + sm_pos;
   // P operand of the 16x16x32 product: position 32 ph + 8 kg + e of head h sits in lane h + 16 kg, element e
   uint16_t* p_dst = pbuf + ((size_t)((sm_pos >> 5) * 64 + sm_h + 16 * ((sm_pos & 31) >> 3)) * 8 + (sm_pos & 7));
-  float m_run = kNegInfS, l_run = 0.f;  // of head sm_h: reference maximum, and this lane's share of the sum
+  float m_run = kNegInfS, m_high = kNegInfS, l_run = 0.f;  // of head sm_h: reference, largest score, and this lane's share of the sum
   struct Softmax {
     float a[4][PPL], s[PPL], mx, pv[PPL], al;
   };
@@ -379,25 +379,28 @@ __device__ __forceinline__ void stationary_split(const DecodeParams& p) {
     }
   };
   auto softmax_c = [&](Softmax& sm) {
-    const float m_new = sm.mx > m_run + kLazy ? sm.mx : m_run;  // (from -inf: any finite maximum)
+    m_high = fmaxf(m_high, sm.mx);
+    const float m_new = fmaxf(sm.mx, m_high - kBelow);
     const float m_ref = fmaxf(m_new, -1e30f);
 #pragma unroll
     for (int i = 0; i < PPL; ++i) sm.pv[i] = __builtin_amdgcn_exp2f(sm.s[i] - m_ref);
-    sm.al = __builtin_amdgcn_exp2f(m_run - m_ref);  // 1 unless the reference moved (0 while there is none: nothing to scale)
+    sm.al = __builtin_amdgcn_exp2f(m_run - m_ref);  // (0 while there is no reference: nothing to scale)
     m_run = m_new;
   };
   auto softmax_d = [&](const Softmax& sm, bool page_ok_) {
+    alpha[sm_h] = sm.al;  // all lanes of a head hold the same value and store it to the same word (no branch in the stream)
+    // The sum takes the weights as they are multiplied (bf16), so that the rounding of a dominant one cancels.  A page that is
+    // not cached counts in the sums (zero keys) but adds nothing to o_lat (zero values): its P is filed as zero, and whatever
+    // finite data the V tile holds is multiplied by it.
+    uint32_t bits[PPL];
     l_run *= sm.al;
 #pragma unroll
-    for (int i = 0; i < PPL; ++i) l_run += sm.pv[i];
-    alpha[sm_h] = sm.al;  // all lanes of a head hold the same value and store it to the same word (no branch in the stream)
-    // A page that is not cached counts in the sums (zero keys) but adds nothing to o_lat (zero values): its P is
-    // filed as zero, and whatever finite data the V tile holds is multiplied by it.
-    if constexpr (PPL == 1) {
-      *p_dst = page_ok_ ? bf16_bits(sm.pv[0]) : (uint16_t)0;
-    } else {
-      *reinterpret_cast<uint32_t*>(p_dst) = page_ok_ ? (uint32_t)bf16_bits(sm.pv[0]) | ((uint32_t)bf16_bits(sm.pv[PPL - 1]) << 16) : 0u;
+    for (int i = 0; i < PPL; ++i) {
+      bits[i] = bf16_bits(sm.pv[i]);
+      l_run += __uint_as_float(bits[i] << 16);
     }
+    if constexpr (PPL == 1) *p_dst = page_ok_ ? (uint16_t)bits[0] : (uint16_t)0;
+    else *reinterpret_cast<uint32_t*>(p_dst) = page_ok_ ? bits[0] | (bits[PPL - 1] << 16) : 0u;
   };
 
   // ---- o_lat = alpha o_lat + P C_v of one tile: wave w owns the 16-wide latent blocks w, w + 8, ...
