@@ -209,7 +209,7 @@ const char* lorc_decode_plan_info(const lorc_layer_desc* desc, int32_t b, int32_
   if (plan.total_bytes == 0) return nullptr;
   if (n_splits) *n_splits = plan.n_splits;
   if (tiles_per_split) *tiles_per_split = plan.tiles_per_split;
-  return plan.wide ? "wide_scores_kernel" : (plan.stationary && desc->rank_k > kStatSmallRank ? "decode_stationary_kernel" : "decode_split_kernel");
+  return plan.wide ? "wide_scores_kernel" : (plan.stationary == 1 && desc->rank_k > kStatSmallRank ? "decode_stationary_kernel" : "decode_split_kernel");
 }
 
 size_t lorc_decode_plain_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx) {

@@ -1147,13 +1147,20 @@ static DecodePlan make_streaming_plan(const lorc_layer_desc& d, int b, int max_c
 }
 
 DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
-  return stationary_shape_ok(d) ? make_stationary_plan(d, b, max_ctx, n_cus) : make_streaming_plan(d, b, max_ctx, n_cus);
+  if (stationary_shape_ok(d)) return make_stationary_plan(d, b, max_ctx, n_cus);
+  if (stationary768_shape_ok(d)) {
+    DecodePlan pl = make_stationary_plan(d, b, max_ctx, n_cus);
+    pl.stationary = 2;
+    return pl;
+  }
+  return make_streaming_plan(d, b, max_ctx, n_cus);
 }
 
 DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes) {
   const DecodePlan pl = make_decode_plan(d, b, max_ctx, n_cus);
   if (pl.total_bytes <= bytes || !pl.stationary) return pl;
-  const DecodePlan few = make_stationary_plan(d, b, max_ctx, n_cus, true);  // (its splits walk at most 512 pages)
+  DecodePlan few = make_stationary_plan(d, b, max_ctx, n_cus, true);  // (its splits walk at most 512 pages)
+  few.stationary = pl.stationary;
   if (few.total_bytes <= bytes) return few;
   const DecodePlan streaming = make_streaming_plan(d, b, max_ctx, n_cus);
   return streaming.total_bytes != 0 && streaming.total_bytes <= bytes ? streaming : pl;
@@ -1237,6 +1244,7 @@ int set_kernel_attributes_decode() {
   if (int rc = dispatch_split<64, 4>(none, plan, nullptr, true)) return rc;
   if (int rc = dispatch_split<64, 2>(none, plan, nullptr, true)) return rc;
   if (int rc = set_kernel_attributes_decode_stationary()) return rc;
+  if (int rc = set_kernel_attributes_decode_stationary768()) return rc;
   if (int rc = set_kernel_attributes_decode_wide()) return rc;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(decode_absorbed_kernel<4>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              160 * 1024) == hipSuccess ? LORC_OK : LORC_EHIP;
@@ -1286,7 +1294,8 @@ int launch_decode(const DecodeParams& p, const DecodePlan& plan, hipStream_t s, 
     }
     return launch_merge(p, s);  // the group merge where its limits hold, the generic one otherwise
   }
-  if (plan.stationary) rc = launch_decode_stationary_split(p, plan, s);
+  if (plan.stationary == 2) rc = launch_decode_stationary768_split(p, plan, s);
+  else if (plan.stationary) rc = launch_decode_stationary_split(p, plan, s);
   else if (p.head_dim == 128) rc = plan.tile == 128 ? dispatch_split<128, 4>(p, plan, s) : dispatch_split<128, 2>(p, plan, s);
   else rc = plan.tile == 128 ? dispatch_split<64, 4>(p, plan, s) : dispatch_split<64, 2>(p, plan, s);
   if (rc != LORC_OK) return rc;

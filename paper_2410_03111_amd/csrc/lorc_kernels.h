@@ -46,7 +46,7 @@ struct AppendParams {
 struct DecodePlan {
   int tile;             // positions per tile (64 or 128)
   int occupancy;        // workgroups meant to share a CU (1 or 2)
-  int stationary;       // 1: the split kernel with the key factor held in registers (lorc_decode_stat.hip)
+  int stationary;       // the split kernels with the key factor held in registers: 1 lorc_decode_stat.hip, 2 lorc_decode_stat768.hip
   int wide;             // lorc_decode_wide.hip: 1 ranks above 1024, 2 uncompressed layer, 3 absorbed query (scores, values, merge;
                         // uncompressed layers of eight KV heads or a multiple: one pass, merge)
   int score_stride;     // wide: positions per score row (max_ctx rounded up to whole tiles)
@@ -137,6 +137,10 @@ constexpr int kStatSmallRank = 384;  // up to here it runs as decode_split_kerne
 bool stationary_shape_ok(const lorc_layer_desc& d);
 DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool fewest_splits = false);
 int launch_decode_stationary_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
+// The same for ranks 544 to 768 (G <= 4, up to 32 query heads); it takes the plan of the other.
+bool stationary768_shape_ok(const lorc_layer_desc& d);
+int set_kernel_attributes_decode_stationary768();
+int launch_decode_stationary768_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
 
 // Three-launch decode (scores, values in column chunks, merge) for ranks above 1024 and for uncompressed layers.
 bool wide_shape_ok(const lorc_layer_desc& d);

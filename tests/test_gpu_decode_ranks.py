@@ -1,6 +1,7 @@
-"""The split kernel with the key factor in registers at the ranks its k-step paddings serve (16, 20, 24, 28 steps of 16), both
-head counts per workgroup (up to eight: one position per lane in the softmax, up to sixteen: two), value ranks that leave
-latent blocks empty, contexts around tile edges; and the fixed-array entry point where only a plan of fewer splits fits."""
+"""The split kernels with the key factor in registers at the ranks their k-step paddings serve (up to 512: 16, 20, 24, 28, 32 steps of 16
+and 64-position tiles; above: 18, 21, 24 steps of 32 and 32-position tiles), head counts per workgroup on both sides of eight, value
+ranks that leave latent blocks empty, contexts around tile edges; and the fixed-array entry point where only a plan of fewer splits
+fits."""
 import ctypes
 
 import numpy as np
@@ -20,13 +21,21 @@ pytestmark = pytest.mark.gpu
     (384, 384, 32, 4, [127, 128, 1000]),
     (448, 480, 20, 4, [65, 500]),                # 28 k-steps, ten heads per workgroup
     (64, 64, 64, 8, [300, 70]),                  # small rank, more than 32 query heads
+    # ranks above 512, 32-position tiles: 18, 21 and 24 k-steps of 32, some of them empty
+    (544, 544, 24, 6, [1, 31, 32, 33, 63, 64, 65, 200]),
+    (576, 576, 32, 8, [700, 129]),
+    (608, 32, 6, 6, [333, 0]),
+    (672, 640, 12, 6, [31, 96, 640]),
+    (704, 768, 18, 6, [97, 1]),
+    (768, 768, 32, 8, [127, 128, 1000]),
+    (160, 576, 24, 6, [75, 300]),                 # value rank above 512 alone
 ])
 def test_ranks_match_oracle(r_k, r_v, h_q, h_kv, ctx):
     pb = Problem(d_model=max(512, h_kv * 128), n_q_heads=h_q, n_kv_heads=h_kv, head_dim=128, rank_k=r_k, rank_v=r_v,
                  rope_base=10000.0, ctx=ctx, seed=r_k + h_q).build()
     layer = GpuLayer(pb)
     name = layer.L.decode_plan_info(layer.desc, len(ctx), max(ctx))[0]
-    assert name == ("decode_stationary_kernel" if r_k > 384 else "decode_split_kernel")
+    assert name == ("decode_stationary_kernel" if 384 < r_k <= 512 else "decode_split_kernel")
     layer.append_all()
     got, ref = layer.decode(), oracle_decode(pb)
     assert np.all(np.isfinite(got))
