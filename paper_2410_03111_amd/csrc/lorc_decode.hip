@@ -680,58 +680,65 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
 
 // ------------------------------------------------------------------------------------------------ merge, common shapes
 // One workgroup of sixteen waves per (sequence, KV head): the G query heads of the group share the factor block
-// B_v^g, which is read once, as matrix-core operands, and requested before anything else; the split partials are
-// requested next (four fp16 columns per thread, 32 splits in flight), the split weights are worked out
-// while they travel.  The up-projection runs on the matrix cores with o_lat split into a bf16 head and a bf16
-// remainder (two products), so that it keeps the accuracy of an fp32 o_lat.  Shapes: G <= 8, at most 64 splits,
-// r_v <= 512.
-// HS = 2: the group's heads are dealt to two workgroups of eight waves (small batches: twice as many workgroups,
-// each with half the partials to fetch; the factor block is then read by both).
-constexpr int kMgMaxG = 8, kMgMaxSplits = 64, kMgMaxRank = 512, kMgBatch = 32;
-
-template <int HD, int HS>
+// B_v^g, which is read once, as matrix-core operands.  The split partials are requested first (eight fp16 columns per thread; up
+// to eight sets of threads share the splits), then the factor operands; the split weights are worked out while both travel.
+// The up-projection runs on the matrix cores with o_lat split into a bf16 head and a bf16 remainder (two products), so that it
+// keeps the accuracy of an fp32 o_lat.  Shapes: G <= 8, at most 64 splits, r_v <= 1024.  Bound by latency: launch, one round trip
+// for both operands, the product's chain.  Value ranks above 512 before, a workgroup per query head and scalar products: 14.5 us
+// for one sequence at rank 768, whole call 36.5 -> 25.2; 1 x 1337 at rank 512 (four columns per thread, all splits in one): 23.0 -> 22.1.
+constexpr int kMgMaxG = 8, kMgMaxSplits = 64, kMgMaxRank = 1024;
+// HS: workgroups that share a group's heads;  CS: workgroups that share the head's columns (each works out the weighted sums of its
+// heads for itself);  MAXR: largest value rank.
+template <int HD, int HS, int CS, int MAXR>
 __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodeParams p) {
-  constexpr int NCB = HD / 32, NKQ = (16 / HS) / NCB, MAXKS = (kMgMaxRank / 16 + NKQ - 1) / NKQ;
-  constexpr int MAXG = kMgMaxG / HS;
+  constexpr int NCB = HD / 32 / CS, NKQ = (16 / HS) / NCB, MAXKS = (MAXR / 16 + NKQ - 1) / NKQ;
+  constexpr int MAXG = kMgMaxG / HS, PITCH = MAXR + 8, COLS = 32 * NCB;
+  constexpr int BATCH = HS == 1 ? 8 : 16;  // partials a thread has in flight (16 bytes each)
   __shared__ float wgt[MAXG][kMgMaxSplits];
-  __shared__ __align__(16) uint16_t o_hi[MAXG][kMgMaxRank];
-  __shared__ __align__(16) uint16_t o_lo[MAXG][kMgMaxRank];
-  __shared__ float red[NKQ][HD][MAXG];
+  __shared__ __align__(16) uint16_t o_hi[MAXG][PITCH];
+  __shared__ __align__(16) uint16_t o_lo[MAXG][PITCH];
+  constexpr int SHARE = 512;               // threads that share the splits at most
+  constexpr int SCRATCH = SHARE * 8 > NKQ * COLS * MAXG ? SHARE * 8 : NKQ * COLS * MAXG;
+  __shared__ __align__(16) float scratch[SCRATCH];         // weighted sums of a thread's splits; later the parts of the product
+  float (*const part)[8] = reinterpret_cast<float (*)[8]>(scratch);
+  float (*const red)[COLS][MAXG] = reinterpret_cast<float (*)[COLS][MAXG]>(scratch);
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int sg = blockIdx.x / HS, seq = sg / p.h_kv, g = sg % p.h_kv;
+  const int cs = blockIdx.x % CS, sg = blockIdx.x / (CS * HS), seq = sg / p.h_kv, g = sg % p.h_kv;
   const int G = p.G / HS, r_v = p.r_v, ns = p.n_splits, nks = r_v >> 4;  // G: heads of this workgroup
-  const int h0 = g * p.G + (blockIdx.x % HS) * G;                        // its first query head
+  const int h0 = g * p.G + (blockIdx.x / CS % HS) * G;                   // its first query head
+
+  // ---- partials: 8 columns of a head per thread; as many sets of threads as there are share the splits
+  const int per_set = G * (r_v >> 3), most = ns < 8 ? ns : 8;
+  const int sets = per_set * most <= SHARE ? most : (2 * per_set <= SHARE ? SHARE / per_set : 1);
+  const int set = tid / per_set, in_set = tid - set * per_set;
+  const bool owner = set < sets;
+  const int oh = owner ? in_set / (r_v >> 3) : 0, oj = owner ? (in_set % (r_v >> 3)) * 8 : 0;
+  const uint16_t* po = p.part_o + (((size_t)seq * ns) * p.h_q + (size_t)h0 + oh) * r_v + oj;
+  const size_t pst = (size_t)p.h_q * r_v;
+  u32x4 pre[BATCH];
+  auto load_batch = [&](int u0) {
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const int s_ = set + (u0 + u) * sets;  // clamped: the tail is loaded again and weighted zero
+      pre[u] = *reinterpret_cast<const u32x4*>(po + (size_t)(s_ < ns ? s_ : ns - 1) * pst);
+    }
+  };
+  if (owner) load_batch(0);
 
   // ---- factor operands of this wave: column block cb of the head, k-steps [ks0, ks1)
-  const int cb = w % NCB, kq = w / NCB;
+  const int cb = cs * NCB + w % NCB, kq = w / NCB;
   const int ks_per = (nks + NKQ - 1) / NKQ;
   const int ks0 = kq * ks_per, ks1 = ks0 + ks_per < nks ? ks0 + ks_per : nks;
   bf16x8 bvf[MAXKS];
   if (!p.latent_out) {
-    const uint16_t* bp = p.bv + ((size_t)(g * NCB + cb) * nks * 64 + lane) * 8;
+    const uint16_t* bp = p.bv + ((size_t)(g * (HD / 32) + cb) * nks * 64 + lane) * 8;
 #pragma unroll
     for (int u = 0; u < MAXKS; ++u) {
       const int ks = ks0 + u < nks ? ks0 + u : nks - 1;
       bvf[u] = load_frag(bp + (size_t)ks * 512);
     }
   }
-
-  // ---- first batch of partials: thread t owns o_lat[head t / (r_v/4)][4 * (t % (r_v/4)) .. +3]
-  const int qpr = r_v >> 2;  // column groups per head
-  const bool owner = tid < G * qpr;
-  const int oh = owner ? tid / qpr : 0, oj = owner ? (tid % qpr) * 4 : 0;
-  const uint16_t* po = p.part_o + (((size_t)seq * ns) * p.h_q + (size_t)h0 + oh) * r_v + oj;
-  const size_t pst = (size_t)p.h_q * r_v;
-  u32x2 pre[kMgBatch];
-  auto load_batch = [&](int s0) {
-#pragma unroll
-    for (int u = 0; u < kMgBatch; ++u) {
-      const int sidx = s0 + u < ns ? s0 + u : ns - 1;  // clamped: the tail is loaded again and weighted zero
-      pre[u] = *reinterpret_cast<const u32x2*>(po + (size_t)sidx * pst);
-    }
-  };
-  if (owner) load_batch(0);
 
   // ---- split weights: wave h < G handles head h, one split per lane
   if (w < G) {
@@ -741,51 +748,83 @@ __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodePar
     const float ms = lane < ns ? ml[lane * st] : kNegInf;
     const float ls = lane < ns ? ml[lane * st + 1] : 0.f;
     float M = ms;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
+    M = fmaxf(M, half_wave_peer<0>(M));
+    M = fmaxf(M, half_wave_peer<1>(M));
+    M = fmaxf(M, half_wave_peer<2>(M));
+    M = fmaxf(M, half_wave_peer<3>(M));
+    const float2 mr = row_pair(M);
+    M = fmaxf(mr.x, mr.y);
+    const float2 mh = half_pair(M);
+    M = fmaxf(mh.x, mh.y);
     const float e = (ms == kNegInf ? 0.f : exp2f(ms - M)) * ls;  // partials are stored normalised
     float L = e;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) L += __shfl_xor(L, off);
+    L += half_wave_peer<0>(L);
+    L += half_wave_peer<1>(L);
+    L += half_wave_peer<2>(L);
+    L += half_wave_peer<3>(L);
+    const float2 lr = row_pair(L);
+    L = lr.x + lr.y;
+    const float2 lh = half_pair(L);
+    L = lh.x + lh.y;
     if (lane < ns) wgt[w][lane] = L > 0.f ? e / L : 0.f;
   }
   __syncthreads();
 
   // ---- o_lat = sum over splits of weight * partial
+  float a[8];
   if (owner) {
-    f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < ns; s0 += kMgBatch) {
-      if (s0 != 0) load_batch(s0);
 #pragma unroll
-      for (int u = 0; u < kMgBatch; ++u) {
-        const float wv = s0 + u < ns ? wgt[oh][s0 + u] : 0.f;
-        typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
-        const f16x4 hv = __builtin_bit_cast(f16x4, pre[u]);
-        const f32x4 fv = {(float)hv[0], (float)hv[1], (float)hv[2], (float)hv[3]};
-        a += wv * fv;
+    for (int i = 0; i < 8; ++i) a[i] = 0.f;
+    const int count = (ns - set + sets - 1) / sets;  // splits of this set
+    for (int u0 = 0; u0 < count; u0 += BATCH) {
+      if (u0 != 0) load_batch(u0);
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const int s_ = set + (u0 + u) * sets;
+        const float wv = s_ < ns ? wgt[oh][s_] : 0.f;
+        typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_;
+        const f16x8_ hv = __builtin_bit_cast(f16x8_, pre[u]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] += wv * (float)hv[i];
       }
     }
-    if (p.latent_out) {
-      uint16_t* dst = p.out + ((size_t)seq * p.h_q + (size_t)h0 + oh) * r_v + oj;
-      u32x2 pk = {(uint32_t)bf16_bits(a[0]) | ((uint32_t)bf16_bits(a[1]) << 16),
-                  (uint32_t)bf16_bits(a[2]) | ((uint32_t)bf16_bits(a[3]) << 16)};
-      *reinterpret_cast<u32x2*>(dst) = pk;
-    } else {
+    if (sets > 1) {
+      *reinterpret_cast<f32x4*>(&part[tid][0]) = f32x4{a[0], a[1], a[2], a[3]};
+      *reinterpret_cast<f32x4*>(&part[tid][4]) = f32x4{a[4], a[5], a[6], a[7]};
+    }
+  }
+  if (sets > 1) __syncthreads();
+  if (set == 0) {
+    for (int o_ = 1; o_ < sets; ++o_) {
+      const f32x4 b0 = *reinterpret_cast<const f32x4*>(&part[tid + o_ * per_set][0]), b1 = *reinterpret_cast<const f32x4*>(&part[tid + o_ * per_set][4]);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const uint16_t hi = bf16_bits(a[i]);
-        o_hi[oh][oj + i] = hi;
-        o_lo[oh][oj + i] = bf16_bits(a[i] - bf16_to_float(hi));
+        a[i] += b0[i];
+        a[4 + i] += b1[i];
       }
+    }
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint16_t h0_ = bf16_bits(a[2 * i]), h1_ = bf16_bits(a[2 * i + 1]);
+      hi[i] = (uint32_t)h0_ | ((uint32_t)h1_ << 16);
+      lo[i] = (uint32_t)bf16_bits(a[2 * i] - bf16_to_float(h0_)) | ((uint32_t)bf16_bits(a[2 * i + 1] - bf16_to_float(h1_)) << 16);
+    }
+    if (p.latent_out) {
+      *reinterpret_cast<u32x4*>(p.out + ((size_t)seq * p.h_q + (size_t)h0 + oh) * r_v + oj) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+    } else {
+      *reinterpret_cast<u32x4*>(&o_hi[oh][oj]) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+      *reinterpret_cast<u32x4*>(&o_lo[oh][oj]) = u32x4{lo[0], lo[1], lo[2], lo[3]};
     }
   }
   if (p.latent_out) return;
   __syncthreads();
 
-  // ---- out^T[c][h] = sum_j B_v[j][c] o_lat[h][j]: A operand = factor tile (m = column), B operand = o_lat^T
-  f32x16 acc;
+  // ---- out^T[c][h] = sum_j B_v[j][c] o_lat[h][j]: A operand = factor tile (m = column), B operand = o_lat^T; head and remainder
+  // of o_lat in accumulators of their own (chains half as long)
+  f32x16 acc, acc_lo;
 #pragma unroll
-  for (int j = 0; j < 16; ++j) acc[j] = 0.f;
+  for (int j = 0; j < 16; ++j) acc[j] = acc_lo[j] = 0.f;
 #pragma unroll
   for (int u = 0; u < MAXKS; ++u) {
     if (ks0 + u < ks1) {
@@ -796,20 +835,20 @@ __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodePar
         fl = load_frag(&o_lo[l32][j0]);
       }
       acc = mfma32(bvf[u], fh, acc);
-      acc = mfma32(bvf[u], fl, acc);
+      acc_lo = mfma32(bvf[u], fl, acc_lo);
     }
   }
   if (l32 < G) {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) red[kq][cb * 32 + acc_row(j, hf)][l32] = acc[j];
+    for (int j = 0; j < 16; ++j) red[kq][(w % NCB) * 32 + acc_row(j, hf)][l32] = acc[j] + acc_lo[j];
   }
   __syncthreads();
-  if (tid < HD * G) {
-    const int c = tid % HD, h = tid / HD;
+  if (tid < COLS * G) {
+    const int c = tid % COLS, h = tid / COLS;
     float v = 0.f;
 #pragma unroll
     for (int i = 0; i < NKQ; ++i) v += red[i][c][h];
-    p.out[((size_t)seq * p.h_q + (size_t)h0 + h) * HD + c] = bf16_bits(v);
+    p.out[((size_t)seq * p.h_q + (size_t)h0 + h) * HD + cs * COLS + c] = bf16_bits(v);
   }
 }
 
@@ -1204,19 +1243,26 @@ static bool merge_group_ok(const DecodeParams& p) {
   return p.G <= kMgMaxG && p.n_splits <= kMgMaxSplits && p.r_v <= kMgMaxRank;
 }
 
+template <int HD, int MAXR>
+static int launch_merge_group(const DecodeParams& p, hipStream_t s) {
+  const bool halves = p.G % 2 == 0 && p.b * p.h_kv <= 256;  // two workgroups per group while that still adds CUs
+  // Four (two) workgroups per half, each with 32 columns, up to 32 groups: 256 workgroups.  Beyond, fetching the partials once
+  // per column block costs more than it saves (us per call, one / all columns per workgroup: 1 x 1337 22.1 / 23.0, 4 x 2000 at rank 544
+  // 28.5 / 30.4, 8 x 2000 at rank 384 36.1 / 33.7, 16 x 4096 105 / 97).
+  const bool columns = halves && p.latent_out == 0 && p.b * p.h_kv <= 32;
+  if (columns) return launch_kernel(decode_merge_group_kernel<HD, 2, HD / 32, MAXR>, dim3(p.b * p.h_kv * 2 * (HD / 32)), dim3(512), 0, s, p);
+  if (halves) return launch_kernel(decode_merge_group_kernel<HD, 2, 1, MAXR>, dim3(p.b * p.h_kv * 2), dim3(512), 0, s, p);
+  return launch_kernel(decode_merge_group_kernel<HD, 1, 1, MAXR>, dim3(p.b * p.h_kv), dim3(1024), 0, s, p);
+}
+
 // The merge launch that follows every split kernel.
 static int launch_merge(const DecodeParams& p, hipStream_t s) {
-  const bool halves = p.G % 2 == 0 && p.b * p.h_kv <= 256;  // two workgroups per group while that still adds CUs
   if (!merge_group_ok(p)) {
     if (p.head_dim == 128) return launch_kernel(decode_merge_kernel<128>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
     return launch_kernel(decode_merge_kernel<64>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
   }
-  if (halves) {
-    if (p.head_dim == 128) return launch_kernel(decode_merge_group_kernel<128, 2>, dim3(p.b * p.h_kv * 2), dim3(512), 0, s, p);
-    return launch_kernel(decode_merge_group_kernel<64, 2>, dim3(p.b * p.h_kv * 2), dim3(512), 0, s, p);
-  }
-  if (p.head_dim == 128) return launch_kernel(decode_merge_group_kernel<128, 1>, dim3(p.b * p.h_kv), dim3(1024), 0, s, p);
-  return launch_kernel(decode_merge_group_kernel<64, 1>, dim3(p.b * p.h_kv), dim3(1024), 0, s, p);
+  if (p.r_v <= 512) return p.head_dim == 128 ? launch_merge_group<128, 512>(p, s) : launch_merge_group<64, 512>(p, s);
+  return p.head_dim == 128 ? launch_merge_group<128, 1024>(p, s) : launch_merge_group<64, 1024>(p, s);
 }
 
 DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
