@@ -36,7 +36,7 @@ constexpr size_t stat768_fixed_lds() {
   size_t b = (size_t)(2 * NK + kVBlocks<NK>) * 1024 + (size_t)16 * FL * 1024;  // K and V tile, factor operands
   b += 1024;                                                 // sink for copies and stores that must not land anywhere
   b += (size_t)4 * kHeads<PACK> * kHalfT * 4;                // partial scores of the four quarters of a head
-  b += (size_t)2 * 1024;                                     // P operands: heads in rows 0 .. , and in rows 8 .. 15
+  b += (size_t)(PACK ? 2 : 1) * 1024;                        // P operands: heads in rows 0 .. ; PACK: and in rows 8 .. 15
   b += (size_t)2 * kHeads<PACK> * kStatQPitch * 4;           // scaled queries (fp16 pairs), rotated for the tile's two halves
   b += (size_t)3 * kStatMaxHeads * 4;                        // alpha; running max and sum at the end
   b += (size_t)64 * 8;                                       // rotation frequencies in turns per position
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kStatThreads, 2) void decode_split_kernel(DecodePar
   unsigned char* sink = fbuf + (size_t)16 * FL * 1024;
   float* sbuf = reinterpret_cast<float*>(sink + 1024);
   uint16_t* pbuf = reinterpret_cast<uint16_t*>(sbuf + 4 * NH * T);
-  uint32_t* qrot = reinterpret_cast<uint32_t*>(pbuf + 1024);
+  uint32_t* qrot = reinterpret_cast<uint32_t*>(pbuf + (PACK ? 1024 : 512));
   float* alpha = reinterpret_cast<float*>(qrot + 2 * NH * kStatQPitch);
   float* m_fin = alpha + kStatMaxHeads;
   float* l_fin = m_fin + kStatMaxHeads;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kStatThreads, 2) void decode_split_kernel(DecodePar
     const int id = p.block_table[(size_t)seq * p.max_pages + page_begin + i];
     ids[i] = id >= 0 && id < p.n_pages ? id : -1;
   }
-  if (tid < 128) reinterpret_cast<u32x4*>(pbuf)[tid] = u32x4{0u, 0u, 0u, 0u};
+  if (tid < (PACK ? 128 : 64)) reinterpret_cast<u32x4*>(pbuf)[tid] = u32x4{0u, 0u, 0u, 0u};
   if (tid < kStatMaxHeads) {
     alpha[tid] = 1.f;
     l_fin[tid] = 0.f;
@@ -511,30 +511,33 @@ struct Stat768Form {
   Stat768Kernel kernel;
   size_t lds;
 };
-Stat768Form stat768_form(int rank) {
+Stat768Form stat768_form(int rank, bool pack) {
+  if (!pack) return rank <= 576 ? Stat768Form{decode_split_kernel<18, 0, false>, stat768_fixed_lds<18, 0, false>()}
+                                : Stat768Form{decode_split_kernel<21, 3, false>, stat768_fixed_lds<21, 3, false>()};
   if (rank <= 576) return {decode_split_kernel<18, 0, true>, stat768_fixed_lds<18, 0, true>()};
   if (rank <= 672) return {decode_split_kernel<21, 1, true>, stat768_fixed_lds<21, 1, true>()};
   return {decode_split_kernel<24, 3, true>, stat768_fixed_lds<24, 3, true>()};
 }
 }  // namespace
 
-// (Groups of more than four heads would need twice the accumulators of o_lat: they take the three launches of lorc_decode_wide.hip.)
 bool stationary768_shape_ok(const lorc_layer_desc& d) {
   const int G = d.n_q_heads / d.n_kv_heads, rank = d.rank_k > d.rank_v ? d.rank_k : d.rank_v;
-  return d.head_dim == 128 && d.n_kv_heads % 2 == 0 && G <= 4 && d.n_q_heads <= 32 && rank > 512 && rank <= 768 && d.rank_k > 128;
+  return d.head_dim == 128 && d.n_kv_heads % 2 == 0 && G <= 8 && rank > 512 && rank <= (G <= 4 && d.n_q_heads <= 32 ? 768 : 672) && d.rank_k > 128;
 }
 
 int set_kernel_attributes_decode_stationary768() {
-  for (int rank : {576, 672, 768})
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(stat768_form(rank).kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            160 * 1024) != hipSuccess) return LORC_EHIP;
+  for (bool pack : {true, false})
+    for (int rank : {576, 672, 768})
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(stat768_form(rank, pack).kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              160 * 1024) != hipSuccess) return LORC_EHIP;
   return LORC_OK;
 }
 
 int launch_decode_stationary768_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s) {
-  const Stat768Form f = stat768_form(p.r_k > p.r_v ? p.r_k : p.r_v);
+  const int rank = p.r_k > p.r_v ? p.r_k : p.r_v;
+  const Stat768Form f = stat768_form(rank, 2 * p.G <= 8);
   const size_t lds = (f.lds + (size_t)plan.tiles_per_split * 4 + 15) & ~(size_t)15;
-  if (lds > 160 * 1024 || plan.tiles_per_split > kStatMaxTiles || 2 * p.G > 8) return LORC_EUNSUPPORTED;
+  if (lds > 160 * 1024 || plan.tiles_per_split > kStatMaxTiles || p.G > 8 || rank > (p.G <= 4 ? 768 : 672)) return LORC_EUNSUPPORTED;
   const int units = p.b * p.n_splits, nq = p.h_kv / 2;
   return launch_kernel(f.kernel, dim3(((units + 7) / 8) * 8 * nq), dim3(kStatThreads), lds, s, p);
 }

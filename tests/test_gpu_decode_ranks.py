@@ -28,6 +28,8 @@ pytestmark = pytest.mark.gpu
     (672, 640, 12, 6, [31, 96, 640]),
     (704, 768, 18, 6, [97, 1]),
     (768, 768, 32, 8, [127, 128, 1000]),
+    (576, 544, 36, 6, [33, 1, 500]),             # groups of six
+    (640, 672, 64, 8, [700, 64, 0]),
     (160, 576, 24, 6, [75, 300]),                 # value rank above 512 alone
 ])
 def test_ranks_match_oracle(r_k, r_v, h_q, h_kv, ctx):
