@@ -686,13 +686,13 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
 // keeps the accuracy of an fp32 o_lat.  Shapes: G <= 8, at most 64 splits, r_v <= 1024.  Bound by latency: launch, one round trip
 // for both operands, the product's chain.  Value ranks above 512 before, a workgroup per query head and scalar products: 14.5 us
 // for one sequence at rank 768, whole call 36.5 -> 25.2; 1 x 1337 at rank 512 (four columns per thread, all splits in one): 23.0 -> 22.1.
-constexpr int kMgMaxG = 8, kMgMaxSplits = 64, kMgMaxRank = 1024;
+constexpr int kMgMaxG = 8, kMgMaxSplits = 64, kMgMaxRank = 1024, kMgMaxRankG1 = 2048;
 // HS: workgroups that share a group's heads;  CS: workgroups that share the head's columns (each works out the weighted sums of its
-// heads for itself);  MAXR: largest value rank.
-template <int HD, int HS, int CS, int MAXR>
+// heads for itself);  MAXR: largest value rank;  MAXG: heads of a workgroup.
+template <int HD, int HS, int CS, int MAXR, int MAXG = kMgMaxG / HS>
 __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodeParams p) {
   constexpr int NCB = HD / 32 / CS, NKQ = (16 / HS) / NCB, MAXKS = (MAXR / 16 + NKQ - 1) / NKQ;
-  constexpr int MAXG = kMgMaxG / HS, PITCH = MAXR + 8, COLS = 32 * NCB;
+  constexpr int PITCH = MAXR + 8, COLS = 32 * NCB;
   constexpr int BATCH = HS == 1 ? 8 : 16;  // partials a thread has in flight (16 bytes each)
   __shared__ float wgt[MAXG][kMgMaxSplits];
   __shared__ __align__(16) uint16_t o_hi[MAXG][PITCH];
@@ -1257,6 +1257,12 @@ static int launch_merge_group(const DecodeParams& p, hipStream_t s) {
 
 // The merge launch that follows every split kernel.
 static int launch_merge(const DecodeParams& p, hipStream_t s) {
+  // Groups of one head: every head reads a factor block of its own for every sequence, so that beyond a few sequences the
+  // kernel below is as fast or faster.  13B shape, us per layer-step, generic merge / this: 1 x 1000 rank 2048 92 / 65 (merge alone
+  // 37 / 8), 4 x 700 rank 1600 122 / 108, 6 x 300 102 / 91, 8 x 500 rank 1280 109.6 / 113, 16 x 300 144 / 165.
+  if (p.G == 1 && p.head_dim == 128 && p.latent_out == 0 && p.r_v > kMgMaxRank && p.r_v <= kMgMaxRankG1 && p.n_splits <= kMgMaxSplits &&
+      p.b * p.h_q <= 256)
+    return launch_kernel(decode_merge_group_kernel<128, 1, 4, kMgMaxRankG1, 1>, dim3(p.b * p.h_q * 4), dim3(1024), 0, s, p);
   if (!merge_group_ok(p)) {
     if (p.head_dim == 128) return launch_kernel(decode_merge_kernel<128>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
     return launch_kernel(decode_merge_kernel<64>, dim3(p.b * p.h_q), dim3(256), 0, s, p);

@@ -520,6 +520,9 @@ Stat768Form stat768_form(int rank, bool pack) {
 }
 }  // namespace
 
+// Groups of more than four heads need twice the accumulators of o_lat, which leaves room for 672 latent indices; beyond, they take
+// the three launches of lorc_decode_wide.hip.  70B shape, us per layer-step, three launches / this: 32 x 8192 rank 640 549 / 439, rank 544
+// 515 / 382; 1 x 1000 rank 640 62 / 27; 16 x 2000 rank 672 112 / 81.
 bool stationary768_shape_ok(const lorc_layer_desc& d) {
   const int G = d.n_q_heads / d.n_kv_heads, rank = d.rank_k > d.rank_v ? d.rank_k : d.rank_v;
   return d.head_dim == 128 && d.n_kv_heads % 2 == 0 && G <= 8 && rank > 512 && rank <= (G <= 4 && d.n_q_heads <= 32 ? 768 : 672) && d.rank_k > 128;

@@ -814,7 +814,15 @@ DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cu
     // uncompressed layers: a workgroup streams only one head's 16 KiB per tile, so many more of them are kept in flight
     const long want = (plain ? 8L : 2L) * cus;
     long ns = (want + (long)b * pl.v_chunks - 1) / ((long)b * pl.v_chunks);
-    if (ns > (n_tiles + 3) / 4) ns = (n_tiles + 3) / 4;
+    // four tiles per split at least, fewer while every split still has a compute unit (and the merge at most 64 splits): values of
+    // one sequence of 1000 positions at rank 2048 24 -> 18 us, of 2 x 1000 (64 heads, rank 768) 27 -> 22
+    long tps_min = 4;
+    if (!plain) {
+      tps_min = ((long)b * pl.v_chunks * n_tiles + cus - 1) / cus;
+      if (tps_min > 4) tps_min = 4;
+      if (tps_min < 4 && tps_min < (n_tiles + 63) / 64) tps_min = (n_tiles + 63) / 64;
+    }
+    if (ns > (n_tiles + tps_min - 1) / tps_min) ns = (n_tiles + tps_min - 1) / tps_min;
     if (ns < 1) ns = 1;
     if (ns > 512) ns = 512;
     pl.tiles_per_split = (int)((n_tiles + ns - 1) / ns);
