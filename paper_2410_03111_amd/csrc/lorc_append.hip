@@ -50,7 +50,7 @@ __global__ void pack_factors_kernel(const uint16_t* __restrict__ A_k, const uint
 }
 
 // ------------------------------------------------------------------------------------------------ append
-// Short prompts.  Block tile: 64 latent rows x 64 tokens, k-tile 64; 4 waves as 2x2.
+// Short prompts.  Block tile: 64 latent rows x 64 tokens, k-tile 64, 4 waves as 2x2; or 32 x 32, each wave a k-step of the k-tile.
 // LDS rows are 64 bf16 = 8 chunks of 16 B; chunk c of row r is stored at c ^ (r & 7) so that the 32 rows a
 // fragment load touches spread over all banks.  With so few workgroups the walk over the model dimension is a
 // chain of memory latencies, so every thread keeps PF k-tiles of both operands in flight in registers (buffer
@@ -59,11 +59,12 @@ constexpr int kApBK = 64;
 
 __device__ __forceinline__ int swz(int row, int chunk) { return (row * 8 + (chunk ^ (row & 7))) * 8; }
 
+template <int BM>
 __global__ __launch_bounds__(256) void append_kernel(AppendParams p) {
-  constexpr int BM = 64, PF = 8, BN = BM, NB = BM / 64, LD = BM / 32;  // accumulator blocks per wave and side; 16-byte loads per thread, operand and k-tile
+  constexpr int PF = 8, BN = BM, NB = 1, LD = BM / 32;  // accumulator blocks per wave and side; 16-byte loads per thread, operand and k-tile
   static_assert(PF % 2 == 0, "the LDS buffer of a k-tile is chosen by its stage's parity");
-  __shared__ __align__(16) uint16_t sA[2][BM * kApBK];
-  __shared__ __align__(16) uint16_t sB[2][BN * kApBK];
+  __shared__ __align__(16) uint16_t sA[4][BM * kApBK];  // two buffers of each operand
+  uint16_t (*const sB)[BM * kApBK] = sA + 2;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wm = w >> 1, wn = w & 1;
   const int hf = lane >> 5, l32 = lane & 31;
   const int j0 = blockIdx.y * BM, t0 = blockIdx.x * BN;
@@ -110,6 +111,11 @@ __global__ __launch_bounds__(256) void append_kernel(AppendParams p) {
   auto multiply = [&](int buf) {
 #pragma unroll
     for (int ks = 0; ks < kApBK / 16; ++ks) {
+      if constexpr (BM == 32) {  // wave w takes k-step w of the k-tile for the whole tile
+        if (ks == 0)
+          acc[0][0] = mfma32(load_frag(sA[buf] + swz(l32, w * 2 + hf)), load_frag(sB[buf] + swz(l32, w * 2 + hf)), acc[0][0]);
+        continue;
+      }
       bf16x8 a[NB], b[NB];
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
@@ -147,10 +153,22 @@ __global__ __launch_bounds__(256) void append_kernel(AppendParams p) {
     }
   }
 
+  // 32 x 32 tiles: the waves' sums meet in LDS; wave w adds and files the rows 8 w + 4 hf .. + 3.
+  f32x4 mine = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (BM == 32) {
+    static_assert(BM != 32 || 4 * BM * kApBK * 2 >= 16 * 1024, "room for sixteen KiB of sums in sA and sB");
+    f32x4* const meet = reinterpret_cast<f32x4*>(&sA[0][0]);  // [quarter][wave][64 lanes]
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+      meet[(q4 * 4 + w) * 64 + lane] = f32x4{acc[0][0][4 * q4], acc[0][0][4 * q4 + 1], acc[0][0][4 * q4 + 2], acc[0][0][4 * q4 + 3]};
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) mine += meet[(w * 4 + i) * 64 + lane];
+  }
   // Epilogue: lane holds token column l32 of each block and 16 latent rows; 4 consecutive rows per group.
 #pragma unroll
   for (int ni = 0; ni < NB; ++ni) {
-    const int t = t0 + wn * (BN / 2) + ni * 32 + l32;
+    const int t = t0 + (BM == 32 ? 0 : wn * (BN / 2) + ni * 32) + l32;
     if (t >= p.T) continue;
     const int seq = p.slot_seq[t], pos = p.slot_pos[t];
     if (seq < 0 || seq >= p.n_seqs || pos < 0 || pos >= p.max_pages * kPage) continue;
@@ -160,14 +178,14 @@ __global__ __launch_bounds__(256) void append_kernel(AppendParams p) {
     uint16_t* base = p.cache + (size_t)page * p.page_elems;
 #pragma unroll
     for (int mi = 0; mi < NB; ++mi) {
-      const int jb = j0 + wm * (BM / 2) + mi * 32;
+      const int jb = j0 + (BM == 32 ? 0 : wm * (BM / 2) + mi * 32);
       if (jb >= rt) continue;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int j = jb + 8 * q4 + 4 * hf;
+      for (int q = 0; q < (BM == 32 ? 1 : 4); ++q) {
+        const int j = jb + 8 * (BM == 32 ? w : q) + 4 * hf;
         uint16_t v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = bf16_bits(acc[mi][ni][4 * q4 + i]);
+        for (int i = 0; i < 4; ++i) v[i] = bf16_bits(BM == 32 ? mine[i] : acc[mi][ni][4 * q + i]);
         if (j < p.r_k) {
           u32x2 pk = {(uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16)};
           *reinterpret_cast<u32x2*>(base + k_index(p.r_k, slot, j)) = pk;
@@ -765,7 +783,7 @@ int set_kernel_attributes_append() {
 //     8192: - / - / 325 / 278;   13B uncompressed: T = 777: 233 / 136 / 112 / 240,  1500: 327 / 171 / 166 / 241.
 // (Sequences whose tokens do not start at a multiple of eight slots store V latents one by one, which costs the 256 x 256 tiles
 // up to 15 %; where tokens go is not known here.)
-constexpr int kSkinnyMaxT = 64;
+constexpr int kSkinnyMaxT = 64, kSkinnyMinTiles = 32;
 
 static double append_tile_cost(AppendForm form, int rows_k, int rows_v, int T, int n_cus) {
   auto up = [](int x, int y) { return (x + y - 1) / y; };
@@ -797,8 +815,18 @@ static double append_tile_cost(AppendForm form, int rows_k, int rows_v, int T, i
   return load <= 1 ? 0.36 + 0.18 * load : (load <= 1.58 ? 0.82 : 0.52 * load);
 }
 
+// 32 x 32 tiles while there are no more than CUs.  A CU takes about 52 bytes of these operands per ns, with 32 workgroups on the chip
+// as with 256, so what counts is the bytes per workgroup: 64 rows of the model dimension instead of 128, or of all tokens in the one-pass
+// kernel, which keeps up to 32 tokens (equal there).  us, weights from HBM, before -> now: 8B rank 512 T = 48 14.2 -> 10.3, 64 18.3 -> 10.4, 100
+// 20.3 -> 10.4, 256 20.8 -> 13.0; rank 256 T = 500 20.8 -> 11.2; 70B rank 512 T = 64 32.6 -> 17.7; 13B rank 2048 T = 64 28.6 -> 16.9.
+// Tried without gain: four groups of waves over the model dimension in a 64 x 64 workgroup (22.3 -> 23.1 at 777 tokens), two in a 128 x 128
+// one (28 -> 35 at 900), another first k-tile per workgroup (22.4 -> 28.6).
+static bool append_small_tiles(int rows, int T, int n_cus) { return (long)((rows + 31) / 32) * ((T + 31) / 32) <= n_cus; }
+
 AppendForm append_form(int D, int rows_k, int rows_v, int T, int n_cus) {
-  if (T <= kSkinnyMaxT) return AppendForm::kSkinny;
+  const bool small = append_small_tiles(rows_k + rows_v, T, n_cus);
+  if (T <= kSkinnyMaxT) return T > kSkinnyMinTiles && D >= 1024 && small ? AppendForm::kTile64 : AppendForm::kSkinny;
+  if (small) return AppendForm::kTile64;
   AppendForm best = AppendForm::kTile64;
   double best_cost = append_tile_cost(best, rows_k, rows_v, T, n_cus);
   for (AppendForm f : {AppendForm::kTile128, AppendForm::kTile256x128, AppendForm::kTile256}) {
@@ -844,7 +872,10 @@ int launch_append(const AppendParams& p, int n_cus, hipStream_t s) {
       return rows > 8 ? launch_skinny<true>(p, rows, s) : launch_skinny<false>(p, rows, s);
     }
     case AppendForm::kTile64:
-      return launch_kernel(append_kernel, dim3((p.T + 63) / 64, (rt + 63) / 64), dim3(256), 0, s, p);
+    {
+      if (append_small_tiles(rt, p.T, n_cus)) return launch_kernel(append_kernel<32>, dim3((p.T + 31) / 32, (rt + 31) / 32), dim3(256), 0, s, p);
+      return launch_kernel(append_kernel<64>, dim3((p.T + 63) / 64, (rt + 63) / 64), dim3(256), 0, s, p);
+    }
     case AppendForm::kTile128: {
       const dim3 grid(tile_grid(p.r_k, p.r_v, p.T, 128));
       if ((int)grid.x <= n_cus) return launch_kernel(append_tile_kernel<2, 5, 4>, grid, dim3(256), rt_ring_bytes<2, 5, 4>(), s, p);
