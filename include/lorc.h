@@ -158,7 +158,9 @@ const char* lorc_append_plan_info(const lorc_layer_desc* desc, int32_t T);
  *            inside ctx_len whose id is negative or >= n_pages is not read, its positions count as zero
  *            latents (key 0, value 0)
  *   out      [b x h_q x d] bf16
- *   workspace  lorc_decode_workspace_bytes(desc, b, max_ctx) bytes, 256-byte aligned (split partials)
+ *   workspace  lorc_decode_workspace_bytes(desc, b, max_ctx) bytes, 256-byte aligned (split partials).  Key ranks up to 384
+ *              and above 512 of head_dim 128 also take one sized for a larger b and max_ctx, where that is smaller: the call
+ *              then uses the splits that fit.
  */
 size_t lorc_decode_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx);
 /* The launch that lorc_decode_attention would make for (desc, b, max_ctx) on the current device: returns the name
@@ -193,7 +195,7 @@ int lorc_decode_attention_plain(const lorc_layer_desc* desc, const void* q, cons
  * capture, serving loops and harnesses that forbid hipMalloc): same arguments, result and kernels, but the split
  * partials live in a fixed array of LORC_STATIC_WORKSPACE_BYTES inside the library's device code, one copy per GPU,
  * held until the process ends.  The call allocates nothing.
- *   - LORC_EWORKSPACE when lorc_decode_workspace_bytes(desc, b, max_ctx) exceeds LORC_STATIC_WORKSPACE_BYTES.
+ *   - LORC_EWORKSPACE where lorc_decode_attention would return it for a workspace of LORC_STATIC_WORKSPACE_BYTES.
  *   - All calls on one GPU share that GPU's array: two calls whose kernels overlap in time (different streams
  *     without an ordering between them) race; calls on one stream, or ordered by events, are safe.  Nothing in the
  *     array has to be cleared between calls: every split writes all of its partials before the merge reads them.

@@ -125,15 +125,14 @@ int decode_params(DecodeParams& p, const lorc_layer_desc* desc, const void* q, c
 int decode_rotary(const lorc_layer_desc* desc, const void* q, const int32_t* q_pos, const int32_t* ctx_len, int32_t b,
                   int32_t max_ctx, const void* packed, const void* cache, const int32_t* block_table, int32_t max_pages,
                   int32_t n_pages, void* out, void* workspace, size_t workspace_bytes, void* stream, void* ev_begin,
-                  void* ev_end, int latent_out, bool plain = false, bool fit = false) {
+                  void* ev_end, int latent_out, bool plain = false) {
   if (int rc = decode_args(desc, q, q_pos, true, ctx_len, b, max_ctx, packed, cache, block_table, max_pages, n_pages, out, workspace))
     return rc;
   if (plain && !plain_shape_ok(*desc)) return LORC_EUNSUPPORTED;
   int n_cus = 0;
   if (int rc = device_ready(&n_cus)) return rc;
   const DecodePlan plan = plain ? make_wide_plan(*desc, b, max_ctx, n_cus, true)
-                          : fit ? make_decode_plan_within(*desc, b, max_ctx, n_cus, workspace_bytes)
-                                : make_decode_plan(*desc, b, max_ctx, n_cus);
+                                : make_decode_plan_within(*desc, b, max_ctx, n_cus, workspace_bytes);
   DecodeParams p;
   if (int rc = decode_params(p, desc, q, q_pos, true, ctx_len, b, max_ctx, packed, cache, block_table, max_pages, n_pages,
                              out, workspace, workspace_bytes, plan, latent_out))
@@ -262,7 +261,7 @@ int lorc_decode_attention_static(const lorc_layer_desc* desc, const void* q, con
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return LORC_EHIP;
   // a problem whose partials do not fit the array in any plan is refused by the workspace check (LORC_EWORKSPACE)
   return decode_rotary(desc, q, q_pos, ctx_len, b, max_ctx, packed, cache, block_table, max_pages, n_pages, out,
-                       g_scratch_ptr[dev], kStaticScratchBytes, stream, nullptr, nullptr, 0, false, true);
+                       g_scratch_ptr[dev], kStaticScratchBytes, stream, nullptr, nullptr, 0);
 }
 
 // ---- decode without positional rotation, absorbed query (Section 4.1, Eq. 7)
@@ -281,7 +280,7 @@ int lorc_decode_attention_absorbed_timed(const lorc_layer_desc* desc, const void
     return rc;
   int n_cus = 0;
   if (int rc = device_ready(&n_cus)) return rc;
-  const DecodePlan plan = make_absorbed_plan(*desc, b, max_ctx, n_cus);
+  const DecodePlan plan = make_absorbed_plan_within(*desc, b, max_ctx, n_cus, workspace_bytes);
   DecodeParams p;
   if (int rc = decode_params(p, desc, q_lat, nullptr, false, ctx_len, b, max_ctx, packed, cache, block_table, max_pages,
                              n_pages, out, workspace, workspace_bytes, plan, 0))

@@ -1197,11 +1197,19 @@ DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_
 
 DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes) {
   const DecodePlan pl = make_decode_plan(d, b, max_ctx, n_cus);
-  if (pl.total_bytes <= bytes || !pl.stationary) return pl;
-  DecodePlan few = make_stationary_plan(d, b, max_ctx, n_cus, true);  // (its splits walk at most 512 pages)
-  few.stationary = pl.stationary;
-  if (few.total_bytes <= bytes) return few;
-  const DecodePlan streaming = make_streaming_plan(d, b, max_ctx, n_cus);
+  if (pl.total_bytes <= bytes) return pl;
+  if (pl.wide) {
+    const DecodePlan four = make_wide_plan(d, b, max_ctx, n_cus, false, true);
+    return four.total_bytes <= bytes ? four : pl;
+  }
+  // decode_stationary_kernel proper takes a workspace of the whole size or none, as the size function's contract says
+  if (!pl.stationary || (pl.stationary == 1 && d.rank_k > kStatSmallRank)) return pl;
+  const size_t per_split = (size_t)b * d.n_q_heads * (8 + 2 * (size_t)d.rank_v), align = 512;
+  const size_t splits = bytes > align ? (bytes - align) / per_split : 0;
+  DecodePlan fewer = make_stationary_plan(d, b, max_ctx, n_cus, splits < 64 ? (int)splits : 64);
+  fewer.stationary = pl.stationary;
+  if (fewer.total_bytes <= bytes) return fewer;
+  const DecodePlan streaming = make_streaming_plan(d, b, max_ctx, n_cus);  // (a split may walk more than 512 pages)
   return streaming.total_bytes != 0 && streaming.total_bytes <= bytes ? streaming : pl;
 }
 
@@ -1286,6 +1294,14 @@ DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int 
   plan_splits(pl, b, max_ctx, 2 * (n_cus > 0 ? n_cus : 256));  // two workgroups per CU
   plan_workspace(pl, d, b);
   return pl;
+}
+
+DecodePlan make_absorbed_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes) {
+  const DecodePlan pl = make_absorbed_plan(d, b, max_ctx, n_cus);
+  if (!pl.wide || pl.total_bytes <= bytes) return pl;
+  DecodePlan four = make_wide_plan(d, b, max_ctx, n_cus, false, true);
+  four.wide = pl.wide;
+  return four.total_bytes <= bytes ? four : pl;
 }
 
 int set_kernel_attributes_decode() {

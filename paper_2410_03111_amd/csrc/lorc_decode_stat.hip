@@ -703,7 +703,7 @@ bool stationary_shape_ok(const lorc_layer_desc& d) {
          (d.rank_k > 128 || d.n_q_heads > 32);
 }
 
-DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool fewest_splits) {
+DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits) {
   DecodePlan pl{};
   pl.tile = kStatTile;
   pl.occupancy = 1;
@@ -717,7 +717,7 @@ DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, in
   int min_splits = (n_tiles + kStatMaxTiles - 1) / kStatMaxTiles;
   int best = min_splits;
   double best_cost = 0;
-  for (int ns = min_splits; ns <= n_tiles && ns <= (fewest_splits ? min_splits : 64); ++ns) {
+  for (int ns = min_splits; ns <= n_tiles && (ns == min_splits || ns <= max_splits); ++ns) {
     const int tps = (n_tiles + ns - 1) / ns;
     const int ns_eff = (n_tiles + tps - 1) / tps;
     const long rounds = (wgs_per_split * ns_eff + cus - 1) / cus;

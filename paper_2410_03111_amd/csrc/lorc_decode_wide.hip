@@ -783,7 +783,7 @@ static bool plain_one_pass(int h_kv) { return h_kv % kPlainHeads == 0; }
 
 // Splits for the value kernel: enough workgroups for about two per CU, each walking at least four tiles; for the one-pass
 // kernel of uncompressed layers see below.
-DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain) {
+DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain, bool four_tiles) {
   DecodePlan pl{};
   pl.tile = kWideT;
   pl.occupancy = 1;
@@ -817,7 +817,7 @@ DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cu
     // four tiles per split at least, fewer while every split still has a compute unit (and the merge at most 64 splits): values of
     // one sequence of 1000 positions at rank 2048 24 -> 18 us, of 2 x 1000 (64 heads, rank 768) 27 -> 22
     long tps_min = 4;
-    if (!plain) {
+    if (!plain && !four_tiles) {
       tps_min = ((long)b * pl.v_chunks * n_tiles + cus - 1) / cus;
       if (tps_min > 4) tps_min = 4;
       if (tps_min < 4 && tps_min < (n_tiles + 63) / 64) tps_min = (n_tiles + 63) / 64;

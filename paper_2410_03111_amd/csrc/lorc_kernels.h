@@ -107,7 +107,8 @@ PrefillPlan make_prefill_plan(const lorc_layer_desc& d, int b, int max_seqlen);
 int launch_prefill(const PrefillParams& p, int n_cus, hipStream_t s, bool plain = false);
 
 DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus);
-// The same for a workspace of a given size: where the plan above does not fit, the one that needs least (which may not fit either).
+// The same for a workspace of a given size.  Where the plan above does not fit (a workspace sized for a larger batch or context, whose
+// sequences take fewer splits): the best one that does.  If there is none, the plan above, which the workspace check refuses.
 DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes);
 
 int launch_pack(const lorc_layer_desc& d, const void* A_k, const void* A_v, const void* B_k, const void* B_v,
@@ -120,6 +121,7 @@ const char* append_kernel_name(int D, int rows_k, int rows_v, int T, int n_cus);
 int launch_append(const AppendParams& p, int n_cus, hipStream_t s);
 int launch_decode(const DecodeParams& p, const DecodePlan& plan, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end);
 DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus);
+DecodePlan make_absorbed_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes);
 int launch_decode_absorbed(const DecodeParams& p, const DecodePlan& plan, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end);
 int launch_stream_probe(const void* src, size_t bytes, void* sink, hipStream_t s);
 int launch_mfma_probe(float* sink, int workgroups, int iters, int operands, hipStream_t s);
@@ -135,7 +137,7 @@ int set_kernel_attributes_decode_stationary();
 // 160 to 512); its plan and launch.  The merge launch that follows is the common one.
 constexpr int kStatSmallRank = 384;  // up to here it runs as decode_split_kernel, above as decode_stationary_kernel
 bool stationary_shape_ok(const lorc_layer_desc& d);
-DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool fewest_splits = false);
+DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits = 64);
 int launch_decode_stationary_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
 // The same for ranks 544 to 768 (G <= 4, up to 32 query heads); it takes the plan of the other.
 bool stationary768_shape_ok(const lorc_layer_desc& d);
@@ -146,7 +148,8 @@ int launch_decode_stationary768_split(const DecodeParams& p, const DecodePlan& p
 bool wide_shape_ok(const lorc_layer_desc& d);
 bool plain_shape_ok(const lorc_layer_desc& d);
 bool wide_absorbed_shape_ok(const lorc_layer_desc& d);
-DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain);
+// four_tiles: splits of four tiles at least, whose partials never grow as the batch or the context shrinks
+DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain, bool four_tiles = false);
 int launch_decode_wide(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
 int set_kernel_attributes_decode_wide();
 

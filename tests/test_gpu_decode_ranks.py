@@ -73,3 +73,32 @@ def test_fixed_array_takes_a_plan_of_fewer_splits_where_the_best_one_does_not_fi
     got, ref = out.float(), ref.float()
     assert bool(torch.isfinite(got).all())
     assert float((got - ref).norm() / ref.norm()) <= 2 ** -8   # bf16 outputs (2^-9 each) and fp16 partials (2^-11)
+
+
+@pytest.mark.parametrize("rank,h_q,b,largest_b,n", [
+    (256, 32, 4, 6, 700),     # factor in registers; one workspace for six sequences is smaller than what four take by themselves
+    (256, 64, 4, 6, 700),
+    (608, 32, 4, 6, 700),
+    (608, 64, 4, 6, 700),
+    (768, 64, 8, 12, 700),    # three launches
+])
+def test_workspace_sized_for_the_largest_batch_serves_smaller_ones(rank, h_q, b, largest_b, n):
+    """The call takes the splits that fit, leaves what follows the workspace alone, and differs from a call with a workspace of its own
+    size by the rounding of the outputs and of the softmax weights (bf16, relative to the tile's or the split's maximum: 1.7e-3 each in the 2-norm)
+    and of the partials (fp16), in both: under 2^-8 together."""
+    import torch
+    pb = Problem(d_model=1024, n_q_heads=h_q, n_kv_heads=8, head_dim=128, rank_k=rank, rank_v=rank, rope_base=10000.0, ctx=[n], seed=7).build()
+    layer = GpuLayer(pb)
+    layer.append_all()
+    L, dev = layer.L, layer.dev
+    need = L.decode_workspace_bytes(layer.desc, largest_b, n)
+    assert need < L.decode_workspace_bytes(layer.desc, b, n)
+    q = torch.randn(b, h_q, 128, generator=torch.Generator().manual_seed(1)).to(dev).to(torch.bfloat16)
+    ctx = torch.tensor([n - 61 * s for s in range(b)], dtype=torch.int32, device=dev)
+    table = layer.block_table.expand(b, -1).contiguous()
+    args = (layer.desc, q, ctx - 1, ctx, n, layer.packed, layer.cache, table)
+    ref = L.decode_attention(*args).float()
+    buf = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=dev)
+    got = L.decode_attention(*args, workspace=buf[:need]).float()
+    assert bool(torch.isfinite(got).all()) and bool((buf[need:] == 0x5A).all())
+    assert float((got - ref).norm() / ref.norm()) <= 2 ** -8
