@@ -19,8 +19,6 @@
 
 namespace lorc {
 
-typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
-constexpr float kMaxSum = 1024.f;  // largest sum of a lane's exponentials in a tile (each stays far below fp16's 65504)
 constexpr float kNegInfP = -__builtin_huge_valf();
 
 
@@ -364,13 +362,8 @@ __global__ __launch_bounds__(64 * kAttnWaves, kAttnWaves == 4 ? 2 : 1) void pref
     for (int a = 0; a < ND; ++a)
 #pragma unroll
       for (int j = 0; j < 16; ++j) o[a][j] = 0.f;
-    // Reference of the query's row (both halves of the wave agree on it), negated, in every register of a score block: the
-    // score products start from it, so that the exponentials take what the matrix cores deliver.  And this half's share of
-    // the row's sum.
-    f32x16 m_neg;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) m_neg[j] = 0.f;
-    float l_half = 0.f;
+    // running maximum of the query's row (both halves of the wave agree on it) and this half's share of its sum
+    float m_run = kNegInfP, l_half = 0.f;
 
     __syncthreads();  // previous head chunk is done with both stages
     tile_dma(0, 0);
@@ -392,10 +385,11 @@ __global__ __launch_bounds__(64 * kAttnWaves, kAttnWaves == 4 ? 2 : 1) void pref
       for (int i = 0; i < RING; ++i) fr[i] = k_at(i);
       __builtin_amdgcn_sched_barrier(0);
       f32x16 s[2];
+      const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       const int tn = t + 1 <= t_wg ? t + 1 : t_wg;  // (clamped: the copies are unconditional)
 #pragma unroll
       for (int i = 0; i < NKF; ++i) {
-        s[i & 1] = mfma32_f16(fr[i % RING], qf[i >> 1], i < 2 ? m_neg : s[i & 1]);
+        s[i & 1] = mfma32_f16(fr[i % RING], qf[i >> 1], i < 2 ? zero : s[i & 1]);
         fr[i % RING] = i + RING < NKF ? k_at(i + RING) : v_at(i + RING - NKF);
         if (i < KI + VI) tile_dma_one(tn, buf ^ 1, i);
       }
@@ -413,51 +407,36 @@ __global__ __launch_bounds__(64 * kAttnWaves, kAttnWaves == 4 ? 2 : 1) void pref
           for (int jj = 0; jj < 16; ++jj)
             if (mb * 32 + acc_row(jj, hf) > dq + l32) s[mb][jj] = kNegInfP;
       }
-      // Softmax.  The scores are relative to a reference that is the maximum of the row's first tile; it moves only where a
-      // lane's 32 exponentials sum to more than kMaxSum, so that ordinary tiles take neither a maximum nor a subtraction nor
-      // a rescaling, and their sum takes the weights in pairs as they are multiplied (fp16).  Vector instructions of either wave
-      // of a SIMD add to its matrix-core ops: 66 instead of 131 of them per wave and tile raise the matrix cores from 57 to 62 % busy
-      // (at 1.55 GHz, the power limit), 4 x 8192 tokens of the 8B shape: 2242 -> 2090 us; 2 x 3001: 170 -> 160.
-      f16x8 pf[4];
-      float sum = 0.f;
-      auto exponentials = [&](float delta) {
-        sum = 0.f;
+      float mx = kNegInfP;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-          for (int jj = 0; jj < 16; jj += 2) {
-            f16x2 pv;
-            pv[0] = static_cast<_Float16>(__builtin_amdgcn_exp2f(s[mb][jj] - delta));
-            pv[1] = static_cast<_Float16>(__builtin_amdgcn_exp2f(s[mb][jj + 1] - delta));
-            sum = __builtin_amdgcn_fdot2(pv, f16x2{(_Float16)1.f, (_Float16)1.f}, sum, false);
-            pf[mb * 2 + (jj >> 3)][jj & 7] = pv[0];
-            pf[mb * 2 + (jj >> 3)][(jj & 7) + 1] = pv[1];
-          }
-      };
-      bool move = t == 0;
-      if (!move) {
-        exponentials(0.f);
-        move = __builtin_amdgcn_ballot_w64(!(sum <= kMaxSum)) != 0;  // (also NaN)
-      }
-      if (move) {
-        float mx = kNegInfP;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int jj = 0; jj < 16; ++jj) mx = fmaxf(mx, s[mb][jj]);
+        for (int jj = 0; jj < 16; ++jj) mx = fmaxf(mx, s[mb][jj]);
+      {
         const float2 both = half_pair(mx);
         mx = fmaxf(both.x, both.y);
-        const float delta = t == 0 ? mx : fmaxf(mx, 0.f), alpha = t == 0 ? 0.f : __builtin_amdgcn_exp2f(-delta);
-        exponentials(delta);
-        l_half *= alpha;
+      }
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      f16x8 pf[4];
+      float sum = 0.f;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) m_neg[j] -= delta;
+      for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int jj = 0; jj < 16; ++jj) {
+          const float pv = __builtin_amdgcn_exp2f(s[mb][jj] - m_new);
+          sum += pv;
+          pf[mb * 2 + (jj >> 3)][jj & 7] = static_cast<_Float16>(pv);
+        }
+      l_half = l_half * alpha + sum;
+      const bool moved = m_new > m_run;
+      m_run = m_new;
+      if (__builtin_amdgcn_ballot_w64(moved) != 0) {  // some row's maximum moved
 #pragma unroll
         for (int db = 0; db < ND; ++db)
 #pragma unroll
           for (int jj = 0; jj < 16; ++jj) o[db][jj] *= alpha;
       }
-      l_half += sum;
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int j = 0; j < NVF; ++j) {

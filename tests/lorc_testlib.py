@@ -196,3 +196,63 @@ class GpuLayer:
 
 def rel_err(got, ref):
     return float(np.max(np.abs(got - ref)) / np.max(np.abs(ref)))
+
+
+class LatentLayer:
+    """A layer whose cached latents and read-side factors are given (bf16 values, nothing appended): pages are written here, by the
+    documented index formulas.  C_k[s], C_v[s]: [N_s, r_k], [N_s, r_v]; B_k, B_v: [r_k, n], [r_v, n]."""
+
+    def __init__(self, n_q_heads, n_kv_heads, head_dim, C_k, C_v, B_k, B_v, rope_base=1e9, softmax_scale=0.0, max_pages=None):
+        import torch
+        import paper_2410_03111_amd as L
+        self.L, self.torch, self.dev = L, torch, torch.device("cuda:0")
+        self.C_k, self.C_v, self.B_k, self.B_v = C_k, C_v, B_k, B_v
+        self.ctx = [len(c) for c in C_k]
+        self.h_q, self.h_kv, self.d, self.base, self.scale = n_q_heads, n_kv_heads, head_dim, rope_base, softmax_scale or None
+        r_k, r_v = B_k.shape[0], B_v.shape[0]
+        self.desc = L.layer_desc(64, n_q_heads, n_kv_heads, head_dim, r_k, r_v, rope_base, softmax_scale)
+        bf = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(self.dev).to(torch.bfloat16).contiguous()
+        self.packed = L.pack_factors(self.desc, bf(np.zeros((64, r_k))), bf(np.zeros((64, r_v))), bf(B_k), bf(B_v))
+        b = len(self.ctx)
+        self.max_pages = max_pages or max(1, max((N + PAGE - 1) // PAGE for N in self.ctx))
+        self.n_pages = b * self.max_pages + 2
+        table = gen.block_table(b, self.max_pages, self.n_pages, seed=3)
+        idx = page_gather_indices(r_k, r_v)
+        pool = np.full((self.n_pages, PAGE * (r_k + r_v)), 0x7FC0, np.uint16)   # NaN where nothing is cached
+        for s, N in enumerate(self.ctx):
+            rows = gen.bf16_bits(np.concatenate([C_k[s], C_v[s]], axis=1).astype(np.float32))
+            for t in range(N):
+                pool[table[s, t // PAGE], idx[t % PAGE]] = rows[t]
+        self.cache = torch.from_numpy(pool.view(np.uint8).reshape(-1)).to(self.dev)
+        self.block_table = torch.from_numpy(table).to(self.dev)
+
+    def tensors(self, q, q_pos=None):
+        """(q, q_pos, ctx_len) on the device; q: [b, h_q, d] on the bf16 grid."""
+        torch = self.torch
+        i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=self.dev)
+        return (torch.from_numpy(np.ascontiguousarray(q, np.float32)).to(self.dev).to(torch.bfloat16).contiguous(),
+                i32([max(N - 1, 0) for N in self.ctx] if q_pos is None else q_pos), i32(self.ctx))
+
+    def decode(self, q, q_pos=None, latent=False):
+        fn = self.L.decode_attention_latent if latent else self.L.decode_attention
+        out = fn(self.desc, *self.tensors(q, q_pos), max(self.ctx), self.packed, self.cache, self.block_table)
+        return out.float().cpu().numpy().astype(np.float64)
+
+    def prefill(self, q):
+        torch = self.torch
+        cu = torch.tensor(np.concatenate([[0], np.cumsum(self.ctx)]), dtype=torch.int32, device=self.dev)
+        q = torch.from_numpy(np.ascontiguousarray(q, np.float32)).to(self.dev).to(torch.bfloat16).contiguous()
+        out = self.L.prefill_attention(self.desc, q, cu, max(self.ctx), self.packed, self.cache, self.block_table)
+        return out.float().cpu().numpy().astype(np.float64)
+
+    def keys_values(self, s):
+        """fp64 keys and values of sequence s, split by KV head."""
+        return (orc.split_heads(self.C_k[s].astype(np.float64) @ self.B_k.astype(np.float64), self.h_kv, self.d),
+                orc.split_heads(self.C_v[s].astype(np.float64) @ self.B_v.astype(np.float64), self.h_kv, self.d))
+
+    def oracle(self, q, q_pos=None):
+        outs = []
+        for s, N in enumerate(self.ctx):
+            K, V = self.keys_values(s)
+            outs.append(orc.attention_decode(q[s].astype(np.float64), N - 1 if q_pos is None else q_pos[s], K, V, np.arange(N), self.base, self.scale))
+        return np.stack(outs)
