@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kStatThreads, 2) void decode_split_kernel(DecodePar
     const int row = PACK ? h + 8 * (ln >> 5) : h;
     uint16_t* p_dst = pbuf + (PACK ? 512 * (ln >> 5) : 0) + (row + 16 * (pos >> 3)) * 8 + (pos & 7);
     const uint32_t bits = bf16_bits(sm.pv);
-    l_run = l_run * sm.al + __uint_as_float(bits << 16);
+    l_run = l_run * sm.al + sm.pv;
     *p_dst = page_ok_ ? (uint16_t)bits : (uint16_t)0;
   };
   struct PV {
