@@ -682,21 +682,21 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
 // One workgroup of sixteen waves per (sequence, KV head): the G query heads of the group share the factor block
 // B_v^g, which is read once, as matrix-core operands.  The split partials are requested first (eight fp16 columns per thread; up
 // to eight sets of threads share the splits), then the factor operands; the split weights are worked out while both travel.
-// The up-projection runs on the matrix cores with o_lat split into a bf16 head and a bf16 remainder (two products), so that it
-// keeps the accuracy of an fp32 o_lat.  Shapes: G <= 8, at most 64 splits, r_v <= 1024.  Bound by latency: launch, one round trip
+// The up-projection runs on the matrix cores with o_lat split into bf16 terms: a head and a remainder up to rank 512 (16 bits), above a
+// third one, with which they hold all 24 bits of the fp32 sum, as the scalar products of decode_merge_kernel take it.
+// Shapes: G <= 8, at most 64 splits, r_v <= 1024.  Bound by latency: launch, one round trip
 // for both operands, the product's chain.  Value ranks above 512 before, a workgroup per query head and scalar products: 14.5 us
 // for one sequence at rank 768, whole call 36.5 -> 25.2; 1 x 1337 at rank 512 (four columns per thread, all splits in one): 23.0 -> 22.1.
 constexpr int kMgMaxG = 8, kMgMaxSplits = 64, kMgMaxRank = 1024, kMgMaxRankG1 = 2048;
 // HS: workgroups that share a group's heads;  CS: workgroups that share the head's columns (each works out the weighted sums of its
-// heads for itself);  MAXR: largest value rank;  MAXG: heads of a workgroup.
-template <int HD, int HS, int CS, int MAXR, int MAXG = kMgMaxG / HS>
+// heads for itself);  MAXR: largest value rank;  MAXG: heads of a workgroup;  TERMS: bf16 terms of o_lat.
+template <int HD, int HS, int CS, int MAXR, int MAXG = kMgMaxG / HS, int TERMS = (MAXR <= 512 ? 2 : 3)>
 __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodeParams p) {
   constexpr int NCB = HD / 32 / CS, NKQ = (16 / HS) / NCB, MAXKS = (MAXR / 16 + NKQ - 1) / NKQ;
   constexpr int PITCH = MAXR + 8, COLS = 32 * NCB;
-  constexpr int BATCH = HS == 1 ? 8 : 16;  // partials a thread has in flight (16 bytes each)
+  constexpr int BATCH = HS == 2 ? 16 : (MAXR == 1024 && CS == 1 ? 4 : 8);  // partials a thread has in flight (16 bytes each)
   __shared__ float wgt[MAXG][kMgMaxSplits];
-  __shared__ __align__(16) uint16_t o_hi[MAXG][PITCH];
-  __shared__ __align__(16) uint16_t o_lo[MAXG][PITCH];
+  __shared__ __align__(16) uint16_t o_terms[TERMS][MAXG][PITCH];
   constexpr int SHARE = 512;               // threads that share the splits at most
   constexpr int SCRATCH = SHARE * 8 > NKQ * COLS * MAXG ? SHARE * 8 : NKQ * COLS * MAXG;
   __shared__ __align__(16) float scratch[SCRATCH];         // weighted sums of a thread's splits; later the parts of the product
@@ -803,25 +803,30 @@ __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodePar
         a[4 + i] += b1[i];
       }
     }
-    uint32_t hi[4], lo[4];
+    uint32_t term[TERMS][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint16_t h0_ = bf16_bits(a[2 * i]), h1_ = bf16_bits(a[2 * i + 1]);
-      hi[i] = (uint32_t)h0_ | ((uint32_t)h1_ << 16);
-      lo[i] = (uint32_t)bf16_bits(a[2 * i] - bf16_to_float(h0_)) | ((uint32_t)bf16_bits(a[2 * i + 1] - bf16_to_float(h1_)) << 16);
+      float x = a[2 * i], y = a[2 * i + 1];
+#pragma unroll
+      for (int k = 0; k < TERMS; ++k) {  // (every remainder is exact in fp32)
+        const uint16_t bx = bf16_bits(x), by = bf16_bits(y);
+        term[k][i] = (uint32_t)bx | ((uint32_t)by << 16);
+        x -= bf16_to_float(bx);
+        y -= bf16_to_float(by);
+      }
     }
     if (p.latent_out) {
-      *reinterpret_cast<u32x4*>(p.out + ((size_t)seq * p.h_q + (size_t)h0 + oh) * r_v + oj) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+      *reinterpret_cast<u32x4*>(p.out + ((size_t)seq * p.h_q + (size_t)h0 + oh) * r_v + oj) = u32x4{term[0][0], term[0][1], term[0][2], term[0][3]};
     } else {
-      *reinterpret_cast<u32x4*>(&o_hi[oh][oj]) = u32x4{hi[0], hi[1], hi[2], hi[3]};
-      *reinterpret_cast<u32x4*>(&o_lo[oh][oj]) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+#pragma unroll
+      for (int k = 0; k < TERMS; ++k) *reinterpret_cast<u32x4*>(&o_terms[k][oh][oj]) = u32x4{term[k][0], term[k][1], term[k][2], term[k][3]};
     }
   }
   if (p.latent_out) return;
   __syncthreads();
 
-  // ---- out^T[c][h] = sum_j B_v[j][c] o_lat[h][j]: A operand = factor tile (m = column), B operand = o_lat^T; head and remainder
-  // of o_lat in accumulators of their own (chains half as long)
+  // ---- out^T[c][h] = sum_j B_v[j][c] o_lat[h][j]: A operand = factor tile (m = column), B operand = o_lat^T; the head of o_lat and
+  // its remainders in accumulators of their own (shorter chains)
   f32x16 acc, acc_lo;
 #pragma unroll
   for (int j = 0; j < 16; ++j) acc[j] = acc_lo[j] = 0.f;
@@ -829,13 +834,12 @@ __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodePar
   for (int u = 0; u < MAXKS; ++u) {
     if (ks0 + u < ks1) {
       const int j0 = (ks0 + u) * 16 + 8 * hf;
-      bf16x8 fh = zero_frag(), fl = zero_frag();
-      if (l32 < G) {
-        fh = load_frag(&o_hi[l32][j0]);
-        fl = load_frag(&o_lo[l32][j0]);
-      }
-      acc = mfma32(bvf[u], fh, acc);
-      acc_lo = mfma32(bvf[u], fl, acc_lo);
+      bf16x8 f[TERMS];
+#pragma unroll
+      for (int k = 0; k < TERMS; ++k) f[k] = l32 < G ? load_frag(&o_terms[k][l32][j0]) : zero_frag();
+      acc = mfma32(bvf[u], f[0], acc);
+#pragma unroll
+      for (int k = 1; k < TERMS; ++k) acc_lo = mfma32(bvf[u], f[k], acc_lo);
     }
   }
   if (l32 < G) {
@@ -1251,16 +1255,33 @@ static bool merge_group_ok(const DecodeParams& p) {
   return p.G <= kMgMaxG && p.n_splits <= kMgMaxSplits && p.r_v <= kMgMaxRank;
 }
 
-template <int HD, int MAXR>
+template <int HD, int HS, int CS, int MAXR, int MAXG = kMgMaxG / HS>
+static int launch_merge_form(const DecodeParams& p, hipStream_t s) {
+  return launch_kernel(decode_merge_group_kernel<HD, HS, CS, MAXR, MAXG>, dim3(p.b * p.h_kv * HS * CS), dim3(1024 / HS), 0, s, p);
+}
+
+template <int HD, int CS>
+static int launch_merge_1024(const DecodeParams& p, hipStream_t s) {
+  if (p.G == 1) return launch_merge_form<HD, 1, CS, 1024, 1>(p, s);
+  if (p.G <= 4) return launch_merge_form<HD, 1, CS, 1024, 4>(p, s);
+  return launch_merge_form<HD, 1, CS, 1024, 8>(p, s);
+}
+
+// Workgroups per group of heads, as many as add CUs (256): us per call, one / more.
+template <int HD>
 static int launch_merge_group(const DecodeParams& p, hipStream_t s) {
-  const bool halves = p.G % 2 == 0 && p.b * p.h_kv <= 256;  // two workgroups per group while that still adds CUs
-  // Four (two) workgroups per half, each with 32 columns, up to 32 groups: 256 workgroups.  Beyond, fetching the partials once
-  // per column block costs more than it saves (us per call, one / all columns per workgroup: 1 x 1337 22.1 / 23.0, 4 x 2000 at rank 544
-  // 28.5 / 30.4, 8 x 2000 at rank 384 36.1 / 33.7, 16 x 4096 105 / 97).
-  const bool columns = halves && p.latent_out == 0 && p.b * p.h_kv <= 32;
-  if (columns) return launch_kernel(decode_merge_group_kernel<HD, 2, HD / 32, MAXR>, dim3(p.b * p.h_kv * 2 * (HD / 32)), dim3(512), 0, s, p);
-  if (halves) return launch_kernel(decode_merge_group_kernel<HD, 2, 1, MAXR>, dim3(p.b * p.h_kv * 2), dim3(512), 0, s, p);
-  return launch_kernel(decode_merge_group_kernel<HD, 1, 1, MAXR>, dim3(p.b * p.h_kv), dim3(1024), 0, s, p);
+  const int groups = p.b * p.h_kv, even = p.G % 2 == 0;
+  // Two halves of the heads x blocks of 32 columns, up to 32 groups: 1 x 1337 23.0 / 22.1, 4 x 2000 at rank 544 30.4 / 28.5, but 8 x 2000
+  // at rank 384 33.7 / 36.1, 16 x 4096 97 / 105 (the partials are fetched once per column block).
+  const bool columns = even && p.latent_out == 0 && groups <= 32;
+  if (p.r_v <= 512) {
+    if (columns) return launch_merge_form<HD, 2, HD / 32, 512>(p, s);
+    return even && groups <= 256 ? launch_merge_form<HD, 2, 1, 512>(p, s) : launch_merge_form<HD, 1, 1, 512>(p, s);
+  }
+  if (columns) return launch_merge_form<HD, 2, HD / 32, 1024>(p, s);
+  // Value ranks above 512, halves of the columns up to 128 groups: 8B shape rank 768, 64 groups 44.0 / 42.3, 128 68.0 / 66.6, 256 70.2 /
+  // 72.9; 40 KV heads rank 640, 40 groups 39.9 / 38.0, 160 87.0 / 89.2.
+  return groups <= 128 && p.latent_out == 0 ? launch_merge_1024<HD, 2>(p, s) : launch_merge_1024<HD, 1>(p, s);
 }
 
 // The merge launch that follows every split kernel.
@@ -1270,13 +1291,12 @@ static int launch_merge(const DecodeParams& p, hipStream_t s) {
   // 37 / 8), 4 x 700 rank 1600 122 / 108, 6 x 300 102 / 91, 8 x 500 rank 1280 109.6 / 113, 16 x 300 144 / 165.
   if (p.G == 1 && p.head_dim == 128 && p.latent_out == 0 && p.r_v > kMgMaxRank && p.r_v <= kMgMaxRankG1 && p.n_splits <= kMgMaxSplits &&
       p.b * p.h_q <= 256)
-    return launch_kernel(decode_merge_group_kernel<128, 1, 4, kMgMaxRankG1, 1>, dim3(p.b * p.h_q * 4), dim3(1024), 0, s, p);
+    return launch_merge_form<128, 1, 4, kMgMaxRankG1, 1>(p, s);
   if (!merge_group_ok(p)) {
     if (p.head_dim == 128) return launch_kernel(decode_merge_kernel<128>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
     return launch_kernel(decode_merge_kernel<64>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
   }
-  if (p.r_v <= 512) return p.head_dim == 128 ? launch_merge_group<128, 512>(p, s) : launch_merge_group<64, 512>(p, s);
-  return p.head_dim == 128 ? launch_merge_group<128, 1024>(p, s) : launch_merge_group<64, 1024>(p, s);
+  return p.head_dim == 128 ? launch_merge_group<128>(p, s) : launch_merge_group<64>(p, s);
 }
 
 DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
