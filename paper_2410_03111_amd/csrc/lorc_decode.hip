@@ -1286,13 +1286,16 @@ static int launch_merge_group(const DecodeParams& p, hipStream_t s) {
 
 // The merge launch that follows every split kernel.
 static int launch_merge(const DecodeParams& p, hipStream_t s) {
-  // Groups of one head: every head reads a factor block of its own for every sequence, so that beyond a few sequences the
-  // kernel below is as fast or faster.  13B shape, us per layer-step, generic merge / this: 1 x 1000 rank 2048 92 / 65 (merge alone
-  // 37 / 8), 4 x 700 rank 1600 122 / 108, 6 x 300 102 / 91, 8 x 500 rank 1280 109.6 / 113, 16 x 300 144 / 165.
-  if (p.G == 1 && p.head_dim == 128 && p.latent_out == 0 && p.r_v > kMgMaxRank && p.r_v <= kMgMaxRankG1 && p.n_splits <= kMgMaxSplits &&
+  // Groups of one head: every head reads a factor block of its own for every sequence, so that beyond a row or two per CU the kernel
+  // below, four rows to a CU, is as fast or faster.  40 heads, us per layer-step, generic merge / this: rank 2048 1 x 700 84 / 54 (merge
+  // alone 37 / 8), 4 x 700 134 / 120, 6 x 300 108 / 98, 8 x 500 143 / 146, 16 x 300 188 / 212; rank 704 8 x 2000 149.4 / 149.3, 16 x 1000
+  // 151 / 157, 64 x 500 278 / 304; rank 1024 4 x 1000 87.6 / 79.6, 8 x 2000 194 / 192, 16 x 1000 196 / 200, 64 x 500 368 / 392; 32 heads
+  // rank 800 16 x 1000 150.9 / 149.5, 64 x 500 288 / 302.
+  const bool one_head = p.G == 1 && p.r_v > 512;
+  if (one_head && p.r_v > kMgMaxRank && p.head_dim == 128 && p.latent_out == 0 && p.r_v <= kMgMaxRankG1 && p.n_splits <= kMgMaxSplits &&
       p.b * p.h_q <= 256)
     return launch_merge_form<128, 1, 4, kMgMaxRankG1, 1>(p, s);
-  if (!merge_group_ok(p)) {
+  if (!merge_group_ok(p) || (one_head && p.b * p.h_q > 512)) {
     if (p.head_dim == 128) return launch_kernel(decode_merge_kernel<128>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
     return launch_kernel(decode_merge_kernel<64>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
   }
