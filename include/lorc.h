@@ -148,6 +148,8 @@ int lorc_append_latent(const lorc_layer_desc* desc, const void* x, int32_t T, co
 /* The name of the kernel that lorc_append_latent would launch for T tokens on the current device (a static string, the symbol
  * a profiler shows; NULL for an invalid desc or T <= 0).  HOST call; for benchmarks, profiles and tests that must name it. */
 const char* lorc_append_plan_info(const lorc_layer_desc* desc, int32_t T);
+/* The same with the template arguments of append_kernel, whose tiles of 32 x 32 and 64 x 64 (latent rows x tokens) share that name. */
+const char* lorc_append_kernel_info(const lorc_layer_desc* desc, int32_t T);
 
 /* Decode attention (Eq. 1 over the cached latents; Section 4.3; Appendix on RoPE).  DEVICE pointers.
  *   q        [b x h_q x d] bf16, un-rotated;  q_pos [b] int32 position of the query token
@@ -169,6 +171,12 @@ size_t lorc_decode_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32
  * HOST call; touches no device memory.  For benchmarks and profiles that must name the kernel they time. */
 const char* lorc_decode_plan_info(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx, int32_t* n_splits,
                                   int32_t* tiles_per_split);
+/* The same for a workspace of workspace_bytes, and with the template arguments of the symbol, which tell apart the forms and
+ * families that share a name: decode_split_kernel<a, b, c, d, e, f> streams the key factor; <a, b> (like
+ * decode_stationary_kernel<a, b>) and <a, b, true / false> hold it in registers, for ranks up to 512 and above.  absorbed != 0:
+ * the launch that lorc_decode_attention_absorbed would make.  NULL also where the call would return LORC_EWORKSPACE. */
+const char* lorc_decode_kernel_info(const lorc_layer_desc* desc, int32_t absorbed, int32_t b, int32_t max_ctx,
+                                    size_t workspace_bytes, int32_t* n_splits, int32_t* tiles_per_split);
 int lorc_decode_attention(const lorc_layer_desc* desc, const void* q, const int32_t* q_pos,
                           const int32_t* ctx_len, int32_t b, int32_t max_ctx, const void* packed,
                           const void* cache, const int32_t* block_table, int32_t max_pages, int32_t n_pages,

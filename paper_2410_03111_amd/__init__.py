@@ -73,8 +73,10 @@ def _load():
         "lorc_cache_index_v": (ctypes.c_int64, [dsc, i32, i32]),
         "lorc_append_latent": (ctypes.c_int, [dsc, vp, i32, vp, vp, vp, vp, i32, i32, i32, vp, vp]),
         "lorc_append_plan_info": (ctypes.c_char_p, [dsc, i32]),
+        "lorc_append_kernel_info": (ctypes.c_char_p, [dsc, i32]),
         "lorc_decode_workspace_bytes": (sz, [dsc, i32, i32]),
         "lorc_decode_plan_info": (ctypes.c_char_p, [dsc, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]),
+        "lorc_decode_kernel_info": (ctypes.c_char_p, [dsc, i32, i32, i32, sz, ctypes.POINTER(i32), ctypes.POINTER(i32)]),
         "lorc_decode_attention": (ctypes.c_int, [dsc, vp, vp, vp, i32, i32, vp, vp, vp, i32, i32, vp, vp, sz, vp]),
         "lorc_decode_plain_workspace_bytes": (sz, [dsc, i32, i32]),
         "lorc_decode_attention_plain": (ctypes.c_int, [dsc, vp, vp, vp, i32, i32, vp, vp, vp, i32, i32, vp, vp, sz, vp]),
@@ -99,8 +101,8 @@ def _load():
 _lib = _load()
 EXPORTS = ("lorc_strerror", "lorc_factorize", "lorc_rank_schedule", "lorc_error_bound", "lorc_packed_bytes", "lorc_pack_factors",
            "lorc_page_bytes", "lorc_cache_index_k", "lorc_cache_index_v", "lorc_append_latent",
-           "lorc_append_plan_info",
-           "lorc_decode_workspace_bytes", "lorc_decode_plan_info", "lorc_decode_attention", "lorc_decode_attention_timed",
+           "lorc_append_plan_info", "lorc_append_kernel_info",
+           "lorc_decode_workspace_bytes", "lorc_decode_plan_info", "lorc_decode_kernel_info", "lorc_decode_attention", "lorc_decode_attention_timed",
            "lorc_decode_attention_latent", "lorc_decode_plain_workspace_bytes", "lorc_decode_attention_plain", "lorc_decode_attention_static", "lorc_decode_absorbed_workspace_bytes", "lorc_decode_attention_absorbed",
            "lorc_decode_attention_absorbed_timed",
            "lorc_prefill_workspace_bytes",
@@ -212,6 +214,24 @@ def decode_plan_info(desc: LayerDesc, b: int, max_ctx: int):
     if name is None:
         raise LorcError(EUNSUPPORTED, "lorc_decode_plan_info")
     return name.decode(), ns.value, tps.value
+
+
+def append_kernel_info(desc: LayerDesc, T: int) -> str:
+    """append_plan_info with the template arguments of append_kernel (see lorc_append_kernel_info)."""
+    name = _lib.lorc_append_kernel_info(ctypes.byref(desc), T)
+    if name is None:
+        raise LorcError(EUNSUPPORTED, "lorc_append_kernel_info")
+    return name.decode()
+
+
+def decode_kernel_info(desc: LayerDesc, b: int, max_ctx: int, workspace_bytes: int | None = None, absorbed: bool = False):
+    """(split kernel with its template arguments, context splits per sequence, tiles per split) of the decode launch with a workspace of
+    that many bytes (default: those that the size function asks for); None where no launch fits or takes the shape."""
+    if workspace_bytes is None:
+        workspace_bytes = (decode_absorbed_workspace_bytes if absorbed else decode_workspace_bytes)(desc, b, max_ctx)
+    ns, tps = ctypes.c_int32(0), ctypes.c_int32(0)
+    name = _lib.lorc_decode_kernel_info(ctypes.byref(desc), int(absorbed), b, max_ctx, workspace_bytes, ctypes.byref(ns), ctypes.byref(tps))
+    return None if name is None else (name.decode(), ns.value, tps.value)
 
 
 def decode_absorbed_workspace_bytes(desc: LayerDesc, b: int, max_ctx: int) -> int:

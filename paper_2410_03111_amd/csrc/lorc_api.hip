@@ -196,6 +196,11 @@ const char* lorc_append_plan_info(const lorc_layer_desc* desc, int32_t T) {
   return append_kernel_name(desc->d_model, desc->rank_k, desc->rank_v, T, cu_count_or_default());
 }
 
+const char* lorc_append_kernel_info(const lorc_layer_desc* desc, int32_t T) {
+  if (!desc || check_desc(*desc) != LORC_OK || T <= 0) return nullptr;
+  return append_kernel_symbol(desc->d_model, desc->rank_k, desc->rank_v, T, cu_count_or_default());
+}
+
 size_t lorc_decode_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx) {
   if (!desc || check_desc(*desc) != LORC_OK || b <= 0 || max_ctx < 0) return 0;
   return make_decode_plan(*desc, b, max_ctx, cu_count_or_default()).total_bytes;
@@ -209,6 +214,18 @@ const char* lorc_decode_plan_info(const lorc_layer_desc* desc, int32_t b, int32_
   if (n_splits) *n_splits = plan.n_splits;
   if (tiles_per_split) *tiles_per_split = plan.tiles_per_split;
   return plan.wide ? "wide_scores_kernel" : (plan.stationary == 1 && desc->rank_k > kStatSmallRank ? "decode_stationary_kernel" : "decode_split_kernel");
+}
+
+const char* lorc_decode_kernel_info(const lorc_layer_desc* desc, int32_t absorbed, int32_t b, int32_t max_ctx,
+                                    size_t workspace_bytes, int32_t* n_splits, int32_t* tiles_per_split) {
+  if (!desc || check_desc(*desc) != LORC_OK || b <= 0 || max_ctx < 0) return nullptr;
+  const int cus = cu_count_or_default();
+  const DecodePlan plan = absorbed ? make_absorbed_plan_within(*desc, b, max_ctx, cus, workspace_bytes)
+                                   : make_decode_plan_within(*desc, b, max_ctx, cus, workspace_bytes);
+  if (plan.total_bytes == 0 || plan.total_bytes > workspace_bytes) return nullptr;
+  if (n_splits) *n_splits = plan.n_splits;
+  if (tiles_per_split) *tiles_per_split = plan.tiles_per_split;
+  return decode_kernel_symbol(*desc, plan, absorbed != 0);
 }
 
 size_t lorc_decode_plain_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx) {

@@ -853,6 +853,11 @@ const char* append_kernel_name(int D, int rows_k, int rows_v, int T, int n_cus) 
   }
 }
 
+const char* append_kernel_symbol(int D, int rows_k, int rows_v, int T, int n_cus) {
+  if (append_form(D, rows_k, rows_v, T, n_cus) != AppendForm::kTile64) return append_kernel_name(D, rows_k, rows_v, T, n_cus);
+  return append_small_tiles(rows_k + rows_v, T, n_cus) ? "append_kernel<32>" : "append_kernel<64>";
+}
+
 template <bool R16>
 static int launch_skinny(const AppendParams& p, int rows, hipStream_t s) {
   const dim3 grid((p.r_k + p.r_v + rows - 1) / rows), block(64 * kSkWaves);

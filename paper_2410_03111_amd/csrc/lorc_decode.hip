@@ -10,6 +10,8 @@
 //   merge    : combine the splits' (m, l, o_lat) and apply the value up-projection o = o_lat B_v
 #include <type_traits>
 
+#include <stdio.h>
+
 #include "lorc_device.h"
 #include "lorc_kernels.h"
 #include "lorc_rebuild.h"
@@ -1218,8 +1220,22 @@ DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx,
 }
 
 template <int HD, int NPB, int QB, int NBW, int JR, int OCC>
-static int launch_split(const DecodeParams& p, hipStream_t s, bool attr_only) {
+static const char* split_symbol() {
+  struct Text {
+    char s[64];
+    Text() { snprintf(s, sizeof(s), "decode_split_kernel<%d, %d, %d, %d, %d, %d>", HD, NPB, QB, NBW, JR, OCC); }
+  };
+  static const Text text;
+  return text.s;
+}
+
+template <int HD, int NPB, int QB, int NBW, int JR, int OCC>
+static int launch_split(const DecodeParams& p, hipStream_t s, bool attr_only, const char** symbol) {
   auto kern = decode_split_kernel<HD, NPB, QB, NBW, JR, OCC>;
+  if (symbol) {
+    *symbol = split_symbol<HD, NPB, QB, NBW, JR, OCC>();
+    return LORC_OK;
+  }
   if (attr_only)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess
                ? LORC_OK : LORC_EHIP;
@@ -1229,26 +1245,26 @@ static int launch_split(const DecodeParams& p, hipStream_t s, bool attr_only) {
 }
 
 // Picks the instantiation for a shape and launches it; with attr_all it walks every instantiation instead and
-// sets its LDS attribute (nothing is launched).
+// sets its LDS attribute, with symbol it only names it (nothing is launched).
 template <int HD, int NPB>
-static int dispatch_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s, bool attr_all = false) {
+static int dispatch_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s, bool attr_all = false, const char** symbol = nullptr) {
   const int qb = (p.h_q + 31) / 32;
   const int nbw = (p.r_v / 32 + 3) / 4;  // V latent blocks per wave
   int rc = LORC_OK;
   if (attr_all || (NPB == 2 && plan.occupancy == 2 && p.G <= 8 && qb == 1 && nbw <= 4)) {
-    rc = launch_split<HD, 2, 1, 4, 4, 2>(p, s, attr_all);
+    rc = launch_split<HD, 2, 1, 4, 4, 2>(p, s, attr_all, symbol);
     if (!attr_all || rc) return rc;
   }
   if (attr_all || p.G <= 8) {
-    if (attr_all || (qb == 1 && nbw <= 4)) { rc = launch_split<HD, NPB, 1, 4, 4, 1>(p, s, attr_all); if (!attr_all || rc) return rc; }
-    if (attr_all || qb == 1) { rc = launch_split<HD, NPB, 1, 8, 4, 1>(p, s, attr_all); if (!attr_all || rc) return rc; }
-    if (attr_all || nbw <= 4) { rc = launch_split<HD, NPB, 2, 4, 4, 1>(p, s, attr_all); if (!attr_all || rc) return rc; }
-    rc = launch_split<HD, NPB, 2, 8, 4, 1>(p, s, attr_all);
+    if (attr_all || (qb == 1 && nbw <= 4)) { rc = launch_split<HD, NPB, 1, 4, 4, 1>(p, s, attr_all, symbol); if (!attr_all || rc) return rc; }
+    if (attr_all || qb == 1) { rc = launch_split<HD, NPB, 1, 8, 4, 1>(p, s, attr_all, symbol); if (!attr_all || rc) return rc; }
+    if (attr_all || nbw <= 4) { rc = launch_split<HD, NPB, 2, 4, 4, 1>(p, s, attr_all, symbol); if (!attr_all || rc) return rc; }
+    rc = launch_split<HD, NPB, 2, 8, 4, 1>(p, s, attr_all, symbol);
     if (!attr_all || rc) return rc;
   }
   // large query groups (G > 8): one generic instantiation per query-block count
-  if (attr_all || qb == 1) { rc = launch_split<HD, NPB, 1, 8, 16, 1>(p, s, attr_all); if (!attr_all || rc) return rc; }
-  return launch_split<HD, NPB, 2, 8, 16, 1>(p, s, attr_all);
+  if (attr_all || qb == 1) { rc = launch_split<HD, NPB, 1, 8, 16, 1>(p, s, attr_all, symbol); if (!attr_all || rc) return rc; }
+  return launch_split<HD, NPB, 2, 8, 16, 1>(p, s, attr_all, symbol);
 }
 
 static bool merge_group_ok(const DecodeParams& p) {
@@ -1325,6 +1341,21 @@ DecodePlan make_absorbed_plan_within(const lorc_layer_desc& d, int b, int max_ct
   DecodePlan four = make_wide_plan(d, b, max_ctx, n_cus, false, true);
   four.wide = pl.wide;
   return four.total_bytes <= bytes ? four : pl;
+}
+
+const char* decode_kernel_symbol(const lorc_layer_desc& d, const DecodePlan& plan, bool absorbed) {
+  if (plan.wide == 3) return d.n_q_heads <= 32 ? "absorbed_scores_kernel<1>" : "absorbed_scores_kernel<2>";
+  if (absorbed) return "decode_absorbed_kernel<4>";
+  if (plan.wide) return "wide_scores_kernel";
+  if (plan.stationary) return plan.stationary == 2 ? stationary768_kernel_symbol(d) : stationary_kernel_symbol(d);
+  DecodeParams p{};
+  p.h_q = d.n_q_heads;
+  p.G = d.n_q_heads / d.n_kv_heads;
+  p.r_v = d.rank_v;
+  const char* symbol = nullptr;
+  if (d.head_dim == 128) plan.tile == 128 ? dispatch_split<128, 4>(p, plan, nullptr, false, &symbol) : dispatch_split<128, 2>(p, plan, nullptr, false, &symbol);
+  else plan.tile == 128 ? dispatch_split<64, 4>(p, plan, nullptr, false, &symbol) : dispatch_split<64, 2>(p, plan, nullptr, false, &symbol);
+  return symbol;
 }
 
 int set_kernel_attributes_decode() {

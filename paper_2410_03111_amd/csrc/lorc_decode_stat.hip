@@ -754,6 +754,17 @@ StatKernel stat_kernel(int nks_pad) {
 }
 }  // namespace
 
+const char* stationary_kernel_symbol(const lorc_layer_desc& d) {
+  const bool one = 2 * (d.n_q_heads / d.n_kv_heads) <= 8;
+  switch (stat_nks(d.rank_k)) {
+    case 16: return one ? "decode_split_kernel<16, 1>" : "decode_split_kernel<16, 2>";
+    case 20: return one ? "decode_split_kernel<20, 1>" : "decode_split_kernel<20, 2>";
+    case 24: return one ? "decode_split_kernel<24, 1>" : "decode_split_kernel<24, 2>";
+    case 28: return one ? "decode_stationary_kernel<28, 1>" : "decode_stationary_kernel<28, 2>";
+    default: return one ? "decode_stationary_kernel<32, 1>" : "decode_stationary_kernel<32, 2>";
+  }
+}
+
 int set_kernel_attributes_decode_stationary() {
   for (int nks_pad = 16; nks_pad <= kStatMaxNks; nks_pad += 4)
     for (StatKernel k : {stat_kernel<1>(nks_pad), stat_kernel<2>(nks_pad)})

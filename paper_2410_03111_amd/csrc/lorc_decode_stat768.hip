@@ -510,13 +510,14 @@ using Stat768Kernel = void (*)(DecodeParams);
 struct Stat768Form {
   Stat768Kernel kernel;
   size_t lds;
+  const char* symbol;
 };
 Stat768Form stat768_form(int rank, bool pack) {
-  if (!pack) return rank <= 576 ? Stat768Form{decode_split_kernel<18, 0, false>, stat768_fixed_lds<18, 0, false>()}
-                                : Stat768Form{decode_split_kernel<21, 3, false>, stat768_fixed_lds<21, 3, false>()};
-  if (rank <= 576) return {decode_split_kernel<18, 0, true>, stat768_fixed_lds<18, 0, true>()};
-  if (rank <= 672) return {decode_split_kernel<21, 1, true>, stat768_fixed_lds<21, 1, true>()};
-  return {decode_split_kernel<24, 3, true>, stat768_fixed_lds<24, 3, true>()};
+  if (!pack) return rank <= 576 ? Stat768Form{decode_split_kernel<18, 0, false>, stat768_fixed_lds<18, 0, false>(), "decode_split_kernel<18, 0, false>"}
+                                : Stat768Form{decode_split_kernel<21, 3, false>, stat768_fixed_lds<21, 3, false>(), "decode_split_kernel<21, 3, false>"};
+  if (rank <= 576) return {decode_split_kernel<18, 0, true>, stat768_fixed_lds<18, 0, true>(), "decode_split_kernel<18, 0, true>"};
+  if (rank <= 672) return {decode_split_kernel<21, 1, true>, stat768_fixed_lds<21, 1, true>(), "decode_split_kernel<21, 1, true>"};
+  return {decode_split_kernel<24, 3, true>, stat768_fixed_lds<24, 3, true>(), "decode_split_kernel<24, 3, true>"};
 }
 }  // namespace
 
@@ -526,6 +527,10 @@ Stat768Form stat768_form(int rank, bool pack) {
 bool stationary768_shape_ok(const lorc_layer_desc& d) {
   const int G = d.n_q_heads / d.n_kv_heads, rank = d.rank_k > d.rank_v ? d.rank_k : d.rank_v;
   return d.head_dim == 128 && d.n_kv_heads % 2 == 0 && G <= 8 && rank > 512 && rank <= (G <= 4 && d.n_q_heads <= 32 ? 768 : 672) && d.rank_k > 128;
+}
+
+const char* stationary768_kernel_symbol(const lorc_layer_desc& d) {
+  return stat768_form(d.rank_k > d.rank_v ? d.rank_k : d.rank_v, 2 * (d.n_q_heads / d.n_kv_heads) <= 8).symbol;
 }
 
 int set_kernel_attributes_decode_stationary768() {

@@ -111,6 +111,11 @@ DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_
 // sequences take fewer splits): the best one that does.  If there is none, the plan above, which the workspace check refuses.
 DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes);
 
+// Symbol of the split kernel that a plan launches, with its template arguments (a static string).
+const char* decode_kernel_symbol(const lorc_layer_desc& d, const DecodePlan& plan, bool absorbed);
+const char* stationary_kernel_symbol(const lorc_layer_desc& d);
+const char* stationary768_kernel_symbol(const lorc_layer_desc& d);
+
 int launch_pack(const lorc_layer_desc& d, const void* A_k, const void* A_v, const void* B_k, const void* B_v,
                 void* packed, hipStream_t s);
 // The kernel of an append of T tokens: all weights in one pass, or a tiled product of 64 x 64, 128 x 128, 256 x 128 or 256 x 256
@@ -118,6 +123,7 @@ int launch_pack(const lorc_layer_desc& d, const void* A_k, const void* A_v, cons
 enum class AppendForm { kSkinny, kTile64, kTile128, kTile256x128, kTile256 };
 AppendForm append_form(int D, int rows_k, int rows_v, int T, int n_cus);
 const char* append_kernel_name(int D, int rows_k, int rows_v, int T, int n_cus);
+const char* append_kernel_symbol(int D, int rows_k, int rows_v, int T, int n_cus);  // ... with the template arguments of append_kernel
 int launch_append(const AppendParams& p, int n_cus, hipStream_t s);
 int launch_decode(const DecodeParams& p, const DecodePlan& plan, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end);
 DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus);

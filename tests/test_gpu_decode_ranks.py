@@ -38,6 +38,13 @@ def test_ranks_match_oracle(r_k, r_v, h_q, h_kv, ctx):
     layer = GpuLayer(pb)
     name = layer.L.decode_plan_info(layer.desc, len(ctx), max(ctx))[0]
     assert name == ("decode_stationary_kernel" if 384 < r_k <= 512 else "decode_split_kernel")
+    heads = 2 * h_q // h_kv
+    if max(r_k, r_v) <= 512:
+        form = f"{name}<{max(16, -(-r_k // 64) * 4)}, {1 if heads <= 8 else 2}>"
+    else:
+        nk = next(k for k in (18, 21, 24) if 32 * k >= max(r_k, r_v))
+        form = f"decode_split_kernel<{nk}, {({18: 0, 21: 1, 24: 3} if heads <= 8 else {18: 0, 21: 3})[nk]}, {'true' if heads <= 8 else 'false'}>"
+    assert layer.L.decode_kernel_info(layer.desc, len(ctx), max(ctx))[0] == form
     layer.append_all()
     got, ref = layer.decode(), oracle_decode(pb)
     assert np.all(np.isfinite(got))

@@ -188,6 +188,24 @@ def test_decode_plan_info_names_the_kernel_and_covers_the_context():
         L.decode_plan_info(L.layer_desc(4096, 32, 8, 96, 512, 512, 1e4), 1, 64)
 
 
+@pytest.mark.parametrize("h_q,h_kv,head_dim,r_k,r_v,symbol", [
+    (32, 8, 128, 128, 128, "decode_split_kernel<128, 2, 1, 4, 4, 2>"), (4, 2, 64, 32, 32, "decode_split_kernel<64, 2, 1, 4, 4, 2>"),
+    (32, 8, 128, 160, 512, "decode_split_kernel<16, 1>"), (64, 8, 128, 32, 32, "decode_split_kernel<16, 2>"),
+    (32, 8, 128, 384, 384, "decode_split_kernel<24, 1>"), (32, 8, 128, 416, 416, "decode_stationary_kernel<28, 1>"),
+    (64, 8, 128, 512, 512, "decode_stationary_kernel<32, 2>"), (15, 5, 128, 512, 512, "decode_split_kernel<128, 2, 1, 4, 4, 2>"),
+    (32, 8, 128, 544, 544, "decode_split_kernel<18, 0, true>"), (32, 8, 128, 160, 672, "decode_split_kernel<21, 1, true>"),
+    (32, 8, 128, 768, 768, "decode_split_kernel<24, 3, true>"), (64, 8, 128, 672, 672, "decode_split_kernel<21, 3, false>"),
+    (64, 8, 128, 704, 704, "wide_scores_kernel"), (32, 8, 128, 800, 800, "decode_split_kernel<128, 2, 1, 8, 4, 1>"),
+    (40, 40, 128, 2048, 2048, "wide_scores_kernel")])
+def test_decode_kernel_info_tells_the_families_apart(h_q, h_kv, head_dim, r_k, r_v, symbol):
+    """Streaming kernel (six template arguments), factor in registers to rank 512 (two) and to 768 (three), three launches."""
+    desc = L.layer_desc(4096, h_q, h_kv, head_dim, r_k, r_v, 1e4)
+    name, ns, tps = L.decode_kernel_info(desc, 4, 2000)
+    assert name == symbol
+    assert (name.split("<")[0], ns, tps) == L.decode_plan_info(desc, 4, 2000)
+    assert L.decode_kernel_info(desc, 4, 2000, workspace_bytes=16) is None
+
+
 @pytest.mark.parametrize("D,r_k,r_v,T,kernel", [
     (256, 32, 32, 64, "append_skinny_kernel"), (4096, 512, 512, 65, "append_kernel"),
     (4096, 512, 512, 1024, "append_kernel"),                # one 64 x 64 tile per CU
