@@ -55,7 +55,7 @@ typedef enum {
   LORC_EINVAL = -1,       /* NULL pointer, non-positive size, inconsistent shape                        */
   LORC_EUNSUPPORTED = -2, /* head_dim / rank / page size that no kernel is built for                    */
   LORC_ENOCONV = -3,      /* the SVD iteration did not converge                                          */
-  LORC_EWORKSPACE = -4,   /* workspace_bytes smaller than lorc_*_workspace_bytes()                       */
+  LORC_EWORKSPACE = -4,   /* workspace_bytes smaller than the call can do with                           */
   LORC_EHIP = -5          /* the HIP runtime reported an error at launch                                 */
 } lorc_status;
 
@@ -160,9 +160,9 @@ const char* lorc_append_kernel_info(const lorc_layer_desc* desc, int32_t T);
  *            inside ctx_len whose id is negative or >= n_pages is not read, its positions count as zero
  *            latents (key 0, value 0)
  *   out      [b x h_q x d] bf16
- *   workspace  lorc_decode_workspace_bytes(desc, b, max_ctx) bytes, 256-byte aligned (split partials).  Key ranks up to 384
- *              and above 512 of head_dim 128 also take one sized for a larger b and max_ctx, where that is smaller: the call
- *              then uses the splits that fit.
+ *   workspace  lorc_decode_workspace_bytes(desc, b, max_ctx) bytes, 256-byte aligned (split partials), or as many as any call with
+ *              at least this b and max_ctx asks for: where those are fewer, the call uses the splits that fit.  LORC_EWORKSPACE
+ *              where not even the fewest do.
  */
 size_t lorc_decode_workspace_bytes(const lorc_layer_desc* desc, int32_t b, int32_t max_ctx);
 /* The launch that lorc_decode_attention would make for (desc, b, max_ctx) on the current device: returns the name
@@ -242,7 +242,8 @@ int lorc_decode_attention_latent(const lorc_layer_desc* desc, const void* q, con
  *   q_lat       [b x h_q x r_k] bf16, q_lat[s][h] = B_k^{g(h)} q[s][h] (the caller folds B_k into its query
  *               projection); the softmax scale of desc is applied here, desc.rope_base is ignored
  *   ctx_len, max_ctx, packed, cache, block_table, max_pages, n_pages, out: as lorc_decode_attention
- *   workspace   lorc_decode_absorbed_workspace_bytes(desc, b, max_ctx) bytes, 256-byte aligned
+ *   workspace   lorc_decode_absorbed_workspace_bytes(desc, b, max_ctx) bytes, 256-byte aligned, or as many as a larger call
+ *               asks for, as for lorc_decode_attention
  * h_q <= 32 and ranks <= 512 run as one streaming kernel + merge; h_q <= 64 and ranks up to 8192 (keys) / 2048 (values)
  * as three launches (scores, softmax weights x value latents in column chunks, merge), the workspace then also holding
  * the fp32 scores; anything else LORC_EUNSUPPORTED (workspace size 0).  The _timed variant records the two HIP events

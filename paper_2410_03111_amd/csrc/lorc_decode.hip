@@ -1140,13 +1140,14 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Context splits: about one tile-walk per workgroup slot of the device, never more than kMaxSplits per sequence.
 // A context of zero positions still gets one split (it writes empty partials, which the merge turns into zeros).
-static void plan_splits(DecodePlan& pl, int b, int max_ctx, int slots) {
+static void plan_splits(DecodePlan& pl, int b, int max_ctx, int slots, int max_splits) {
   int n_tiles = (max_ctx + pl.tile - 1) / pl.tile;
   if (n_tiles < 1) n_tiles = 1;
   long tps = (long)b * n_tiles / slots;
   if (tps < 1) tps = 1;
   if (tps > n_tiles) tps = n_tiles;
-  if ((n_tiles + tps - 1) / tps > kMaxSplits) tps = (n_tiles + kMaxSplits - 1) / kMaxSplits;
+  const int most = max_splits < kMaxSplits ? max_splits : kMaxSplits;
+  if ((n_tiles + tps - 1) / tps > most) tps = (n_tiles + most - 1) / most;
   pl.tiles_per_split = (int)tps;
   pl.n_splits = (int)((n_tiles + tps - 1) / tps);
 }
@@ -1161,15 +1162,15 @@ static void plan_workspace(DecodePlan& pl, const lorc_layer_desc& d, int b) {
 }
 
 // The plan of every shape that the stationary kernel does not take (and of those that it does, had it not been there).
-static DecodePlan make_streaming_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
+static DecodePlan make_streaming_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits) {
   const int qb_ = (d.n_q_heads + 31) / 32;
   // More than 32 query heads: the streaming kernel needs two score blocks per wave and spills; scores + values + merge
   // as three launches is 1.1x (rank 256) to 1.6x (rank 1024) faster at 64 heads, b 32, context 8192.
-  if (qb_ > 1 && wide_shape_ok(d)) return make_wide_plan(d, b, max_ctx, n_cus, false);
+  if (qb_ > 1 && wide_shape_ok(d)) return make_wide_plan(d, b, max_ctx, n_cus, false, max_splits);
   if (d.rank_k > kStreamMaxRank || d.rank_v > kStreamMaxRank ||
       decode_lds_bytes(64, qb_, d.n_q_heads / d.n_kv_heads, d.rank_k, d.head_dim / 2) > 160 * 1024) {
     // no single-pass kernel holds this shape: the three-launch path, or nothing (total_bytes = 0: unsupported)
-    if (wide_shape_ok(d)) return make_wide_plan(d, b, max_ctx, n_cus, false);
+    if (wide_shape_ok(d)) return make_wide_plan(d, b, max_ctx, n_cus, false, max_splits);
     return DecodePlan{};
   }
   DecodePlan pl{};
@@ -1186,36 +1187,43 @@ static DecodePlan make_streaming_plan(const lorc_layer_desc& d, int b, int max_c
   const bool fits128 = decode_lds_bytes(128, qb, G, d.rank_k, d.head_dim / 2) <= 160 * 1024;
   pl.tile = (d.rank_k <= 512 && !two_wg && fits128) ? 128 : 64;
   pl.occupancy = two_wg ? 2 : 1;
-  plan_splits(pl, b, max_ctx, (n_cus > 0 ? n_cus : 256) * pl.occupancy);
+  plan_splits(pl, b, max_ctx, (n_cus > 0 ? n_cus : 256) * pl.occupancy, max_splits);
   plan_workspace(pl, d, b);
   return pl;
 }
 
-DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
-  if (stationary_shape_ok(d)) return make_stationary_plan(d, b, max_ctx, n_cus);
+DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits) {
+  if (stationary_shape_ok(d)) return make_stationary_plan(d, b, max_ctx, n_cus, max_splits);
   if (stationary768_shape_ok(d)) {
-    DecodePlan pl = make_stationary_plan(d, b, max_ctx, n_cus);
+    DecodePlan pl = make_stationary_plan(d, b, max_ctx, n_cus, max_splits);
     pl.stationary = 2;
     return pl;
   }
-  return make_streaming_plan(d, b, max_ctx, n_cus);
+  return make_streaming_plan(d, b, max_ctx, n_cus, max_splits);
+}
+
+// A plan of at most as many splits as a workspace of `bytes` holds, or, if there is none, the one without that limit.
+template <typename Make>
+static DecodePlan plan_within(const lorc_layer_desc& d, int b, size_t bytes, Make make) {
+  const DecodePlan pl = make(kAnySplits);
+  if (pl.total_bytes <= bytes) return pl;
+  const size_t per_split = (size_t)b * d.n_q_heads * (8 + 2 * (size_t)d.rank_v);
+  const size_t scores = pl.wide ? pl.total_bytes - pl.off_scores : 0;
+  size_t most = bytes > scores ? (bytes - scores) / per_split : 0;
+  if (most >= (size_t)pl.n_splits) most = pl.n_splits - 1;
+  for (; most >= 1; --most) {  // (a few steps: what the alignment of the parts takes)
+    const DecodePlan fewer = make((int)most);
+    if (fewer.total_bytes <= bytes) return fewer;
+    if (fewer.n_splits > (int)most) break;  // the fewest that the kernel can walk
+  }
+  return pl;
 }
 
 DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes) {
-  const DecodePlan pl = make_decode_plan(d, b, max_ctx, n_cus);
-  if (pl.total_bytes <= bytes) return pl;
-  if (pl.wide) {
-    const DecodePlan four = make_wide_plan(d, b, max_ctx, n_cus, false, true);
-    return four.total_bytes <= bytes ? four : pl;
-  }
-  // decode_stationary_kernel proper takes a workspace of the whole size or none, as the size function's contract says
-  if (!pl.stationary || (pl.stationary == 1 && d.rank_k > kStatSmallRank)) return pl;
-  const size_t per_split = (size_t)b * d.n_q_heads * (8 + 2 * (size_t)d.rank_v), align = 512;
-  const size_t splits = bytes > align ? (bytes - align) / per_split : 0;
-  DecodePlan fewer = make_stationary_plan(d, b, max_ctx, n_cus, splits < 64 ? (int)splits : 64);
-  fewer.stationary = pl.stationary;
-  if (fewer.total_bytes <= bytes) return fewer;
-  const DecodePlan streaming = make_streaming_plan(d, b, max_ctx, n_cus);  // (a split may walk more than 512 pages)
+  const DecodePlan pl = plan_within(d, b, bytes, [&](int most) { return make_decode_plan(d, b, max_ctx, n_cus, most); });
+  if (pl.total_bytes <= bytes || !pl.stationary) return pl;
+  // (a split of the streaming kernel may walk more than the 512 pages of the stationary ones)
+  const DecodePlan streaming = plan_within(d, b, bytes, [&](int most) { return make_streaming_plan(d, b, max_ctx, n_cus, most); });
   return streaming.total_bytes != 0 && streaming.total_bytes <= bytes ? streaming : pl;
 }
 
@@ -1318,11 +1326,11 @@ static int launch_merge(const DecodeParams& p, hipStream_t s) {
   return p.head_dim == 128 ? launch_merge_group<128>(p, s) : launch_merge_group<64>(p, s);
 }
 
-DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus) {
+DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits) {
   if (d.n_q_heads > 32 || d.rank_k > kAbsMaxRankK || d.rank_v > 512) {
     // beyond the single-pass kernel (one register ring per wave): scores, values in column chunks, merge
     if (!wide_absorbed_shape_ok(d)) return DecodePlan{};
-    DecodePlan pl = make_wide_plan(d, b, max_ctx, n_cus, false);
+    DecodePlan pl = make_wide_plan(d, b, max_ctx, n_cus, false, max_splits);
     pl.wide = 3;
     return pl;
   }
@@ -1330,17 +1338,13 @@ DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int 
   pl.stationary = 0;
   pl.tile = kPage;
   pl.occupancy = 2;
-  plan_splits(pl, b, max_ctx, 2 * (n_cus > 0 ? n_cus : 256));  // two workgroups per CU
+  plan_splits(pl, b, max_ctx, 2 * (n_cus > 0 ? n_cus : 256), max_splits);  // two workgroups per CU
   plan_workspace(pl, d, b);
   return pl;
 }
 
 DecodePlan make_absorbed_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes) {
-  const DecodePlan pl = make_absorbed_plan(d, b, max_ctx, n_cus);
-  if (!pl.wide || pl.total_bytes <= bytes) return pl;
-  DecodePlan four = make_wide_plan(d, b, max_ctx, n_cus, false, true);
-  four.wide = pl.wide;
-  return four.total_bytes <= bytes ? four : pl;
+  return plan_within(d, b, bytes, [&](int most) { return make_absorbed_plan(d, b, max_ctx, n_cus, most); });
 }
 
 const char* decode_kernel_symbol(const lorc_layer_desc& d, const DecodePlan& plan, bool absorbed) {

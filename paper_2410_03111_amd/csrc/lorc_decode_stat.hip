@@ -717,6 +717,7 @@ DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, in
   int min_splits = (n_tiles + kStatMaxTiles - 1) / kStatMaxTiles;
   int best = min_splits;
   double best_cost = 0;
+  if (max_splits > 64) max_splits = 64;  // the group merge's limit
   for (int ns = min_splits; ns <= n_tiles && (ns == min_splits || ns <= max_splits); ++ns) {
     const int tps = (n_tiles + ns - 1) / ns;
     const int ns_eff = (n_tiles + tps - 1) / tps;

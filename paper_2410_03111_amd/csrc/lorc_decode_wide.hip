@@ -781,9 +781,9 @@ bool plain_shape_ok(const lorc_layer_desc& d) {
 // 10 KV heads 100 us (eight in one pass: 68 us for 268 MB of pages, against 134 and 336 MB).
 static bool plain_one_pass(int h_kv) { return h_kv % kPlainHeads == 0; }
 
-// Splits for the value kernel: enough workgroups for about two per CU, each walking at least four tiles; for the one-pass
-// kernel of uncompressed layers see below.
-DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain, bool four_tiles) {
+// Splits for the value kernel: enough workgroups for about two per CU, each walking at least four tiles (uncompressed layers) or, while
+// every split has a compute unit, one (the others); for the one-pass kernel of uncompressed layers see below.
+DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain, int max_splits) {
   DecodePlan pl{};
   pl.tile = kWideT;
   pl.occupancy = 1;
@@ -817,14 +817,15 @@ DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cu
     // four tiles per split at least, fewer while every split still has a compute unit (and the merge at most 64 splits): values of
     // one sequence of 1000 positions at rank 2048 24 -> 18 us, of 2 x 1000 (64 heads, rank 768) 27 -> 22
     long tps_min = 4;
-    if (!plain && !four_tiles) {
+    if (!plain) {
       tps_min = ((long)b * pl.v_chunks * n_tiles + cus - 1) / cus;
       if (tps_min > 4) tps_min = 4;
       if (tps_min < 4 && tps_min < (n_tiles + 63) / 64) tps_min = (n_tiles + 63) / 64;
     }
     if (ns > (n_tiles + tps_min - 1) / tps_min) ns = (n_tiles + tps_min - 1) / tps_min;
-    if (ns < 1) ns = 1;
     if (ns > 512) ns = 512;
+    if (ns > max_splits) ns = max_splits;
+    if (ns < 1) ns = 1;
     pl.tiles_per_split = (int)((n_tiles + ns - 1) / ns);
   }
   pl.n_splits = (n_tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;

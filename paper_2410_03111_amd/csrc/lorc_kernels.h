@@ -102,13 +102,17 @@ struct PrefillParams {
   float rope_base, q_scale;
 };
 
+constexpr int kAnySplits = 1 << 20;  // no limit of a plan's splits
+
 // Every launcher returns LORC_OK or the lorc_status of the first launch (or event record) that failed.
 PrefillPlan make_prefill_plan(const lorc_layer_desc& d, int b, int max_seqlen);
 int launch_prefill(const PrefillParams& p, int n_cus, hipStream_t s, bool plain = false);
 
-DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus);
+DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits = kAnySplits);
 // The same for a workspace of a given size.  Where the plan above does not fit (a workspace sized for a larger batch or context, whose
-// sequences take fewer splits): the best one that does.  If there is none, the plan above, which the workspace check refuses.
+// sequences take fewer splits): one of fewer splits that does.  If there is none, the plan above, which the workspace check refuses.
+// No call asks for more than b x (splits that its longest context cannot do without), and those grow with b and max_ctx: a workspace
+// sized for a larger call always fits.
 DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes);
 
 // Symbol of the split kernel that a plan launches, with its template arguments (a static string).
@@ -126,7 +130,7 @@ const char* append_kernel_name(int D, int rows_k, int rows_v, int T, int n_cus);
 const char* append_kernel_symbol(int D, int rows_k, int rows_v, int T, int n_cus);  // ... with the template arguments of append_kernel
 int launch_append(const AppendParams& p, int n_cus, hipStream_t s);
 int launch_decode(const DecodeParams& p, const DecodePlan& plan, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end);
-DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus);
+DecodePlan make_absorbed_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits = kAnySplits);
 DecodePlan make_absorbed_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes);
 int launch_decode_absorbed(const DecodeParams& p, const DecodePlan& plan, hipStream_t s, hipEvent_t ev_begin, hipEvent_t ev_end);
 int launch_stream_probe(const void* src, size_t bytes, void* sink, hipStream_t s);
@@ -140,12 +144,12 @@ int set_kernel_attributes_prefill();
 int set_kernel_attributes_decode_stationary();
 
 // Split kernel that keeps the key factor in registers (head_dim 128, an even number of KV heads, G <= 8, ranks
-// 160 to 512); its plan and launch.  The merge launch that follows is the common one.
+// to 512, from 160 on with up to 32 query heads); its plan and launch.  The merge launch that follows is the common one.
 constexpr int kStatSmallRank = 384;  // up to here it runs as decode_split_kernel, above as decode_stationary_kernel
 bool stationary_shape_ok(const lorc_layer_desc& d);
-DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits = 64);
+DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits);
 int launch_decode_stationary_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
-// The same for ranks 544 to 768 (G <= 4, up to 32 query heads); it takes the plan of the other.
+// The same for ranks 544 to 768 (G <= 4 and up to 32 query heads; 672 otherwise); it takes the plan of the other.
 bool stationary768_shape_ok(const lorc_layer_desc& d);
 int set_kernel_attributes_decode_stationary768();
 int launch_decode_stationary768_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
@@ -154,8 +158,7 @@ int launch_decode_stationary768_split(const DecodeParams& p, const DecodePlan& p
 bool wide_shape_ok(const lorc_layer_desc& d);
 bool plain_shape_ok(const lorc_layer_desc& d);
 bool wide_absorbed_shape_ok(const lorc_layer_desc& d);
-// four_tiles: splits of four tiles at least, whose partials never grow as the batch or the context shrinks
-DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain, bool four_tiles = false);
+DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, bool plain, int max_splits = kAnySplits);
 int launch_decode_wide(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
 int set_kernel_attributes_decode_wide();
 

@@ -117,3 +117,27 @@ def test_absorbed_decode_refuses_shapes_it_is_not_built_for():
     assert L.decode_absorbed_workspace_bytes(L.layer_desc(2560, 20, 20, 128, 512, 2304, 10000.0), 1, 64) == 0
     assert L.decode_absorbed_workspace_bytes(L.layer_desc(2560, 20, 20, 128, 2304, 2048, 10000.0), 1, 64) > 0
     assert L.decode_absorbed_workspace_bytes(L.layer_desc(1024, 64, 8, 128, 128, 128, 10000.0), 1, 64) > 0
+
+
+@pytest.mark.parametrize("rank,h_q,b,largest_b,n", [(256, 32, 20, 38, 1700), (768, 64, 8, 12, 700)])
+def test_absorbed_decode_with_a_workspace_sized_for_a_larger_batch(rank, h_q, b, largest_b, n):
+    """The call takes the splits that fit and leaves what follows the workspace alone; the results differ by the rounding of the outputs
+    and of the softmax weights (bf16) and of the partials (fp16), in both: under 2^-8 in the 2-norm."""
+    import torch
+    import paper_2410_03111_amd as L
+    gen_ = torch.Generator().manual_seed(5)
+    rand = lambda *s: torch.randn(*s, generator=gen_).to("cuda:0").to(torch.bfloat16)
+    desc = L.layer_desc(1024, h_q, 8, 128, rank, rank, 1e4)
+    need = L.decode_absorbed_workspace_bytes(desc, largest_b, n)
+    assert need < L.decode_absorbed_workspace_bytes(desc, b, n)
+    packed = L.pack_factors(desc, rand(1024, rank), rand(1024, rank), rand(rank, 1024), rand(rank, 1024) * 0.03)
+    pages = (n + 63) // 64
+    cache = rand(pages * L.page_bytes(desc) // 2).view(torch.uint8)
+    table = torch.arange(pages, dtype=torch.int32, device="cuda:0").expand(b, -1).contiguous()
+    ctx = torch.tensor([max(1, n - 61 * s) for s in range(b)], dtype=torch.int32, device="cuda:0")
+    args = (desc, rand(b, h_q, rank), ctx, n, packed, cache, table)
+    ref = L.decode_attention_absorbed(*args).float()
+    buf = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    got = L.decode_attention_absorbed(*args, workspace=buf[:need]).float()
+    assert bool(torch.isfinite(got).all()) and bool((buf[need:] == 0x5A).all())
+    assert float((got - ref).norm() / ref.norm()) <= 2 ** -8

@@ -88,6 +88,11 @@ def test_fixed_array_takes_a_plan_of_fewer_splits_where_the_best_one_does_not_fi
     (608, 32, 4, 6, 700),
     (608, 64, 4, 6, 700),
     (768, 64, 8, 12, 700),    # three launches
+    (1024, 64, 10, 15, 550),
+    (512, 32, 6, 11, 350),
+    (512, 64, 6, 11, 350),
+    (128, 32, 20, 38, 1700),  # streaming kernel
+    (1024, 32, 17, 32, 1000),
 ])
 def test_workspace_sized_for_the_largest_batch_serves_smaller_ones(rank, h_q, b, largest_b, n):
     """The call takes the splits that fit, leaves what follows the workspace alone, and differs from a call with a workspace of its own

@@ -169,6 +169,31 @@ def test_uncompressed_workspace_grows_with_context_and_batch(n_q_heads, n_kv_hea
         previous = sizes
 
 
+@pytest.mark.parametrize("h_q,h_kv,head_dim,rank,absorbed", [
+    (32, 8, 128, 128, False), (32, 8, 64, 256, False), (15, 5, 128, 512, False), (32, 2, 128, 256, False),    # streaming kernel
+    (32, 8, 128, 1024, False), (32, 8, 128, 256, False), (32, 8, 128, 512, False), (64, 8, 128, 512, False), (40, 40, 128, 416, False),
+    (32, 8, 128, 768, False), (64, 8, 128, 640, False), (64, 8, 128, 768, False), (40, 40, 128, 2048, False), (40, 40, 128, 640, False),
+    (32, 8, 128, 512, True), (64, 8, 128, 512, True), (40, 40, 128, 2048, True)])
+def test_a_workspace_sized_for_the_largest_call_serves_them_all(h_q, h_kv, head_dim, rank, absorbed):
+    """A plan of few splits exists for every call with no more sequences and no longer contexts, and it covers the context; a workspace
+    that holds less than one split per sequence is refused."""
+    desc = L.layer_desc(4096, h_q, h_kv, head_dim, rank, rank, 1e4)
+    size = L.decode_absorbed_workspace_bytes if absorbed else L.decode_workspace_bytes
+    rng = np.random.default_rng(7)
+    fewer = 0
+    for B, N in [(1, 700), (6, 700), (12, 700), (32, 2000), (16, 4096), (5, 6720), (9, 7488), (64, 300), (3, 40000)] + \
+            [(int(rng.integers(2, 80)), int(rng.integers(64, 9000))) for _ in range(30)]:
+        need = size(desc, B, N)
+        calls = [(b, n) for b in {1, B // 2, B - 1, B} for n in {0, 1, N // 3, N - 64, N - 1, N} if b >= 1 and n >= 0]
+        for b, n in calls + [(int(rng.integers(1, B + 1)), int(rng.integers(0, N + 1))) for _ in range(30)]:
+            info = L.decode_kernel_info(desc, b, n, need, absorbed)
+            assert info is not None, (B, N, b, n)
+            assert info[1] * info[2] * 128 >= n and (info[1] - 1) * info[2] * 64 <= n
+            fewer += size(desc, b, n) > need
+        assert L.decode_kernel_info(desc, B, N, B * h_q * (8 + 2 * rank) - 1, absorbed) is None
+    assert fewer > 0   # (some of the calls would have taken more splits)
+
+
 def test_decode_plan_info_names_the_kernel_and_covers_the_context():
     """Host-only: the reported plan names the kernel the launch will use and its splits cover every tile."""
     for desc, b, ctx in ((L.layer_desc(4096, 32, 8, 128, 512, 512, 5e5), 16, 4096),
