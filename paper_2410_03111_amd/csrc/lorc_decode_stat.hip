@@ -711,9 +711,11 @@ DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, in
   int n_tiles = (max_ctx + kStatTile - 1) / kStatTile;
   if (n_tiles < 1) n_tiles = 1;
   const int cus = n_cus > 0 ? n_cus : 256;
-  const long wgs_per_split = (long)b * (d.n_kv_heads / 2);
-  // Context splits: the count that minimises (rounds of workgroups over the device) x (tiles per workgroup + the
-  // fixed cost of a workgroup, about two tiles' worth: factor load, first tile, write-out).
+  const long pairs = d.n_kv_heads / 2, xcd_cus = (cus + 7) / 8;
+  // Context splits: the count that minimises (rounds of workgroups) x (tiles per workgroup + the fixed cost of a workgroup, about two
+  // tiles' worth: factor load, first tile, write-out).  The head pairs of a (sequence, split) sit on one XCD, so the rounds are an XCD's:
+  // with 20 pairs two of them are 40 workgroups for 32 CUs, three 60 for 64.  us per layer-step of 40 / 40 heads, rounds of the whole
+  // device / of an XCD: 4 x 4000 rank 256 113 / 71, rank 512 165 / 107, rank 544 208 / 126; 2 x 1000 rank 384 38.7 / 29.1.
   int min_splits = (n_tiles + kStatMaxTiles - 1) / kStatMaxTiles;
   int best = min_splits;
   double best_cost = 0;
@@ -721,7 +723,7 @@ DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, in
   for (int ns = min_splits; ns <= n_tiles && (ns == min_splits || ns <= max_splits); ++ns) {
     const int tps = (n_tiles + ns - 1) / ns;
     const int ns_eff = (n_tiles + tps - 1) / tps;
-    const long rounds = (wgs_per_split * ns_eff + cus - 1) / cus;
+    const long per_xcd = ((long)b * ns_eff + 7) / 8 * pairs, rounds = (per_xcd + xcd_cus - 1) / xcd_cus;
     const double cost = (double)rounds * (tps + 2.0);
     if (ns == min_splits || cost < best_cost * 0.999) {
       best = ns_eff;

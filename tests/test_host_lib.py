@@ -194,6 +194,19 @@ def test_a_workspace_sized_for_the_largest_call_serves_them_all(h_q, h_kv, head_
     assert fewer > 0   # (some of the calls would have taken more splits)
 
 
+@pytest.mark.parametrize("h_q,h_kv,rank", [(40, 40, 256), (40, 40, 512), (24, 24, 512), (48, 12, 640), (40, 10, 256), (32, 8, 512)])
+def test_stationary_splits_fill_the_xcds(h_q, h_kv, rank):
+    """The head pairs of a (sequence, split) share one of eight XCDs of 32 CUs: no other split count gives fewer rounds of an XCD's
+    workgroups x (tiles of a split + 2)."""
+    desc = L.layer_desc(4096, h_q, h_kv, 128, rank, rank, 1e4)
+    for b, n in ((1, 1000), (2, 1000), (4, 4000), (3, 2000), (12, 1000), (16, 4096), (33, 700)):
+        tiles = -(-n // 64)
+        cost = lambda tps: -(-(-(-b * -(-tiles // tps) // 8) * (h_kv // 2)) // 32) * (tps + 2)
+        _, ns, tps = L.decode_kernel_info(desc, b, n)
+        assert ns == -(-tiles // tps)
+        assert cost(tps) <= min(cost(t) for t in range(1, tiles + 1) if -(-tiles // t) <= 64) * 1.002
+
+
 def test_decode_plan_info_names_the_kernel_and_covers_the_context():
     """Host-only: the reported plan names the kernel the launch will use and its splits cover every tile."""
     for desc, b, ctx in ((L.layer_desc(4096, 32, 8, 128, 512, 512, 5e5), 16, 4096),
