@@ -818,8 +818,8 @@ DecodePlan make_wide_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cu
     // one sequence of 1000 positions at rank 2048 24 -> 18 us, of 2 x 1000 (64 heads, rank 768) 27 -> 22
     long tps_min = 4;
     if (!plain) {
-      tps_min = ((long)b * pl.v_chunks * n_tiles + cus - 1) / cus;
-      if (tps_min > 4) tps_min = 4;
+      tps_min = 1;
+      while (tps_min < 4 && (long)b * pl.v_chunks * ((n_tiles + tps_min - 1) / tps_min) > cus) ++tps_min;
       if (tps_min < 4 && tps_min < (n_tiles + 63) / 64) tps_min = (n_tiles + 63) / 64;
     }
     if (ns > (n_tiles + tps_min - 1) / tps_min) ns = (n_tiles + tps_min - 1) / tps_min;

@@ -207,6 +207,16 @@ def test_stationary_splits_fill_the_xcds(h_q, h_kv, rank):
         assert cost(tps) <= min(cost(t) for t in range(1, tiles + 1) if -(-tiles // t) <= 64) * 1.002
 
 
+@pytest.mark.parametrize("h_q,h_kv,rank", [(64, 8, 768), (64, 8, 1024), (40, 40, 1280), (40, 40, 2048)])
+def test_value_splits_of_fewer_than_four_tiles_have_a_compute_unit_each(h_q, h_kv, rank):
+    """Three launches: one workgroup per (sequence, split, 512 value columns)."""
+    desc = L.layer_desc(4096, h_q, h_kv, 128, rank, rank, 1e4)
+    for b in range(1, 70):
+        for n in (64, 300, 500, 1000, 1500, 2000, 4096):
+            _, ns, tps = L.decode_kernel_info(desc, b, n)
+            assert tps >= 4 or ns == 1 or b * ns * -(-rank // 512) <= 256
+
+
 def test_decode_plan_info_names_the_kernel_and_covers_the_context():
     """Host-only: the reported plan names the kernel the launch will use and its splits cover every tile."""
     for desc, b, ctx in ((L.layer_desc(4096, 32, 8, 128, 512, 512, 5e5), 16, 4096),
