@@ -700,10 +700,15 @@ __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodePar
   __shared__ float wgt[MAXG][kMgMaxSplits];
   __shared__ __align__(16) uint16_t o_terms[TERMS][MAXG][PITCH];
   constexpr int SHARE = 512;               // threads that share the splits at most
-  constexpr int SCRATCH = SHARE * 8 > NKQ * COLS * MAXG ? SHARE * 8 : NKQ * COLS * MAXG;
-  __shared__ __align__(16) float scratch[SCRATCH];         // weighted sums of a thread's splits; later the parts of the product
+  // Weighted sums of a thread's splits; later the parts of the product.  Three terms: their parts take three times the columns and meet
+  // where the terms were.
+  constexpr bool PACK = TERMS == 3;
+  constexpr int RC = PACK ? 3 * MAXG : MAXG, PARTS = NKQ * COLS * RC;
+  constexpr int SCRATCH = PACK || SHARE * 8 > PARTS ? SHARE * 8 : PARTS;
+  static_assert(!PACK || (PARTS * 4 <= (int)sizeof(o_terms) && 3 * MAXG <= 32), "parts of the product; columns of an operand");
+  __shared__ __align__(16) float scratch[SCRATCH];
   float (*const part)[8] = reinterpret_cast<float (*)[8]>(scratch);
-  float (*const red)[COLS][MAXG] = reinterpret_cast<float (*)[COLS][MAXG]>(scratch);
+  float (*const red)[COLS][RC] = reinterpret_cast<float (*)[COLS][RC]>(PACK ? reinterpret_cast<float*>(&o_terms[0][0][0]) : scratch);
   const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cs = blockIdx.x % CS, sg = blockIdx.x / (CS * HS), seq = sg / p.h_kv, g = sg % p.h_kv;
@@ -827,33 +832,35 @@ __global__ __launch_bounds__(1024 / HS) void decode_merge_group_kernel(DecodePar
   if (p.latent_out) return;
   __syncthreads();
 
-  // ---- out^T[c][h] = sum_j B_v[j][c] o_lat[h][j]: A operand = factor tile (m = column), B operand = o_lat^T; the head of o_lat and
-  // its remainders in accumulators of their own (shorter chains)
+  // ---- out^T[c][h] = sum_j B_v[j][c] o_lat[h][j]: A operand = factor tile (m = column), B operand = o_lat^T.  Three terms are columns of
+  // one operand (24 of 32 at most), two have a product and an accumulator each.
   f32x16 acc, acc_lo;
 #pragma unroll
   for (int j = 0; j < 16; ++j) acc[j] = acc_lo[j] = 0.f;
+  const int term = l32 < G ? 0 : (l32 < 2 * G ? 1 : 2), cols = PACK ? 3 * G : G;
+  const uint16_t* const o_src = &o_terms[PACK && l32 < cols ? term : 0][PACK && l32 < cols ? l32 - term * G : (l32 < G ? l32 : 0)][8 * hf];
 #pragma unroll
   for (int u = 0; u < MAXKS; ++u) {
     if (ks0 + u < ks1) {
-      const int j0 = (ks0 + u) * 16 + 8 * hf;
-      bf16x8 f[TERMS];
-#pragma unroll
-      for (int k = 0; k < TERMS; ++k) f[k] = l32 < G ? load_frag(&o_terms[k][l32][j0]) : zero_frag();
-      acc = mfma32(bvf[u], f[0], acc);
-#pragma unroll
-      for (int k = 1; k < TERMS; ++k) acc_lo = mfma32(bvf[u], f[k], acc_lo);
+      const int j0 = (ks0 + u) * 16;
+      acc = mfma32(bvf[u], l32 < cols ? load_frag(o_src + j0) : zero_frag(), acc);
+      if constexpr (!PACK) acc_lo = mfma32(bvf[u], l32 < G ? load_frag(o_src + MAXG * PITCH + j0) : zero_frag(), acc_lo);
     }
   }
-  if (l32 < G) {
+  if constexpr (PACK) __syncthreads();
+  if (l32 < cols) {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) red[kq][(w % NCB) * 32 + acc_row(j, hf)][l32] = acc[j] + acc_lo[j];
+    for (int j = 0; j < 16; ++j) red[kq][(w % NCB) * 32 + acc_row(j, hf)][l32] = PACK ? acc[j] : acc[j] + acc_lo[j];
   }
   __syncthreads();
   if (tid < COLS * G) {
     const int c = tid % COLS, h = tid / COLS;
     float v = 0.f;
 #pragma unroll
-    for (int i = 0; i < NKQ; ++i) v += red[i][c][h];
+    for (int i = 0; i < NKQ; ++i) {
+      if constexpr (PACK) v += red[i][c][h] + (red[i][c][G + h] + red[i][c][2 * G + h]);
+      else v += red[i][c][h];
+    }
     p.out[((size_t)seq * p.h_q + (size_t)h0 + h) * HD + cs * COLS + c] = bf16_bits(v);
   }
 }
@@ -1302,8 +1309,8 @@ static int launch_merge_group(const DecodeParams& p, hipStream_t s) {
     if (columns) return launch_merge_form<HD, 2, HD / 32, 512>(p, s);
     return even && groups <= 256 ? launch_merge_form<HD, 2, 1, 512>(p, s) : launch_merge_form<HD, 1, 1, 512>(p, s);
   }
-  if (columns) return launch_merge_form<HD, 2, HD / 32, 1024>(p, s);
-  // Value ranks above 512, halves of the columns up to 128 groups: 8B shape rank 768, 64 groups 44.0 / 42.3, 128 68.0 / 66.6, 256 70.2 /
+  if (columns && groups <= 16) return launch_merge_form<HD, 2, HD / 32, 1024>(p, s);
+  // Value ranks above 512, both to 16 groups (32 groups at rank 1024: 62.7, 60.6 below), halves of the columns up to 128 groups: 8B shape rank 768, 64 groups 44.0 / 42.3, 128 68.0 / 66.6, 256 70.2 /
   // 72.9; 40 KV heads rank 640, 40 groups 39.9 / 38.0, 160 87.0 / 89.2.
   return groups <= 128 && p.latent_out == 0 ? launch_merge_1024<HD, 2>(p, s) : launch_merge_1024<HD, 1>(p, s);
 }
@@ -1315,11 +1322,12 @@ static int launch_merge(const DecodeParams& p, hipStream_t s) {
   // alone 37 / 8), 4 x 700 134 / 120, 6 x 300 108 / 98, 8 x 500 143 / 146, 16 x 300 188 / 212; rank 704 8 x 2000 149.4 / 149.3, 16 x 1000
   // 151 / 157, 64 x 500 278 / 304; rank 1024 4 x 1000 87.6 / 79.6, 8 x 2000 194 / 192, 16 x 1000 196 / 200, 64 x 500 368 / 392; 32 heads
   // rank 800 16 x 1000 150.9 / 149.5, 64 x 500 288 / 302.
-  const bool one_head = p.G == 1 && p.r_v > 512;
-  if (one_head && p.r_v > kMgMaxRank && p.head_dim == 128 && p.latent_out == 0 && p.r_v <= kMgMaxRankG1 && p.n_splits <= kMgMaxSplits &&
+  if (p.G == 1 && p.r_v > kMgMaxRank && p.head_dim == 128 && p.latent_out == 0 && p.r_v <= kMgMaxRankG1 && p.n_splits <= kMgMaxSplits &&
       p.b * p.h_q <= 256)
     return launch_merge_form<128, 1, 4, kMgMaxRankG1, 1>(p, s);
-  if (!merge_group_ok(p) || (one_head && p.b * p.h_q > 512)) {
+  // Groups of two likewise: 64 / 32 heads, rank 544 64 x 100 104 / 114, 64 x 500 213 / 224, rank 768 128 x 100 200 / 224; 32 / 16 heads, 512
+  // groups, rank 544 40.7 / 41.0, rank 768 47.4 / 46.6.  (Three: 48 / 16 heads, 2048 groups, rank 768 135 / 132.)
+  if (!merge_group_ok(p) || (p.G <= 2 && p.r_v > 512 && p.b * p.h_kv > 512)) {
     if (p.head_dim == 128) return launch_kernel(decode_merge_kernel<128>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
     return launch_kernel(decode_merge_kernel<64>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
   }
