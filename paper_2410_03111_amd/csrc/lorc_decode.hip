@@ -1199,12 +1199,34 @@ static DecodePlan make_streaming_plan(const lorc_layer_desc& d, int b, int max_c
   return pl;
 }
 
+static DecodePlan make_any_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits) {
+  DecodePlan pl = make_stationary_plan(d, b, max_ctx, n_cus, max_splits);
+  if (!stationary_shape_ok(d)) pl.stationary = 2;
+  return pl;
+}
+
+// Groups of one or two heads leave a stationary workgroup little work per factor load, and layers of them have many head pairs: many
+// short sequences, or pairs that do not divide an XCD's CUs, are then faster elsewhere.  us per layer-step, three launches / stationary,
+// overhead (and even share where it decides) in brackets: 64 / 64 heads rank 544 16 x 1000 [4] 199 / 192, 16 x 4000 [4] 663 / 631, 32 x 1000 [8]
+// 362 / 390, 64 x 100 [16] 143 / 246; 40 / 40 heads rank 544 12 x 1000 [5] 112 / 106, 8 x 2000 [6] 134 / 134, 16 x 1000 [10] 132 / 149; 40 / 40
+// heads rank 64 (padded to 256) 12 x 1000 [5] 61 / 57, 32 x 1000 [10] 114 / 133, rank 128 32 x 1000 [10] 138 / 137.  Groups of two: 40 / 20 heads
+// rank 544 16 x 1000 [8 of 10] 89 / 85, 32 x 1000 [10 of 20] 138 / 147, 200 x 300 [17 of 39] 349 / 297; 36 / 18 heads rank 640 64 x 500 [12 of 18]
+// 155 / 173; 64 / 32 heads rank 544 64 x 500 [8 of 32] 218 / 214.  Groups of three and more gain (48 / 16 heads rank 544 128 x 100 [8] 115 / 114,
+// 200 x 300 [18] 324 / 281).  Up to 32 heads, streaming / stationary: 32 / 32 heads 200 x 300 [28] rank 160 246 / 301, rank 384 352 / 385,
+// 128 x 100 [16] rank 160 136 / 135.
+static bool stationary_loses(const lorc_layer_desc& d, int b, int max_ctx, const DecodePlan& pl, int n_cus) {
+  const int G = d.n_q_heads / d.n_kv_heads;
+  double share;
+  const double overhead = stationary_overhead(d, b, max_ctx, pl, n_cus, &share);
+  if (G == 1 && d.n_q_heads > 32) return overhead >= 6 && (pl.stationary == 2 || d.rank_k <= 96);
+  if (G == 1) return pl.stationary == 1 && d.rank_k <= 384 && overhead >= 18;
+  return G == 2 && d.n_q_heads > 32 && pl.stationary == 2 && overhead >= 9.5 && overhead >= 0.5 * share;
+}
+
 DecodePlan make_decode_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits) {
-  if (stationary_shape_ok(d)) return make_stationary_plan(d, b, max_ctx, n_cus, max_splits);
-  if (stationary768_shape_ok(d)) {
-    DecodePlan pl = make_stationary_plan(d, b, max_ctx, n_cus, max_splits);
-    pl.stationary = 2;
-    return pl;
+  if (stationary_shape_ok(d) || stationary768_shape_ok(d)) {
+    const DecodePlan pl = make_any_stationary_plan(d, b, max_ctx, n_cus, kAnySplits);
+    if (!stationary_loses(d, b, max_ctx, pl, n_cus)) return max_splits >= kAnySplits ? pl : make_any_stationary_plan(d, b, max_ctx, n_cus, max_splits);
   }
   return make_streaming_plan(d, b, max_ctx, n_cus, max_splits);
 }
@@ -1228,10 +1250,13 @@ static DecodePlan plan_within(const lorc_layer_desc& d, int b, size_t bytes, Mak
 
 DecodePlan make_decode_plan_within(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, size_t bytes) {
   const DecodePlan pl = plan_within(d, b, bytes, [&](int most) { return make_decode_plan(d, b, max_ctx, n_cus, most); });
-  if (pl.total_bytes <= bytes || !pl.stationary) return pl;
-  // (a split of the streaming kernel may walk more than the 512 pages of the stationary ones)
-  const DecodePlan streaming = plan_within(d, b, bytes, [&](int most) { return make_streaming_plan(d, b, max_ctx, n_cus, most); });
-  return streaming.total_bytes != 0 && streaming.total_bytes <= bytes ? streaming : pl;
+  if (pl.total_bytes <= bytes || !(stationary_shape_ok(d) || stationary768_shape_ok(d))) return pl;
+  // Shapes of two kernels: the other one's plan.  The stationary kernels have no scores to keep, a split of the streaming one may walk
+  // more than their 512 pages.
+  const DecodePlan other = plan_within(d, b, bytes, [&](int most) {
+    return pl.stationary ? make_streaming_plan(d, b, max_ctx, n_cus, most) : make_any_stationary_plan(d, b, max_ctx, n_cus, most);
+  });
+  return other.total_bytes != 0 && other.total_bytes <= bytes ? other : pl;
 }
 
 template <int HD, int NPB, int QB, int NBW, int JR, int OCC>

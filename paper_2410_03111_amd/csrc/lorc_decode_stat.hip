@@ -703,6 +703,19 @@ bool stationary_shape_ok(const lorc_layer_desc& d) {
          (d.rank_k > 128 || d.n_q_heads > 32);
 }
 
+// Rounds of workgroups over the eight XCDs (the head pairs of a (sequence, split) sit on one) x (tiles per workgroup + the fixed cost of
+// a workgroup, about two tiles' worth: factor load, first tile, write-out).
+static double stationary_cost(const lorc_layer_desc& d, int b, int n_splits, int tiles_per_split, int n_cus) {
+  const long per_xcd = ((long)b * n_splits + 7) / 8 * (d.n_kv_heads / 2), xcd_cus = ((n_cus > 0 ? n_cus : 256) + 7) / 8;
+  return (double)((per_xcd + xcd_cus - 1) / xcd_cus) * (tiles_per_split + 2.0);
+}
+
+double stationary_overhead(const lorc_layer_desc& d, int b, int max_ctx, const DecodePlan& pl, int n_cus, double* share) {
+  const int n_tiles = max_ctx > 0 ? (max_ctx + kStatTile - 1) / kStatTile : 1;
+  *share = (double)b * n_tiles * (d.n_kv_heads / 2) / (n_cus > 0 ? n_cus : 256);
+  return stationary_cost(d, b, pl.n_splits, pl.tiles_per_split, n_cus) - *share;
+}
+
 DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits) {
   DecodePlan pl{};
   pl.tile = kStatTile;
@@ -710,12 +723,9 @@ DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, in
   pl.stationary = 1;
   int n_tiles = (max_ctx + kStatTile - 1) / kStatTile;
   if (n_tiles < 1) n_tiles = 1;
-  const int cus = n_cus > 0 ? n_cus : 256;
-  const long pairs = d.n_kv_heads / 2, xcd_cus = (cus + 7) / 8;
-  // Context splits: the count that minimises (rounds of workgroups) x (tiles per workgroup + the fixed cost of a workgroup, about two
-  // tiles' worth: factor load, first tile, write-out).  The head pairs of a (sequence, split) sit on one XCD, so the rounds are an XCD's:
-  // with 20 pairs two of them are 40 workgroups for 32 CUs, three 60 for 64.  us per layer-step of 40 / 40 heads, rounds of the whole
-  // device / of an XCD: 4 x 4000 rank 256 113 / 71, rank 512 165 / 107, rank 544 208 / 126; 2 x 1000 rank 384 38.7 / 29.1.
+  // Context splits: the count of least cost.  Rounds are an XCD's: with 20 pairs two (sequences, splits) are 40 workgroups for 32 CUs,
+  // three 60 for 64.  us per layer-step of 40 / 40 heads, rounds of the whole device / of an XCD: 4 x 4000 rank 256 113 / 71, rank 512
+  // 165 / 107, rank 544 208 / 126; 2 x 1000 rank 384 38.7 / 29.1.
   int min_splits = (n_tiles + kStatMaxTiles - 1) / kStatMaxTiles;
   int best = min_splits;
   double best_cost = 0;
@@ -723,8 +733,7 @@ DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, in
   for (int ns = min_splits; ns <= n_tiles && (ns == min_splits || ns <= max_splits); ++ns) {
     const int tps = (n_tiles + ns - 1) / ns;
     const int ns_eff = (n_tiles + tps - 1) / tps;
-    const long per_xcd = ((long)b * ns_eff + 7) / 8 * pairs, rounds = (per_xcd + xcd_cus - 1) / xcd_cus;
-    const double cost = (double)rounds * (tps + 2.0);
+    const double cost = stationary_cost(d, b, ns_eff, tps, n_cus);
     if (ns == min_splits || cost < best_cost * 0.999) {
       best = ns_eff;
       best_cost = cost;

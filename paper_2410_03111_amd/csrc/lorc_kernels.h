@@ -148,6 +148,8 @@ int set_kernel_attributes_decode_stationary();
 constexpr int kStatSmallRank = 384;  // up to here it runs as decode_split_kernel, above as decode_stationary_kernel
 bool stationary_shape_ok(const lorc_layer_desc& d);
 DecodePlan make_stationary_plan(const lorc_layer_desc& d, int b, int max_ctx, int n_cus, int max_splits);
+// What set-up and partly idle XCDs add to a plan's even share of tiles per CU, in tiles.
+double stationary_overhead(const lorc_layer_desc& d, int b, int max_ctx, const DecodePlan& pl, int n_cus, double* share);
 int launch_decode_stationary_split(const DecodeParams& p, const DecodePlan& plan, hipStream_t s);
 // The same for ranks 544 to 768 (G <= 4 and up to 32 query heads; 672 otherwise); it takes the plan of the other.
 bool stationary768_shape_ok(const lorc_layer_desc& d);

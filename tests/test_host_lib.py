@@ -173,6 +173,7 @@ def test_uncompressed_workspace_grows_with_context_and_batch(n_q_heads, n_kv_hea
     (32, 8, 128, 128, False), (32, 8, 64, 256, False), (15, 5, 128, 512, False), (32, 2, 128, 256, False),    # streaming kernel
     (32, 8, 128, 1024, False), (32, 8, 128, 256, False), (32, 8, 128, 512, False), (64, 8, 128, 512, False), (40, 40, 128, 416, False),
     (32, 8, 128, 768, False), (64, 8, 128, 640, False), (64, 8, 128, 768, False), (40, 40, 128, 2048, False), (40, 40, 128, 640, False),
+    (64, 64, 128, 64, False), (64, 64, 128, 544, False), (64, 32, 128, 672, False), (32, 32, 128, 256, False),
     (32, 8, 128, 512, True), (64, 8, 128, 512, True), (40, 40, 128, 2048, True)])
 def test_a_workspace_sized_for_the_largest_call_serves_them_all(h_q, h_kv, head_dim, rank, absorbed):
     """A plan of few splits exists for every call with no more sequences and no longer contexts, and it covers the context; a workspace
@@ -205,6 +206,23 @@ def test_stationary_splits_fill_the_xcds(h_q, h_kv, rank):
         _, ns, tps = L.decode_kernel_info(desc, b, n)
         assert ns == -(-tiles // tps)
         assert cost(tps) <= min(cost(t) for t in range(1, tiles + 1) if -(-tiles // t) <= 64) * 1.002
+
+
+@pytest.mark.parametrize("h_q,h_kv,rank,b,n,symbol", [
+    (64, 64, 544, 16, 1000, "decode_split_kernel<18, 0, true>"), (64, 64, 544, 32, 1000, "wide_scores_kernel"),
+    (64, 64, 544, 64, 100, "wide_scores_kernel"), (64, 64, 544, 16, 4000, "decode_split_kernel<18, 0, true>"),
+    (40, 40, 672, 12, 1000, "decode_split_kernel<21, 1, true>"), (40, 40, 672, 16, 1000, "wide_scores_kernel"),
+    (64, 32, 672, 32, 1000, "decode_split_kernel<21, 1, true>"), (64, 32, 672, 128, 100, "wide_scores_kernel"),
+    (40, 20, 544, 16, 1000, "decode_split_kernel<18, 0, true>"), (40, 20, 544, 32, 1000, "wide_scores_kernel"),
+    (40, 20, 544, 200, 300, "decode_split_kernel<18, 0, true>"), (40, 20, 384, 32, 1000, "decode_split_kernel<24, 1>"),
+    (40, 40, 64, 1, 1000, "decode_split_kernel<16, 1>"), (40, 40, 64, 32, 1000, "wide_scores_kernel"),
+    (40, 40, 128, 32, 1000, "decode_split_kernel<16, 1>"), (40, 40, 384, 64, 100, "decode_split_kernel<24, 1>"),
+    (48, 16, 544, 200, 300, "decode_split_kernel<18, 0, true>"), (32, 32, 256, 64, 100, "decode_split_kernel<16, 1>"),
+    (32, 32, 256, 200, 300, "decode_split_kernel<128, 2, 1, 4, 4, 2>"), (32, 32, 544, 200, 300, "decode_split_kernel<18, 0, true>"),
+    (32, 8, 256, 200, 300, "decode_split_kernel<16, 1>"), (64, 8, 544, 64, 100, "decode_split_kernel<18, 0, false>")])
+def test_decode_takes_the_kernel_measured_fastest(h_q, h_kv, rank, b, n, symbol):
+    """Sizes on either side of the lines between the stationary kernels and the ones that they replace for most shapes (256 CUs)."""
+    assert L.decode_kernel_info(L.layer_desc(4096, h_q, h_kv, 128, rank, rank, 1e4), b, n)[0] == symbol
 
 
 @pytest.mark.parametrize("h_q,h_kv,rank", [(64, 8, 768), (64, 8, 1024), (40, 40, 1280), (40, 40, 2048)])
