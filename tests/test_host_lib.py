@@ -232,7 +232,7 @@ def test_value_splits_of_fewer_than_four_tiles_have_a_compute_unit_each(h_q, h_k
     for b in range(1, 70):
         for n in (64, 300, 500, 1000, 1500, 2000, 4096):
             _, ns, tps = L.decode_kernel_info(desc, b, n)
-            assert tps >= 4 or ns == 1 or b * ns * -(-rank // 512) <= 256
+            assert ns <= -(-n // 256) or b * ns * -(-rank // 512) <= 256   # (no more than splits of four tiles, or a CU for each)
 
 
 def test_decode_plan_info_names_the_kernel_and_covers_the_context():
