@@ -178,7 +178,7 @@ __device__ __forceinline__ void stationary_split(const DecodeParams& p) {
   constexpr int H = sched.H, NG = sched.NG, D = sched.D;
   constexpr int kB0 = sched.kB0, kB1 = sched.kB1, kB2 = sched.kB2, kB3 = sched.kB3, kB4 = sched.kB4;
   // descriptor of one part of a cached page (id < 0: not cached, or no such tile: a descriptor of size zero, whose
-  // copies fetch nothing)
+  // copies fetch nothing and deliver zeros)
   auto page_rsrc = [&](int id, uint32_t part_off, uint32_t part_bytes) {
     const bool ok = id >= 0 && id < p.n_pages;
     const uint16_t* base = p.cache + (ok ? (size_t)id * p.page_elems : 0);

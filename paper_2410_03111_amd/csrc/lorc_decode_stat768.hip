@@ -101,7 +101,10 @@ __global__ __launch_bounds__(kStatThreads, 2) void decode_split_kernel(DecodePar
   }
   __syncthreads();  // page ids
 
-  // ---- latent copies (1 KiB each, lane order; a descriptor of size zero delivers zeros)
+  // ---- latent copies (1 KiB each, lane order).  A descriptor of size zero delivers zeros, on which this kernel relies for all that
+  // has to be finite before or without a copy of latents: the K tile's padding (multiplied by zero factors), the V tile of the tile
+  // before the first one and of pages that are not cached (multiplied by zero weights).  Clearing both tiles by hand costs 0.4 us per
+  // call, and at rank 768 registers: 32 x 4096 positions 233 -> 244 us.
   const uint32_t lane16 = (uint32_t)lane * 16u;
   auto tile_page = [&](int t) {  // page id of tile t of the split, -1 outside
     const bool in = t >= 0 && t < nt;
