@@ -81,7 +81,7 @@ int decode_args(const lorc_layer_desc* desc, const void* q, const int32_t* q_pos
 int decode_params(DecodeParams& p, const lorc_layer_desc* desc, const void* q, const int32_t* q_pos, bool needs_q_pos,
                   const int32_t* ctx_len, int32_t b, int32_t max_ctx, const void* packed, const void* cache,
                   const int32_t* block_table, int32_t max_pages, int32_t n_pages, void* out, void* workspace,
-                  size_t workspace_bytes, const DecodePlan& plan, int latent_out) {
+                  size_t workspace_bytes, const DecodePlan& plan, int latent_out, int n_cus) {
   if (plan.total_bytes == 0) return LORC_EUNSUPPORTED;  // no kernel path takes this shape
   if (workspace_bytes < plan.total_bytes) return LORC_EWORKSPACE;
   const int n = desc->n_kv_heads * desc->head_dim;
@@ -119,6 +119,7 @@ int decode_params(DecodeParams& p, const lorc_layer_desc* desc, const void* q, c
   p.page_elems = page_elems(desc->rank_k, desc->rank_v);
   p.rope_base = desc->rope_base;
   p.q_scale = softmax_scale_log2(*desc);
+  p.n_cus = n_cus;
   return LORC_OK;
 }
 
@@ -135,7 +136,7 @@ int decode_rotary(const lorc_layer_desc* desc, const void* q, const int32_t* q_p
                                 : make_decode_plan_within(*desc, b, max_ctx, n_cus, workspace_bytes);
   DecodeParams p;
   if (int rc = decode_params(p, desc, q, q_pos, true, ctx_len, b, max_ctx, packed, cache, block_table, max_pages, n_pages,
-                             out, workspace, workspace_bytes, plan, latent_out))
+                             out, workspace, workspace_bytes, plan, latent_out, n_cus))
     return rc;
   return launch_decode(p, plan, static_cast<hipStream_t>(stream), static_cast<hipEvent_t>(ev_begin),
                        static_cast<hipEvent_t>(ev_end));
@@ -300,7 +301,7 @@ int lorc_decode_attention_absorbed_timed(const lorc_layer_desc* desc, const void
   const DecodePlan plan = make_absorbed_plan_within(*desc, b, max_ctx, n_cus, workspace_bytes);
   DecodeParams p;
   if (int rc = decode_params(p, desc, q_lat, nullptr, false, ctx_len, b, max_ctx, packed, cache, block_table, max_pages,
-                             n_pages, out, workspace, workspace_bytes, plan, 0))
+                             n_pages, out, workspace, workspace_bytes, plan, 0, n_cus))
     return rc;
   return launch_decode_absorbed(p, plan, static_cast<hipStream_t>(stream), static_cast<hipEvent_t>(ev_split_begin),
                                 static_cast<hipEvent_t>(ev_split_end));

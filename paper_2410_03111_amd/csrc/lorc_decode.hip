@@ -1323,21 +1323,21 @@ static int launch_merge_1024(const DecodeParams& p, hipStream_t s) {
   return launch_merge_form<HD, 1, CS, 1024, 8>(p, s);
 }
 
-// Workgroups per group of heads, as many as add CUs (256): us per call, one / more.
+// Workgroups per group of heads, as many as add CUs (the figures are of 256 of them): us per call, one / more.
 template <int HD>
 static int launch_merge_group(const DecodeParams& p, hipStream_t s) {
   const int groups = p.b * p.h_kv, even = p.G % 2 == 0;
   // Two halves of the heads x blocks of 32 columns, up to 32 groups: 1 x 1337 23.0 / 22.1, 4 x 2000 at rank 544 30.4 / 28.5, but 8 x 2000
   // at rank 384 33.7 / 36.1, 16 x 4096 97 / 105 (the partials are fetched once per column block).
-  const bool columns = even && p.latent_out == 0 && groups <= 32;
+  const bool columns = even && p.latent_out == 0 && groups <= p.n_cus / 8;
   if (p.r_v <= 512) {
     if (columns) return launch_merge_form<HD, 2, HD / 32, 512>(p, s);
-    return even && groups <= 256 ? launch_merge_form<HD, 2, 1, 512>(p, s) : launch_merge_form<HD, 1, 1, 512>(p, s);
+    return even && groups <= p.n_cus ? launch_merge_form<HD, 2, 1, 512>(p, s) : launch_merge_form<HD, 1, 1, 512>(p, s);
   }
-  if (columns && groups <= 16) return launch_merge_form<HD, 2, HD / 32, 1024>(p, s);
-  // Value ranks above 512, both to 16 groups (32 groups at rank 1024: 62.7, 60.6 below), halves of the columns up to 128 groups: 8B shape rank 768, 64 groups 44.0 / 42.3, 128 68.0 / 66.6, 256 70.2 /
-  // 72.9; 40 KV heads rank 640, 40 groups 39.9 / 38.0, 160 87.0 / 89.2.
-  return groups <= 128 && p.latent_out == 0 ? launch_merge_1024<HD, 2>(p, s) : launch_merge_1024<HD, 1>(p, s);
+  if (columns && groups <= p.n_cus / 16) return launch_merge_form<HD, 2, HD / 32, 1024>(p, s);
+  // Value ranks above 512: both to 16 groups (8B shape rank 1024, 32 groups 62.7, halves of the columns 60.6), halves of the columns up to
+  // 128 groups (rank 768, 64 groups 44.0 / 42.3, 128 68.0 / 66.6, 256 70.2 / 72.9; 40 KV heads rank 640, 40 groups 39.9 / 38.0, 160 87.0 / 89.2).
+  return groups <= p.n_cus / 2 && p.latent_out == 0 ? launch_merge_1024<HD, 2>(p, s) : launch_merge_1024<HD, 1>(p, s);
 }
 
 // The merge launch that follows every split kernel.
@@ -1348,11 +1348,11 @@ static int launch_merge(const DecodeParams& p, hipStream_t s) {
   // 151 / 157, 64 x 500 278 / 304; rank 1024 4 x 1000 87.6 / 79.6, 8 x 2000 194 / 192, 16 x 1000 196 / 200, 64 x 500 368 / 392; 32 heads
   // rank 800 16 x 1000 150.9 / 149.5, 64 x 500 288 / 302.
   if (p.G == 1 && p.r_v > kMgMaxRank && p.head_dim == 128 && p.latent_out == 0 && p.r_v <= kMgMaxRankG1 && p.n_splits <= kMgMaxSplits &&
-      p.b * p.h_q <= 256)
+      p.b * p.h_q <= p.n_cus)
     return launch_merge_form<128, 1, 4, kMgMaxRankG1, 1>(p, s);
   // Groups of two likewise: 64 / 32 heads, rank 544 64 x 100 104 / 114, 64 x 500 213 / 224, rank 768 128 x 100 200 / 224; 32 / 16 heads, 512
   // groups, rank 544 40.7 / 41.0, rank 768 47.4 / 46.6.  (Three: 48 / 16 heads, 2048 groups, rank 768 135 / 132.)
-  if (!merge_group_ok(p) || (p.G <= 2 && p.r_v > 512 && p.b * p.h_kv > 512)) {
+  if (!merge_group_ok(p) || (p.G <= 2 && p.r_v > 512 && p.b * p.h_kv > 2 * p.n_cus)) {
     if (p.head_dim == 128) return launch_kernel(decode_merge_kernel<128>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
     return launch_kernel(decode_merge_kernel<64>, dim3(p.b * p.h_q), dim3(256), 0, s, p);
   }

@@ -77,6 +77,7 @@ struct DecodeParams {
   int b, h_q, h_kv, G, head_dim, r_k, r_v, n_tasks, max_ctx, max_pages, n_pages, n_splits, tiles_per_split;
   size_t page_elems;
   float rope_base, q_scale;  // q_scale = softmax scale * log2(e)
+  int n_cus;                // of the device (for the merge's launch)
 };
 
 struct PrefillPlan {
