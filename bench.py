@@ -9,7 +9,7 @@ HBM before the timed region; the step cycles over several copies of the cache so
 cannot be served from the 256 MB last-level cache.
 
 Prints ONE JSON line: metric/value/unit (decode tok/s of the step above), ms_per_step, `roofline` (the dominant
-kernel, decode_split_kernel: achieved TFLOP/s against the bf16 matrix-core peak from HIP events recorded around it
+kernel, decode_stationary_kernel: achieved TFLOP/s against the bf16 matrix-core peak from HIP events recorded around it
 on the launch stream on every fifth step of the timed region, plus its latent stream in GB/s, the profiled HBM bytes per launch, and the HBM read rate
 and matrix-core rate this machine sustains by the library's two probes), `cpu_baseline` (the
 fp64 oracle timed on the host cores on a bounded sample of the same workload), `prefill` (down-projection and
