@@ -7,7 +7,8 @@ import ctypes
 import numpy as np
 import pytest
 
-from lorc_testlib import GpuLayer, Problem, TOL, oracle_decode, rel_err
+import lorc_inputs as gen
+from lorc_testlib import GpuLayer, LatentLayer, Problem, TOL, oracle_decode, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +115,39 @@ def test_workspace_sized_for_the_largest_batch_serves_smaller_ones(rank, h_q, b,
     got = L.decode_attention(*args, workspace=buf[:need]).float()
     assert bool(torch.isfinite(got).all()) and bool((buf[need:] == 0x5A).all())
     assert float((got - ref).norm() / ref.norm()) <= 2 ** -8
+
+
+@pytest.mark.parametrize("h_q,h_kv,r_k,r_v,b,n,symbol", [
+    # layers of one or two heads per group on either side of the lines to the three launches and to the streaming kernel
+    (40, 40, 64, 64, 12, 130, "decode_split_kernel<16, 1>"), (40, 40, 64, 64, 70, 130, "wide_scores_kernel"),
+    (40, 40, 544, 544, 4, 130, "decode_split_kernel<18, 0, true>"), (40, 40, 544, 544, 64, 100, "wide_scores_kernel"),
+    (36, 18, 672, 640, 16, 130, "decode_split_kernel<21, 1, true>"), (36, 18, 672, 640, 128, 100, "wide_scores_kernel"),
+    (32, 32, 256, 256, 200, 300, "decode_split_kernel<128, 2, 1, 4, 4, 2>"),
+    # value ranks above 512, groups on either side of the merge's lines (128, 512): one, two, three, four and eight heads
+    (6, 6, 704, 768, 21, 100, None), (6, 6, 704, 768, 22, 100, None), (6, 6, 704, 768, 86, 70, None),
+    (12, 6, 544, 576, 85, 70, None), (12, 6, 544, 576, 86, 70, None),
+    (18, 6, 96, 608, 22, 100, None), (24, 6, 768, 768, 2, 300, None), (24, 6, 768, 768, 3, 300, None), (24, 6, 768, 768, 100, 70, None),
+    (48, 6, 96, 736, 2, 200, None), (48, 6, 640, 672, 22, 100, None), (20, 20, 96, 1280, 12, 100, None), (20, 20, 96, 1280, 13, 100, None),
+])
+def test_dispatch_lines_match_oracle(h_q, h_kv, r_k, r_v, b, n, symbol):
+    """Three sequences, repeated to the batch: each against the oracle on its latents, and every repetition bit for bit the same."""
+    import torch
+    rng = np.random.default_rng(b + r_k)
+    bf = lambda a: gen.bf16_round(a.astype(np.float32))
+    ctx = [n, 1, max(1, n - 37)]
+    fall = lambda r: 4.0 * (1.0 + np.arange(r)) ** -0.7
+    C_k, C_v = ([bf(rng.standard_normal((m, r)) * fall(r)) for m in ctx] for r in (r_k, r_v))
+    B_k, B_v = (bf(rng.standard_normal((r, h_kv * 128)) / np.sqrt(r)) for r in (r_k, r_v))
+    q = bf(rng.standard_normal((3, h_q, 128)))
+    layer = LatentLayer(h_q, h_kv, 128, C_k, C_v, B_k, B_v, rope_base=10000.0)
+    L = layer.L
+    info = L.decode_kernel_info(layer.desc, b, n)
+    assert symbol is None or info[0] == symbol
+    rep = torch.arange(b, device=layer.dev) % 3
+    tq, q_pos, cl = layer.tensors(q)
+    got = L.decode_attention(layer.desc, tq[rep].contiguous(), q_pos[rep], cl[rep], n, layer.packed, layer.cache, layer.block_table[rep].contiguous())
+    for s in range(min(3, b)):
+        same = got[s::3].view(torch.int16)
+        assert bool((same == same[:1]).all())
+    live = min(3, b)
+    assert rel_err(got[:live].float().cpu().numpy().astype(np.float64), layer.oracle(q)[:live]) <= TOL
