@@ -825,7 +825,14 @@ static bool append_small_tiles(int rows, int T, int n_cus) { return (long)((rows
 
 AppendForm append_form(int D, int rows_k, int rows_v, int T, int n_cus) {
   const bool small = append_small_tiles(rows_k + rows_v, T, n_cus);
-  if (T <= kSkinnyMaxT) return T > kSkinnyMinTiles && D >= 1024 && small ? AppendForm::kTile64 : AppendForm::kSkinny;
+  if (T <= kSkinnyMaxT) {
+    // Rows 4 KiB apart (D 2048) cost the 32 x 32 tiles, which read 32 of them side by side, more than the one-pass kernel with few tokens for
+    // many rows.  us, one pass / tiles: 4096 rows T = 33 8.6 / 10.9, 48 9.9 / 11.0, 56 11.1 / 11.0; 3072 rows T = 40 8.7 / 9.0, 48 9.4 / 9.2; 2560
+    // rows T = 36 8.1 / 8.2, 40 8.5 / 8.2; 2048 rows T = 36 7.5 / 7.4.  4096 rows, T = 33 elsewhere: D 1024 6.8 / 6.3, 3072 12.9 / 10.4, 4096
+    // 14.4 / 14.9, 5120 19.5 / 15.4, 8192 25.8 / 29.4.
+    const bool few = D == 2048 && 5 * T * n_cus < 70 * n_cus + 12 * (rows_k + rows_v);
+    return T > kSkinnyMinTiles && D >= 1024 && small && !few ? AppendForm::kTile64 : AppendForm::kSkinny;
+  }
   if (small) return AppendForm::kTile64;
   AppendForm best = AppendForm::kTile64;
   double best_cost = append_tile_cost(best, rows_k, rows_v, T, n_cus);

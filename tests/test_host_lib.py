@@ -274,6 +274,9 @@ def test_decode_kernel_info_tells_the_families_apart(h_q, h_kv, head_dim, r_k, r
 
 @pytest.mark.parametrize("D,r_k,r_v,T,kernel", [
     (256, 32, 32, 64, "append_skinny_kernel"), (4096, 512, 512, 65, "append_kernel"),
+    (2048, 2048, 2048, 48, "append_skinny_kernel"), (2048, 2048, 2048, 56, "append_kernel"),   # 16 and
+    (2048, 1280, 1280, 36, "append_skinny_kernel"), (2048, 1280, 1280, 40, "append_kernel"),   # 10 rows per CU
+    (3072, 2048, 2048, 33, "append_kernel"), (5120, 2048, 2048, 33, "append_kernel"), (4096, 512, 512, 33, "append_kernel"),
     (4096, 512, 512, 1024, "append_kernel"),                # one 64 x 64 tile per CU
     (4096, 576, 576, 1000, "append_kernel"),                # a few more, token tiles a multiple of eight
     (4096, 576, 576, 900, "append_tile_kernel<2, 5, 4>"),   # ... or not
