@@ -1334,9 +1334,12 @@ static int launch_merge_group(const DecodeParams& p, hipStream_t s) {
     if (columns) return launch_merge_form<HD, 2, HD / 32, 512>(p, s);
     return even && groups <= p.n_cus ? launch_merge_form<HD, 2, 1, 512>(p, s) : launch_merge_form<HD, 1, 1, 512>(p, s);
   }
-  if (columns && groups <= p.n_cus / 16) return launch_merge_form<HD, 2, HD / 32, 1024>(p, s);
-  // Value ranks above 512: both to 16 groups (8B shape rank 1024, 32 groups 62.7, halves of the columns 60.6), halves of the columns up to
-  // 128 groups (rank 768, 64 groups 44.0 / 42.3, 128 68.0 / 66.6, 256 70.2 / 72.9; 40 KV heads rank 640, 40 groups 39.9 / 38.0, 160 87.0 / 89.2).
+  // Value ranks above 512.  Up to four heads: both to 16 groups (8B shape rank 1024, 32 groups 62.7, halves of the columns 60.6).  More, in
+  // even number: both to 32 (70B shape rank 576 4 x 2000 29.7, halves of the columns 30.8), halves of both to 64 (7 x 546 25.1 / 26.7).
+  // Then halves of the columns up to 128 groups (rank 768, 64 groups 44.0 / 42.3, 128 68.0 / 66.6, 256 70.2 / 72.9; 40 KV heads rank 640, 40
+  // groups 39.9 / 38.0, 160 87.0 / 89.2).
+  if (columns && groups <= p.n_cus / (p.G > 4 ? 8 : 16)) return launch_merge_form<HD, 2, HD / 32, 1024>(p, s);
+  if (even && p.G > 4 && p.latent_out == 0 && groups <= p.n_cus / 4) return launch_merge_form<HD, 2, 2, 1024>(p, s);
   return groups <= p.n_cus / 2 && p.latent_out == 0 ? launch_merge_1024<HD, 2>(p, s) : launch_merge_1024<HD, 1>(p, s);
 }
 

@@ -127,7 +127,7 @@ def test_workspace_sized_for_the_largest_batch_serves_smaller_ones(rank, h_q, b,
     (6, 6, 704, 768, 21, 100, None), (6, 6, 704, 768, 22, 100, None), (6, 6, 704, 768, 86, 70, None),
     (12, 6, 544, 576, 85, 70, None), (12, 6, 544, 576, 86, 70, None),
     (18, 6, 96, 608, 22, 100, None), (24, 6, 768, 768, 2, 300, None), (24, 6, 768, 768, 3, 300, None), (24, 6, 768, 768, 100, 70, None),
-    (48, 6, 96, 736, 2, 200, None), (48, 6, 640, 672, 22, 100, None), (20, 20, 96, 1280, 12, 100, None), (20, 20, 96, 1280, 13, 100, None),
+    (48, 6, 96, 736, 2, 200, None), (48, 6, 640, 672, 8, 100, None), (36, 6, 96, 704, 9, 100, None), (48, 6, 640, 672, 22, 100, None), (20, 20, 96, 1280, 12, 100, None), (20, 20, 96, 1280, 13, 100, None),
 ])
 def test_dispatch_lines_match_oracle(h_q, h_kv, r_k, r_v, b, n, symbol):
     """Three sequences, repeated to the batch: each against the oracle on its latents, and every repetition bit for bit the same."""

@@ -41,7 +41,7 @@ def test_row_sums_take_the_weights_unrounded(h_q, h_kv, head_dim, r_k, r_v):
 @pytest.mark.parametrize("h_q,h_kv,head_dim,r_v,b", [
     (32, 8, 128, 1024, 1), (32, 8, 128, 768, 9), (32, 8, 128, 544, 17),   # 8, 72 and 136 groups of four heads
     (24, 8, 128, 768, 2), (40, 8, 128, 1024, 3), (40, 8, 128, 576, 17),   # odd groups
-    (64, 8, 128, 1024, 2), (64, 8, 128, 1024, 20),                        # groups of eight
+    (64, 8, 128, 1024, 2), (64, 8, 128, 1024, 6), (64, 8, 128, 1024, 20),  # groups of eight
     (16, 16, 128, 768, 2), (16, 16, 128, 768, 16), (16, 16, 128, 768, 33), (32, 16, 64, 1024, 1), (16, 16, 64, 640, 9),
     (40, 40, 128, 1280, 1), (40, 40, 128, 2048, 6),                       # one head per group, ranks above 1024
 ])
